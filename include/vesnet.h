@@ -91,8 +91,9 @@ typedef struct {
   int32_t pair_form;          /* 0: automatic - vesnet_farfield_stokeslet takes the symmetric form
                                     when targets == sources (the same pointer), the precision is
                                     VESNET_FP32_COMPENSATED or VESNET_FP64, accumulate is 1 and the
-                                    problem is large enough (at least four units per compute
-                                    unit); every other call takes the direct form;
+                                    problem is large enough (compensated: at least four units per
+                                    compute unit; float64: at least 4096 points); every other call
+                                    takes the direct form;
                                  1: direct form - one gather per target over all source vesicles;
                                  2: symmetric form (compensated and float64) - each unordered pair
                                     of points of different vesicles is evaluated once and serves
@@ -100,14 +101,15 @@ typedef struct {
                                     reciprocals; the targets must be the points the workspace was
                                     prepared with (vesnet_farfield_stokeslet requires targets ==
                                     sources).  targets_per_thread (compensated 1, 2, 3, 4 or 8,
-                                    default 3; float64 1, 2, 3 or 4, default 4; the default drops to 2,
-                                    then 1, for problems too small for four units per compute
-                                    unit) sets its blocks of 256 T points (one
+                                    default 3, dropping to 2, then 1, for problems too small for four units
+                                    per compute unit; float64 1, 2, 3 or 4, default 4, or 2 below
+                                    about 92,000 points) sets its blocks of 256 T points (one
                                     256-thread workgroup per pair of blocks); block_threads,
                                     source_splits and source_staging are unused.  The automatic
                                     choice always uses the default.  Its partial sums are added as
                                     64-bit fixed-point integers (float64: a high and a low word,
-                                    40 bits finer), so the result is bitwise reproducible.         */
+                                    40 bits finer), so the result is bitwise reproducible.  Non-finite
+                                    float64 partial sums make the outputs they enter NaN.          */
 } vesnet_tile_config;
 
 /* Library version string and the thread-local description of the last error. */

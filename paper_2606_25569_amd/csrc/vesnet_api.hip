@@ -49,16 +49,15 @@ size_t rec_bytes(int prec) { return prec == P64 ? sizeof(double4) : sizeof(float
 // forces and the per-vesicle |F|_1 sums that the symmetric form needs.
 bool fwd_forces(int prec) { return prec == P32C || prec == P64; }
 
-// The precisions with a symmetric form (one evaluation per unordered pair), and the 64-bit accumulator
-// words it needs per point and component (float64: a high and a low fixed-point word).
+// The precisions with a symmetric form (one evaluation per unordered pair).
 bool has_symmetric(int prec) { return prec == P32C || prec == P64; }
-int acc_words(int prec) { return prec == P64 ? 2 : 1; }
 
 size_t prepared_bytes(int32_t P, int32_t M, int prec, bool forces = false) {
   size_t b = align_up((size_t)M * sizeof(int2)) + align_up((size_t)P * sizeof(int32_t)) +
              align_up((size_t)M * sizeof(double4)) + align_up((size_t)M * sizeof(double)) +
              align_up((size_t)P * rec_bytes(prec));
-  if (forces) b += align_up((size_t)P * sizeof(double2)) + align_up((size_t)M * sizeof(double2));
+  if (forces && prec != P64) b += align_up((size_t)P * sizeof(double2));  // float64 records hold w f themselves
+  if (forces) b += align_up((size_t)M * sizeof(double2));
   return b;
 }
 
@@ -76,8 +75,10 @@ PreparedView carve_prepared(char*& cursor, int32_t P, int32_t M, int prec, bool 
   pv.rec = cursor;
   cursor += align_up((size_t)P * rec_bytes(prec));
   if (forces) {
-    pv.f64 = reinterpret_cast<double2*>(cursor);
-    cursor += align_up((size_t)P * sizeof(double2));
+    if (prec != P64) {
+      pv.f64 = reinterpret_cast<double2*>(cursor);
+      cursor += align_up((size_t)P * sizeof(double2));
+    }
     pv.vaux = reinterpret_cast<double2*>(cursor);
     cursor += align_up((size_t)M * sizeof(double2));
   }
@@ -85,13 +86,13 @@ PreparedView carve_prepared(char*& cursor, int32_t P, int32_t M, int prec, bool 
 }
 
 // The symmetric form's region: cycle table, plan values, cycle net forces, fixed-point sums.
-size_t symmetric_bytes(int32_t P, int32_t M, int words = 1) {
+size_t symmetric_bytes(int32_t P, int32_t M) {
   return align_up((size_t)sym_max_cycles(P, M) * sizeof(int4)) + align_up(4 * sizeof(int32_t)) +
          align_up((size_t)sym_max_cycles(P, M) * sizeof(double2)) +
-         align_up((size_t)2 * words * P * sizeof(unsigned long long));
+         align_up((size_t)2 * P * sizeof(unsigned long long));
 }
 
-SymmetricView carve_symmetric(char*& cursor, int32_t P, int32_t M, int words = 1) {
+SymmetricView carve_symmetric(char*& cursor, int32_t P, int32_t M) {
   SymmetricView sv;
   sv.cyc = reinterpret_cast<int4*>(cursor);
   cursor += align_up((size_t)sym_max_cycles(P, M) * sizeof(int4));
@@ -100,7 +101,26 @@ SymmetricView carve_symmetric(char*& cursor, int32_t P, int32_t M, int words = 1
   sv.fcyc = reinterpret_cast<double2*>(cursor);
   cursor += align_up((size_t)sym_max_cycles(P, M) * sizeof(double2));
   sv.acc = reinterpret_cast<unsigned long long*>(cursor);
-  cursor += align_up((size_t)2 * words * P * sizeof(unsigned long long));
+  cursor += align_up((size_t)2 * P * sizeof(unsigned long long));
+  return sv;
+}
+
+// The float64 symmetric form's region: plan values, log table, two-word fixed-point sums, marks.
+size_t symmetric64_bytes(int32_t P) {
+  return align_up(64 * sizeof(int32_t)) + align_up(1024 * sizeof(double2)) +
+         align_up((size_t)4 * P * sizeof(unsigned long long)) + align_up((size_t)2 * P + 3);
+}
+
+Symmetric64View carve_symmetric64(char*& cursor, int32_t P) {
+  Symmetric64View sv;
+  sv.meta = reinterpret_cast<int32_t*>(cursor);
+  cursor += align_up(64 * sizeof(int32_t));
+  sv.tab = reinterpret_cast<double2*>(cursor);
+  cursor += align_up(1024 * sizeof(double2));
+  sv.acc = reinterpret_cast<unsigned long long*>(cursor);
+  cursor += align_up((size_t)4 * P * sizeof(unsigned long long));
+  sv.bad = reinterpret_cast<uint8_t*>(cursor);
+  cursor += align_up((size_t)2 * P + 3);
   return sv;
 }
 
@@ -115,14 +135,14 @@ struct Shape {
   int T, B, splits, bpc, staging, accumulate;
   int pair;  // 0 automatic, 1 direct, 2 symmetric
   int symT;  // targets per thread of the symmetric form (0: too few units for it)
+  int symNs; // column strips per block pair (float64 symmetric form)
 };
 
 // Targets per thread of the symmetric form: the largest of `top`, 2 and 1 that gives at least four units
 // per compute unit (a unit is one workgroup of 256 threads on one pair of blocks of 256 T points),
 // estimated with vesicles of a multiple of 16 points; 0 when even 1 gives fewer (direct form).  `top` is
 // the fastest measured on the 2000 x 128 suspension: 3 for the compensated forward (14.9 ms against
-// 15.7 ms at 2, 17.1 ms at 4 and 17.7 ms at 1) and adjoint (31.3 ms against 32.2 ms at 2 and 36.6 ms at
-// 4), 4 for the float64 forward (41.7 ms against 42.3 ms at 3 and 43.4 ms at 2).
+// 15.7 ms at 2, 17.1 ms at 4 and 17.7 ms at 1) and adjoint (31.3 ms against 32.2 ms at 2 and 36.6 ms at 4).
 int sym_default_T(int32_t P, int top) {
   for (int T : {top, 2, 1}) {
     const int64_t cyc = (int64_t)P / 16;
@@ -130,6 +150,21 @@ int sym_default_T(int32_t P, int top) {
     if (sym_units((cyc + cb - 1) / cb) >= 1024) return T;
   }
   return 0;
+}
+
+// Targets per thread and column strips of the float64 symmetric form (T = 0: too small for it); want_T: the
+// caller's targets per thread, or 0.  Four targets per thread where that alone gives 4096 units (four rounds of
+// the 1024 workgroups that fit at once; 2000 x 128: 34.2 ms against 35.1 at two), else two, with strips until
+// there are 4096 units or a strip is down to four cycles (40,008 points: 0.96 ms with two strips, 1.00 without;
+// 16,128 points: 0.178 ms with eight, 0.246 without), or to two where even that leaves the chip idle (4,096
+// points: 31 us against 36).  Below 4096 points the direct form is as fast (2,048 points: 23 us against 26).
+void sym64_shape(int32_t P, int want_T, int* T, int* ns) {
+  auto units = [&](int t) { return sym_units(sym64_blocks(P, t)); };
+  *T = want_T ? want_T : units(4) >= 4096 ? 4 : P >= 4096 ? 2 : 0;
+  *ns = 1;
+  if (*T == 0) return;
+  while (*ns < 8 && units(*T) * *ns < 4096) *ns *= 2;
+  if (units(*T) * *ns < 1024) *ns = 16;
 }
 
 // The default launch shape is the one the autotuner picks on the 2000 x 128 suspension
@@ -149,7 +184,10 @@ Shape default_shape(int32_t P, int32_t M, int prec) {
   while (waves * splits < want && splits < 16) splits *= 2;
   s.splits = std::max(1, std::min<int>(splits, std::max(1, M)));
   s.pair = 0;
-  s.symT = has_symmetric(prec) ? sym_default_T(P, prec == P32C ? 3 : 4) : 0;
+  s.symT = 0;
+  s.symNs = 1;
+  if (prec == P32C) s.symT = sym_default_T(P, 3);
+  if (prec == P64) sym64_shape(P, 0, &s.symT, &s.symNs);
   return s;
 }
 
@@ -193,11 +231,13 @@ int resolve_shape(const vesnet_tile_config* cfg, int32_t P, int32_t M, int prec,
   if (s.pair == 2 && s.accumulate == 2)
     return fail(VESNET_ERR_UNSUPPORTED, "the symmetric pair form accumulates on the VALU only");
   if (s.pair == 2 && s.symT == 0) s.symT = 1;
-  if (s.symT && !sym_fits(P, M, s.symT)) {
+  if (prec == P64 && s.symT) sym64_shape(P, s.symT, &s.symT, &s.symNs);
+  auto fits = [&](int T) { return prec == P64 ? sym_units(sym64_blocks(P, T)) <= (int64_t)INT32_MAX : sym_fits(P, M, T); };
+  if (s.symT && !fits(s.symT)) {
     if (s.pair == 2)
       return fail(VESNET_ERR_UNSUPPORTED, "too many points for the symmetric form at %d targets per thread (its "
                   "units exceed one launch); use more targets per thread or the direct form", s.symT);
-    s.symT = sym_fits(P, M, 4) ? 4 : prec != P64 && sym_fits(P, M, 8) ? 8 : 0;
+    s.symT = fits(4) ? 4 : prec != P64 && fits(8) ? 8 : 0;
   }
   *out = s;
   return VESNET_OK;
@@ -208,7 +248,7 @@ int resolve_shape(const vesnet_tile_config* cfg, int32_t P, int32_t M, int prec,
 size_t forward_bytes(int32_t P, int32_t M, int prec, const Shape& s) {
   size_t b = kAlign + prepared_bytes(P, M, prec, fwd_forces(prec));
   if (s.pair != 2 && s.splits > 1) b += align_up((size_t)2 * s.splits * P * sizeof(double));
-  if (has_symmetric(prec) && s.pair != 1) b += symmetric_bytes(P, M, acc_words(prec));
+  if (has_symmetric(prec) && s.pair != 1) b += prec == P64 ? symmetric64_bytes(P) : symmetric_bytes(P, M);
   return b;
 }
 
@@ -332,9 +372,8 @@ int evaluate_resolved(const double* targets, int32_t M, int32_t P, double mu, do
   hipError_t e;
   if (symmetric) {
     if (s.pair != 2 && s.splits > 1) cur += align_up((size_t)2 * s.splits * P * sizeof(double));
-    SymmetricView sv = carve_symmetric(cur, P, M, acc_words(prec));
-    e = prec == P64 ? launch_forward_symmetric64(s.symT, P, M, pv, sv, scale, out, stream)
-                    : launch_forward_symmetric(s.symT, P, M, pv, sv, scale, out, stream);
+    e = prec == P64 ? launch_forward_symmetric64(s.symT, s.symNs, P, M, pv, carve_symmetric64(cur, P), scale, out, stream)
+                    : launch_forward_symmetric(s.symT, P, M, pv, carve_symmetric(cur, P, M), scale, out, stream);
     if (e != hipSuccess) return hip_fail(e, "symmetric forward launch");
   } else {
     double* partial = s.splits > 1 ? reinterpret_cast<double*>(cur) : nullptr;
@@ -969,7 +1008,8 @@ int points_bwd_T(int32_t P, int32_t M, int prec) {
 size_t backward_points_bytes(int32_t P, int32_t M, int prec) {
   const size_t vec = align_up((size_t)2 * P * sizeof(double));
   if (points_bwd_T(P, M, prec))
-    return kAlign + 2 * prepared_bytes(P, M, prec, true) + symmetric_bytes(P, M) + vec;
+    return kAlign + 2 * prepared_bytes(P, M, prec, true) + symmetric_bytes(P, M) + vec +
+           (prec == P64 ? 2 * align_up((size_t)P * sizeof(double2)) : 0);
   return backward_bytes(P, M, prec) + vec;
 }
 

@@ -142,8 +142,15 @@ struct SymmetricView {
                              // blocks (one suspension) or of units (batched; then [4..12] the XCD queues and
                              // [16..23] their counters)
   double2* fcyc;             // [P/16 + M + 1] float64 net force w f of each cycle
-  unsigned long long* acc;   // [2][P] fixed-point sums (two's complement int64 at 2^-S); float64 form:
-                             // [2][2][P], the high words then the low words at 2^-(S + 40)
+  unsigned long long* acc;   // [2][P] fixed-point sums (two's complement int64 at 2^-S)
+};
+
+// Device views of the float64 symmetric form's region.
+struct Symmetric64View {
+  int32_t* meta;             // [64] [1] fixed-point exponent S, [3] 1 when its bound is not finite
+  double2* tab;              // [1024] log table
+  unsigned long long* acc;   // [2][2][P] fixed-point sums: the high words at 2^-S, then the low ones at 2^-(S + 40)
+  uint8_t* bad;              // [2][P] (padded to words) 1 where a partial sum was not finite
 };
 
 // Device views of the batched symmetric form's plan (after the symmetric region).
@@ -176,9 +183,10 @@ int64_t sym_units(int64_t nb);
 bool sym_fits(int P, int M, int T);
 hipError_t launch_forward_symmetric(int T, int P, int M, const PreparedView& pv, const SymmetricView& sv,
                                     double scale, double* out, void* stream);
-// The float64 symmetric form (T = 1 or 2; sv.acc holds 4P words: the high words of both components, then
-// the low words).
-hipError_t launch_forward_symmetric64(int T, int P, int M, const PreparedView& pv, const SymmetricView& sv,
+// The float64 symmetric form, T = 1 .. 4: blocks of 256 T points, each block pair cut into ns strips of columns
+// (ns divides 16; ns times the unordered block pairs must fit one launch).
+int64_t sym64_blocks(int64_t P, int T);
+hipError_t launch_forward_symmetric64(int T, int ns, int P, int M, const PreparedView& pv, const Symmetric64View& sv,
                                       double scale, double* out, void* stream);
 // Batched symmetric form (float32-compensated, targets = sources, S independent suspensions): a bound
 // of its unit count, the workgroups of its persistent kernel one compute unit holds, and the launch

@@ -62,6 +62,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "vesnet_internal.h"
 
@@ -199,14 +200,19 @@ __device__ __forceinline__ void sym_unit_blocks(int nb, int L, int& bx, int& by)
   if (by >= nb) by -= nb;
 }
 
+// The position of workgroup g of n in that XCD-contiguous order.
+__device__ __forceinline__ int xcd_contiguous(int g, int n) {
+  const int q = n / kXcds, r = n % kXcds;
+  const int x = g % kXcds;
+  return x * q + min(x, r) + g / kXcds;
+}
+
 __device__ __forceinline__ bool sym_unit(int nb, int& bx, int& by) {
   const int h = nb >> 1;
   const int units = (nb & 1) ? nb * (h + 1) : nb * h + h;
   const int g = blockIdx.x;
   if (g >= units) return false;
-  const int q = units / kXcds, r = units % kXcds;
-  const int x = g % kXcds;
-  sym_unit_blocks(nb, x * q + min(x, r) + g / kXcds, bx, by);
+  sym_unit_blocks(nb, xcd_contiguous(g, units), bx, by);
   return true;
 }
 
@@ -469,19 +475,37 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_main(
 }
 
 // ------------------------------------------------------------------ float64 symmetric form
-// The same schedule (cycles, blocks, circulant units, rings of 16 lanes) in float64 on global coordinates:
-// float64 needs no compensation, so a segment's set-up only selects the target or a far point with zero
-// force, and its rows are flushed without a log correction.  The logarithm is the table logarithm of the
-// direct float64 kernel with a 512-entry table (two fewer series terms than its 64 entries), the reciprocal
-// that kernel's refined hardware estimate; column sums travel around the ring
-// by DPP moves of both halves of each double.  Sums leave the workgroup as two 64-bit fixed-point words:
+// The same circulant schedule of unordered block pairs and rings of 16 lanes, in float64 on global coordinates.
+// Float64 needs no compensation per source vesicle, so nothing here follows the vesicles: blocks are 256 T
+// consecutive points, ring cycles 16 consecutive points whatever vesicles they belong to (only the last cycle
+// of a suspension is padded; cut at the vesicles, 17 to 63 points each, 47% of the pair evaluations were
+// padding), rows are summed over a whole unit without flushes, and the block table needs no plan kernel.  The
+// own vesicle is dropped pair by pair, but only in units whose row and column points share a vesicle (ids are
+// compared at both ends; at most the diagonal and the neighbouring block pairs): there the accumulations are
+// selected, so that not even a non-finite value of an own-vesicle pair enters.
+//
+// Work split: a unit is the row block against one of `ns` equal strips of the column block.  One unit per
+// block pair leaves most of the chip idle on small problems and a nearly empty last round on middling ones;
+// strips cost one more set of row additions each.
+//
+// Per unordered pair: with l = -1/2 ln q, rho = 1/q the Stokeslet is (A c; c B), A = l + rx^2 rho,
+// B = l + ry^2 rho, c = rx ry rho, the same for both directions: 9 float64 operations besides l and rho, and 4
+// FMAs per direction (33.3 instructions in the ring at T = 4, against 36.6 with projections and separate log and
+// rr sums).  The logarithm is the table logarithm of the direct float64 kernel, halved and negated in
+// the table, with 1024 entries (series through r^4); the table is built once per call and copied to LDS by each
+// unit.  Column sums travel around the ring by DPP moves of both halves of each double.  What bounds it is
+// float64 VALU issue (4 cycles per instruction and wavefront, 16 for the hardware reciprocal).  Measured before
+// and after: 2000 x 128 35.6 -> 34.2 ms, 1020 vesicles of 17 to 63 points (40,008 points) 1.45 -> 0.95 ms.
+//
+// Sums leave the workgroup as two 64-bit fixed-point words:
 // hi = rint(x 2^S) and lo = rint((x - hi 2^-S) 2^(S + kLoBits)) (the first difference is exact), each added
-// by an integer atomic, so the result is again independent of the order of the atomics while the
+// by an integer atomic, so the result is independent of the order of the atomics while the
 // resolution is 2^-(S + kLoBits), far below float64 rounding of the sum.  |lo| <= 2^(kLoBits - 1), so up to
-// 2^(62 - kLoBits + 1) partials per point stay exact.
+// 2^(62 - kLoBits + 1) partials per point stay exact.  A partial that is not finite (coincident points of two
+// vesicles, non-finite inputs) marks its output in `bad`, which the last kernel turns into NaN.
 constexpr int kLoBits = 40;
 constexpr int kChunk64 = 4;                         // source cycles per LDS chunk
-constexpr int kLogTab64 = 512;                     // entries of the float64 kernels' log table (8 KB of LDS)
+constexpr int kLogTab64 = 512;                     // entries of the float64 adjoint's log table (8 KB of LDS)
 constexpr double kFar64 = 3.2733906078961419e150;   // 2^500: position of an inactive target
 static_assert(kChunk64 * 2 * kRing <= kSymThreads, "one thread per staged record and per column sum of a chunk");
 
@@ -498,120 +522,140 @@ __device__ __forceinline__ double dfrom(unsigned lo, unsigned hi) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-// Adds x to the two fixed-point words of one accumulator entry (hi at a, lo at a + 2P).
-__device__ __forceinline__ void fixed_add2(unsigned long long* __restrict__ a, size_t two_p, double x, int S) {
+constexpr int kSymTab = 1024;                      // entries of the float64 forward's log table (16 KB of LDS)
+
+// Entry i of the forward's table: (a, 1/2 ln 2a), a as in log_tab_entry_n.
+__device__ __forceinline__ double2 half_log_entry(int i) {
+  const double2 t = log_tab_entry_n<kSymTab>(i);
+  return make_double2(0.5 * t.x, -0.5 * t.y);
+}
+
+// -1/2 ln q for a finite q > 0: q = mant 2^e, r = mant a - 1/2, |r| < 2.8e-4, -1/2 log1p(2r) =
+// -r + r^2 - 4/3 r^3 + 2 r^4 (the next term is below 5.5e-18; the table entry alone carries up to 2.8e-17),
+// e ln 2 by one FMA as in log_reduced_n.  With 2r every coefficient but 4/3 is an inline constant, so no step
+// needs a second scalar operand (a copy to a VGPR).
+__device__ __forceinline__ double neg_half_log(double q, const double2* __restrict__ tab) {
+  int e;
+  const double mant = frexp(q, &e);
+  const double2 t = tab[(__double2hiint(mant) >> 10) & (kSymTab - 1)];  // in range for every input
+  const double r = fma(mant, t.x, -0.5);
+  double pol = fma(r, 2.0, -4.0 / 3.0);
+  pol = fma(pol, r, 1.0);
+  pol = fma(pol, r, -1.0);
+  return fma((double)e, -0.5 * kLn2d, fma(r, pol, t.y));
+}
+
+// Adds x to the two fixed-point words of one accumulator entry (hi at a, lo at a + 2P), or marks it.
+__device__ __forceinline__ void fixed_add2(unsigned long long* __restrict__ a, uint8_t* __restrict__ bad, size_t two_p,
+                                           double x, int S) {
+  if (!isfinite(x)) {
+    *bad = 1;
+    return;
+  }
   const double h = rint(ldexp(x, S));
   const double r = x - ldexp(h, -S);  // exact
   atomicAdd(a, (unsigned long long)(long long)h);
   atomicAdd(a + two_p, (unsigned long long)(long long)rint(ldexp(r, S + kLoBits)));
 }
 
+// Fixed-point exponent of partial sums bounded by 520 sum |F|_1 (see k_sym_plan).
+__device__ __forceinline__ int sym_exponent(double fsum) {
+  const double bound = 520.0 * fsum;
+  if (!(bound > 0.0 && isfinite(bound))) return 0;
+  int e;
+  frexp(bound, &e);  // bound < 2^e
+  return 62 - e;
+}
+
+// Start of a float64 call: the accumulator words and marks cleared and the log table built (every workgroup a
+// share), and for a single suspension (M > 0) its exponent (workgroup 0; the vesicles' sums in a fixed order).
+// meta[3]: 1 when the bound itself is not finite (then every output is NaN).
+__global__ __launch_bounds__(1024) void k_sym64_init(const double2* __restrict__ vaux, int M, int64_t nwords,
+                                                     unsigned long long* __restrict__ acc,
+                                                     uint32_t* __restrict__ bad, int64_t nbad,
+                                                     double2* __restrict__ tab, int32_t* __restrict__ meta) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  for (int64_t e = first; e < nwords; e += stride) acc[e] = 0ull;
+  for (int64_t e = first; e < nbad; e += stride) bad[e] = 0u;
+  // the last workgroup builds the table, the first the exponent (one workgroup does both when it is alone)
+  if (blockIdx.x == gridDim.x - 1) tab[threadIdx.x] = half_log_entry(threadIdx.x);
+  if (blockIdx.x != 0 || M <= 0) return;
+  __shared__ double s_dsum[16];
+  double fa = 0.0;
+  for (int v = threadIdx.x; v < M; v += 1024) fa += vaux[v].x;
+  fa = wave_sum_d(fa);
+  if ((threadIdx.x & 63) == 0) s_dsum[threadIdx.x >> 6] = fa;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double tot = 0.0;
+    for (int k = 0; k < 16; ++k) tot += s_dsum[k];
+    meta[1] = sym_exponent(tot);
+    meta[3] = isfinite(520.0 * tot) ? 0 : 1;
+  }
+}
+static_assert(kSymTab == 1024, "k_sym64_init builds one entry per thread");
+
+// One unit: row points [r0, r1) (at most 256 T) against column points [c0, c1); diag: the column strip lies in
+// the row block.  ltab is in LDS.  Called by the whole workgroup.
 template <int T>
-__global__ __launch_bounds__(kSymThreads) void k_sym64_main(
-    int P, const double4* __restrict__ rec, const int4* __restrict__ cyc, const int32_t* __restrict__ meta,
-    unsigned long long* __restrict__ acc) {
-  constexpr int CB = kRows * T;
-  __shared__ int4 s_ti[CB];                          // (vesicle or -1, count, first point, 0)
+__device__ __forceinline__ void sym64_eval_unit(int P, const double4* __restrict__ rec,
+                                                const int32_t* __restrict__ vid, const double2* __restrict__ ltab,
+                                                int S, int r0, int r1, int c0, int c1, bool diag,
+                                                unsigned long long* __restrict__ acc, uint8_t* __restrict__ bad) {
   __shared__ double4 s_rec[2][kChunk64][2 * kRing];  // source cycles (x, y, F_x, F_y), each stored twice
+  __shared__ int32_t s_vid[2][kChunk64][2 * kRing];
   __shared__ double s_col[2][kSymWaves][kChunk64][2][kRing];
-  __shared__ double2 ltab[kLogTab64];
-
-  const int ncyc = meta[0];
-  const int S = meta[1];
-  const int nb = meta[2];
-  if (nb <= 0) return;
-  int bx, by;
-  if (!sym_unit(nb, bx, by)) return;
-  const bool diag = bx == by;
-  const int tc0 = bx * CB, tc1 = min(ncyc, tc0 + CB);
-  const int sc0 = by * CB, sc1 = min(ncyc, sc0 + CB);
   const size_t two_p = 2 * (size_t)P;
-
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = lane & 15;
   const int row = tid >> 4;
-  for (int e = tid; e < kLogTab64; e += kSymThreads) ltab[e] = log_tab_entry_n<kLogTab64>(e);
-  for (int t = tid; t < CB; t += kSymThreads) {
-    const int c = tc0 + t;
-    if (c < tc1) {
-      const int4 cy = cyc[c];
-      s_ti[t] = make_int4(cy.z, cy.y, cy.x, 0);
-    } else {
-      s_ti[t] = make_int4(-1, 0, 0, 0);
-    }
-  }
-  __syncthreads();
+  // vesicle ids do not decrease: the two point ranges share a vesicle when their id ranges meet
+  const bool masked = diag || !(vid[r1 - 1] < vid[c0] || vid[c1 - 1] < vid[r0]);
 
-  // this lane's targets (slot k: target cycle k * 16 + row, point p of it)
-  double4 tr[T];
-  int4 ti[T];
+  double tx[T], ty[T], fx[T], fy[T], ax[T], ay[T];
+  int tv[T];
 #pragma unroll
   for (int k = 0; k < T; ++k) {
-    ti[k] = s_ti[k * kRows + row];
-    tr[k] = ti[k].x >= 0 && p < ti[k].y ? rec[ti[k].z + p] : make_double4(0.0, 0.0, 0.0, 0.0);
+    const int i = r0 + (k * kRows + row) * kRing + p;
+    const bool in = i < r1;
+    const double4 t = in ? rec[i] : make_double4(kFar64, 0.0, 0.0, 0.0);
+    tv[k] = in ? vid[i] : -1;
+    tx[k] = t.x;
+    ty[k] = t.y;
+    fx[k] = t.z;
+    fy[k] = t.w;
+    ax[k] = ay[k] = 0.0;
   }
-  double dx[T], dy[T], fcx[T], fcy[T], fhx[T], fhy[T], lx[T], ly[T], rvx[T], rvy[T], ax[T], ay[T];
-  int actm = 0;
-#pragma unroll
-  for (int k = 0; k < T; ++k) {
-    dx[k] = dy[k] = fcx[k] = fcy[k] = fhx[k] = fhy[k] = 0.0;
-    lx[k] = ly[k] = rvx[k] = rvy[k] = ax[k] = ay[k] = 0.0;
-  }
 
-  auto setup = [&](int B) {
-    actm = 0;
-#pragma unroll
-    for (int k = 0; k < T; ++k) {
-      const bool act = ti[k].x >= 0 && ti[k].x != B && (!diag || ti[k].x < B) && p < ti[k].y;
-      actm |= act ? (1 << k) : 0;
-      dx[k] = act ? tr[k].x : kFar64;
-      dy[k] = act ? tr[k].y : 0.0;
-      fcx[k] = act ? tr[k].z : 0.0;
-      fcy[k] = act ? tr[k].w : 0.0;
-      fhx[k] = -0.5 * fcx[k];
-      fhy[k] = -0.5 * fcy[k];
-      lx[k] = ly[k] = rvx[k] = rvy[k] = 0.0;
-    }
-  };
-
-  auto flush = [&]() {
-#pragma unroll
-    for (int k = 0; k < T; ++k) {
-      const bool act = (actm >> k) & 1;
-      ax[k] += act ? fma(-0.5, lx[k], rvx[k]) : 0.0;
-      ay[k] += act ? fma(-0.5, ly[k], rvy[k]) : 0.0;
-    }
-  };
-
-  auto ring = [&](int buf, int cc) {
+  auto ring = [&](int buf, int cc, auto mask_tag) __attribute__((always_inline)) {
+    constexpr bool kMask = decltype(mask_tag)::value;
     const double4* rb = &s_rec[buf][cc][p];
+    const int32_t* vb = &s_vid[buf][cc][p];
     double cax = 0.0, cay = 0.0;
 #pragma unroll 1
     for (int s = 0; s < kRing; ++s) {
       const double4 sr = rb[s];
+      const int sv = kMask ? vb[s] : 0;
       double lcx = 0.0, lcy = 0.0;
 #pragma unroll
       for (int k = 0; k < T; ++k) {
-        const double rx = dx[k] - sr.x;
-        const double ry = dy[k] - sr.y;
+        const double rx = tx[k] - sr.x;
+        const double ry = ty[k] - sr.y;
         const double q = fma(ry, ry, rx * rx);
-        const double L = log_reduced_n<kLogTab64>(q, ltab);
+        const double l = neg_half_log(q, ltab);
         const double rho = recip(q);
-        const double rxr = rx * rho, ryr = ry * rho;
-        const double b = fma(ryr, sr.w, rxr * sr.z);       // (r . F_j)/q
-        lx[k] = fma(L, sr.z, lx[k]);
-        ly[k] = fma(L, sr.w, ly[k]);
-        rvx[k] = fma(b, rx, rvx[k]);
-        rvy[k] = fma(b, ry, rvy[k]);
-        const double b2 = fma(ryr, fcy[k], rxr * fcx[k]);  // (r . F_i)/q
-        if (k == 0) {
-          lcx = L * fhx[k];
-          lcy = L * fhy[k];
-        } else {
-          lcx = fma(L, fhx[k], lcx);
-          lcy = fma(L, fhy[k], lcy);
-        }
-        lcx = fma(b2, rx, lcx);
-        lcy = fma(b2, ry, lcy);
+        const double t = rx * rho, u = ry * rho;
+        const double A = fma(rx, t, l), B = fma(ry, u, l), c = ry * t;
+        const double nax = fma(A, sr.z, fma(c, sr.w, ax[k]));
+        const double nay = fma(c, sr.z, fma(B, sr.w, ay[k]));
+        const double ncx = fma(A, fx[k], k == 0 ? c * fy[k] : fma(c, fy[k], lcx));
+        const double ncy = fma(c, fx[k], k == 0 ? B * fy[k] : fma(B, fy[k], lcy));
+        // own-vesicle pairs, and in the diagonal block one of each two orderings (ids do not decrease)
+        const bool act = !kMask || (diag ? tv[k] < sv : tv[k] != sv);
+        ax[k] = act ? nax : ax[k];
+        ay[k] = act ? nay : ay[k];
+        lcx = act ? ncx : lcx;
+        lcy = act ? ncy : lcy;
       }
       cax = ring_next64(cax) + lcx;
       cay = ring_next64(cay) + lcy;
@@ -629,80 +673,119 @@ __global__ __launch_bounds__(kSymThreads) void k_sym64_main(
     if ((lane & 16) == 0) s_col[buf][wv][cc][lane >> 5][(p + kRing - 1) & (kRing - 1)] = tot;
   };
 
-  const int nchunks = (sc1 - sc0 + kChunk64 - 1) / kChunk64;
+  // Points of chunk g: slots 0..15 and again 16..31 of each cycle; slots past c1 repeat the last point with
+  // zero force.
+  const int ncyc = (c1 - c0 + kRing - 1) / kRing;
+  const int nchunks = (ncyc + kChunk64 - 1) / kChunk64;
   const bool stager = tid < kChunk64 * 2 * kRing;
-  const int st_cc = tid >> 5, st_q = tid & 31, st_m = st_q & (kRing - 1);
-  auto stage_load = [&](int g) {
+  const int st_cc = tid >> 5, st_q = tid & 31;
+  auto stage_load = [&](int g, int& v) {
     double4 r = make_double4(0.0, 0.0, 0.0, 0.0);
-    const int c = sc0 + g * kChunk64 + st_cc;
-    if (stager && c < sc1) {
-      const int4 cy = cyc[c];
-      r = rec[cy.x + (st_m < cy.y ? st_m : 0)];
-      if (st_m >= cy.y) r.z = r.w = 0.0;
+    v = -1;
+    const int j = c0 + (g * kChunk64 + st_cc) * kRing + (st_q & (kRing - 1));
+    if (stager && g < nchunks) {
+      const int jj = min(j, c1 - 1);
+      r = rec[jj];
+      v = vid[jj];
+      if (j >= c1) r.z = r.w = 0.0;
     }
     return r;
   };
-  auto stage_store = [&](int buf, const double4& r) {
-    if (stager) s_rec[buf][st_cc][st_q] = r;
+  auto stage_store = [&](int buf, const double4& r, int v) {
+    if (stager) {
+      s_rec[buf][st_cc][st_q] = r;
+      s_vid[buf][st_cc][st_q] = v;
+    }
   };
   // column sums of chunk g: the four wavefronts added in a fixed order, then two fixed-point words
   auto reduce = [&](int g, int buf) {
     if (tid >= kChunk64 * 2 * kRing) return;
     const int cc = tid >> 5, comp = (tid >> 4) & 1, m = tid & (kRing - 1);
-    const int c = sc0 + g * kChunk64 + cc;
-    if (c >= sc1) return;
-    const int4 cy = cyc[c];
-    if (m >= cy.y) return;
+    const int j = c0 + (g * kChunk64 + cc) * kRing + m;
+    if (j >= c1) return;
     const double v = ((s_col[buf][0][cc][comp][m] + s_col[buf][1][cc][comp][m]) + s_col[buf][2][cc][comp][m]) +
                      s_col[buf][3][cc][comp][m];
-    fixed_add2(&acc[(size_t)comp * P + cy.x + m], two_p, v, S);
+    const size_t e = (size_t)comp * P + j;
+    fixed_add2(&acc[e], &bad[e], two_p, v, S);
   };
 
-  int curB = -1;
-  stage_store(0, stage_load(0));
+  {
+    int v;
+    const double4 r = stage_load(0, v);
+    stage_store(0, r, v);
+  }
   __syncthreads();
   for (int g = 0; g < nchunks; ++g) {
     const int buf = g & 1;
-    const double4 nxt = stage_load(g + 1);
+    int nv;
+    const double4 nxt = stage_load(g + 1, nv);
     if (g > 0) reduce(g - 1, buf ^ 1);
-    const int cbase = sc0 + g * kChunk64;
-    const int ncc = min(kChunk64, sc1 - cbase);
-    for (int cc = 0; cc < ncc; ++cc) {
-      const int4 cy = cyc[cbase + cc];
-      if (cy.z != curB) {
-        if (curB >= 0) flush();
-        setup(cy.z);
-        curB = cy.z;
-      }
-      ring(buf, cc);
-    }
-    stage_store(buf ^ 1, nxt);
+    const int ncc = min(kChunk64, ncyc - g * kChunk64);
+    if (masked)
+      for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::true_type{});
+    else
+      for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::false_type{});
+    stage_store(buf ^ 1, nxt, nv);
     __syncthreads();
   }
-  if (nchunks > 0) {
-    reduce(nchunks - 1, (nchunks - 1) & 1);
-    flush();
-  }
+  reduce(nchunks - 1, (nchunks - 1) & 1);
 #pragma unroll
   for (int k = 0; k < T; ++k) {
-    if (ti[k].x >= 0 && p < ti[k].y) {
-      const int i = ti[k].z + p;
-      fixed_add2(&acc[i], two_p, ax[k], S);
-      fixed_add2(&acc[(size_t)P + i], two_p, ay[k], S);
+    const int i = r0 + (k * kRows + row) * kRing + p;
+    if (i < r1) {
+      fixed_add2(&acc[i], &bad[i], two_p, ax[k], S);
+      fixed_add2(&acc[(size_t)P + i], &bad[(size_t)P + i], two_p, ay[k], S);
     }
   }
 }
 
+// Strip number s of ns of the column block [c0, c1): 256 T / ns points (a whole number of cycles).
+template <int T>
+__device__ __forceinline__ void sym64_strip(int ns, int s, int& c0, int& c1) {
+  const int w = kSymThreads * T / ns;
+  c0 += s * w;
+  c1 = min(c1, c0 + w);
+}
+
+// One unit per workgroup: block pair and strip from the workgroup number, in the XCD order of sym_unit.
+template <int T>
+__global__ __launch_bounds__(kSymThreads) void k_sym64_main(int P, int ns, const double4* __restrict__ rec,
+                                                            const int32_t* __restrict__ vid,
+                                                            const double2* __restrict__ tab,
+                                                            const int32_t* __restrict__ meta,
+                                                            unsigned long long* __restrict__ acc,
+                                                            uint8_t* __restrict__ bad) {
+  __shared__ double2 ltab[kSymTab];
+  constexpr int BP = kSymThreads * T;  // points per block
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int nb = (P + BP - 1) / BP;
+  int bx, by;
+  sym_unit_blocks(nb, L / ns, bx, by);
+  int c0 = by * BP, c1 = min(P, c0 + BP);
+  sym64_strip<T>(ns, L % ns, c0, c1);
+  if (c0 >= c1) return;
+  for (int e = threadIdx.x; e < kSymTab; e += kSymThreads) ltab[e] = tab[e];
+  const int r0 = bx * BP;
+  sym64_eval_unit<T>(P, rec, vid, ltab, meta[1], r0, min(P, r0 + BP), c0, c1, bx == by, acc, bad);
+}
+
+__device__ __forceinline__ double sym64_value(const unsigned long long* __restrict__ acc,
+                                              const uint8_t* __restrict__ bad, int64_t n, int64_t e, double scale, int S,
+                                              bool all_bad) {
+  const double hi = (double)(long long)acc[e];
+  const double lo = (double)(long long)acc[n + e];
+  return all_bad || bad[e] ? NAN : ldexp(fma(lo, ldexp(1.0, -kLoBits), hi) * scale, -S);
+}
+
 __global__ __launch_bounds__(256) void k_sym64_finish(const unsigned long long* __restrict__ acc,
+                                                      const uint8_t* __restrict__ bad,
                                                       const int32_t* __restrict__ meta, int P, double scale,
                                                       double* __restrict__ out) {
   const int S = meta[1];
+  const bool all_bad = meta[3] != 0;
   const int64_t n = 2 * (int64_t)P;
-  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-    const double hi = (double)(long long)acc[e];
-    const double lo = (double)(long long)acc[n + e];
-    out[e] = ldexp(fma(lo, ldexp(1.0, -kLoBits), hi) * scale, -S);
-  }
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
+    out[e] = sym64_value(acc, bad, n, e, scale, S, all_bad);
 }
 
 // ------------------------------------------------------------------ batched symmetric form
@@ -1672,31 +1755,39 @@ hipError_t launch_batched_symmetric(int T, int grid, int P, int M, const Prepare
   return hipGetLastError();
 }
 
-hipError_t launch_forward_symmetric64(int T, int P, int M, const PreparedView& pv, const SymmetricView& sv,
+int64_t sym64_blocks(int64_t P, int T) { return (P + kSymThreads * T - 1) / (kSymThreads * T); }
+
+// Clears the float64 region's sums and marks and builds its table (and the exponent of a single suspension).
+static void launch_sym64_init(const double2* vaux, int M, int P, const Symmetric64View& sv, hipStream_t st) {
+  const int64_t words = 4 * (int64_t)P, marks = ((int64_t)2 * P + 3) / 4;
+  const int grid = (int)std::min<int64_t>((words + 1023) / 1024, 1024);
+  hipLaunchKernelGGL(k_sym64_init, dim3(grid), dim3(1024), 0, st, vaux, M, words, sv.acc,
+                     reinterpret_cast<uint32_t*>(sv.bad), marks, sv.tab, sv.meta);
+}
+
+hipError_t launch_forward_symmetric64(int T, int ns, int P, int M, const PreparedView& pv, const Symmetric64View& sv,
                                       double scale, double* out, void* stream) {
   if (P == 0) return hipSuccess;
+  if (ns < 1 || kRows % ns != 0) return hipErrorInvalidValue;
   hipStream_t st = Sx_(stream);
-  const int cb = sym_cycles_per_block(T);
-  const int ncyc_max = (int)sym_max_cycles(P, M);
-  const int nb_max = (int)sym_max_blocks(P, M, T);
-  hipLaunchKernelGGL(k_sym_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, M, cb, ncyc_max, sv.cyc, sv.meta);
-  // cycle forces (unused here) and the first 2P accumulator words; the low words are zeroed below
-  const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pv.f64, P, sv.fcyc, sv.acc);
-  hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, reinterpret_cast<double*>(sv.acc + 2 * (size_t)P),
-                     2 * (int64_t)P);
-  const dim3 grid((unsigned)sym_units(nb_max));
+  launch_sym64_init(pv.vaux, M, P, sv, st);
+  const int64_t units = sym_units(sym64_blocks(P, T)) * ns;
+  if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)units);
   const double4* rec = static_cast<const double4*>(pv.rec);
   switch (T) {
-    case 1: hipLaunchKernelGGL(k_sym64_main<1>, grid, dim3(kSymThreads), 0, st, P, rec, sv.cyc, sv.meta, sv.acc); break;
-    case 2: hipLaunchKernelGGL(k_sym64_main<2>, grid, dim3(kSymThreads), 0, st, P, rec, sv.cyc, sv.meta, sv.acc); break;
-    case 3: hipLaunchKernelGGL(k_sym64_main<3>, grid, dim3(kSymThreads), 0, st, P, rec, sv.cyc, sv.meta, sv.acc); break;
-    case 4: hipLaunchKernelGGL(k_sym64_main<4>, grid, dim3(kSymThreads), 0, st, P, rec, sv.cyc, sv.meta, sv.acc); break;
+#define VESNET_SYM64_CASE(TT)                                                                                       \
+  case TT:                                                                                                          \
+    hipLaunchKernelGGL(k_sym64_main<TT>, grid, dim3(kSymThreads), 0, st, P, ns, rec, pv.vid, sv.tab, sv.meta, sv.acc, \
+                       sv.bad);                                                                                     \
+    break;
+    VESNET_SYM64_CASE(1) VESNET_SYM64_CASE(2) VESNET_SYM64_CASE(3) VESNET_SYM64_CASE(4)
+#undef VESNET_SYM64_CASE
     default: return hipErrorInvalidValue;
   }
   const int64_t n = 2 * (int64_t)P;
   const int fgrid = (int)((n + 255) / 256 < 16384 ? (n + 255) / 256 : 16384);
-  hipLaunchKernelGGL(k_sym64_finish, dim3(fgrid), dim3(256), 0, st, sv.acc, sv.meta, P, scale, out);
+  hipLaunchKernelGGL(k_sym64_finish, dim3(fgrid), dim3(256), 0, st, sv.acc, sv.bad, sv.meta, P, scale, out);
   return hipGetLastError();
 }
 
