@@ -368,22 +368,26 @@ VESNET_API int vesnet_farfield_fmm_nearmasked(const double* points, const double
    its own points; the call needs no host-side copy of the tables (they are
    read on the device, so the call can be captured once and replayed).
    Two forms, chosen as in the single call (cfg->pair_form):
-   * symmetric (VESNET_FP32_COMPENSATED, targets == sources, pair_form 0 or 2):
-     the single call's symmetric form for every suspension in one persistent
-     launch.  A plan kernel cuts each suspension into blocks of 256 T points
-     (T = targets_per_thread: 1, 2, 3 or 4 when pair_form is 2, else the single
-     call's default for the total point count) that never reach into another
-     suspension; the unordered pairs of a suspension's blocks are its units,
-     numbered suspension by suspension and split into eight contiguous queues,
-     one per XCD, drained through counters in the workspace by
-     blocks_per_cu workgroups per compute unit (0: as many as fit).  Every
-     suspension's output equals that of a single symmetric call with the same
-     T bit for bit (the fixed-point sums do not depend on the order).
-   * direct (every other call, or pair_form 1): work items (suspension, block
+   * symmetric (VESNET_FP32_COMPENSATED or VESNET_FP64, targets == sources,
+     pair_form 0 or 2): the single call's symmetric form for every suspension in
+     one persistent launch.  A plan kernel cuts each suspension into blocks of
+     256 T points (T = targets_per_thread: 1, 2, 3 or 4 when pair_form is 2, of
+     which float64 uses at most 2; else compensated: the single call's default
+     for the total point count, float64: 2 for suspensions of 1,536 points or
+     more on average, else 1) that never reach into another suspension; the
+     unordered pairs of a suspension's blocks (float64: their strips) are its
+     units, numbered suspension by suspension and split into eight contiguous
+     queues, one per XCD, drained through counters in the workspace by
+     blocks_per_cu workgroups per compute unit (0: as many as fit).  The results
+     are bitwise reproducible (the fixed-point sums do not depend on the order),
+     and a compensated suspension's output equals that of a single symmetric
+     call with the same T bit for bit.
+  * direct (every other call, or pair_form 1): work items (suspension, block
      of targets) ordered largest suspension first on the device and handed
      out through a counter in the workspace.
-   Errors: VESNET_ERR_UNSUPPORTED when the symmetric form's units could exceed
-   one launch (about 2^31; use pair_form 1), else as the single call. */
+   Errors: VESNET_ERR_UNSUPPORTED when the compensated symmetric form's units
+   could exceed one launch (about 2^31; use pair_form 1; float64 takes the
+   direct form then), else as the single call. */
 VESNET_API size_t vesnet_batched_workspace_bytes(int32_t n_points, int32_t n_vesicles, int32_t n_suspensions, int precision);
 
 VESNET_API int vesnet_farfield_stokeslet_batched(const double* targets, const double* sources, const double* force_density,

@@ -704,7 +704,7 @@ size_t plan_bytes(int32_t S) { return align_up((size_t)(4 * (size_t)S + 2) * siz
 // The batched symmetric form's tables: per-suspension (cycles, blocks, exponent), first units and points.
 size_t symb_bytes(int32_t S) {
   return align_up((size_t)S * sizeof(int4)) + 2 * align_up((size_t)(S + 1) * sizeof(int32_t)) +
-         align_up((size_t)S * sizeof(int2));
+         align_up((size_t)S * sizeof(int2)) + align_up(kQueueCounters * sizeof(int32_t));
 }
 
 SymBatchView carve_symb(char*& cur, int32_t S) {
@@ -717,6 +717,8 @@ SymBatchView carve_symb(char*& cur, int32_t S) {
   cur += align_up((size_t)(S + 1) * sizeof(int32_t));
   bv.vr = reinterpret_cast<int2*>(cur);
   cur += align_up((size_t)S * sizeof(int2));
+  bv.count = reinterpret_cast<int32_t*>(cur);
+  cur += align_up(kQueueCounters * sizeof(int32_t));
   return bv;
 }
 
@@ -753,10 +755,24 @@ int check_batched_args(const double* targets, const double* sources, const doubl
   return VESNET_OK;
 }
 
-// The batched call takes the symmetric form when the precision is compensated, targets and sources are
-// one array and the call does not ask for the direct form (or matrix-core accumulation).
+// Targets per thread and column strips of the batched float64 symmetric form, 0 when its units could exceed one
+// launch (the direct form then).  Two targets per thread where a suspension averages three blocks of 512 points
+// or the caller asks for two or more, else one; strips as in the single call.
+int batched64_shape(const vesnet_tile_config* cfg, int32_t P, int32_t S, int* ns) {
+  const int64_t mean = (int64_t)P / std::max(1, S);
+  int T = mean >= 1536 ? 2 : 1;
+  if (cfg && cfg->pair_form == 2 && cfg->targets_per_thread) T = std::min(2, cfg->targets_per_thread);
+  *ns = 1;
+  while (*ns < 8 && sym_units(sym64_blocks(mean, T)) * S * *ns < 4096) *ns *= 2;
+  while (*ns > 1 && symb64_max_units(P, S, T, *ns) > (int64_t)INT32_MAX) *ns /= 2;
+  if (symb64_max_units(P, S, T, *ns) > (int64_t)INT32_MAX) T = 2;
+  return symb64_max_units(P, S, T, *ns) <= (int64_t)INT32_MAX ? T : 0;
+}
+
+// The batched call takes the symmetric form when the precision is compensated or float64, targets and sources
+// are one array and the call does not ask for the direct form (or matrix-core accumulation).
 bool batched_symmetric(const double* targets, const double* sources, int prec, const Shape& s) {
-  return prec == P32C && targets == sources && s.accumulate == 1 && s.pair != 1;
+  return has_symmetric(prec) && targets == sources && s.accumulate == 1 && s.pair != 1;
 }
 
 // Targets per thread and workgroups of the batched symmetric form: the caller's targets_per_thread when
@@ -786,7 +802,17 @@ int enqueue_batched(const double* targets, const double* sources, const double* 
   PlanView pl = carve_plan(cur, S);
   hipError_t e = launch_prepare(prec, sources, f, w, off, M, P, pv, stream);
   if (e != hipSuccess) return hip_fail(e, "prepare launch");
-  if (batched_symmetric(targets, sources, prec, s)) {
+  int ns = 1;
+  const int T64 = prec == P64 && batched_symmetric(targets, sources, prec, s) ? batched64_shape(cfg, P, S, &ns) : 0;
+  if (T64) {
+    const int bpc = cfg && cfg->blocks_per_cu ? cfg->blocks_per_cu : symb64_units_per_cu(T64);
+    Symmetric64View sv = carve_symmetric64(cur, P);
+    SymBatchView bv = carve_symb(cur, S);
+    e = launch_batched_symmetric64(T64, ns, num_cus() * bpc, P, M, pv, sv, bv, sus_off, S, mu, out, stream);
+    if (e != hipSuccess) return hip_fail(e, "batched float64 symmetric launch");
+    return VESNET_OK;
+  }
+  if (prec == P32C && batched_symmetric(targets, sources, prec, s)) {
     int T = 0, grid = 0;
     int rc = batched_symmetric_shape(cfg, P, M, S, s, &T, &grid);
     if (rc) return rc;
@@ -810,6 +836,7 @@ extern "C" size_t vesnet_batched_workspace_bytes(int32_t P, int32_t M, int32_t S
   if (check_sizes(P, M) || !valid_precision(prec) || S < 0) return 0;
   size_t b = kAlign + prepared_bytes(P, M, prec, fwd_forces(prec)) + plan_bytes(S);
   if (prec == P32C) b += symmetric_bytes(P, M) + symb_bytes(S);
+  if (prec == P64) b += symmetric64_bytes(P) + symb_bytes(S);
   return b;
 }
 
@@ -847,8 +874,11 @@ extern "C" int vesnet_graph_create_batched(const double* targets, const double* 
   Shape s;
   if ((rc = resolve_shape(cfg, P, M, prec, &s))) return rc;
   if ((rc = check_workspace(ws, ws_bytes, vesnet_batched_workspace_bytes(P, M, S, prec)))) return rc;
-  if (batched_symmetric(targets, sources, prec, s)) {
-    // resolve the symmetric shape (and its occupancy query) before the capture begins
+  // resolve the symmetric shape (and its occupancy query) before the capture begins
+  if (prec == P64) {
+    int ns = 1;
+    (void)symb64_units_per_cu(batched64_shape(cfg, P, S, &ns));
+  } else if (batched_symmetric(targets, sources, prec, s)) {
     int T = 0, grid = 0;
     if ((rc = batched_symmetric_shape(cfg, P, M, S, s, &T, &grid))) return rc;
   }
@@ -1111,7 +1141,7 @@ extern "C" int vesnet_autotune(const double* targets, const double* sources, con
   // Direct-form shapes (pair_form 1 where the symmetric form could run, so that each candidate is the
   // shape it names) and, for one compensated point array, the symmetric form's targets per thread
   // (batched: also its workgroups per compute unit, 0 = as many as fit).
-  const bool sym_ok = (prec == VESNET_FP32_COMPENSATED || (prec == VESNET_FP64 && !batched)) && targets == sources;
+  const bool sym_ok = has_symmetric(prec) && targets == sources;
   const int direct = sym_ok ? 1 : 0;
   std::vector<vesnet_tile_config> cands;
   for (int acc : {1, 2}) {
@@ -1134,7 +1164,7 @@ extern "C" int vesnet_autotune(const double* targets, const double* sources, con
   if (sym_ok) {
     for (int T : {1, 2, 3, 4, 8}) {
       if (batched) {
-        if (T == 8) continue;
+        if (T == 8 || (prec == VESNET_FP64 && T > 2)) continue;
         for (int bpc : {0, 2, 4, 8}) cands.push_back({T, 0, 0, bpc, 0, 1, 2});
       } else {
         if (prec == VESNET_FP64 && T > 4) continue;

@@ -139,15 +139,15 @@ struct PreparedView {
 struct SymmetricView {
   int4* cyc;                 // [P/16 + M + 1] cycles: (first point, count <= 16, vesicle, 0)
   int32_t* meta;             // [64] plan values: [0] number of cycles, [1] fixed-point exponent S, [2] number of
-                             // blocks (one suspension) or of units (batched; then [4..12] the XCD queues and
-                             // [16..23] their counters)
+                             // blocks (one suspension) or of units (batched; then [4..12] the XCD queues)
   double2* fcyc;             // [P/16 + M + 1] float64 net force w f of each cycle
   unsigned long long* acc;   // [2][P] fixed-point sums (two's complement int64 at 2^-S)
 };
 
 // Device views of the float64 symmetric form's region.
 struct Symmetric64View {
-  int32_t* meta;             // [64] [1] fixed-point exponent S, [3] 1 when its bound is not finite
+  int32_t* meta;             // [64] [1] fixed-point exponent S, [3] 1 when its bound is not finite; batched: units
+                             // and queues as in SymmetricView
   double2* tab;              // [1024] log table
   unsigned long long* acc;   // [2][2][P] fixed-point sums: the high words at 2^-S, then the low ones at 2^-(S + 40)
   uint8_t* bad;              // [2][P] (padded to words) 1 where a partial sum was not finite
@@ -155,11 +155,14 @@ struct Symmetric64View {
 
 // Device views of the batched symmetric form's plan (after the symmetric region).
 struct SymBatchView {
-  int4* stab;       // [S]   per suspension: (first cycle, end cycle, blocks, fixed-point exponent)
+  int4* stab;       // [S]   per suspension: (first cycle, end cycle, blocks, fixed-point exponent); float64 form:
+                    //       (first point, end point, 1 when its bound is not finite, exponent)
   int32_t* ustart;  // [S+1] first unit of each suspension
   int32_t* pstart;  // [S+1] first point of each suspension
   int2* vr;         // [S]   vesicle range of each suspension, clamped, disjoint and non-decreasing
+  int32_t* count;   // [kQueueCounters] next position in each XCD's queue, a cache line apart
 };
+constexpr int kQueueCounters = 256;
 
 // Device views of the batched work plan.
 struct PlanView {
@@ -196,6 +199,12 @@ int symb_units_per_cu(int T);
 hipError_t launch_batched_symmetric(int T, int grid, int P, int M, const PreparedView& pv, const SymmetricView& sv,
                                     const SymBatchView& bv, const int32_t* sus_off, const int32_t* off, int S,
                                     const double* mu, double* out, void* stream);
+// The same in float64, T = 1 or 2 targets per thread and ns column strips per block pair.
+int64_t symb64_max_units(int P, int S, int T, int ns);
+int symb64_units_per_cu(int T);
+hipError_t launch_batched_symmetric64(int T, int ns, int grid, int P, int M, const PreparedView& pv,
+                                      const Symmetric64View& sv, const SymBatchView& bv, const int32_t* sus_off, int S,
+                                      const double* mu, double* out, void* stream);
 // a[e] += b[e] for e < n (float64)
 hipError_t launch_add_f64(double* a, const double* b, int64_t n, void* stream);
 // Its adjoint for targets = sources: pvF prepared from (points, f, w), pvG from (points, dL/du, no

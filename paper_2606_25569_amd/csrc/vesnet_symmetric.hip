@@ -596,16 +596,24 @@ __global__ __launch_bounds__(1024) void k_sym64_init(const double2* __restrict__
 }
 static_assert(kSymTab == 1024, "k_sym64_init builds one entry per thread");
 
+// LDS of a unit besides the table: source cycles (x, y, F_x, F_y) and vesicle ids, each stored twice, and the
+// wavefronts' column sums, double buffered by chunk.
+struct Sym64Lds {
+  double4 rec[2][kChunk64][2 * kRing];
+  int32_t vid[2][kChunk64][2 * kRing];
+  double col[2][kSymWaves][kChunk64][2][kRing];
+};
+
 // One unit: row points [r0, r1) (at most 256 T) against column points [c0, c1); diag: the column strip lies in
 // the row block.  ltab is in LDS.  Called by the whole workgroup.
 template <int T>
-__device__ __forceinline__ void sym64_eval_unit(int P, const double4* __restrict__ rec,
+__device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const double4* __restrict__ rec,
                                                 const int32_t* __restrict__ vid, const double2* __restrict__ ltab,
                                                 int S, int r0, int r1, int c0, int c1, bool diag,
                                                 unsigned long long* __restrict__ acc, uint8_t* __restrict__ bad) {
-  __shared__ double4 s_rec[2][kChunk64][2 * kRing];  // source cycles (x, y, F_x, F_y), each stored twice
-  __shared__ int32_t s_vid[2][kChunk64][2 * kRing];
-  __shared__ double s_col[2][kSymWaves][kChunk64][2][kRing];
+  auto& s_rec = lds.rec;
+  auto& s_vid = lds.vid;
+  auto& s_col = lds.col;
   const size_t two_p = 2 * (size_t)P;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = lane & 15;
   const int row = tid >> 4;
@@ -739,12 +747,24 @@ __device__ __forceinline__ void sym64_eval_unit(int P, const double4* __restrict
   }
 }
 
-// Strip number s of ns of the column block [c0, c1): 256 T / ns points (a whole number of cycles).
+// Strip s of ns of the block pair {bx, by} of the points [p0, p1).  In the diagonal block, rows past the strip
+// have no pair in it (the ids there are not smaller); row ranges that fit half the targets per thread or fewer
+// (those, and the last block) take the narrower form instead of evaluating empty slots.
 template <int T>
-__device__ __forceinline__ void sym64_strip(int ns, int s, int& c0, int& c1) {
-  const int w = kSymThreads * T / ns;
-  c0 += s * w;
-  c1 = min(c1, c0 + w);
+__device__ __forceinline__ void sym64_run(Sym64Lds& lds, int P, const double4* __restrict__ rec,
+                                          const int32_t* __restrict__ vid, const double2* __restrict__ ltab, int S,
+                                          int p0, int p1, int bx, int by, int ns, int s,
+                                          unsigned long long* __restrict__ acc, uint8_t* __restrict__ bad) {
+  constexpr int BP = kSymThreads * T;  // points per block; a strip is a whole number of cycles
+  const int c0 = p0 + by * BP + s * (BP / ns), c1 = min(p1, c0 + BP / ns);
+  if (c0 >= c1) return;
+  const int r0 = p0 + bx * BP, r1 = min(bx == by ? c1 : p1, r0 + BP);
+  if (T > 1 && r1 - r0 <= kSymThreads)
+    sym64_eval_unit<1>(lds, P, rec, vid, ltab, S, r0, r1, c0, c1, bx == by, acc, bad);
+  else if (T > 2 && r1 - r0 <= 2 * kSymThreads)
+    sym64_eval_unit<2>(lds, P, rec, vid, ltab, S, r0, r1, c0, c1, bx == by, acc, bad);
+  else
+    sym64_eval_unit<T>(lds, P, rec, vid, ltab, S, r0, r1, c0, c1, bx == by, acc, bad);
 }
 
 // One unit per workgroup: block pair and strip from the workgroup number, in the XCD order of sym_unit.
@@ -755,18 +775,13 @@ __global__ __launch_bounds__(kSymThreads) void k_sym64_main(int P, int ns, const
                                                             const int32_t* __restrict__ meta,
                                                             unsigned long long* __restrict__ acc,
                                                             uint8_t* __restrict__ bad) {
+  __shared__ Sym64Lds lds;
   __shared__ double2 ltab[kSymTab];
-  constexpr int BP = kSymThreads * T;  // points per block
   const int L = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int nb = (P + BP - 1) / BP;
   int bx, by;
-  sym_unit_blocks(nb, L / ns, bx, by);
-  int c0 = by * BP, c1 = min(P, c0 + BP);
-  sym64_strip<T>(ns, L % ns, c0, c1);
-  if (c0 >= c1) return;
+  sym_unit_blocks((P + kSymThreads * T - 1) / (kSymThreads * T), L / ns, bx, by);
   for (int e = threadIdx.x; e < kSymTab; e += kSymThreads) ltab[e] = tab[e];
-  const int r0 = bx * BP;
-  sym64_eval_unit<T>(P, rec, vid, ltab, meta[1], r0, min(P, r0 + BP), c0, c1, bx == by, acc, bad);
+  sym64_run<T>(lds, P, rec, vid, ltab, meta[1], 0, P, bx, by, ns, L % ns, acc, bad);
 }
 
 __device__ __forceinline__ double sym64_value(const unsigned long long* __restrict__ acc,
@@ -800,8 +815,10 @@ __global__ __launch_bounds__(256) void k_sym64_finish(const unsigned long long* 
 // Slots of the plan values in the symmetric region's meta array.
 constexpr int kMetaUnits = 2;    // total number of units
 constexpr int kMetaQueue = 4;    // [kXcds + 1] first unit of each XCD's queue
-constexpr int kMetaCount = 16;   // [kXcds] next position in each queue
-static_assert(kMetaCount + kXcds <= 64, "plan values fit the 256-byte meta slot");
+static_assert(kMetaQueue + kXcds + 1 <= 64, "plan values fit the 256-byte meta slot");
+// The queues' counters lie kCountStride ints (a cache line) apart: additions to one line are performed one at a
+// time, wherever they come from.
+constexpr int kCountStride = kQueueCounters / kXcds;
 
 __device__ __forceinline__ int wave_scan_incl(int x, int lane) {
 #pragma unroll
@@ -810,6 +827,71 @@ __device__ __forceinline__ int wave_scan_incl(int x, int lane) {
     if (lane >= o) x += y;
   }
   return x;
+}
+
+// The range holding x: start[s] <= x < start[s + 1] for one of the n ranges (the last one beyond the end).
+__device__ __forceinline__ int range_of(const int32_t* __restrict__ start, int n, int x) {
+  int lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (start[mid] <= x)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
+// Thread 0 takes the next unit from the XCD queues (own XCD's first, then the others' in turn); -1 when all are
+// empty.  A queue is looked at before it is added to: without that every workgroup ended with eight additions
+// to exhausted queues, 8192 in one line, about 90 us of a call.  Every turn of the loop returns or advances
+// `probe`, so it ends.
+__device__ __forceinline__ int next_unit(const int32_t* __restrict__ meta, int32_t* __restrict__ count, int xcd,
+                                         int& probe) {
+  while (probe < kXcds) {
+    const int q = xcd + probe < kXcds ? xcd + probe : xcd + probe - kXcds;
+    const int lo = meta[kMetaQueue + q], n = meta[kMetaQueue + q + 1] - lo;
+    int32_t* c = count + q * kCountStride;
+    if (__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n) {
+      const int k = atomicAdd(c, 1);
+      if (k < n) return lo + k;
+    }
+    ++probe;
+  }
+  return -1;
+}
+
+// Disjoint, non-decreasing ranges [max(a_s, every earlier b), max(b_s, that)) of s = 0 .. n - 1 from the ends
+// get(s) = (a_s, b_s), by a running maximum; put(s, range) stores them.  Called by 1024 threads, s_w in LDS.
+template <class Get, class Put>
+__device__ __forceinline__ void disjoint_ranges(int n, int* s_w, Get get, Put put) {
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  int pm = 0;
+  for (int base = 0; base < n; base += 1024) {
+    const int s = base + t;
+    const int2 r = s < n ? get(s) : make_int2(0, 0);
+    int x = r.y;  // inclusive running maximum of the ends within the wavefront
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (lane >= o) x = max(x, y);
+    }
+    if (lane == 63) s_w[wv] = x;
+    __syncthreads();
+    int pre = pm, tot = pm;
+    for (int k = 0; k < 16; ++k) {
+      pre = k < wv ? max(pre, s_w[k]) : pre;
+      tot = max(tot, s_w[k]);
+    }
+    int ex = __shfl_up(x, 1, 64);  // the maximum over the earlier lanes of this wavefront
+    ex = lane == 0 ? pre : max(pre, ex);
+    if (s < n) {
+      const int v0 = max(r.x, ex);
+      put(s, make_int2(v0, max(r.y, v0)));
+    }
+    pm = tot;
+    __syncthreads();
+  }
 }
 
 // Plan: per suspension s, stab[s] = (first cycle, end cycle, blocks, fixed-point exponent), ustart[s] its
@@ -824,37 +906,13 @@ __global__ __launch_bounds__(1024) void k_symb_plan(const int2* __restrict__ vra
                                                     int cb, int ncyc_max, int4* __restrict__ cyc,
                                                     int4* __restrict__ stab, int32_t* __restrict__ ustart,
                                                     int32_t* __restrict__ pstart, int2* __restrict__ vr,
-                                                    int32_t* __restrict__ meta) {
+                                                    int32_t* __restrict__ meta, int32_t* __restrict__ count) {
   __shared__ int s_wc[16], s_wu[16];
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  // disjoint, non-decreasing vesicle ranges (a running maximum of the clamped ends)
-  int pm = 0;
-  for (int base = 0; base < nsus; base += 1024) {
-    const int s = base + t;
-    const int a = s < nsus ? min(max(sus_off[s], 0), M) : 0;
-    const int b = s < nsus ? min(max(sus_off[s + 1], 0), M) : 0;
-    int x = b;  // inclusive running maximum of the ends within the wavefront
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o, 64);
-      if (lane >= o) x = max(x, y);
-    }
-    if (lane == 63) s_wc[wv] = x;
-    __syncthreads();
-    int pre = pm, tot = pm;
-    for (int k = 0; k < 16; ++k) {
-      pre = k < wv ? max(pre, s_wc[k]) : pre;
-      tot = max(tot, s_wc[k]);
-    }
-    int ex = __shfl_up(x, 1, 64);  // the maximum over the earlier lanes of this wavefront
-    ex = lane == 0 ? pre : max(pre, ex);
-    if (s < nsus) {
-      const int v0 = max(a, ex);
-      vr[s] = make_int2(v0, max(b, v0));
-    }
-    pm = tot;
-    __syncthreads();
-  }
+  disjoint_ranges(
+      nsus, s_wc,
+      [&](int s) { return make_int2(min(max(sus_off[s], 0), M), min(max(sus_off[s + 1], 0), M)); },
+      [&](int s, int2 r) { vr[s] = r; });
   __syncthreads();
   // cycles and the bound of the partial sums of each suspension, one wavefront per suspension
   for (int s = wv; s < nsus; s += 16) {
@@ -920,7 +978,7 @@ __global__ __launch_bounds__(1024) void k_symb_plan(const int2* __restrict__ vra
     const int q = runu / kXcds, r = runu % kXcds;
     for (int x = 0; x <= kXcds; ++x) meta[kMetaQueue + x] = x * q + min(x, r);
   }
-  if (t < kXcds) meta[kMetaCount + t] = 0;
+  if (t < kXcds) count[t * kCountStride] = 0;
   __syncthreads();
   // the cycles of every vesicle, one wavefront per suspension
   for (int s = wv; s < nsus; s += 16) {
@@ -946,7 +1004,8 @@ template <int T>
 __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(T == 2 ? 5 : T == 3 ? 4 : 1))) void k_symb_main(
     int P, const double4* __restrict__ vtab, const double2* __restrict__ vaux, const float4* __restrict__ rec,
     const int4* __restrict__ cyc, const double2* __restrict__ fcyc, const int4* __restrict__ stab,
-    const int32_t* __restrict__ ustart, int nsus, int32_t* __restrict__ meta, unsigned long long* __restrict__ acc) {
+    const int32_t* __restrict__ ustart, int nsus, const int32_t* __restrict__ meta, int32_t* __restrict__ count,
+    unsigned long long* __restrict__ acc) {
   constexpr int CB = kRows * T;
   __shared__ int s_job[2];
   const int xcd = blockIdx.x % kXcds;
@@ -954,29 +1013,11 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(T =
   int slo = 0, shi = 0, scur = 0;   // thread 0: unit range of the last suspension found
   for (;;) {
     if (threadIdx.x == 0) {
-      int u = -1;
-      while (probe < kXcds) {
-        const int q = xcd + probe < kXcds ? xcd + probe : xcd + probe - kXcds;
-        const int lo = meta[kMetaQueue + q], n = meta[kMetaQueue + q + 1] - lo;
-        const int k = atomicAdd(&meta[kMetaCount + q], 1);
-        if (k < n) {
-          u = lo + k;
-          break;
-        }
-        ++probe;
-      }
+      const int u = next_unit(meta, count, xcd, probe);
       if (u >= 0 && (u < slo || u >= shi)) {
-        int lo = 0, hi = nsus;  // ustart[lo] <= u < ustart[hi]
-        while (hi - lo > 1) {
-          const int mid = (lo + hi) >> 1;
-          if (ustart[mid] <= u)
-            lo = mid;
-          else
-            hi = mid;
-        }
-        scur = lo;
-        slo = ustart[lo];
-        shi = ustart[lo + 1];
+        scur = range_of(ustart, nsus, u);
+        slo = ustart[scur];
+        shi = ustart[scur + 1];
       }
       s_job[0] = u;
       s_job[1] = scur;
@@ -1003,16 +1044,135 @@ __global__ __launch_bounds__(256) void k_symb_finish(const unsigned long long* _
   for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < 2 * (int64_t)P;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int j = (int)(e < P ? e : e - P);
-    int lo = 0, hi = nsus;  // pstart[lo] <= j < pstart[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (pstart[mid] <= j)
-        lo = mid;
-      else
-        hi = mid;
-    }
+    const int lo = range_of(pstart, nsus, j);
     const double scale = 1.0 / (4.0 * kPi * mu[lo]);
     out[e] = ldexp((double)(long long)acc[e] * scale, -stab[lo].w);
+  }
+}
+
+// ---- batched float64 form: the float64 symmetric units of many suspensions in one persistent launch, queued
+// as above.  Blocks and cycles are cut from each suspension's contiguous points, so the plan holds only point
+// ranges, exponents and first units.
+
+// Plan: per suspension stab[s] = (first point, end point, 1 when its bound is not finite, exponent) and its first
+// unit (ns strips per block pair of bp points); ranges of vesicles and of points are made disjoint, so no input
+// can make the units outrun the host's bound.  One workgroup of 1024 threads, in a fixed order.
+__global__ __launch_bounds__(1024) void k_symb64_plan(const int2* __restrict__ vrange,
+                                                      const double2* __restrict__ vaux,
+                                                      const int32_t* __restrict__ sus_off, int M, int P, int nsus,
+                                                      int bp, int ns, int4* __restrict__ stab,
+                                                      int32_t* __restrict__ ustart, int32_t* __restrict__ pstart,
+                                                      int2* __restrict__ vr, int32_t* __restrict__ meta,
+                                                      int32_t* __restrict__ count) {
+  __shared__ int s_w[16];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  disjoint_ranges(
+      nsus, s_w,
+      [&](int s) { return make_int2(min(max(sus_off[s], 0), M), min(max(sus_off[s + 1], 0), M)); },
+      [&](int s, int2 r) { vr[s] = r; });
+  __syncthreads();
+  for (int s = wv; s < nsus; s += 16) {  // one wavefront per suspension
+    const int2 rs = vr[s];
+    double fs = 0.0;
+    for (int v = rs.x + lane; v < rs.y; v += 64) fs += vaux[v].x;
+    fs = wave_sum_d(fs);
+    if (lane == 0) stab[s] = make_int4(0, 0, isfinite(520.0 * fs) ? 0 : 1, sym_exponent(fs));
+  }
+  __syncthreads();
+  disjoint_ranges(
+      nsus, s_w,
+      [&](int s) {
+        const int2 rs = vr[s];
+        return rs.x < rs.y ? make_int2(vrange[rs.x].x, vrange[rs.y - 1].y) : make_int2(0, 0);
+      },
+      [&](int s, int2 r) {
+        stab[s].x = r.x;
+        stab[s].y = r.y;
+        pstart[s] = r.x;
+      });
+  __syncthreads();
+  int run = 0;
+  for (int base = 0; base < nsus; base += 1024) {
+    const int s = base + t;
+    int nu = 0;
+    if (s < nsus) {
+      const int64_t nb = (stab[s].y - stab[s].x + bp - 1) / bp;
+      nu = (int)(nb * (nb + 1) / 2 * ns);
+    }
+    const int x = wave_scan_incl(nu, lane);
+    if (lane == 63) s_w[wv] = x;
+    __syncthreads();
+    int pre = run, tot = run;
+    for (int k = 0; k < 16; ++k) {
+      pre += k < wv ? s_w[k] : 0;
+      tot += s_w[k];
+    }
+    if (s < nsus) ustart[s] = pre + x - nu;
+    run = tot;
+    __syncthreads();
+  }
+  if (t == 0) {
+    ustart[nsus] = run;
+    pstart[nsus] = P;
+    meta[kMetaUnits] = run;
+    const int q = run / kXcds, r = run % kXcds;
+    for (int x = 0; x <= kXcds; ++x) meta[kMetaQueue + x] = x * q + min(x, r);
+  }
+  if (t < kXcds) count[t * kCountStride] = 0;
+}
+
+template <int T>
+__global__ __launch_bounds__(kSymThreads) void k_symb64_main(int P, int ns, const double4* __restrict__ rec,
+                                                             const int32_t* __restrict__ vid,
+                                                             const double2* __restrict__ tab,
+                                                             const int4* __restrict__ stab,
+                                                             const int32_t* __restrict__ ustart, int nsus,
+                                                             const int32_t* __restrict__ meta,
+                                                             int32_t* __restrict__ count,
+                                                             unsigned long long* __restrict__ acc,
+                                                             uint8_t* __restrict__ bad) {
+  __shared__ Sym64Lds lds;
+  __shared__ double2 ltab[kSymTab];
+  __shared__ int s_job[2];
+  constexpr int BP = kSymThreads * T;
+  for (int e = threadIdx.x; e < kSymTab; e += kSymThreads) ltab[e] = tab[e];
+  const int xcd = blockIdx.x % kXcds;
+  int probe = 0, slo = 0, shi = 0, scur = 0;  // thread 0: queues found empty, units of the last suspension found
+  for (;;) {
+    if (threadIdx.x == 0) {
+      const int u = next_unit(meta, count, xcd, probe);
+      if (u >= 0 && (u < slo || u >= shi)) {
+        scur = range_of(ustart, nsus, u);
+        slo = ustart[scur];
+        shi = ustart[scur + 1];
+      }
+      s_job[0] = u;
+      s_job[1] = scur;
+    }
+    __syncthreads();
+    const int u = s_job[0], sus = s_job[1];
+    __syncthreads();
+    if (u < 0) return;
+    const int4 st = stab[sus];
+    const int L = u - ustart[sus];
+    int bx, by;
+    sym_unit_blocks((st.y - st.x + BP - 1) / BP, L / ns, bx, by);
+    sym64_run<T>(lds, P, rec, vid, ltab, st.w, st.x, st.y, bx, by, ns, L % ns, acc, bad);
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void k_symb64_finish(const unsigned long long* __restrict__ acc,
+                                                       const uint8_t* __restrict__ bad,
+                                                       const int4* __restrict__ stab,
+                                                       const int32_t* __restrict__ pstart,
+                                                       const double* __restrict__ mu, int nsus, int P,
+                                                       double* __restrict__ out) {
+  const int64_t n = 2 * (int64_t)P;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
+    const int s = range_of(pstart, nsus, (int)(e < P ? e : e - P));
+    const int4 st = stab[s];
+    out[e] = sym64_value(acc, bad, n, e, 1.0 / (4.0 * kPi * mu[s]), st.w, st.z != 0);
   }
 }
 
@@ -1735,7 +1895,7 @@ hipError_t launch_batched_symmetric(int T, int grid, int P, int M, const Prepare
   const int cb = sym_cycles_per_block(T);
   const int ncyc_max = (int)sym_max_cycles(P, M);
   hipLaunchKernelGGL(k_symb_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, sus_off, M, P, S, cb, ncyc_max,
-                     sv.cyc, bv.stab, bv.ustart, bv.pstart, bv.vr, sv.meta);
+                     sv.cyc, bv.stab, bv.ustart, bv.pstart, bv.vr, sv.meta, bv.count);
   const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
   hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pv.f64, P, sv.fcyc, sv.acc);
   const float4* rec = static_cast<const float4*>(pv.rec);
@@ -1743,7 +1903,7 @@ hipError_t launch_batched_symmetric(int T, int grid, int P, int M, const Prepare
 #define VESNET_SYMB_MAIN(TT)                                                                                     \
   case TT:                                                                                                       \
     hipLaunchKernelGGL(k_symb_main<TT>, dim3(grid), dim3(kSymThreads), 0, st, P, pv.vtab, pv.vaux, rec, sv.cyc, \
-                       sv.fcyc, bv.stab, bv.ustart, S, sv.meta, sv.acc);                                          \
+                       sv.fcyc, bv.stab, bv.ustart, S, sv.meta, bv.count, sv.acc);                                \
     break;
     VESNET_SYMB_MAIN(1) VESNET_SYMB_MAIN(2) VESNET_SYMB_MAIN(3) VESNET_SYMB_MAIN(4)
 #undef VESNET_SYMB_MAIN
@@ -1763,6 +1923,48 @@ static void launch_sym64_init(const double2* vaux, int M, int P, const Symmetric
   const int grid = (int)std::min<int64_t>((words + 1023) / 1024, 1024);
   hipLaunchKernelGGL(k_sym64_init, dim3(grid), dim3(1024), 0, st, vaux, M, words, sv.acc,
                      reinterpret_cast<uint32_t*>(sv.bad), marks, sv.tab, sv.meta);
+}
+
+int64_t symb64_max_units(int P, int S, int T, int ns) {
+  // the blocks of all suspensions number at most P / (256 T) + S, and n (n + 1) / 2 is superadditive
+  return sym_units(sym64_blocks(P, T) + S) * ns;
+}
+
+// Cached after the first query (every device this library runs on is a gfx950).
+int symb64_units_per_cu(int T) {
+  static std::atomic<int> cache[3] = {};
+  if (T < 1 || T > 2) return 1;
+  int n = cache[T].load(std::memory_order_relaxed);
+  if (n > 0) return n;
+  const hipError_t e = T == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_symb64_main<1>, kSymThreads, 0)
+                              : hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_symb64_main<2>, kSymThreads, 0);
+  if (e != hipSuccess || n <= 0) return 1;
+  cache[T].store(n, std::memory_order_relaxed);
+  return n;
+}
+
+hipError_t launch_batched_symmetric64(int T, int ns, int grid, int P, int M, const PreparedView& pv,
+                                      const Symmetric64View& sv, const SymBatchView& bv, const int32_t* sus_off, int S,
+                                      const double* mu, double* out, void* stream) {
+  if (P == 0 || S == 0) return hipSuccess;
+  if (grid < 1 || ns < 1 || kRows % ns != 0) return hipErrorInvalidValue;
+  hipStream_t st = Sx_(stream);
+  launch_sym64_init(pv.vaux, 0, P, sv, st);
+  hipLaunchKernelGGL(k_symb64_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, sus_off, M, P, S, kSymThreads * T,
+                     ns, bv.stab, bv.ustart, bv.pstart, bv.vr, sv.meta, bv.count);
+  const double4* rec = static_cast<const double4*>(pv.rec);
+  if (T == 1)
+    hipLaunchKernelGGL(k_symb64_main<1>, dim3(grid), dim3(kSymThreads), 0, st, P, ns, rec, pv.vid, sv.tab, bv.stab,
+                       bv.ustart, S, sv.meta, bv.count, sv.acc, sv.bad);
+  else if (T == 2)
+    hipLaunchKernelGGL(k_symb64_main<2>, dim3(grid), dim3(kSymThreads), 0, st, P, ns, rec, pv.vid, sv.tab, bv.stab,
+                       bv.ustart, S, sv.meta, bv.count, sv.acc, sv.bad);
+  else
+    return hipErrorInvalidValue;
+  const int64_t n = 2 * (int64_t)P;
+  const int fgrid = (int)((n + 255) / 256 < 16384 ? (n + 255) / 256 : 16384);
+  hipLaunchKernelGGL(k_symb64_finish, dim3(fgrid), dim3(256), 0, st, sv.acc, sv.bad, bv.stab, bv.pstart, mu, S, P, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_forward_symmetric64(int T, int ns, int P, int M, const PreparedView& pv, const Symmetric64View& sv,

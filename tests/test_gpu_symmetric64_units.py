@@ -68,3 +68,66 @@ def test_not_finite_inputs_reach_the_outputs(V, what):
     assert not np.isfinite(out[:, hit]).any()
     if what == "coincident":
         assert np.isfinite(out[:, ~hit]).all()
+
+
+def _batch(sizes_per_member, nan_member=None):
+    """Ragged suspensions as one batch; one of them may hold a NaN force."""
+    from synth import suspension as S
+    members = [_ragged_suspension(seed=30 + k, sizes=z, spacing=4.5) for k, z in enumerate(sizes_per_member)]
+    b = S.batch_of(members, np.linspace(0.5, 2.0, len(members)))
+    if nan_member is not None:
+        b.f[0, sum(m.n_points for m in members[:nan_member]) + 3] = np.nan
+    return b
+
+
+@pytest.mark.parametrize("T", [None, 1, 2, 4])
+@pytest.mark.parametrize("graph", [False, True])
+def test_batched_float64_symmetric(V, T, graph):
+    """Suspensions from empty to several blocks, every one against the oracle; repeated passes (and graph
+    replays) agree bit for bit; a NaN stays in its suspension."""
+    import torch
+    sizes = [_sizes(n, n) for n in (40, 255, 257, 513, 3000, 1, 1500, 1024)]
+    sizes.insert(3, [0, 0])
+    cfg = None if T is None else {"pair_form": 2, "targets_per_thread": T}
+    dev = lambda a: torch.tensor(a, dtype=torch.float64, device="cuda")  # noqa: E731
+    for nan_member in (None, 4):
+        b = _batch(sizes, nan_member)
+        X, f, w = dev(b.X), dev(b.f), dev(b.w)
+        pr = V.BatchedProblem(X, X, f, w, b.vesicle_offsets, b.suspension_offsets, b.mu, "fp64", cfg)
+        runs = []
+        for _ in range(3):
+            runs.append((pr.replay() if graph else pr.run()).clone())
+            pr.out.fill_(7.0)  # eager work between the passes
+        torch.cuda.synchronize()
+        pr.close()
+        assert all(torch.equal(r[~torch.isnan(r)], runs[0][~torch.isnan(r)]) for r in runs)
+        out = runs[0].cpu().numpy()
+        at = 0
+        for k, m in enumerate(b.members):
+            o = out[:, at:at + m.n_points]
+            at += m.n_points
+            if k == nan_member:
+                own = np.repeat(np.arange(m.n_vesicles), np.diff(m.offsets))
+                assert not np.isfinite(o[:, own != own[3]]).any()
+            elif m.n_points:
+                ref = O.farfield_suspension(m.X, m.f, m.w, m.offsets, b.mu[k])
+                assert np.abs(o - ref).max() <= BAR * np.abs(ref).max()
+
+
+def test_batched_float64_malformed_device_offsets(V):
+    """Suspension offsets that overlap or run backwards on the device (the host's are valid): the call ends and
+    the library still works."""
+    import torch
+    b = _batch([_sizes(700, 1), _sizes(300, 2), _sizes(600, 3)])
+    dev = lambda a: torch.tensor(a, dtype=torch.float64, device="cuda")  # noqa: E731
+    X, f, w = dev(b.X), dev(b.f), dev(b.w)
+    pr = V.BatchedProblem(X, X, f, w, b.vesicle_offsets, b.suspension_offsets, b.mu, "fp64")
+    good = pr.run().clone()
+    keep = pr.sus_off.clone()
+    M = int(keep[-1])
+    for bad in ([0, M, M, M], [M, 0, M, 0], [-5, 1 << 30, 3, M], [0, M, 0, M]):
+        pr.sus_off.copy_(torch.tensor(bad, dtype=torch.int32, device="cuda"))
+        pr.run()
+    pr.sus_off.copy_(keep)
+    assert torch.equal(pr.run(), good)
+    pr.close()
