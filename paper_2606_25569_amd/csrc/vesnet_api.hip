@@ -1019,27 +1019,57 @@ int sym_bwd_T(int32_t P, int32_t M) {
   return sym_fits(P, M, 4) ? 4 : 0;
 }
 
-// Targets per thread of the float64 symmetric adjoint: two where they give at least four units per compute
-// unit (200 VGPRs, two wavefronts per SIMD: 69.4 ms against 74.6 ms at one on 2000 x 128, equal at
-// 512 x 64), else one (126 VGPRs); two when the units of one would not fit a launch; 0: the gathers.
-int sym64_bwd_T(int32_t P, int32_t M) {
-  const int T = sym_default_T(P, 2);
-  if (sym_fits(P, M, T ? T : 1)) return T ? T : 1;
-  return sym_fits(P, M, 2) ? 2 : 0;
+// Targets per thread and strips of the float64 symmetric adjoint (0: its units would not fit a launch, the
+// gathers run).  Three targets per thread where that alone gives 4096 units (2000 x 128: 59.6 ms against 61.6 at
+// two and 60.0 at four), else two with strips until there are 6000 units or a strip is down to four cycles (512 x
+// 64: 1.035 ms with four strips, 1.10 without; 16,128 points: 0.28 ms with eight, 0.39 without), or two cycles
+// where that leaves fewer than 2048 units (8,192 points: 83 us against 90); one with eight strips up to 6144
+// points (4,096 points: 33 us against 36; 1,536: 23.5 against 36 at two).
+int sym64_bwd_shape(int32_t P, int* ns) {
+  auto units = [&](int t) { return sym_units(sym64_blocks(P, t)); };
+  int T = units(3) >= 4096 ? 3 : P > 6144 ? 2 : 1;
+  *ns = T == 1 ? 8 : 1;
+  while (*ns < 8 && units(T) * *ns < (T == 3 ? 4096 : 6000)) *ns *= 2;
+  if (T == 2 && units(T) * *ns < 2048) *ns = 16;
+  if (units(T) * *ns > (int64_t)INT32_MAX) T = 4;
+  return units(T) * *ns <= (int64_t)INT32_MAX ? T : 0;
 }
 
 int points_bwd_T(int32_t P, int32_t M, int prec) {
-  return prec == VESNET_FP32_COMPENSATED ? sym_bwd_T(P, M) : prec == VESNET_FP64 ? sym64_bwd_T(P, M) : 0;
+  int ns;
+  return prec == VESNET_FP32_COMPENSATED ? sym_bwd_T(P, M) : prec == VESNET_FP64 ? sym64_bwd_shape(P, &ns) : 0;
 }
 
-// The symmetric pass (FP32-compensated and FP64): two prepared regions with forces, the cycle tables
-// and a [2][P] buffer for the position gradient when the caller does not ask for it; otherwise the
-// gathers' workspace and a [2][P] buffer for the source-role gradient.
+size_t adjoint64_bytes(int32_t P) {
+  return align_up((size_t)P * sizeof(double4)) + align_up((size_t)P * sizeof(int32_t)) +
+         align_up(1024 * sizeof(double2)) + align_up((size_t)2 * P * sizeof(double));
+}
+
+Adjoint64View carve_adjoint64(char*& cur, int32_t P) {
+  Adjoint64View av;
+  av.rec = reinterpret_cast<double4*>(cur);
+  cur += align_up((size_t)P * sizeof(double4));
+  av.vid = reinterpret_cast<int32_t*>(cur);
+  cur += align_up((size_t)P * sizeof(int32_t));
+  av.tab = reinterpret_cast<double2*>(cur);
+  cur += align_up(1024 * sizeof(double2));
+  av.vsum = reinterpret_cast<double*>(cur);
+  cur += align_up((size_t)2 * P * sizeof(double));
+  return av;
+}
+
+// The symmetric pass: FP32-compensated: two prepared regions with forces, the cycle tables and a [2][P] buffer
+// for the position gradient when the caller does not ask for it; FP64: records, ids, table and sums, and that
+// buffer (no less than the two prepared regions it had, which callers may count on).  Otherwise the gathers'
+// workspace and a [2][P] buffer for the source-role gradient.
 size_t backward_points_bytes(int32_t P, int32_t M, int prec) {
   const size_t vec = align_up((size_t)2 * P * sizeof(double));
-  if (points_bwd_T(P, M, prec))
-    return kAlign + 2 * prepared_bytes(P, M, prec, true) + symmetric_bytes(P, M) + vec +
-           (prec == P64 ? 2 * align_up((size_t)P * sizeof(double2)) : 0);
+  if (points_bwd_T(P, M, prec)) {
+    if (prec == P64)
+      return kAlign + std::max(adjoint64_bytes(P) + vec, 2 * prepared_bytes(P, M, prec, true) + symmetric_bytes(P, M) +
+                                                             2 * align_up((size_t)P * sizeof(double2)) + vec);
+    return kAlign + 2 * prepared_bytes(P, M, prec, true) + symmetric_bytes(P, M) + vec;
+  }
   return backward_bytes(P, M, prec) + vec;
 }
 
@@ -1082,6 +1112,15 @@ extern "C" int vesnet_farfield_stokeslet_backward_points(const double* points, c
   char* cur = aligned_base(ws);
   hipError_t e = hipSuccess;
   const int symT = points_bwd_T(P, M, prec);
+  if (symT && prec == P64) {
+    int ns = 1;
+    const int T = sym64_bwd_shape(P, &ns);
+    const Adjoint64View av = carve_adjoint64(cur, P);
+    double* gx = grad_points ? grad_points : reinterpret_cast<double*>(cur);
+    e = launch_backward_symmetric64(T, ns, P, M, points, f, w, off, gout, av, scale, gx, grad_f, grad_w, stream);
+    if (e != hipSuccess) return hip_fail(e, "symmetric backward launch");
+    return ok();
+  }
   if (symT) {
     // one symmetric pass: (points, w f) and (points, g) records, cycles and their sums of g
     PreparedView pvF = carve_prepared(cur, P, M, prec, true);
@@ -1091,11 +1130,8 @@ extern "C" int vesnet_farfield_stokeslet_backward_points(const double* points, c
     e = launch_prepare(prec, points, f, w, off, M, P, pvF, stream);
     if (e == hipSuccess) e = launch_prepare(prec, points, gout, nullptr, off, M, P, pvG, stream);
     if (e != hipSuccess) return hip_fail(e, "backward prepare launch");
-    e = prec == VESNET_FP64
-            ? launch_backward_symmetric64(symT, P, M, pvF, pvG, sv, reinterpret_cast<double*>(sv.acc), f, w, scale,
-                                          gx, grad_f, grad_w, stream)
-            : launch_backward_symmetric(symT, P, M, pvF, pvG, sv, reinterpret_cast<double*>(sv.acc), f, w, scale, gx,
-                                        grad_f, grad_w, stream);
+    e = launch_backward_symmetric(symT, P, M, pvF, pvG, sv, reinterpret_cast<double*>(sv.acc), f, w, scale, gx,
+                                  grad_f, grad_w, stream);
     if (e != hipSuccess) return hip_fail(e, "symmetric backward launch");
     return ok();
   }

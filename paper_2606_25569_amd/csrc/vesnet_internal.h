@@ -153,6 +153,14 @@ struct Symmetric64View {
   uint8_t* bad;              // [2][P] (padded to words) 1 where a partial sum was not finite
 };
 
+// Device views of the float64 symmetric adjoint's workspace.
+struct Adjoint64View {
+  double4* rec;   // [P] (x, y, w f_x, w f_y)
+  int32_t* vid;   // [P] vesicle id
+  double2* tab;   // [1024] log table
+  double* vsum;   // [2][P] sums of G g
+};
+
 // Device views of the batched symmetric form's plan (after the symmetric region).
 struct SymBatchView {
   int4* stab;       // [S]   per suspension: (first cycle, end cycle, blocks, fixed-point exponent); float64 form:
@@ -213,11 +221,10 @@ hipError_t launch_backward_symmetric(int T, int P, int M, const PreparedView& pv
                                      const SymmetricView& sv, double* vsum, const double* f, const double* w,
                                      double scale, double* grad_points, double* grad_f, double* grad_w,
                                      void* stream);
-// The same in float64 (T = 1 or 2; pvF and pvG prepared in float64 with forces).
-hipError_t launch_backward_symmetric64(int T, int P, int M, const PreparedView& pvF, const PreparedView& pvG,
-                                       const SymmetricView& sv, double* vsum, const double* f, const double* w,
-                                       double scale, double* grad_points, double* grad_f, double* grad_w,
-                                       void* stream);
+// The same in float64 (T = 1 .. 4, ns column strips per block pair) from the arrays themselves.
+hipError_t launch_backward_symmetric64(int T, int ns, int P, int M, const double* X, const double* f, const double* w,
+                                       const int32_t* off, const double* gout, const Adjoint64View& av, double scale,
+                                       double* grad_points, double* grad_f, double* grad_w, void* stream);
 hipError_t launch_forward_near(int prec, int T, bool lds, int splits, const double* tg, int P, int M,
                                const PreparedView& pv, double scale, double* out, double* partial, int32_t* count,
                                int32_t* pairs, int32_t capacity, void* stream);

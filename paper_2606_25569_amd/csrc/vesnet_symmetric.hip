@@ -505,7 +505,6 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_main(
 // vesicles, non-finite inputs) marks its output in `bad`, which the last kernel turns into NaN.
 constexpr int kLoBits = 40;
 constexpr int kChunk64 = 4;                         // source cycles per LDS chunk
-constexpr int kLogTab64 = 512;                     // entries of the float64 adjoint's log table (8 KB of LDS)
 constexpr double kFar64 = 3.2733906078961419e150;   // 2^500: position of an inactive target
 static_assert(kChunk64 * 2 * kRing <= kSymThreads, "one thread per staged record and per column sum of a chunk");
 
@@ -522,7 +521,7 @@ __device__ __forceinline__ double dfrom(unsigned lo, unsigned hi) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-constexpr int kSymTab = 1024;                      // entries of the float64 forward's log table (16 KB of LDS)
+constexpr int kSymTab = 1024;                      // entries of the log table (16 KB of LDS)
 
 // Entry i of the forward's table: (a, 1/2 ln 2a), a as in log_tab_entry_n.
 __device__ __forceinline__ double2 half_log_entry(int i) {
@@ -1488,153 +1487,123 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_bwd(
   }
 }
 
-// Float64 adjoint for targets = sources, on the schedule of k_sym64_main: per pair the same v (G(r) g_j to
-// the row, G(r) g_i to the column) and H (+H to the row, -H to the column) as k_sym_bwd, on global
-// coordinates without compensation; four float64 sums travel around the ring.  Sums are added with float64
-// atomics, as in k_sym_bwd.
+// ---- float64 adjoint for targets = sources, on the blocks, strips and cycles of the float64 forward (points,
+// not vesicles; own-vesicle pairs dropped by selects in the units that hold any).
+//
+// With t = rx rho, u = ry rho, e = rx t, m = 1 - 2e, G = (A c; c B) as in the forward and
+//   a = g_ix F_jx + F_ix g_jx,  b = g_iy F_jy + F_iy g_jy,  d = g_ix F_jy + g_iy F_jx + F_ix g_jy + F_iy g_jx,
+// H = grad (a A + b B + d c) = ( t (m (a - b) - 2 b) + u d m,  u (m (a - b) - 2 a) - t d m ):
+// 55 instructions per unordered pair with the logarithm and the reciprocal.  The four sums are added with
+// float64 atomics, as in k_sym_bwd.
+constexpr int kChunkA = 2;  // source cycles per LDS chunk: 31 KB with the table, so LDS holds five units
+
+// Records, vesicle ids and table, and the cleared sums of v and H: one wavefront per vesicle (its points, offsets
+// clamped), the rest dealt over the grid.
+__global__ __launch_bounds__(64) void k_sym64_adj_init(const double* __restrict__ X, const double* __restrict__ f,
+                                                       const double* __restrict__ w, const int32_t* __restrict__ off,
+                                                       int M, int P, double4* __restrict__ rec,
+                                                       int32_t* __restrict__ vid, double2* __restrict__ tab,
+                                                       double* __restrict__ vsum, double* __restrict__ gsum) {
+  const int lane = threadIdx.x;
+  for (int v = blockIdx.x; v < M; v += gridDim.x) {
+    const int j0 = min(max(off[v], 0), P), j1 = max(j0, min(max(off[v + 1], 0), P));
+    for (int j = j0 + lane; j < j1; j += 64) {
+      rec[j] = make_double4(X[j], X[P + j], w[j] * f[j], w[j] * f[P + j]);
+      vid[j] = v;
+    }
+  }
+  const int64_t stride = (int64_t)gridDim.x * 64, first = blockIdx.x * (int64_t)64 + lane;
+  for (int64_t e = first; e < 2 * (int64_t)P; e += stride) vsum[e] = gsum[e] = 0.0;
+  for (int64_t e = first; e < kSymTab; e += stride) tab[e] = half_log_entry((int)e);
+}
+
+struct Adj64Lds {
+  double4 rec[2][kChunkA][2 * kRing];
+  double2 g[2][kChunkA][2 * kRing];
+  int32_t vid[2][kChunkA][2 * kRing];
+  double col[2][kSymWaves][kChunkA][4][kRing];
+};
+
+// One unit of the adjoint: rows [r0, r1) against columns [c0, c1) (as sym64_eval_unit); g planar [2][P].
 template <int T>
-__global__ __launch_bounds__(kSymThreads) void k_sym64_bwd(const double4* __restrict__ recF,
-                                                           const double4* __restrict__ recG,
-                                                           const int4* __restrict__ cyc,
-                                                           const int32_t* __restrict__ meta, int P,
-                                                           double* __restrict__ gsum, double* __restrict__ vsum) {
-  constexpr int CB = kRows * T;
-  __shared__ int4 s_ti[CB];                          // (vesicle or -1, count, first point, 0)
-  __shared__ double4 s_rec[2][kChunk64][2 * kRing];  // source cycles (x, y, F_x, F_y), twice
-  __shared__ double2 s_reg[2][kChunk64][2 * kRing];  // source g, twice
-  __shared__ double s_col[2][kSymWaves][kChunk64][4][kRing];
-  __shared__ double2 ltab[kLogTab64];
-
-  const int ncyc = meta[0];
-  const int nb = meta[2];
-  if (nb <= 0) return;
-  int bx, by;
-  if (!sym_unit(nb, bx, by)) return;
-  const bool diag = bx == by;
-  const int tc0 = bx * CB, tc1 = min(ncyc, tc0 + CB);
-  const int sc0 = by * CB, sc1 = min(ncyc, sc0 + CB);
-
+__device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const double4* __restrict__ rec,
+                                                const double* __restrict__ g, const int32_t* __restrict__ vid,
+                                                const double2* __restrict__ ltab, int r0, int r1, int c0, int c1,
+                                                bool diag, double* __restrict__ gsum, double* __restrict__ vsum) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = lane & 15;
   const int row = tid >> 4;
-  for (int e = tid; e < kLogTab64; e += kSymThreads) ltab[e] = log_tab_entry_n<kLogTab64>(e);
-  for (int t = tid; t < CB; t += kSymThreads) {
-    const int c = tc0 + t;
-    if (c < tc1) {
-      const int4 cy = cyc[c];
-      s_ti[t] = make_int4(cy.z, cy.y, cy.x, 0);
-    } else {
-      s_ti[t] = make_int4(-1, 0, 0, 0);
-    }
-  }
-  __syncthreads();
+  const bool masked = diag || !(vid[r1 - 1] < vid[c0] || vid[c1 - 1] < vid[r0]);
 
-  double4 tf[T];
-  double2 tg[T];
-  int4 ti[T];
+  double tx[T], ty[T], fx[T], fy[T], gx[T], gy[T], vx[T], vy[T], hx[T], hy[T];
+  int tv[T];
 #pragma unroll
   for (int k = 0; k < T; ++k) {
-    ti[k] = s_ti[k * kRows + row];
-    const bool in = ti[k].x >= 0 && p < ti[k].y;
-    tf[k] = in ? recF[ti[k].z + p] : make_double4(0.0, 0.0, 0.0, 0.0);
-    const double4 g4 = in ? recG[ti[k].z + p] : make_double4(0.0, 0.0, 0.0, 0.0);
-    tg[k] = make_double2(g4.z, g4.w);
-  }
-  // per target slot k: position (or a far point), F and g (zero when inactive), -1/2 g, the segment's
-  // partials (log and rr parts of v, H) and the unit's sums
-  double dx[T], dy[T], fix[T], fiy[T], gix[T], giy[T], ghx[T], ghy[T];
-  double lvx[T], lvy[T], rvx[T], rvy[T], gax[T], gay[T], avx[T], avy[T], agx[T], agy[T];
-  int actm = 0;
-#pragma unroll
-  for (int k = 0; k < T; ++k) {
-    dx[k] = dy[k] = fix[k] = fiy[k] = gix[k] = giy[k] = ghx[k] = ghy[k] = 0.0;
-    lvx[k] = lvy[k] = rvx[k] = rvy[k] = gax[k] = gay[k] = avx[k] = avy[k] = agx[k] = agy[k] = 0.0;
+    const int i = r0 + (k * kRows + row) * kRing + p;
+    const bool in = i < r1;
+    const double4 t = in ? rec[i] : make_double4(kFar64, 0.0, 0.0, 0.0);
+    tv[k] = in ? vid[i] : -1;
+    tx[k] = t.x;
+    ty[k] = t.y;
+    fx[k] = t.z;
+    fy[k] = t.w;
+    gx[k] = in ? g[i] : 0.0;
+    gy[k] = in ? g[(size_t)P + i] : 0.0;
+    vx[k] = vy[k] = hx[k] = hy[k] = 0.0;
   }
 
-  auto setup = [&](int B) {
-    actm = 0;
-#pragma unroll
-    for (int k = 0; k < T; ++k) {
-      const bool act = ti[k].x >= 0 && ti[k].x != B && (!diag || ti[k].x < B) && p < ti[k].y;
-      actm |= act ? (1 << k) : 0;
-      dx[k] = act ? tf[k].x : kFar64;
-      dy[k] = act ? tf[k].y : 0.0;
-      fix[k] = act ? tf[k].z : 0.0;
-      fiy[k] = act ? tf[k].w : 0.0;
-      gix[k] = act ? tg[k].x : 0.0;
-      giy[k] = act ? tg[k].y : 0.0;
-      ghx[k] = -0.5 * gix[k];
-      ghy[k] = -0.5 * giy[k];
-      lvx[k] = lvy[k] = rvx[k] = rvy[k] = gax[k] = gay[k] = 0.0;
-    }
-  };
-
-  auto flush = [&]() {
-#pragma unroll
-    for (int k = 0; k < T; ++k) {
-      const bool act = (actm >> k) & 1;
-      avx[k] += act ? fma(-0.5, lvx[k], rvx[k]) : 0.0;
-      avy[k] += act ? fma(-0.5, lvy[k], rvy[k]) : 0.0;
-      agx[k] += act ? gax[k] : 0.0;
-      agy[k] += act ? gay[k] : 0.0;
-    }
-  };
-
-  auto ring = [&](int buf, int cc) {
-    const double4* rb = &s_rec[buf][cc][p];
-    const double2* gb = &s_reg[buf][cc][p];
-    double cvx = 0.0, cvy = 0.0, cgx = 0.0, cgy = 0.0;
+  auto ring = [&](int buf, int cc, auto mask_tag) __attribute__((always_inline)) {
+    constexpr bool kMask = decltype(mask_tag)::value;
+    const double4* rb = &lds.rec[buf][cc][p];
+    const double2* gb = &lds.g[buf][cc][p];
+    const int32_t* vb = &lds.vid[buf][cc][p];
+    double cvx = 0.0, cvy = 0.0, chx = 0.0, chy = 0.0;
 #pragma unroll 1
     for (int s = 0; s < kRing; ++s) {
       const double4 sr = rb[s];
       const double2 sg = gb[s];
-      double lvcx = 0.0, lvcy = 0.0, lgcx = 0.0, lgcy = 0.0;
+      const int sv = kMask ? vb[s] : 0;
+      double lvx = 0.0, lvy = 0.0, lhx = 0.0, lhy = 0.0;
 #pragma unroll
       for (int k = 0; k < T; ++k) {
-        const double rx = dx[k] - sr.x;
-        const double ry = dy[k] - sr.y;
+        const double rx = tx[k] - sr.x;
+        const double ry = ty[k] - sr.y;
         const double q = fma(ry, ry, rx * rx);
-        const double L = log_reduced_n<kLogTab64>(q, ltab);
+        const double l = neg_half_log(q, ltab);
         const double rho = recip(q);
-        const double ux = rx * rho, uy = ry * rho;
-        const double p3 = fma(uy, sg.y, ux * sg.x);        // (r . g_j)/q
-        const double p2 = fma(uy, giy[k], ux * gix[k]);    // (r . g_i)/q
-        const double p1 = fma(uy, sr.w, ux * sr.z);        // (r . F_j)/q
-        const double p4 = fma(uy, fiy[k], ux * fix[k]);    // (r . F_i)/q
-        lvx[k] = fma(L, sg.x, lvx[k]);
-        lvy[k] = fma(L, sg.y, lvy[k]);
-        rvx[k] = fma(p3, rx, rvx[k]);
-        rvy[k] = fma(p3, ry, rvy[k]);
-        // H = -(rho (g_i . F_j + F_i . g_j) + 2 (p1 p2 + p3 p4)) r + g_i p1 + F_j p2 + F_i p3 + g_j p4
-        const double ab = fma(gix[k], sr.z, fma(giy[k], sr.w, fma(fix[k], sg.x, fiy[k] * sg.y)));
-        const double m = fma(2.0, fma(p1, p2, p3 * p4), rho * ab);
-        const double hx = fma(sg.x, p4, fma(fix[k], p3, fma(sr.z, p2, fma(gix[k], p1, -m * rx))));
-        const double hy = fma(sg.y, p4, fma(fiy[k], p3, fma(sr.w, p2, fma(giy[k], p1, -m * ry))));
-        gax[k] += hx;
-        gay[k] += hy;
-        if (k == 0) {
-          lvcx = L * ghx[k];
-          lvcy = L * ghy[k];
-          lgcx = -hx;
-          lgcy = -hy;
-        } else {
-          lvcx = fma(L, ghx[k], lvcx);
-          lvcy = fma(L, ghy[k], lvcy);
-          lgcx -= hx;
-          lgcy -= hy;
-        }
-        lvcx = fma(p2, rx, lvcx);
-        lvcy = fma(p2, ry, lvcy);
+        const double t = rx * rho, u = ry * rho;
+        const double e = rx * t;
+        const double A = l + e, B = fma(ry, u, l), c = ry * t, m = fma(-2.0, e, 1.0);
+        const double a = fma(fx[k], sg.x, gx[k] * sr.z);
+        const double b = fma(fy[k], sg.y, gy[k] * sr.w);
+        const double d = fma(gx[k], sr.w, fma(gy[k], sr.z, fma(fx[k], sg.y, fy[k] * sg.x)));
+        const double n = m * (a - b), dm = d * m;
+        const double Hx = fma(t, fma(-2.0, b, n), u * dm);
+        const double Hy = fma(u, fma(-2.0, a, n), -t * dm);
+        const double nvx = fma(A, sg.x, fma(c, sg.y, vx[k])), nvy = fma(c, sg.x, fma(B, sg.y, vy[k]));
+        const double nhx = hx[k] + Hx, nhy = hy[k] + Hy;
+        const double nlvx = fma(A, gx[k], k == 0 ? c * gy[k] : fma(c, gy[k], lvx));
+        const double nlvy = fma(c, gx[k], k == 0 ? B * gy[k] : fma(B, gy[k], lvy));
+        const double nlhx = k == 0 ? Hx : lhx + Hx, nlhy = k == 0 ? Hy : lhy + Hy;
+        const bool act = !kMask || (diag ? tv[k] < sv : tv[k] != sv);
+        vx[k] = act ? nvx : vx[k];
+        vy[k] = act ? nvy : vy[k];
+        hx[k] = act ? nhx : hx[k];
+        hy[k] = act ? nhy : hy[k];
+        lvx = act ? nlvx : lvx;
+        lvy = act ? nlvy : lvy;
+        lhx = act ? nlhx : lhx;
+        lhy = act ? nlhy : lhy;
       }
-      cvx = ring_next64(cvx) + lvcx;
-      cvy = ring_next64(cvy) + lvcy;
-      cgx = ring_next64(cgx) + lgcx;
-      cgy = ring_next64(cgy) + lgcy;
+      cvx = ring_next64(cvx) + lvx;
+      cvy = ring_next64(cvy) + lvy;
+      chx = ring_next64(chx) - lhx;
+      chy = ring_next64(chy) - lhy;
     }
     // add the four rows of the wavefront (both halves of each double swapped alike): v, then H
-    auto rows4 = [&](double a, double b) {
-      const unsigned long long ba = dlo(a), bb = dlo(b);
-      const auto hl = __builtin_amdgcn_permlane32_swap((unsigned)ba, (unsigned)bb, false, false);
-      const auto hh = __builtin_amdgcn_permlane32_swap((unsigned)(ba >> 32), (unsigned)(bb >> 32), false, false);
+    auto rows4 = [&](double x, double y) {
+      const unsigned long long bx = dlo(x), by = dlo(y);
+      const auto hl = __builtin_amdgcn_permlane32_swap((unsigned)bx, (unsigned)by, false, false);
+      const auto hh = __builtin_amdgcn_permlane32_swap((unsigned)(bx >> 32), (unsigned)(by >> 32), false, false);
       const double z = dfrom(hl[0], hh[0]) + dfrom(hl[1], hh[1]);
       const unsigned long long bz = dlo(z);
       const auto gl = __builtin_amdgcn_permlane16_swap((unsigned)bz, (unsigned)bz, false, false);
@@ -1642,94 +1611,106 @@ __global__ __launch_bounds__(kSymThreads) void k_sym64_bwd(const double4* __rest
       return dfrom(gl[0], gh[0]) + dfrom(gl[1], gh[1]);
     };
     const double totv = rows4(cvx, cvy);
-    const double totg = rows4(cgx, cgy);
+    const double toth = rows4(chx, chy);
     if ((lane & 16) == 0) {
       const int slot = (p + kRing - 1) & (kRing - 1);
-      s_col[buf][wv][cc][lane >> 5][slot] = totv;
-      s_col[buf][wv][cc][2 + (lane >> 5)][slot] = totg;
+      lds.col[buf][wv][cc][lane >> 5][slot] = totv;
+      lds.col[buf][wv][cc][2 + (lane >> 5)][slot] = toth;
     }
   };
 
-  const int nchunks = (sc1 - sc0 + kChunk64 - 1) / kChunk64;
-  const bool stager = tid < kChunk64 * 2 * kRing;
-  const int st_cc = tid >> 5, st_q = tid & 31, st_m = st_q & (kRing - 1);
-  auto stage_load = [&](int g, double2& gg) {
-    double4 r = make_double4(0.0, 0.0, 0.0, 0.0);
-    gg = make_double2(0.0, 0.0);
-    const int c = sc0 + g * kChunk64 + st_cc;
-    if (stager && c < sc1) {
-      const int4 cy = cyc[c];
-      const int j = cy.x + (st_m < cy.y ? st_m : 0);
-      r = recF[j];
-      const double4 rg = recG[j];
-      if (st_m >= cy.y) {
-        r.z = r.w = 0.0;
-      } else {
-        gg = make_double2(rg.z, rg.w);
-      }
-    }
-    return r;
+  const int ncyc = (c1 - c0 + kRing - 1) / kRing;
+  const int nchunks = (ncyc + kChunkA - 1) / kChunkA;
+  const bool stager = tid < kChunkA * 2 * kRing;
+  const int st_cc = tid >> 5, st_q = tid & 31;
+  struct Src {
+    double4 r;
+    double2 g;
+    int v;
   };
-  auto stage_store = [&](int buf, const double4& r, const double2& gg) {
+  auto stage_load = [&](int ch) {
+    Src o = {make_double4(0.0, 0.0, 0.0, 0.0), make_double2(0.0, 0.0), -1};
+    const int j = c0 + (ch * kChunkA + st_cc) * kRing + (st_q & (kRing - 1));
+    if (stager && ch < nchunks) {
+      const int jj = min(j, c1 - 1);  // past the end: the last point with zero force and g
+      o.r = rec[jj];
+      o.v = vid[jj];
+      if (j >= c1)
+        o.r.z = o.r.w = 0.0;
+      else
+        o.g = make_double2(g[jj], g[(size_t)P + jj]);
+    }
+    return o;
+  };
+  auto stage_store = [&](int buf, const Src& o) {
     if (stager) {
-      s_rec[buf][st_cc][st_q] = r;
-      s_reg[buf][st_cc][st_q] = gg;
+      lds.rec[buf][st_cc][st_q] = o.r;
+      lds.g[buf][st_cc][st_q] = o.g;
+      lds.vid[buf][st_cc][st_q] = o.v;
     }
   };
-  // column sums of chunk g: v and H added over the wavefronts in a fixed order, one float64 atomic
-  // addition per (source, quantity, component)
-  auto reduce = [&](int g, int buf) {
+  // column sums of a chunk: v and H added over the wavefronts in a fixed order, one float64 atomic addition per
+  // (source, quantity, component)
+  auto reduce = [&](int ch, int buf) {
+    if (tid >= kChunkA * 4 * kRing) return;
     const int cc = tid >> 6, comp = (tid >> 4) & 3, m = tid & (kRing - 1);
-    const int c = sc0 + g * kChunk64 + cc;
-    if (cc >= kChunk64 || c >= sc1) return;
-    const int4 cy = cyc[c];
-    if (m >= cy.y) return;
-    const double v = ((s_col[buf][0][cc][comp][m] + s_col[buf][1][cc][comp][m]) + s_col[buf][2][cc][comp][m]) +
-                     s_col[buf][3][cc][comp][m];
+    const int j = c0 + (ch * kChunkA + cc) * kRing + m;
+    if (j >= c1) return;
+    const double v = ((lds.col[buf][0][cc][comp][m] + lds.col[buf][1][cc][comp][m]) + lds.col[buf][2][cc][comp][m]) +
+                     lds.col[buf][3][cc][comp][m];
     double* dst = comp < 2 ? vsum : gsum;
-    atomicAdd(&dst[(size_t)(comp & 1) * P + cy.x + m], v);
+    atomicAdd(&dst[(size_t)(comp & 1) * P + j], v);
   };
 
-  int curB = -1;
-  {
-    double2 g0;
-    const double4 r0 = stage_load(0, g0);
-    stage_store(0, r0, g0);
-  }
+  stage_store(0, stage_load(0));
   __syncthreads();
-  for (int g = 0; g < nchunks; ++g) {
-    const int buf = g & 1;
-    double2 ng;
-    const double4 nxt = stage_load(g + 1, ng);
-    if (g > 0) reduce(g - 1, buf ^ 1);
-    const int cbase = sc0 + g * kChunk64;
-    const int ncc = min(kChunk64, sc1 - cbase);
-    for (int cc = 0; cc < ncc; ++cc) {
-      const int4 cy = cyc[cbase + cc];
-      if (cy.z != curB) {
-        if (curB >= 0) flush();
-        setup(cy.z);
-        curB = cy.z;
-      }
-      ring(buf, cc);
-    }
-    stage_store(buf ^ 1, nxt, ng);
+  for (int ch = 0; ch < nchunks; ++ch) {
+    const int buf = ch & 1;
+    const Src nxt = stage_load(ch + 1);
+    if (ch > 0) reduce(ch - 1, buf ^ 1);
+    const int ncc = min(kChunkA, ncyc - ch * kChunkA);
+    if (masked)
+      for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::true_type{});
+    else
+      for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::false_type{});
+    stage_store(buf ^ 1, nxt);
     __syncthreads();
   }
-  if (nchunks > 0) {
-    reduce(nchunks - 1, (nchunks - 1) & 1);
-    flush();
-  }
+  reduce(nchunks - 1, (nchunks - 1) & 1);
 #pragma unroll
   for (int k = 0; k < T; ++k) {
-    if (ti[k].x >= 0 && p < ti[k].y) {
-      const int i = ti[k].z + p;
-      atomicAdd(&vsum[i], avx[k]);
-      atomicAdd(&vsum[(size_t)P + i], avy[k]);
-      atomicAdd(&gsum[i], agx[k]);
-      atomicAdd(&gsum[(size_t)P + i], agy[k]);
+    const int i = r0 + (k * kRows + row) * kRing + p;
+    if (i < r1) {
+      atomicAdd(&vsum[i], vx[k]);
+      atomicAdd(&vsum[(size_t)P + i], vy[k]);
+      atomicAdd(&gsum[i], hx[k]);
+      atomicAdd(&gsum[(size_t)P + i], hy[k]);
     }
   }
+}
+
+// One unit per workgroup, as k_sym64_main.
+template <int T>
+__global__ __launch_bounds__(kSymThreads) void k_sym64_bwd(int P, int ns, const double4* __restrict__ rec,
+                                                           const double* __restrict__ g,
+                                                           const int32_t* __restrict__ vid,
+                                                           const double2* __restrict__ tab,
+                                                           double* __restrict__ gsum, double* __restrict__ vsum) {
+  __shared__ Adj64Lds lds;
+  __shared__ double2 ltab[kSymTab];
+  constexpr int BP = kSymThreads * T;
+  const int L = xcd_contiguous(blockIdx.x, gridDim.x);
+  int bx, by;
+  sym_unit_blocks((P + BP - 1) / BP, L / ns, bx, by);
+  const int c0 = by * BP + (L % ns) * (BP / ns), c1 = min(P, c0 + BP / ns);
+  if (c0 >= c1) return;
+  for (int e = threadIdx.x; e < kSymTab; e += kSymThreads) ltab[e] = tab[e];
+  // the diagonal block's rows past the strip hold no pair of it; half the rows or fewer take the narrower form
+  const int r0 = bx * BP, r1 = min(bx == by ? c1 : P, r0 + BP);
+  if (T > 1 && r1 - r0 <= kSymThreads)
+    adj64_eval_unit<1>(lds, P, rec, g, vid, ltab, r0, r1, c0, c1, bx == by, gsum, vsum);
+  else
+    adj64_eval_unit<T>(lds, P, rec, g, vid, ltab, r0, r1, c0, c1, bx == by, gsum, vsum);
 }
 
 __global__ __launch_bounds__(256) void k_zero_f64(double* __restrict__ a, int64_t n) {
@@ -1826,32 +1807,30 @@ hipError_t launch_backward_symmetric(int T, int P, int M, const PreparedView& pv
   return hipGetLastError();
 }
 
-hipError_t launch_backward_symmetric64(int T, int P, int M, const PreparedView& pvF, const PreparedView& pvG,
-                                       const SymmetricView& sv, double* vsum, const double* f, const double* w,
-                                       double scale, double* grad_points, double* grad_f, double* grad_w,
-                                       void* stream) {
+hipError_t launch_backward_symmetric64(int T, int ns, int P, int M, const double* X, const double* f, const double* w,
+                                       const int32_t* off, const double* gout, const Adjoint64View& av, double scale,
+                                       double* grad_points, double* grad_f, double* grad_w, void* stream) {
   if (P == 0) return hipSuccess;
-  if (!grad_points || !vsum) return hipErrorInvalidValue;
+  if (!grad_points || ns < 1 || kRows % ns != 0) return hipErrorInvalidValue;
   hipStream_t st = Sx_(stream);
-  const int cb = sym_cycles_per_block(T);
-  const int ncyc_max = (int)sym_max_cycles(P, M);
-  const int nb_max = (int)sym_max_blocks(P, M, T);
-  hipLaunchKernelGGL(k_sym_plan, dim3(1), dim3(1024), 0, st, pvF.vrange, pvF.vaux, M, cb, ncyc_max, sv.cyc, sv.meta);
-  const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, grad_points, 2 * (int64_t)P);
-  hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, vsum, 2 * (int64_t)P);
-  const dim3 grid((unsigned)sym_units(nb_max));
-  const double4* recF = static_cast<const double4*>(pvF.rec);
-  const double4* recG = static_cast<const double4*>(pvG.rec);
+  const int igrid = (int)std::min<int64_t>(std::max<int64_t>(M, (2 * (int64_t)P + 255) / 256), 65535);
+  hipLaunchKernelGGL(k_sym64_adj_init, dim3(igrid), dim3(64), 0, st, X, f, w, off, M, P, av.rec, av.vid, av.tab, av.vsum,
+                     grad_points);
+  const int64_t units = sym_units(sym64_blocks(P, T)) * ns;
+  if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)units);
   switch (T) {
-    case 1: hipLaunchKernelGGL(k_sym64_bwd<1>, grid, dim3(kSymThreads), 0, st, recF, recG, sv.cyc, sv.meta, P,
-                               grad_points, vsum); break;
-    case 2: hipLaunchKernelGGL(k_sym64_bwd<2>, grid, dim3(kSymThreads), 0, st, recF, recG, sv.cyc, sv.meta, P,
-                               grad_points, vsum); break;
+#define VESNET_ADJ64_CASE(TT)                                                                                     \
+  case TT:                                                                                                        \
+    hipLaunchKernelGGL(k_sym64_bwd<TT>, grid, dim3(kSymThreads), 0, st, P, ns, av.rec, gout, av.vid, av.tab,      \
+                       grad_points, av.vsum);                                                                     \
+    break;
+    VESNET_ADJ64_CASE(1) VESNET_ADJ64_CASE(2) VESNET_ADJ64_CASE(3) VESNET_ADJ64_CASE(4)
+#undef VESNET_ADJ64_CASE
     default: return hipErrorInvalidValue;
   }
   const int fgrid = (P + 255) / 256 < 16384 ? (P + 255) / 256 : 16384;
-  hipLaunchKernelGGL(k_sym_bwd_finish, dim3(fgrid), dim3(256), 0, st, vsum, f, w, P, scale, grad_points, grad_f,
+  hipLaunchKernelGGL(k_sym_bwd_finish, dim3(fgrid), dim3(256), 0, st, av.vsum, f, w, P, scale, grad_points, grad_f,
                      grad_w);
   return hipGetLastError();
 }

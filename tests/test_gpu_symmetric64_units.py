@@ -131,3 +131,35 @@ def test_batched_float64_malformed_device_offsets(V):
     pr.sus_off.copy_(keep)
     assert torch.equal(pr.run(), good)
     pr.close()
+
+
+@pytest.mark.parametrize("total", [31, 256, 257, 513, 4097, 6145, 9217])
+def test_adjoint_point_counts_around_blocks_and_strips(V, total):
+    """Gradients of one float64 point array against the oracle's at one, two and three targets per thread's
+    edges; 1e-12 of the largest component, as in test_gpu_adjoint_points.py."""
+    import torch
+    s = _ragged_suspension(seed=total, sizes=_sizes(total, total), spacing=4.5)
+    g = np.random.default_rng(total).normal(size=s.X.shape)
+    X, f, w = dev_inputs(s)
+    got = V.farfield_backward_points(X, f, w, s.offsets, s.mu, torch.tensor(g, device="cuda"), "fp64")
+    ref = O.grad_suspension(s.X, s.f, s.w, s.offsets, s.mu, g)
+    for name, a in zip(("grad_X", "grad_f", "grad_w"), got):
+        err = float(np.abs(a.cpu().numpy() - ref[name]).max())
+        say(f"float64 adjoint P={total} {name}: {err:.3e}")
+        assert err <= 1e-12 * np.abs(ref[name]).max()
+
+
+def test_adjoint_not_finite_inputs_reach_the_gradients(V):
+    """A NaN in dL/du enters every gradient of the other vesicles and none of its own vesicle's other points."""
+    import torch
+    s = _ragged_suspension(seed=11, sizes=_sizes(1500, 5), spacing=4.5)
+    own = np.repeat(np.arange(s.n_vesicles), np.diff(s.offsets))
+    j = 700
+    g = np.random.default_rng(1).normal(size=s.X.shape)
+    g[0, j] = np.nan
+    X, f, w = dev_inputs(s)
+    gx, gf, _ = V.farfield_backward_points(X, f, w, s.offsets, s.mu, torch.tensor(g, device="cuda"), "fp64")
+    hit = own != own[j]
+    rest = ~hit & (np.arange(s.n_points) != j)
+    assert not np.isfinite(gx.cpu().numpy()[:, hit]).any() and not np.isfinite(gf.cpu().numpy()[:, hit]).any()
+    assert np.isfinite(gx.cpu().numpy()[:, rest]).all() and np.isfinite(gf.cpu().numpy()[:, rest]).all()
