@@ -152,6 +152,27 @@ int sym_default_T(int32_t P, int top) {
   return 0;
 }
 
+// Column strips per block pair of the compensated symmetric kernels at T targets per thread (powers of two): until
+// there are `want` units, while a strip keeps a chunk of eight source cycles.  Strips end at vesicle starts, so they
+// pay where the mean vesicle is a whole number of cycles that divides the strip (512 x 64, two vesicles per strip:
+// 348 -> 305 us forward) and come out uneven otherwise (200 vesicles of 100 to 128 points, two per strip: 217 -> 239
+// us; 1020 of 17 to 63 points: adjoint 1.287 -> 1.312 ms).  Fewer than four units per compute unit take strips of
+// four cycles and one vesicle too, whatever the sizes: the chip is idle without them.
+int sym_strips(int32_t P, int32_t M, int T, int64_t want) {
+  if (M < 1) return 1;
+  const int64_t vcyc = ((int64_t)P / M + 15) / 16;  // cycles of a mean vesicle
+  const int cb = sym_cycles_per_block(T);
+  const int64_t units = sym_units((vcyc * M + cb - 1) / cb);
+  const bool whole = vcyc > 0 && P == 16 * vcyc * M;
+  int ns = 1;
+  while (units * ns < want) {
+    const int64_t strip = cb / (2 * ns);
+    if (!(strip >= 8 && whole && strip % vcyc == 0) && !(units * ns < 1024 && strip >= 4 && strip >= vcyc)) break;
+    ns *= 2;
+  }
+  return sym_units(sym_max_blocks(P, M, T)) * ns <= (int64_t)INT32_MAX ? ns : 1;
+}
+
 // Targets per thread and column strips of the float64 symmetric form (T = 0: too small for it); want_T: the
 // caller's targets per thread, or 0.  Four targets per thread where that alone gives 4096 units (four rounds of
 // the 1024 workgroups that fit at once; 2000 x 128: 34.2 ms against 35.1 at two), else two, with strips until
@@ -231,6 +252,11 @@ int resolve_shape(const vesnet_tile_config* cfg, int32_t P, int32_t M, int prec,
   if (s.pair == 2 && s.accumulate == 2)
     return fail(VESNET_ERR_UNSUPPORTED, "the symmetric pair form accumulates on the VALU only");
   if (s.pair == 2 && s.symT == 0) s.symT = 1;
+  // Forward strips up to 4500 units: 512 x 64 348 -> 305 us (four strips), 504 x 32 111 -> 106 us (two), 64,000
+  // points 1.06 -> 1.03 ms (two); with more units (40,008 points, 4,656) strips gain nothing.  A caller's own targets_per_thread
+  // keeps whole block pairs (its result is then that of a batched call bit for bit).
+  if (prec == P32C && s.symT && !(s.pair == 2 && cfg && cfg->targets_per_thread))
+    s.symNs = sym_strips(P, M, s.symT, 4500);
   if (prec == P64 && s.symT) sym64_shape(P, s.symT, &s.symT, &s.symNs);
   auto fits = [&](int T) { return prec == P64 ? sym_units(sym64_blocks(P, T)) <= (int64_t)INT32_MAX : sym_fits(P, M, T); };
   if (s.symT && !fits(s.symT)) {
@@ -373,7 +399,7 @@ int evaluate_resolved(const double* targets, int32_t M, int32_t P, double mu, do
   if (symmetric) {
     if (s.pair != 2 && s.splits > 1) cur += align_up((size_t)2 * s.splits * P * sizeof(double));
     e = prec == P64 ? launch_forward_symmetric64(s.symT, s.symNs, P, M, pv, carve_symmetric64(cur, P), scale, out, stream)
-                    : launch_forward_symmetric(s.symT, P, M, pv, carve_symmetric(cur, P, M), scale, out, stream);
+                    : launch_forward_symmetric(s.symT, s.symNs, P, M, pv, carve_symmetric(cur, P, M), scale, out, stream);
     if (e != hipSuccess) return hip_fail(e, "symmetric forward launch");
   } else {
     double* partial = s.splits > 1 ? reinterpret_cast<double*>(cur) : nullptr;
@@ -1122,6 +1148,8 @@ extern "C" int vesnet_farfield_stokeslet_backward_points(const double* points, c
     return ok();
   }
   if (symT) {
+    // strips up to 4096 units: 512 x 64 backward 672 -> 630 us (two), 4,096 points 67 -> 45 us (four); 40,008 points
+    // with 4,656 units lose 2% by two
     // one symmetric pass: (points, w f) and (points, g) records, cycles and their sums of g
     PreparedView pvF = carve_prepared(cur, P, M, prec, true);
     PreparedView pvG = carve_prepared(cur, P, M, prec, true);
@@ -1130,7 +1158,7 @@ extern "C" int vesnet_farfield_stokeslet_backward_points(const double* points, c
     e = launch_prepare(prec, points, f, w, off, M, P, pvF, stream);
     if (e == hipSuccess) e = launch_prepare(prec, points, gout, nullptr, off, M, P, pvG, stream);
     if (e != hipSuccess) return hip_fail(e, "backward prepare launch");
-    e = launch_backward_symmetric(symT, P, M, pvF, pvG, sv, reinterpret_cast<double*>(sv.acc), f, w, scale, gx,
+    e = launch_backward_symmetric(symT, sym_strips(P, M, symT, 4096), P, M, pvF, pvG, sv, reinterpret_cast<double*>(sv.acc), f, w, scale, gx,
                                   grad_f, grad_w, stream);
     if (e != hipSuccess) return hip_fail(e, "symmetric backward launch");
     return ok();

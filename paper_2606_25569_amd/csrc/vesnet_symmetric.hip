@@ -207,13 +207,40 @@ __device__ __forceinline__ int xcd_contiguous(int g, int n) {
   return x * q + min(x, r) + g / kXcds;
 }
 
-__device__ __forceinline__ bool sym_unit(int nb, int& bx, int& by) {
+// First vesicle start at or after cycle c of the block's cycles [c0, c1) (c0 and c1 count as starts).  The same
+// for every lane; called by whole wavefronts.
+__device__ __forceinline__ int vesicle_cut(const int4* __restrict__ cyc, int c0, int c1, int c) {
+  if (c <= c0) return c0;
+  for (; c < c1; c += 64) {
+    const int e = c + (int)(threadIdx.x & 63);
+    const unsigned long long m = __ballot(e >= c1 || cyc[e].z != cyc[e - 1].z);
+    if (m) return min(c1, c + __ffsll(m) - 1);
+  }
+  return c1;
+}
+
+// The unit of this workgroup among the nb blocks' pairs, each cut into ns strips of the column block: row block
+// bx, column block by, and the strip's cycles [s0, s1) of block by's [by cb, min(ncyc, (by + 1) cb)); false when
+// it has none.  Strips end at vesicle starts, so that the float32 partial sums of a (target, vesicle) are the
+// same for every ns (a vesicle longer than a strip leaves the following ones empty).
+__device__ __forceinline__ bool sym_unit(int nb, int ns, int cb, int ncyc, const int4* __restrict__ cyc, int& bx,
+                                         int& by, int& s0, int& s1) {
   const int h = nb >> 1;
-  const int units = (nb & 1) ? nb * (h + 1) : nb * h + h;
+  const int units = ((nb & 1) ? nb * (h + 1) : nb * h + h) * ns;
   const int g = blockIdx.x;
   if (g >= units) return false;
-  sym_unit_blocks(nb, xcd_contiguous(g, units), bx, by);
-  return true;
+  const int L = xcd_contiguous(g, units);
+  sym_unit_blocks(nb, L / ns, bx, by);
+  const int c0 = by * cb, c1 = min(ncyc, c0 + cb);
+  if (ns == 1) {
+    s0 = c0;
+    s1 = c1;
+  } else {
+    const int k = L % ns, w = cb / ns;
+    s0 = vesicle_cut(cyc, c0, c1, c0 + k * w);
+    s1 = k == ns - 1 ? c1 : vesicle_cut(cyc, c0, c1, c0 + (k + 1) * w);
+  }
+  return s0 < s1;
 }
 
 // One unit: target cycles [tc0, tc1) against source cycles [sc0, sc1) (diag: the two blocks are one),
@@ -459,7 +486,7 @@ __device__ __forceinline__ void sym_eval_unit(int P, const double4* __restrict__
 // One unit {bx, by} per workgroup (see the file header).
 template <int T>
 __global__ __launch_bounds__(kSymThreads) void k_sym_main(
-    int P, const double4* __restrict__ vtab, const double2* __restrict__ vaux, const float4* __restrict__ rec,
+    int P, int ns, const double4* __restrict__ vtab, const double2* __restrict__ vaux, const float4* __restrict__ rec,
     const int4* __restrict__ cyc, const double2* __restrict__ fcyc, const int32_t* __restrict__ meta,
     unsigned long long* __restrict__ acc) {
   constexpr int CB = kRows * T;
@@ -467,11 +494,10 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_main(
   const int S = meta[1];
   const int nb = meta[2];
   if (nb <= 0) return;
-  int bx, by;
-  if (!sym_unit(nb, bx, by)) return;
-  const int tc0 = bx * CB, sc0 = by * CB;
-  sym_eval_unit<T>(P, vtab, vaux, rec, cyc, fcyc, S, tc0, min(ncyc, tc0 + CB), sc0, min(ncyc, sc0 + CB), bx == by,
-                   acc);
+  int bx, by, s0, s1;
+  if (!sym_unit(nb, ns, CB, ncyc, cyc, bx, by, s0, s1)) return;
+  const int tc0 = bx * CB;
+  sym_eval_unit<T>(P, vtab, vaux, rec, cyc, fcyc, S, tc0, min(ncyc, tc0 + CB), s0, s1, bx == by, acc);
 }
 
 // ------------------------------------------------------------------ float64 symmetric form
@@ -1189,7 +1215,7 @@ template <int T>
 __global__ __launch_bounds__(kSymThreads) void k_sym_bwd(
     const double4* __restrict__ vtab, const double2* __restrict__ vaux, const float4* __restrict__ recF,
     const float4* __restrict__ recG, const int4* __restrict__ cyc, const double2* __restrict__ gcyc,
-    const int32_t* __restrict__ meta, int P, double* __restrict__ gsum, double* __restrict__ vsum) {
+    const int32_t* __restrict__ meta, int P, int strips, double* __restrict__ gsum, double* __restrict__ vsum) {
   constexpr int CB = kRows * T;
   __shared__ float4 s_tx[CB][kRing];               // target records (local coordinates, w f)
   __shared__ float2 s_tg[CB][kRing];               // target g
@@ -1204,14 +1230,13 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_bwd(
   const int ncyc = meta[0];
   const int nb = meta[2];
   if (nb <= 0) return;
-  int bx, by;
-  if (!sym_unit(nb, bx, by)) return;
+  int bx, by, sc0, sc1;
+  if (!sym_unit(nb, strips, CB, ncyc, cyc, bx, by, sc0, sc1)) return;
   const bool diag = bx == by;
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = lane & 15;
   const int row = tid >> 4;
   const int tc0 = bx * CB, tc1 = min(ncyc, tc0 + CB);
-  const int sc0 = by * CB, sc1 = min(ncyc, sc0 + CB);
 
   for (int e = tid; e < CB * kRing; e += kSymThreads) {
     const int t = e / kRing, m = e % kRing;
@@ -1772,7 +1797,7 @@ int64_t sym_units(int64_t nb) {
 
 bool sym_fits(int P, int M, int T) { return sym_units(sym_max_blocks(P, M, T)) <= (int64_t)INT32_MAX; }
 
-hipError_t launch_backward_symmetric(int T, int P, int M, const PreparedView& pvF, const PreparedView& pvG,
+hipError_t launch_backward_symmetric(int T, int ns, int P, int M, const PreparedView& pvF, const PreparedView& pvG,
                                      const SymmetricView& sv, double* vsum, const double* f, const double* w,
                                      double scale, double* grad_points, double* grad_f, double* grad_w,
                                      void* stream) {
@@ -1788,14 +1813,14 @@ hipError_t launch_backward_symmetric(int T, int P, int M, const PreparedView& pv
   hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pvG.f64, P, sv.fcyc, sv.acc);
   hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, grad_points, 2 * (int64_t)P);
   hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, vsum, 2 * (int64_t)P);
-  const dim3 grid((unsigned)sym_units(nb_max));
+  const dim3 grid((unsigned)(sym_units(nb_max) * ns));
   const float4* recF = static_cast<const float4*>(pvF.rec);
   const float4* recG = static_cast<const float4*>(pvG.rec);
   switch (T) {
 #define VESNET_SYMB_CASE(TT)                                                                                   \
   case TT:                                                                                                     \
     hipLaunchKernelGGL(k_sym_bwd<TT>, grid, dim3(kSymThreads), 0, st, pvF.vtab, pvF.vaux, recF, recG, sv.cyc,  \
-                       sv.fcyc, sv.meta, P, grad_points, vsum);                                                 \
+                       sv.fcyc, sv.meta, P, ns, grad_points, vsum);                                             \
     break;
     VESNET_SYMB_CASE(1) VESNET_SYMB_CASE(2) VESNET_SYMB_CASE(3) VESNET_SYMB_CASE(4)
 #undef VESNET_SYMB_CASE
@@ -1972,7 +1997,7 @@ hipError_t launch_forward_symmetric64(int T, int ns, int P, int M, const Prepare
   return hipGetLastError();
 }
 
-hipError_t launch_forward_symmetric(int T, int P, int M, const PreparedView& pv, const SymmetricView& sv,
+hipError_t launch_forward_symmetric(int T, int ns, int P, int M, const PreparedView& pv, const SymmetricView& sv,
                                     double scale, double* out, void* stream) {
   if (P == 0) return hipSuccess;
   hipStream_t st = Sx_(stream);
@@ -1982,12 +2007,12 @@ hipError_t launch_forward_symmetric(int T, int P, int M, const PreparedView& pv,
   hipLaunchKernelGGL(k_sym_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, M, cb, ncyc_max, sv.cyc, sv.meta);
   const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
   hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pv.f64, P, sv.fcyc, sv.acc);
-  const dim3 grid((unsigned)sym_units(nb_max));
+  const dim3 grid((unsigned)(sym_units(nb_max) * ns));
   const float4* rec = static_cast<const float4*>(pv.rec);
   switch (T) {
 #define VESNET_SYM_CASE(TT)                                                                                    \
   case TT:                                                                                                     \
-    hipLaunchKernelGGL(k_sym_main<TT>, grid, dim3(kSymThreads), 0, st, P, pv.vtab, pv.vaux, rec, sv.cyc,      \
+    hipLaunchKernelGGL(k_sym_main<TT>, grid, dim3(kSymThreads), 0, st, P, ns, pv.vtab, pv.vaux, rec, sv.cyc,   \
                        sv.fcyc, sv.meta, sv.acc);                                                               \
     break;
     VESNET_SYM_CASE(1) VESNET_SYM_CASE(2) VESNET_SYM_CASE(3) VESNET_SYM_CASE(4) VESNET_SYM_CASE(8)
