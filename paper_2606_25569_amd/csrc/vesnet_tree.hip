@@ -17,13 +17,13 @@
 // directly, skipping its own vesicle; own-vesicle sources outside those leaves, which the expansions
 // included, are subtracted exactly (k_tc_own).  Everything is FP64.
 //
-// Treecode: every target evaluates the series of every box of its lists (k_tc_eval<false>); the
+// Treecode: every target evaluates the series of every box of its lists (k_tc_eval); the
 // evaluation merges the conj-F log series and Psi into one series D, and writes w conj(Phi) as
 // (w / conj w) conj(E), E = sum_k M_k[F] t^k: three Horner chains per box.
 // Fast multipole method: each box's series becomes a Taylor polynomial of degree p about the centre of
 // every box whose list holds it (k_fmm_m2l, on the matrix cores), the polynomials of a leaf's ancestors
 // are re-centred onto the leaf (k_fmm_l2l), and every target evaluates its leaf's polynomial
-// (k_tc_eval<true>).
+// (k_fmm_eval).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -810,54 +810,20 @@ __device__ __forceinline__ void direct_term(double zx, double zy, double sx, dou
   uy = fma(lg, Fy, fma(s, ry, uy));
 }
 
-// Walk over the interaction lists of a leaf (ix, iy), levels 2..depth, candidates in a fixed order;
-// the same in every lane.  Yields the non-empty boxes (level, sx, sy).
-struct ListWalk {
-  int l, a, b;
-};
-
-__device__ __forceinline__ bool next_box(ListWalk& s, int depth, int ix, int iy, const int32_t* __restrict__ bcount,
-                                         int& lo, int& sxo, int& syo) {
-  while (s.l <= depth) {
-    const int l = s.l, nl = 1 << l;
-    const int bx = ix >> (depth - l), by = iy >> (depth - l);
-    const int sx = 2 * (bx >> 1) + s.a, sy = 2 * (by >> 1) + s.b;
-    if (++s.b > 3) {
-      s.b = -2;
-      if (++s.a > 3) {
-        s.a = -2;
-        ++s.l;
-      }
-    }
-    if (sx < 0 || sx >= nl || sy < 0 || sy >= nl) continue;
-    if (abs(sx - bx) <= 1 && abs(sy - by) <= 1) continue;
-    if (bcount[level_box_base(l) + (size_t)sx * nl + sy] == 0) continue;
-    lo = l;
-    sxo = sx;
-    syo = sy;
-    return true;
-  }
-  return false;
-}
-
-// Targets per wavefront of the evaluation: the treecode's far part costs the same per wavefront whatever
-// its target count, so it takes 64; the fast multipole method's is a short polynomial per target and
-// takes 16, four times the wavefronts to hide the direct part's latencies (at 2000 x 128, order 30:
+// Targets per wavefront of the fast multipole method's evaluation: its far part is a short polynomial per target,
+// and 16 targets give four times the wavefronts of 64 to hide the direct part's latencies (at 2000 x 128, order 30:
 // 0.58 ms against 0.63 ms at 32 and 0.60 ms at 8 targets).
-template <bool kFmm> constexpr int eval_chunk_shift() { return kFmm ? 4 : 6; }
+constexpr int kFmmChunkShift = 4;
 
-// One wavefront per (leaf, chunk of kChunk of its points); every lane one target.  The far part is the
-// treecode's walk over the interaction lists (kFmm false: mom holds the finalised moments) or the leaf's
-// local expansion (kFmm true: loc holds it); the direct part is shared.
-template <bool kFmm>
-__global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, const double* __restrict__ f,
+// One wavefront per (leaf, chunk of kChunk of its points); every lane one target: the leaf's local expansion and the
+// 3 x 3 leaves around it directly.
+__global__ __launch_bounds__(64) void k_fmm_eval(const double* __restrict__ X, const double* __restrict__ f,
                                                 const double* __restrict__ w, int P, const int32_t* __restrict__ vid,
                                                 const int32_t* __restrict__ perm, const int32_t* __restrict__ starts,
                                                 const int32_t* __restrict__ wstart, const Geom* __restrict__ geom,
-                                                int depth, int p, const double2* __restrict__ mom,
-                                                const double2* __restrict__ loc, const int32_t* __restrict__ bcount,
-                                                double scale, double* __restrict__ out) {
-  constexpr int kChunk = 1 << eval_chunk_shift<kFmm>();
+                                                int depth, int p, const double2* __restrict__ loc, double scale,
+                                                double* __restrict__ out) {
+  constexpr int kChunk = 1 << kFmmChunkShift;
   const int n = 1 << depth;
   const int nleaf = n * n;
   const int item = blockIdx.x;
@@ -886,7 +852,6 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, co
   const int vi = vid[i];
   const int ix = leaf / n, iy = leaf % n;
   const Geom g = *geom;
-  const int stride = 4 * (p + 1);
   double ux = 0.0, uy = 0.0;
   // per-wavefront staging: the moments of one box, then chunks of 64 direct sources
   __shared__ double2 cf[4 * 64];  // 4 (p + 1) <= 196 entries used; padded for whole-wave copies
@@ -895,82 +860,23 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, co
   __shared__ double2 ltab[kLogTab];
   ltab[threadIdx.x] = log_tab_entry(threadIdx.x);  // read after the first barrier below
 
-  if constexpr (kFmm) {
-    // the leaf's local expansion: u += -A(zeta)/2 - conj(B(zeta))/2 + zeta conj(C(zeta))/2
-    if (depth >= 2) {
-      const double2* lb = loc + (level_box_base(depth) + (size_t)leaf) * 3 * (p + 1);
-      cf[threadIdx.x] = lb[threadIdx.x];  // 3 x 64 >= 3 (kMaxOrder + 1); the array has 192 spare entries
-      cf[threadIdx.x + 64] = lb[threadIdx.x + 64];
-      cf[threadIdx.x + 128] = lb[threadIdx.x + 128];
-      __syncthreads();
-      const double2 c = box_center(g, n, ix, iy);
-      const double2 zt = make_double2(zx - c.x, zy - c.y);
-      double2 A = cf[p], B = cf[2 * p + 1], C = cf[3 * p + 2];
-      for (int k = p - 1; k >= 0; --k) {
-        A = cfma(A, zt, cf[k]);
-        B = cfma(B, zt, cf[(p + 1) + k]);
-        C = cfma(C, zt, cf[2 * (p + 1) + k]);
-      }
-      ux += -0.5 * A.x - 0.5 * B.x + 0.5 * (zt.x * C.x + zt.y * C.y);
-      uy += -0.5 * A.y + 0.5 * B.y + 0.5 * (zt.y * C.x - zt.x * C.y);
+  // the leaf's local expansion: u += -A(zeta)/2 - conj(B(zeta))/2 + zeta conj(C(zeta))/2
+  if (depth >= 2) {
+    const double2* lb = loc + (level_box_base(depth) + (size_t)leaf) * 3 * (p + 1);
+    cf[threadIdx.x] = lb[threadIdx.x];  // 3 x 64 >= 3 (kMaxOrder + 1); the array has 192 spare entries
+    cf[threadIdx.x + 64] = lb[threadIdx.x + 64];
+    cf[threadIdx.x + 128] = lb[threadIdx.x + 128];
+    __syncthreads();
+    const double2 c = box_center(g, n, ix, iy);
+    const double2 zt = make_double2(zx - c.x, zy - c.y);
+    double2 A = cf[p], B = cf[2 * p + 1], C = cf[3 * p + 2];
+    for (int k = p - 1; k >= 0; --k) {
+      A = cfma(A, zt, cf[k]);
+      B = cfma(B, zt, cf[(p + 1) + k]);
+      C = cfma(C, zt, cf[2 * (p + 1) + k]);
     }
-  } else {
-    // expansions of the interaction lists: box by box, the next box's moments loaded into registers
-    // while the current one is evaluated from LDS
-    // four entries per lane: 4 x 64 >= 4 (kMaxOrder + 1); the moment array has 256 spare entries
-    double2 n0 = make_double2(0.0, 0.0), n1 = n0, n2 = n0, n3 = n0;
-    ListWalk it = {2, -2, -2};
-    int nl_ = 0, nsx = 0, nsy = 0;
-    bool have = next_box(it, depth, ix, iy, bcount, nl_, nsx, nsy);
-    if (have) {
-      const double2* mb = mom + (level_box_base(nl_) + (size_t)nsx * (1 << nl_) + nsy) * stride;
-      n0 = mb[threadIdx.x];
-      n1 = mb[threadIdx.x + 64];
-      n2 = mb[threadIdx.x + 128];
-      n3 = mb[threadIdx.x + 192];
-    }
-    while (have) {
-      __syncthreads();  // the previous box is done with cf
-      cf[threadIdx.x] = n0;
-      cf[threadIdx.x + 64] = n1;
-      cf[threadIdx.x + 128] = n2;
-      cf[threadIdx.x + 192] = n3;
-      __syncthreads();
-      const int l = nl_, sx = nsx, sy = nsy;
-      have = next_box(it, depth, ix, iy, bcount, nl_, nsx, nsy);
-      if (have) {
-        const double2* mb = mom + (level_box_base(nl_) + (size_t)nsx * (1 << nl_) + nsy) * stride;
-        n0 = mb[threadIdx.x];
-        n1 = mb[threadIdx.x + 64];
-        n2 = mb[threadIdx.x + 128];
-        n3 = mb[threadIdx.x + 192];
-      }
-      {
-        const double2 c = box_center(g, 1 << l, sx, sy);
-        const double2 wv = make_double2(zx - c.x, zy - c.y);
-        const double w2 = wv.x * wv.x + wv.y * wv.y;
-        const double2 t = make_double2(wv.x / w2, -wv.y / w2);
-        // Three series in t, highest order first:
-        //   S = sum_{k>=1} M_k[F] / k t^k,  D = sum_k D_k t^(k+1),  E = sum_k M_k[F] t^k;
-        // the box contributes S/2 + M_0/2 - M_0 ln|w| + conj(D) + (w / conj w) conj(E) / 2.
-        double2 aS = make_double2(0.0, 0.0), aD = aS, aE = aS;
-        for (int k = p; k >= 1; --k) {
-          aS = cfma(aS, t, cf[3 * (p + 1) + k]);
-          aD = cfma(aD, t, cf[2 * (p + 1) + k]);
-          aE = cfma(aE, t, cf[k]);
-        }
-        const double2 M0 = cf[0];
-        aD = cfma(aD, t, cf[2 * (p + 1)]);
-        aE = cfma(aE, t, M0);
-        aS = cmul(aS, t);
-        aD = cmul(aD, t);
-        const double lnw = 0.5 * log_pos(w2);
-        const double2 rot = make_double2((wv.x * wv.x - wv.y * wv.y) / w2, 2.0 * wv.x * wv.y / w2);  // w / conj w
-        const double2 pe = cmul(rot, make_double2(aE.x, -aE.y));
-        ux += 0.5 * aS.x + 0.5 * M0.x - M0.x * lnw + aD.x + 0.5 * pe.x;
-        uy += 0.5 * aS.y + 0.5 * M0.y - M0.y * lnw - aD.y + 0.5 * pe.y;
-      }
-    }
+    ux += -0.5 * A.x - 0.5 * B.x + 0.5 * (zt.x * C.x + zt.y * C.y);
+    uy += -0.5 * A.y + 0.5 * B.y + 0.5 * (zt.y * C.x - zt.x * C.y);
   }
   // 3 x 3 leaves directly, own vesicle skipped
   double dx = 0.0, dy = 0.0;
@@ -1015,6 +921,184 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, co
   if (active && lane < K) {
     out[i] = (ux + dx) * scale;
     out[P + i] = (uy + dy) * scale;
+  }
+}
+
+// ---------------------------------------------------------------- treecode evaluation
+//
+// One wavefront per (leaf, chunk of 2 L of its points): L lanes take two targets each, and the G = 64 / L lane groups
+// share the work, in the far part every G-th box of the interaction lists and in the direct part every G-th source;
+// the groups' sums are added at the end.  (With one target per lane and 64 per wavefront, leaves of about 20 points
+// left two thirds of the lanes repeating the others' boxes; and the three Horner chains read 48 bytes of LDS per 12
+// FMAs, twice what LDS delivers beside the FMAs: two targets per lane use each coefficient twice.)
+// The list of boxes is made level by level with one candidate per lane; each step stages the coefficients of G boxes
+// (rows M, D and M / k) in LDS.  What bounds it is float64 VALU issue (73% of the kernel's cycles at L = 16).  Whole
+// calls: 89,457 ragged points, order 20, depth 6, 580 -> 402 us; 29,283, order 30, 347 -> 207 us; 2000 x 128, order
+// 30, 1.26 -> 1.11 ms.
+constexpr int kTreeT = 2;  // targets per lane
+
+// L = 16 where the leaves average more than 44 points, else 8: chunks of 32 leave a sparse leaf's wavefront half
+// empty (28 points per leaf: 249 us at 16, 207 at 8), chunks of 16 stage twice as many boxes per target (62 per
+// leaf: 1.11 ms at 16, 1.30 at 8).
+int tree_lanes(int P, int depth) { return (int64_t)P > (int64_t)44 << (2 * depth) ? 16 : 8; }
+
+constexpr int kListMax = 27 * (kMaxDepth - 1);     // boxes of all interaction lists of a leaf
+
+// Box of a list entry: level in bits 20-23, column in 10-19, row in 0-9.
+__device__ __forceinline__ int list_entry(int l, int sx, int sy) { return l << 20 | sx << 10 | sy; }
+
+template <int kTreeLanes>
+__global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, const double* __restrict__ f,
+                                                const double* __restrict__ w, int P, const int32_t* __restrict__ vid,
+                                                const int32_t* __restrict__ perm, const int32_t* __restrict__ starts,
+                                                const int32_t* __restrict__ wstart, const Geom* __restrict__ geom,
+                                                int depth, int p, const double2* __restrict__ mom,
+                                                const int32_t* __restrict__ bcount, double scale,
+                                                double* __restrict__ out) {
+  constexpr int kTreeGroups = 64 / kTreeLanes;
+  extern __shared__ double2 cf[];  // [kTreeGroups][3 (p + 1)] coefficients of the step's boxes
+  __shared__ int32_t list[kListMax + 1];
+  __shared__ double4 src[64];
+  __shared__ int32_t sv[64];
+  __shared__ double2 ltab[kLogTab];
+  const int n = 1 << depth;
+  const int nleaf = n * n;
+  const int item = blockIdx.x;
+  if (item >= wstart[nleaf]) return;
+  int lo = 0, hi = nleaf;  // wstart[lo] <= item < wstart[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (wstart[mid] <= item) lo = mid; else hi = mid;
+  }
+  const int leaf = lo;
+  const int s0 = starts[leaf], s1 = starts[leaf + 1];
+  const int lane = threadIdx.x, tl = lane & (kTreeLanes - 1), grp = lane / kTreeLanes;
+  ltab[lane] = log_tab_entry(lane);
+  const int base = s0 + (item - wstart[leaf]) * kTreeT * kTreeLanes;
+  double zx[kTreeT], zy[kTreeT], ux[kTreeT], uy[kTreeT];
+  int ti[kTreeT], vi[kTreeT];
+#pragma unroll
+  for (int k = 0; k < kTreeT; ++k) {
+    const int slot = base + tl + kTreeLanes * k;
+    ti[k] = perm[slot < s1 ? slot : base];  // an empty slot repeats the first target
+    zx[k] = X[ti[k]];
+    zy[k] = X[P + ti[k]];
+    vi[k] = vid[ti[k]];
+    ux[k] = uy[k] = 0.0;
+  }
+  const int ix = leaf / n, iy = leaf % n;
+  const Geom g = *geom;
+  // the non-empty boxes of the interaction lists, levels 2 .. depth: lane c examines candidate c of a level
+  int nbox = 0;
+  for (int l = 2; l <= depth; ++l) {
+    const int nl = 1 << l, bx = ix >> (depth - l), by = iy >> (depth - l);
+    const int sx = 2 * (bx >> 1) + lane / 6 - 2, sy = 2 * (by >> 1) + lane % 6 - 2;
+    bool ok = lane < 36 && sx >= 0 && sx < nl && sy >= 0 && sy < nl && (abs(sx - bx) > 1 || abs(sy - by) > 1);
+    if (ok) ok = bcount[level_box_base(l) + (size_t)sx * nl + sy] != 0;
+    const unsigned long long m = __ballot(ok);
+    if (ok) list[nbox + __popcll(m & ((1ull << lane) - 1ull))] = list_entry(l, sx, sy);
+    nbox += __popcll(m);
+  }
+  wave_sync();
+  const int np = p + 1, row3 = 3 * np;
+  const unsigned inv_row3 = (1u << 20) / (unsigned)row3 + 1u;  // e / row3 = e inv_row3 / 2^20 for e < 8 row3 <= 1176
+  for (int b0 = 0; b0 < nbox; b0 += kTreeGroups) {
+    wave_sync();  // the previous step is done with cf
+    {
+      // entry e of the step's coefficients: box e / (3 np), then rows M, D, M / k (rows 0, 2 and 3 of the moments);
+      // four loads in flight per lane
+      const int cnt = min(kTreeGroups, nbox - b0) * row3;
+      for (int e0 = lane; e0 < cnt; e0 += 256) {
+        double2 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int e = min(e0 + 64 * u, cnt - 1);
+          const int b = (int)(((unsigned)e * inv_row3) >> 20);
+          const int r = e - b * row3;
+          const int en = list[b0 + b], l = en >> 20;
+          const size_t box = level_box_base(l) + (size_t)((en >> 10) & 1023) * (1 << l) + (en & 1023);
+          v[u] = mom[box * 4 * np + r + (r >= np ? np : 0)];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (e0 + 64 * u < cnt) cf[e0 + 64 * u] = v[u];
+      }
+    }
+    wave_sync();
+    if (b0 + grp < nbox) {
+      const int en = list[b0 + grp];
+      const double2 c = box_center(g, 1 << (en >> 20), (en >> 10) & 1023, en & 1023);
+      const double2* cb = cf + grp * row3;
+      // Three series in t = 1 / w, highest order first:
+      //   S = sum_{k>=1} M_k[F] / k t^k,  D = sum_k D_k t^(k+1),  E = sum_k M_k[F] t^k;
+      // the box contributes S/2 + M_0/2 - M_0 ln|w| + conj(D) + (w / conj w) conj(E) / 2.
+      double2 wv[kTreeT], t[kTreeT], aS[kTreeT], aD[kTreeT], aE[kTreeT];
+      double w2[kTreeT], rw[kTreeT];
+#pragma unroll
+      for (int k = 0; k < kTreeT; ++k) {
+        wv[k] = make_double2(zx[k] - c.x, zy[k] - c.y);
+        w2[k] = wv[k].x * wv[k].x + wv[k].y * wv[k].y;
+        rw[k] = recip(w2[k]);
+        t[k] = make_double2(wv[k].x * rw[k], -wv[k].y * rw[k]);
+        aS[k] = aD[k] = aE[k] = make_double2(0.0, 0.0);
+      }
+#pragma unroll 1
+      for (int q = p; q >= 1; --q) {
+        const double2 cE = cb[q], cD = cb[np + q], cS = cb[2 * np + q];
+#pragma unroll
+        for (int k = 0; k < kTreeT; ++k) {
+          aS[k] = cfma(aS[k], t[k], cS);
+          aD[k] = cfma(aD[k], t[k], cD);
+          aE[k] = cfma(aE[k], t[k], cE);
+        }
+      }
+      const double2 M0 = cb[0], D0 = cb[np];
+#pragma unroll
+      for (int k = 0; k < kTreeT; ++k) {
+        const double2 e = cfma(aE[k], t[k], M0);
+        const double2 d = cmul(cfma(aD[k], t[k], D0), t[k]);
+        const double2 sS = cmul(aS[k], t[k]);
+        const double lnw = 0.5 * log_reduced(w2[k], ltab);
+        const double2 rot = make_double2((wv[k].x * wv[k].x - wv[k].y * wv[k].y) * rw[k],
+                                         2.0 * wv[k].x * wv[k].y * rw[k]);  // w / conj w
+        const double2 pe = cmul(rot, make_double2(e.x, -e.y));
+        ux[k] += 0.5 * sS.x + 0.5 * M0.x - M0.x * lnw + d.x + 0.5 * pe.x;
+        uy[k] += 0.5 * sS.y + 0.5 * M0.y - M0.y * lnw - d.y + 0.5 * pe.y;
+      }
+    }
+  }
+  // 3 x 3 leaves directly, own vesicle skipped: the three leaves of a column are one run of the leaf order
+  for (int jx = max(ix - 1, 0); jx <= min(ix + 1, n - 1); ++jx) {
+    const int e0 = starts[jx * n + max(iy - 1, 0)], e1 = starts[jx * n + min(iy + 1, n - 1) + 1];
+    for (int c0 = e0; c0 < e1; c0 += 64) {
+      const int cnt = min(64, e1 - c0);
+      wave_sync();  // the previous chunk is done
+      if (lane < cnt) {
+        const int j = perm[c0 + lane];
+        src[lane] = make_double4(X[j], X[P + j], w[j] * f[j], w[j] * f[P + j]);
+        sv[lane] = vid[j];
+      }
+      wave_sync();
+      for (int q = grp; q < cnt; q += kTreeGroups) {
+        const double4 s = src[q];
+        const int cv = sv[q];
+#pragma unroll
+        for (int k = 0; k < kTreeT; ++k)
+          if (cv != vi[k]) direct_term(zx[k], zy[k], s.x, s.y, s.z, s.w, ltab, ux[k], uy[k]);
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kTreeT; ++k) {  // the groups' sums, pairwise in a fixed order
+#pragma unroll
+    for (int o = kTreeLanes; o < 64; o <<= 1) {
+      ux[k] += __shfl_xor(ux[k], o);
+      uy[k] += __shfl_xor(uy[k], o);
+    }
+    if (grp == 0 && base + tl + kTreeLanes * k < s1) {
+      out[ti[k]] = ux[k] * scale;
+      out[P + ti[k]] = uy[k] * scale;
+    }
   }
 }
 
@@ -1153,7 +1237,7 @@ __global__ __launch_bounds__(64) void k_fmm_near(const double* __restrict__ X, c
                                                 const double* __restrict__ h2, double scale, double* __restrict__ out,
                                                 int32_t* __restrict__ pairs, int capacity, int32_t* __restrict__ count,
                                                 int32_t* __restrict__ flag) {
-  constexpr int kChunk = 1 << eval_chunk_shift<true>();
+  constexpr int kChunk = 1 << kFmmChunkShift;
   constexpr int kGroups = 64 / kChunk;  // lanes per target: group g scans every kGroups-th source from g on
   static_assert(kGroups >= 2 && kGroups * kChunk == 64, "a power-of-two chunk of at most 32 targets");
   __shared__ double sx_[kNearStage], sy_[kNearStage], sh[kNearStage];
@@ -1433,15 +1517,12 @@ void launch_upward(const double* X, const double* f, const double* w, const int3
   }
 }
 
-template <bool kFmm>
-void launch_eval(const double* X, const double* f, const double* w, const int32_t* off, int M, int P, int p, int depth,
-                 double scale, const TreeRun& r, double* out, hipStream_t st) {
-  const int nleaf = 1 << (2 * depth);
-  constexpr int kChunk = 1 << eval_chunk_shift<kFmm>();
-  const int items = nleaf + (P + kChunk - 1) / kChunk;  // bound on sum over leaves of ceil(count / kChunk)
-  hipLaunchKernelGGL(k_tc_eval<kFmm>, dim3(items), dim3(64), 0, st, X, f, w, P, r.vid, r.perm, r.starts, r.wstart,
-                     r.geom, depth, p, r.mom, r.loc, r.bcount, scale, out);
-  // without expansions (depth < 2) every own-vesicle source is in the 3 x 3 leaves
+// Work items of an evaluation: a bound on sum over leaves of ceil(count / 2^shift).
+int eval_items(int P, int depth, int shift) { return (1 << (2 * depth)) + ((P + (1 << shift) - 1) >> shift); }
+
+// Own-vesicle correction; without expansions (depth < 2) every own-vesicle source is in the 3 x 3 leaves.
+void launch_own(const double* X, const double* f, const double* w, const int32_t* off, int M, int P, int depth,
+                double scale, const TreeRun& r, double* out, hipStream_t st) {
   if (depth >= 2)
     hipLaunchKernelGGL(k_tc_own, dim3(M), dim3(kOwnThreads), 0, st, X, f, w, P, off, r.leafid, depth, scale, out);
 }
@@ -1455,13 +1536,22 @@ hipError_t launch_treecode(const double* X, const double* f, const double* w, co
   if (depth < 0 || depth > kMaxDepth || p < 1 || p > kMaxOrder) return hipErrorInvalidValue;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, false), depth, p);
-  launch_upward(X, f, w, off, M, P, p, depth, eval_chunk_shift<false>(), false, false, r, st);
+  const int lanes = tree_lanes(P, depth), shift = lanes == 16 ? 5 : 4;  // 2 lanes targets per wavefront
+  launch_upward(X, f, w, off, M, P, p, depth, shift, false, false, r, st);
   if (depth >= 2) {
     const size_t work = r.nbox * (p + 1);
     const int gb = (int)((work + kTB - 1) / kTB < 4096 ? (work + kTB - 1) / kTB : 4096);
     hipLaunchKernelGGL(k_tc_finalize, dim3(gb), dim3(kTB), 0, st, r.mom, r.nbox, p);
   }
-  launch_eval<false>(X, f, w, off, M, P, p, depth, scale, r, out, st);
+  const dim3 grid((unsigned)eval_items(P, depth, shift));
+  const size_t lds = sizeof(double2) * (size_t)(64 / lanes) * 3 * (p + 1);
+  if (lanes == 16)
+    hipLaunchKernelGGL(k_tc_eval<16>, grid, dim3(64), lds, st, X, f, w, P, r.vid, r.perm, r.starts, r.wstart, r.geom,
+                       depth, p, r.mom, r.bcount, scale, out);
+  else
+    hipLaunchKernelGGL(k_tc_eval<8>, grid, dim3(64), lds, st, X, f, w, P, r.vid, r.perm, r.starts, r.wstart, r.geom,
+                       depth, p, r.mom, r.bcount, scale, out);
+  launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   return hipGetLastError();
 }
 
@@ -1470,7 +1560,7 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
                           int32_t* pairs, int capacity, int32_t* count) {
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, true, near ? M : 0), depth, p);
   if (near) hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(kTB), 0, st, count, r.flag, 1);
-  launch_upward(X, f, w, off, M, P, p, depth, eval_chunk_shift<true>(), depth >= 2, near, r, st);
+  launch_upward(X, f, w, off, M, P, p, depth, kFmmChunkShift, depth >= 2, near, r, st);
   if (depth >= 2) {
     const dim3 g((unsigned)r.nbox), bl(64);
     const size_t lds = m2l_lds_bytes(p);
@@ -1486,11 +1576,11 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
                          st, r.geom, depth, p, r.bcount, r.loc);
     }
   }
-  launch_eval<true>(X, f, w, off, M, P, p, depth, scale, r, out, st);
+  const int items = eval_items(P, depth, kFmmChunkShift);
+  hipLaunchKernelGGL(k_fmm_eval, dim3(items), dim3(64), 0, st, X, f, w, P, r.vid, r.perm, r.starts, r.wstart, r.geom,
+                     depth, p, r.loc, scale, out);
+  launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   if (near) {
-    constexpr int kChunk = 1 << eval_chunk_shift<true>();
-    const int nleaf = 1 << (2 * depth);
-    const int items = nleaf + (P + kChunk - 1) / kChunk;
     hipLaunchKernelGGL(k_fmm_near, dim3(items), dim3(64), 0, st, X, f, w, P, M, off, r.vid, r.perm, r.starts, r.wstart,
                        depth, r.h2, scale, out, pairs, capacity, count, r.flag);
     hipLaunchKernelGGL(k_fmm_near_status, dim3(1), dim3(64), 0, st, r.flag, count);
