@@ -124,6 +124,29 @@ __device__ __forceinline__ double log_reduced(double q, const double2* __restric
   return log_reduced_n<kLogTab>(q, tab);
 }
 
+// The 1024-entry form of -1/2 ln q, the factor of the Stokeslet's log term (the symmetric float64 kernels and the
+// fast multipole evaluation; 16 KB of LDS, built once per call).  Entry i: (a, 1/2 ln 2a), a as in log_tab_entry_n.
+constexpr int kHalfLogTab = 1024;
+__device__ __forceinline__ double2 half_log_entry(int i) {
+  const double2 t = log_tab_entry_n<kHalfLogTab>(i);
+  return make_double2(0.5 * t.x, -0.5 * t.y);
+}
+
+// -1/2 ln q for a finite q > 0: q = mant 2^e, r = mant a - 1/2, |r| < 2.8e-4, -1/2 log1p(2r) =
+// -r + r^2 - 4/3 r^3 + 2 r^4 (the next term is below 5.5e-18; the table entry alone carries up to 2.8e-17),
+// e ln 2 by one FMA as in log_reduced_n.  With 2r every coefficient but 4/3 is an inline constant, so no step
+// needs a second scalar operand (a copy to a VGPR).
+__device__ __forceinline__ double neg_half_log(double q, const double2* __restrict__ tab) {
+  int e;
+  const double mant = frexp(q, &e);
+  const double2 t = tab[(__double2hiint(mant) >> 10) & (kHalfLogTab - 1)];  // in range for every input
+  const double r = fma(mant, t.x, -0.5);
+  double pol = fma(r, 2.0, -4.0 / 3.0);
+  pol = fma(pol, r, 1.0);
+  pol = fma(pol, r, -1.0);
+  return fma((double)e, -0.5 * 0.69314718055994530942, fma(r, pol, t.y));
+}
+
 // Device views of a prepared workspace region.
 struct PreparedView {
   int2* vrange;    // [M]   clamped point range (j0, j1) of each vesicle

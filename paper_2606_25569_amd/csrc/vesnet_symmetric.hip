@@ -547,28 +547,7 @@ __device__ __forceinline__ double dfrom(unsigned lo, unsigned hi) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
-constexpr int kSymTab = 1024;                      // entries of the log table (16 KB of LDS)
-
-// Entry i of the forward's table: (a, 1/2 ln 2a), a as in log_tab_entry_n.
-__device__ __forceinline__ double2 half_log_entry(int i) {
-  const double2 t = log_tab_entry_n<kSymTab>(i);
-  return make_double2(0.5 * t.x, -0.5 * t.y);
-}
-
-// -1/2 ln q for a finite q > 0: q = mant 2^e, r = mant a - 1/2, |r| < 2.8e-4, -1/2 log1p(2r) =
-// -r + r^2 - 4/3 r^3 + 2 r^4 (the next term is below 5.5e-18; the table entry alone carries up to 2.8e-17),
-// e ln 2 by one FMA as in log_reduced_n.  With 2r every coefficient but 4/3 is an inline constant, so no step
-// needs a second scalar operand (a copy to a VGPR).
-__device__ __forceinline__ double neg_half_log(double q, const double2* __restrict__ tab) {
-  int e;
-  const double mant = frexp(q, &e);
-  const double2 t = tab[(__double2hiint(mant) >> 10) & (kSymTab - 1)];  // in range for every input
-  const double r = fma(mant, t.x, -0.5);
-  double pol = fma(r, 2.0, -4.0 / 3.0);
-  pol = fma(pol, r, 1.0);
-  pol = fma(pol, r, -1.0);
-  return fma((double)e, -0.5 * kLn2d, fma(r, pol, t.y));
-}
+constexpr int kSymTab = kHalfLogTab;               // entries of the log table (16 KB of LDS)
 
 // Adds x to the two fixed-point words of one accumulator entry (hi at a, lo at a + 2P), or marks it.
 __device__ __forceinline__ void fixed_add2(unsigned long long* __restrict__ a, uint8_t* __restrict__ bad, size_t two_p,

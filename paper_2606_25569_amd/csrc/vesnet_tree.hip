@@ -73,35 +73,25 @@ __device__ __forceinline__ size_t level_box_base(int l) { return (((size_t)1 << 
 
 // ---------------------------------------------------------------- tree construction
 
-// Binomial table T[m][l] = C(m + l - 1, l) for m = 1..p+1, l = 0..p, zero elsewhere, over rows m = 0..kTabM-1
-// and columns l = 0..63 (stride kTabL): the whole zero-padded range the matrix-core tiles read.  Row 0 holds
-// 1, 0, 0, ... while it is built (the start of the recurrence) and zeros once done.  Pascal's rule
-// T[m][l] = T[m-1][l] + T[m][l-1] runs along anti-diagonals: sums of integers, exact below 2^53.  The same
-// table holds C(m, l) = T[m - l + 1][l].  Run by the one wavefront (lane = l) of the bounding-box kernel.
+// Binomial table: entry [m - 1][l] = C(m + l - 1, l), m = 1 .. kTabM, l = 0 .. kTabL - 1, over the whole padded range
+// that the matrix-core tiles read, by Pascal's rule (sums of integers, exact below 2^53), made by the compiler.
 constexpr int kTabL = 64;
-constexpr int kTabM = 4 * ((kMaxOrder + 1 + 3) / 4) + 1;  // m up to 4 ceil((p + 1) / 4)
-
-__device__ void build_binomials(int p, double* __restrict__ tab) {
-  __shared__ double prev[64];
-  const int l = threadIdx.x;
-  for (int m = 0; m < kTabM; ++m) tab[m * kTabL + l] = 0.0;
-  double v = l == 0 ? 1.0 : 0.0;  // T[0][l]
-  for (int s = 1; s <= 2 * p + 1; ++s) {
-    prev[l] = v;  // this lane's latest entry, T[s - 1 - l][l]
-    __syncthreads();
-    const int m = s - l;
-    if (l <= p && m >= 1 && m <= p + 1) {
-      v += l > 0 ? prev[l - 1] : 0.0;  // + T[m][l - 1], written by lane l - 1 one step earlier
-      tab[m * kTabL + l] = v;
-    }
-    __syncthreads();
+constexpr int kTabM = 4 * ((kMaxOrder + 1 + 3) / 4);  // m up to 4 ceil((p + 1) / 4)
+struct Binomials {
+  double t[kTabM][kTabL];
+  constexpr Binomials() : t() {
+    for (int m = 0; m < kTabM; ++m)
+      for (int l = 0; l < kTabL; ++l) t[m][l] = m == 0 || l == 0 ? 1.0 : t[m - 1][l] + t[m][l - 1];
   }
-}
+};
+__device__ constexpr Binomials kBinomials{};
 
-
+// Also builds the evaluation's log table when tab is not null.
 __global__ __launch_bounds__(kTB) void k_tc_bbox_partial(const double* __restrict__ X, int P,
-                                                         double* __restrict__ part) {
+                                                         double* __restrict__ part, double2* __restrict__ tab) {
   __shared__ double red[4][kTB];
+  if (tab != nullptr)
+    for (int e = blockIdx.x * kTB + threadIdx.x; e < kHalfLogTab; e += gridDim.x * kTB) tab[e] = half_log_entry(e);
   double xl = INFINITY, xh = -INFINITY, yl = INFINITY, yh = -INFINITY;
   for (int j = blockIdx.x * kTB + threadIdx.x; j < P; j += gridDim.x * kTB) {
     const double x = X[j], y = X[P + j];
@@ -127,10 +117,8 @@ __global__ __launch_bounds__(kTB) void k_tc_bbox_partial(const double* __restric
   if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Also builds the binomial table of the fast multipole method when tab is not null.
 __global__ __launch_bounds__(64) void k_tc_bbox_final(const double* __restrict__ part, int nparts,
-                                                      Geom* __restrict__ geom, int p, double* __restrict__ tab) {
-  if (tab != nullptr) build_binomials(p, tab);
+                                                      Geom* __restrict__ geom) {
   double xl = INFINITY, xh = -INFINITY, yl = INFINITY, yh = -INFINITY;
   for (int b = threadIdx.x; b < nparts; b += 64) {
     xl = fmin(xl, part[4 * b]);
@@ -289,19 +277,31 @@ __global__ __launch_bounds__(kTB) void k_tc_scatter(const int32_t* __restrict__ 
 
 // Points of each leaf in ascending index order (deterministic sums).  One wavefront per leaf: the
 // keys (distinct point indices) go to LDS and each is written at its rank, the number of smaller
-// keys in the leaf.
-__global__ __launch_bounds__(64) void k_tc_sort(const int32_t* __restrict__ starts, int32_t* __restrict__ perm) {
+// keys in the leaf.  The points' records (x, y, w f_x, w f_y) and vesicle ids are stored in the same order: later
+// kernels read whole leaves contiguously instead of gathering five arrays through the permutation.
+__global__ __launch_bounds__(64) void k_tc_sort(const double* __restrict__ X, const double* __restrict__ f,
+                                                const double* __restrict__ w, int P, const int32_t* __restrict__ vid,
+                                                const int32_t* __restrict__ starts, int32_t* __restrict__ perm,
+                                                double4* __restrict__ srec, int32_t* __restrict__ svid) {
   __shared__ int32_t key[kSortMax];
   const int leaf = blockIdx.x;
   const int s0 = starts[leaf], n = starts[leaf + 1] - s0;
-  if (n < 2 || n > kSortMax) return;
-  for (int a = threadIdx.x; a < n; a += 64) key[a] = perm[s0 + a];
-  __syncthreads();
+  const bool sort = n <= kSortMax;
+  if (sort) {
+    for (int a = threadIdx.x; a < n; a += 64) key[a] = perm[s0 + a];
+    __syncthreads();
+  }
   for (int a = threadIdx.x; a < n; a += 64) {
-    const int32_t k = key[a];
-    int rank = 0;
-    for (int b = 0; b < n; ++b) rank += key[b] < k;
-    perm[s0 + rank] = k;
+    const int32_t j = sort ? key[a] : perm[s0 + a];
+    int slot = s0 + a;
+    if (sort) {
+      int rank = 0;
+      for (int b = 0; b < n; ++b) rank += key[b] < j;
+      slot = s0 + rank;
+      perm[slot] = j;
+    }
+    srec[slot] = make_double4(X[j], X[P + j], w[j] * f[j], w[j] * f[P + j]);
+    svid[slot] = vid[j];
   }
 }
 
@@ -325,8 +325,7 @@ __device__ __forceinline__ double2 cpow_int(double2 z, int k) {
 // its powers zeta^0 .. zeta^p (by repeated multiplication), so lane k reads zeta^k instead of forming it.
 constexpr int kP2MChunk = 32;
 
-__global__ __launch_bounds__(64) void k_tc_p2m(const double* __restrict__ X, const double* __restrict__ f,
-                                               const double* __restrict__ w, int P, const int32_t* __restrict__ perm,
+__global__ __launch_bounds__(64) void k_tc_p2m(const double4* __restrict__ srec,
                                                const int32_t* __restrict__ starts, const Geom* __restrict__ geom,
                                                int depth, int p, double2* __restrict__ mom,
                                                int32_t* __restrict__ bcount) {
@@ -344,9 +343,9 @@ __global__ __launch_bounds__(64) void k_tc_p2m(const double* __restrict__ X, con
     const int cnt = min(kP2MChunk, s1 - c0);
     __syncthreads();  // the previous chunk is done
     if (k < cnt) {
-      const int j = perm[c0 + k];
-      const double2 zeta = make_double2(X[j] - c.x, X[P + j] - c.y);
-      Fs[k] = make_double2(w[j] * f[j], w[j] * f[P + j]);
+      const double4 s = srec[c0 + k];
+      const double2 zeta = make_double2(s.x - c.x, s.y - c.y);
+      Fs[k] = make_double2(s.z, s.w);
       Zc[k] = make_double2(zeta.x, -zeta.y);
       double2 z = make_double2(1.0, 0.0);
       for (int m = 0; m <= p; ++m) {
@@ -497,7 +496,7 @@ __global__ __launch_bounds__(kTB) void k_tc_finalize(double2* __restrict__ mom, 
 typedef double double4v __attribute__((ext_vector_type(4)));
 
 // Dynamic LDS of k_fmm_m2l for order p, KS = ceil((p + 1) / 4) steps of four m and RT = ceil((p + 1) / 16)
-// tiles of 16 orders: the binomial tile T[m - 1][l] (4 KS x 16 RT), the source list, the scaled coefficients
+// tiles of 16 orders: the source list, the scaled coefficients
 // X[v][m - 1][s] of a batch (3 series x 4 KS x 8 sources, complex; also the final exchange of 3 x 64 sums),
 // the powers (-t_s)^l (8 sources x 4 KS, complex), and per source lambda_A, lambda_B (complex) and ln|d|.
 // (Splitting a box's batches over several waves, or taking one series at a time to save registers, both
@@ -505,14 +504,13 @@ typedef double double4v __attribute__((ext_vector_type(4)));
 constexpr int kM2LBatch = 8;  // source boxes per batch: 8 complex columns fill one 16-column tile
 __host__ __device__ inline int m2l_ksteps(int p) { return (p + 1 + 3) / 4; }
 __host__ __device__ inline int m2l_rtiles(int p) { return (p + 1 + 15) / 16; }
-__host__ __device__ inline int m2l_tsize(int p) { return (4 * m2l_ksteps(p) * 16 * m2l_rtiles(p) + 1) / 2; }  // double2
 __host__ __device__ inline int m2l_xsize(int p) {  // in double2
   const int mm = 4 * m2l_ksteps(p);
   return 3 * mm * kM2LBatch > 3 * 64 ? 3 * mm * kM2LBatch : 3 * 64;
 }
 inline size_t m2l_lds_bytes(int p) {
   const int mm = 4 * m2l_ksteps(p);
-  return sizeof(double2) * ((size_t)m2l_tsize(p) + 36 + m2l_xsize(p) + (size_t)kM2LBatch * mm + 2 * kM2LBatch +
+  return sizeof(double2) * ((size_t)36 + m2l_xsize(p) + (size_t)kM2LBatch * mm + 2 * kM2LBatch +
                             kM2LBatch / 2);
 }
 
@@ -527,25 +525,26 @@ inline size_t m2l_lds_bytes(int p) {
 // four rows below, so that every lane (l = lane mod 16, q = lane / 16) receives both parts of sources q and
 // q + 4 for its order l and scales them itself.  Sources go eight at a time, in the fixed candidate order;
 // at the end the sums of the four lanes of every order are added in q order.  RT = ceil((p + 1) / 16).
+// At least two wavefronts per SIMD: with 256 VGPRs at most the compiler keeps D in VGPRs, where the matrix
+// instructions can add to it; with more it copied all of D to accumulation registers and back at every step (96 of
+// its 125 instructions).  The binomials come from L1 one step ahead: staged in LDS they were a third of the LDS that
+// held the kernel to six wavefronts per CU.  2000 x 128, order 30: 124 -> 84 us.  (48 orders need more registers.)
 template <int RT>
-__global__ __launch_bounds__(64) void k_fmm_m2l(const Geom* __restrict__ geom, int depth, int p,
+__global__ __launch_bounds__(64, RT < 4 ? 2 : 1) void k_fmm_m2l(const Geom* __restrict__ geom, int depth, int p,
                                                            const double2* __restrict__ mom,
                                                            const int32_t* __restrict__ bcount,
-                                                           const double* __restrict__ tab, double2* __restrict__ loc) {
+                                                           double2* __restrict__ loc) {
   extern __shared__ double2 sm[];
   const size_t box = blockIdx.x;
   if (bcount[box] == 0) return;
   const int lane = threadIdx.x;
   const int np = p + 1;
   const int KS = m2l_ksteps(p), MM = 4 * KS;
-  constexpr int TL = 16 * RT;                                    // orders per table row
-  double* Tt = reinterpret_cast<double*>(sm);                    // [MM][TL]
-  int32_t* lst = reinterpret_cast<int32_t*>(sm + m2l_tsize(p));  // [36][2]: source box coordinates
-  double2* X = sm + m2l_tsize(p) + 36;                           // [3][MM][8]
+  int32_t* lst = reinterpret_cast<int32_t*>(sm);                 // [36][2]: source box coordinates
+  double2* X = sm + 36;                                          // [3][MM][8]
   double2* pw = X + m2l_xsize(p);                                // [8][MM]: (-t_s)^l
   double2* lam = pw + kM2LBatch * MM;                            // [8][2]: lambda_A, lambda_B
   double* lnd = reinterpret_cast<double*>(lam + 2 * kM2LBatch);  // [8]
-  for (int e = threadIdx.x; e < MM * TL; e += blockDim.x) Tt[e] = tab[(size_t)(e / TL + 1) * kTabL + e % TL];
   int l2 = 2;
   while (l2 < depth && box >= level_box_base(l2 + 1)) ++l2;
   const int n = 1 << l2;
@@ -568,7 +567,7 @@ __global__ __launch_bounds__(64) void k_fmm_m2l(const Geom* __restrict__ geom, i
       lst[2 * rank + 1] = sy;
     }
   }
-  wave_sync();  // table and list ready
+  wave_sync();  // list ready
   const int j = lane & 15, q = lane >> 4;  // result lanes: order j (+ 16 rt), sources q and q + 4
   const int ai = lane & 15, ak = lane >> 4;  // operand lanes: column / order ai, step row ak
   const int acol = (ai & 3) + 4 * (ai >> 3), apart = (ai >> 2) & 1;  // column ai: source acol, re or im
@@ -644,13 +643,19 @@ __global__ __launch_bounds__(64) void k_fmm_m2l(const Geom* __restrict__ geom, i
     for (int v = 0; v < 3; ++v)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) D[v][rt] = (double4v){0.0, 0.0, 0.0, 0.0};
+    double bn[RT];  // the next step's binomials, loaded one step ahead
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) bn[rt] = kBinomials.t[ak][ai + 16 * rt];
     for (int ks = 0; ks < KS; ++ks) {
-      const int mi = 4 * ks + ak;  // m - 1
+      const int mi = 4 * ks + ak, mn = 4 * min(ks + 1, KS - 1) + ak;  // m - 1, and the next step's
       double av[3], bv[RT];
 #pragma unroll
       for (int v = 0; v < 3; ++v) av[v] = Xd[2 * ((v * MM + mi) * kM2LBatch + acol) + apart];
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) bv[rt] = Tt[mi * TL + ai + 16 * rt];
+      for (int rt = 0; rt < RT; ++rt) {
+        bv[rt] = bn[rt];
+        bn[rt] = kBinomials.t[mn][ai + 16 * rt];
+      }
 #pragma unroll
       for (int v = 0; v < 3; ++v)
 #pragma unroll
@@ -810,23 +815,43 @@ __device__ __forceinline__ void direct_term(double zx, double zy, double sx, dou
   uy = fma(lg, Fy, fma(s, ry, uy));
 }
 
-// Targets per wavefront of the fast multipole method's evaluation: its far part is a short polynomial per target,
-// and 16 targets give four times the wavefronts of 64 to hide the direct part's latencies (at 2000 x 128, order 30:
-// 0.58 ms against 0.63 ms at 32 and 0.60 ms at 8 targets).
-constexpr int kFmmChunkShift = 4;
+// ---------------------------------------------------------------- fast multipole evaluation
+//
+// One wavefront per (leaf, chunk of 16 of its points), four to a workgroup, which share the 1024-entry log table:
+// 8 lanes take two targets each and the 8 lane groups share the sources of the 3 x 3 leaves (every 8th) and the
+// terms of the leaf's local expansion (group g the powers g, g + 8, ...: Horner in zeta^8, then zeta^g); the groups'
+// sums are added at the end.  The three leaves of a column are one run of the leaf order, and the three runs are
+// staged as one list, 64 records at a time with the next 64 loading meanwhile.  Two targets per lane use each record
+// read from LDS twice.  What bounds it is float64 VALU issue, 30 instructions per (target, source).
+// 2000 x 128, order 30: 263 -> 194 us (160 at one instruction per 4 cycles).
+constexpr int kFmmT = 2;
+constexpr int kFmmLanes = 8;
+constexpr int kFmmGroups = 64 / kFmmLanes;
+constexpr int kFmmChunkShift = 4;  // log2 of the targets per wavefront
+constexpr int kFmmWaves = 4;       // wavefronts per workgroup
+static_assert(1 << kFmmChunkShift == kFmmT * kFmmLanes, "every lane of a group takes kFmmT targets");
 
-// One wavefront per (leaf, chunk of kChunk of its points); every lane one target: the leaf's local expansion and the
-// 3 x 3 leaves around it directly.
-__global__ __launch_bounds__(64) void k_fmm_eval(const double* __restrict__ X, const double* __restrict__ f,
-                                                const double* __restrict__ w, int P, const int32_t* __restrict__ vid,
-                                                const int32_t* __restrict__ perm, const int32_t* __restrict__ starts,
-                                                const int32_t* __restrict__ wstart, const Geom* __restrict__ geom,
-                                                int depth, int p, const double2* __restrict__ loc, double scale,
-                                                double* __restrict__ out) {
-  constexpr int kChunk = 1 << kFmmChunkShift;
+__global__ __launch_bounds__(64 * kFmmWaves) void k_fmm_eval(const double4* __restrict__ srec,
+                                                             const int32_t* __restrict__ svid, int P,
+                                                             const int32_t* __restrict__ perm,
+                                                             const int32_t* __restrict__ starts,
+                                                             const int32_t* __restrict__ wstart,
+                                                             const Geom* __restrict__ geom, int depth, int p,
+                                                             const double2* __restrict__ loc,
+                                                             const double2* __restrict__ tab, double scale,
+                                                             double* __restrict__ out) {
+  __shared__ double2 ltab[kHalfLogTab];
+  // per wavefront: the local expansion (3 (p + 1) <= 147 entries), then 64 source records and ids
+  __shared__ double2 stage[kFmmWaves][3 * 64];
+  for (int e = threadIdx.x; e < kHalfLogTab; e += 64 * kFmmWaves) ltab[e] = tab[e];
+  __syncthreads();
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double2* cf = stage[wv];
+  double4* src = reinterpret_cast<double4*>(stage[wv]);
+  int32_t* sv = reinterpret_cast<int32_t*>(stage[wv] + 2 * 64);
   const int n = 1 << depth;
   const int nleaf = n * n;
-  const int item = blockIdx.x;
+  const int item = blockIdx.x * kFmmWaves + wv;
   if (item >= wstart[nleaf]) return;
   int lo = 0, hi = nleaf;  // wstart[lo] <= item < wstart[hi]
   while (hi - lo > 1) {
@@ -834,93 +859,110 @@ __global__ __launch_bounds__(64) void k_fmm_eval(const double* __restrict__ X, c
     if (wstart[mid] <= item) lo = mid; else hi = mid;
   }
   const int leaf = lo;
-  const int s0 = starts[leaf], s1 = starts[leaf + 1];
-  // A chunk of at most 32 targets splits the wave into S = 64 / K lane groups (K = the target count
-  // rounded up to a power of two): lane = g K + t takes target t, and in the direct part every S-th
-  // source from g on; the groups' direct sums are added at the end.  The far part is the same in every
-  // group.
-  const int lane = threadIdx.x;
-  const int base = s0 + (item - wstart[leaf]) * kChunk;
-  const int tcnt = min(kChunk, s1 - base);
-  int K = 1;
-  while (K < tcnt) K <<= 1;
-  const int S = 64 / K;
-  const int slot = base + (lane & (K - 1));
-  const bool active = slot < s1;
-  const int i = active ? perm[slot] : perm[s0];
-  const double zx = X[i], zy = X[P + i];
-  const int vi = vid[i];
+  const int s1 = starts[leaf + 1];
+  const int base = starts[leaf] + ((item - wstart[leaf]) << kFmmChunkShift);
+  const int tl = lane & (kFmmLanes - 1), grp = lane / kFmmLanes;
   const int ix = leaf / n, iy = leaf % n;
-  const Geom g = *geom;
-  double ux = 0.0, uy = 0.0;
-  // per-wavefront staging: the moments of one box, then chunks of 64 direct sources
-  __shared__ double2 cf[4 * 64];  // 4 (p + 1) <= 196 entries used; padded for whole-wave copies
-  __shared__ double sx_[64], sy_[64], sfx[64], sfy[64];
-  __shared__ int32_t sv[64];
-  __shared__ double2 ltab[kLogTab];
-  ltab[threadIdx.x] = log_tab_entry(threadIdx.x);  // read after the first barrier below
+  // the source runs of columns ix - 1 .. ix + 1 (empty outside the grid), as one list of nsrc slots
+  int run0[3], cum[4];
+  cum[0] = 0;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int jx = ix + a - 1;
+    const bool in = jx >= 0 && jx < n;
+    run0[a] = in ? starts[jx * n + max(iy - 1, 0)] : 0;
+    cum[a + 1] = cum[a] + (in ? starts[jx * n + min(iy + 1, n - 1) + 1] - run0[a] : 0);
+  }
+  const int nsrc = cum[3];
+  auto slot_of = [&](int e) {
+    return e < cum[1] ? run0[0] + e : e < cum[2] ? run0[1] + e - cum[1] : run0[2] + e - cum[2];
+  };
+  // nsrc >= 1: the leaf itself is in the list
+  double4 nrec = srec[slot_of(min(lane, nsrc - 1))];
+  int nvid = svid[slot_of(min(lane, nsrc - 1))];
 
-  // the leaf's local expansion: u += -A(zeta)/2 - conj(B(zeta))/2 + zeta conj(C(zeta))/2
+  double zx[kFmmT], zy[kFmmT], ux[kFmmT], uy[kFmmT];
+  int ti[kFmmT], vi[kFmmT];
+#pragma unroll
+  for (int k = 0; k < kFmmT; ++k) {
+    const int slot = base + tl + kFmmLanes * k;
+    const int sl = slot < s1 ? slot : base;  // an empty slot repeats the first target
+    ti[k] = perm[sl];
+    const double4 z = srec[sl];
+    zx[k] = z.x;
+    zy[k] = z.y;
+    vi[k] = svid[sl];
+    ux[k] = uy[k] = 0.0;
+  }
+  // the leaf's local expansion: u += -A(zeta)/2 - conj(B(zeta))/2 + zeta conj(C(zeta))/2, linear in the terms
   if (depth >= 2) {
-    const double2* lb = loc + (level_box_base(depth) + (size_t)leaf) * 3 * (p + 1);
-    cf[threadIdx.x] = lb[threadIdx.x];  // 3 x 64 >= 3 (kMaxOrder + 1); the array has 192 spare entries
-    cf[threadIdx.x + 64] = lb[threadIdx.x + 64];
-    cf[threadIdx.x + 128] = lb[threadIdx.x + 128];
-    __syncthreads();
-    const double2 c = box_center(g, n, ix, iy);
-    const double2 zt = make_double2(zx - c.x, zy - c.y);
-    double2 A = cf[p], B = cf[2 * p + 1], C = cf[3 * p + 2];
-    for (int k = p - 1; k >= 0; --k) {
-      A = cfma(A, zt, cf[k]);
-      B = cfma(B, zt, cf[(p + 1) + k]);
-      C = cfma(C, zt, cf[2 * (p + 1) + k]);
-    }
-    ux += -0.5 * A.x - 0.5 * B.x + 0.5 * (zt.x * C.x + zt.y * C.y);
-    uy += -0.5 * A.y + 0.5 * B.y + 0.5 * (zt.y * C.x - zt.x * C.y);
-  }
-  // 3 x 3 leaves directly, own vesicle skipped
-  double dx = 0.0, dy = 0.0;
-  for (int jx = max(ix - 1, 0); jx <= min(ix + 1, n - 1); ++jx)
-    for (int jy = max(iy - 1, 0); jy <= min(iy + 1, n - 1); ++jy) {
-      const int nl = jx * n + jy;
-      const int e0 = starts[nl], e1 = starts[nl + 1];
-      for (int c0 = e0; c0 < e1; c0 += 64) {
-        const int cnt = min(64, e1 - c0);
-        __syncthreads();  // the previous chunk is done
-        if ((int)threadIdx.x < cnt) {
-          const int j = perm[c0 + threadIdx.x];
-          sx_[threadIdx.x] = X[j];
-          sy_[threadIdx.x] = X[P + j];
-          sfx[threadIdx.x] = w[j] * f[j];
-          sfy[threadIdx.x] = w[j] * f[P + j];
-          sv[threadIdx.x] = vid[j];
+    const int np = p + 1;
+    const double2* lb = loc + (level_box_base(depth) + (size_t)leaf) * 3 * np;
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (lane + 64 * u < 3 * np) cf[lane + 64 * u] = lb[lane + 64 * u];
+    wave_sync();
+    const double2 c = box_center(*geom, n, ix, iy);
+    const int k1 = grp + kFmmGroups * ((p - grp) / kFmmGroups);  // highest power of the group (if grp <= p)
+#pragma unroll
+    for (int k = 0; k < kFmmT; ++k) {
+      const double2 zt = make_double2(zx[k] - c.x, zy[k] - c.y);
+      const double2 z2 = cmul(zt, zt), z4 = cmul(z2, z2), z8 = cmul(z4, z4);
+      double2 zg = (grp & 1) ? zt : make_double2(1.0, 0.0);
+      if (grp & 2) zg = cmul(zg, z2);
+      if (grp & 4) zg = cmul(zg, z4);
+      double2 A = make_double2(0.0, 0.0), B = A, C = A;
+      if (grp <= p)
+        for (int q = k1; q >= 0; q -= kFmmGroups) {
+          A = cfma(A, z8, cf[q]);
+          B = cfma(B, z8, cf[np + q]);
+          C = cfma(C, z8, cf[2 * np + q]);
         }
-        __syncthreads();
-        // the next source's data is read while the current one is evaluated
-        int q = lane / K;
-        const int qq = q < cnt ? q : 0;
-        double nx = sx_[qq], ny = sy_[qq], nfx = sfx[qq], nfy = sfy[qq];
-        int nv = sv[qq];
-        for (; q < cnt; q += S) {
-          const double cx = nx, cy = ny, cfx = nfx, cfy = nfy;
-          const int cv = nv;
-          const int qn = q + S < cnt ? q + S : q;
-          nx = sx_[qn];
-          ny = sy_[qn];
-          nfx = sfx[qn];
-          nfy = sfy[qn];
-          nv = sv[qn];
-          if (cv != vi) direct_term(zx, zy, cx, cy, cfx, cfy, ltab, dx, dy);
-        }
-      }
+      A = cmul(A, zg);
+      B = cmul(B, zg);
+      C = cmul(C, zg);
+      ux[k] += -0.5 * A.x - 0.5 * B.x + 0.5 * (zt.x * C.x + zt.y * C.y);
+      uy[k] += -0.5 * A.y + 0.5 * B.y + 0.5 * (zt.y * C.x - zt.x * C.y);
     }
-  for (int o = K; o < 64; o <<= 1) {  // groups' direct sums, pairwise in a fixed order
-    dx += __shfl_down(dx, o);
-    dy += __shfl_down(dy, o);
   }
-  if (active && lane < K) {
-    out[i] = (ux + dx) * scale;
-    out[P + i] = (uy + dy) * scale;
+  // the 3 x 3 leaves directly, own vesicle skipped
+  for (int c0 = 0; c0 < nsrc; c0 += 64) {
+    const int cnt = min(64, nsrc - c0);
+    wave_sync();  // the previous records are done
+    src[lane] = nrec;
+    sv[lane] = nvid;
+    wave_sync();
+    if (c0 + 64 < nsrc) {
+      const int sl = slot_of(min(c0 + 64 + lane, nsrc - 1));
+      nrec = srec[sl];
+      nvid = svid[sl];
+    }
+    for (int q = grp; q < cnt; q += kFmmGroups) {
+      const double4 s = src[q];
+      const int cv = sv[q];
+#pragma unroll
+      for (int k = 0; k < kFmmT; ++k)
+        if (cv != vi[k]) {
+          const double rx = zx[k] - s.x, ry = zy[k] - s.y;
+          const double d2 = fma(ry, ry, rx * rx);
+          const double l = neg_half_log(d2, ltab);
+          const double t = fma(ry, s.w, rx * s.z) * recip(d2);
+          ux[k] = fma(l, s.z, fma(t, rx, ux[k]));
+          uy[k] = fma(l, s.w, fma(t, ry, uy[k]));
+        }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kFmmT; ++k) {  // the groups' sums, pairwise in a fixed order
+#pragma unroll
+    for (int o = kFmmLanes; o < 64; o <<= 1) {
+      ux[k] += __shfl_xor(ux[k], o);
+      uy[k] += __shfl_xor(uy[k], o);
+    }
+    if (grp == 0 && base + tl + kFmmLanes * k < s1) {
+      out[ti[k]] = ux[k] * scale;
+      out[P + ti[k]] = uy[k] * scale;
+    }
   }
 }
 
@@ -948,9 +990,9 @@ constexpr int kListMax = 27 * (kMaxDepth - 1);     // boxes of all interaction l
 __device__ __forceinline__ int list_entry(int l, int sx, int sy) { return l << 20 | sx << 10 | sy; }
 
 template <int kTreeLanes>
-__global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, const double* __restrict__ f,
-                                                const double* __restrict__ w, int P, const int32_t* __restrict__ vid,
-                                                const int32_t* __restrict__ perm, const int32_t* __restrict__ starts,
+__global__ __launch_bounds__(64) void k_tc_eval(const double4* __restrict__ srec, const int32_t* __restrict__ svid,
+                                                int P, const int32_t* __restrict__ perm,
+                                                const int32_t* __restrict__ starts,
                                                 const int32_t* __restrict__ wstart, const Geom* __restrict__ geom,
                                                 int depth, int p, const double2* __restrict__ mom,
                                                 const int32_t* __restrict__ bcount, double scale,
@@ -980,10 +1022,12 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, co
 #pragma unroll
   for (int k = 0; k < kTreeT; ++k) {
     const int slot = base + tl + kTreeLanes * k;
-    ti[k] = perm[slot < s1 ? slot : base];  // an empty slot repeats the first target
-    zx[k] = X[ti[k]];
-    zy[k] = X[P + ti[k]];
-    vi[k] = vid[ti[k]];
+    const int sl = slot < s1 ? slot : base;  // an empty slot repeats the first target
+    ti[k] = perm[sl];
+    const double4 z = srec[sl];
+    zx[k] = z.x;
+    zy[k] = z.y;
+    vi[k] = svid[sl];
     ux[k] = uy[k] = 0.0;
   }
   const int ix = leaf / n, iy = leaf % n;
@@ -1074,9 +1118,8 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double* __restrict__ X, co
       const int cnt = min(64, e1 - c0);
       wave_sync();  // the previous chunk is done
       if (lane < cnt) {
-        const int j = perm[c0 + lane];
-        src[lane] = make_double4(X[j], X[P + j], w[j] * f[j], w[j] * f[P + j]);
-        sv[lane] = vid[j];
+        src[lane] = srec[c0 + lane];
+        sv[lane] = svid[c0 + lane];
       }
       wave_sync();
       for (int q = grp; q < cnt; q += kTreeGroups) {
@@ -1403,7 +1446,8 @@ __global__ __launch_bounds__(64) void k_fmm_near_status(const int32_t* __restric
 // Workspace layout shared by the size queries and the launchers; the fast multipole method adds the
 // local expansions (3 rows per box) and the binomial table.
 struct TreeLayout {
-  size_t geom, part, leafid, vid, perm, counts, cursor, starts, wstart, bcount, mom, loc, tab, h2, flag, total;
+  size_t geom, part, leafid, vid, perm, srec, svid, counts, cursor, starts, wstart, bcount, mom, loc, ltab, h2, flag,
+      total;
 };
 
 static size_t align_up(size_t x) { return (x + 255) / 256 * 256; }
@@ -1420,6 +1464,8 @@ static TreeLayout tree_layout(int P, int depth, int p, bool fmm, int near_M = 0)
   t.leafid = o;     o += align_up(sizeof(int32_t) * (size_t)P);
   t.vid = o;        o += align_up(sizeof(int32_t) * (size_t)P);
   t.perm = o;       o += align_up(sizeof(int32_t) * (size_t)P);
+  t.srec = o;       o += align_up(sizeof(double4) * (size_t)P);
+  t.svid = o;       o += align_up(sizeof(int32_t) * (size_t)P);
   t.counts = o;     o += align_up(sizeof(int32_t) * nleaf);
   t.cursor = o;     o += align_up(sizeof(int32_t) * nleaf);
   t.starts = o;     o += align_up(sizeof(int32_t) * (nleaf + 1));
@@ -1427,10 +1473,10 @@ static TreeLayout tree_layout(int P, int depth, int p, bool fmm, int near_M = 0)
   t.bcount = o;     o += align_up(sizeof(int32_t) * (boxes > 0 ? boxes : 1));
   t.mom = o;        o += align_up(sizeof(double2) * (moms + 256));  // 256 spare entries: whole-wave copies
   t.loc = o;
-  t.tab = o;
+  t.ltab = o;
   if (fmm) {
     t.loc = o;      o += align_up(sizeof(double2) * (boxes * 3 * (size_t)(p + 1) + 192));  // 192 spare: as above
-    t.tab = o;      o += align_up(sizeof(double) * (size_t)kTabM * kTabL);
+    t.ltab = o;     o += align_up(sizeof(double2) * (size_t)kHalfLogTab);
   }
   t.h2 = o;
   t.flag = o;
@@ -1452,8 +1498,9 @@ struct TreeRun {
   Geom* geom;
   double* part;
   int32_t *leafid, *vid, *perm, *counts, *cursor, *starts, *wstart, *bcount;
-  double2 *mom, *loc;
-  double* tab;
+  double4* srec;   // records and vesicle ids in leaf order
+  int32_t* svid;
+  double2 *mom, *loc, *ltab;
   double* h2;
   int32_t* flag;
   Levels lv;       // first box and first moment entry of every level
@@ -1468,6 +1515,9 @@ TreeRun tree_run(void* ws, const TreeLayout& t, int depth, int p) {
   r.leafid = reinterpret_cast<int32_t*>(base + t.leafid);
   r.vid = reinterpret_cast<int32_t*>(base + t.vid);
   r.perm = reinterpret_cast<int32_t*>(base + t.perm);
+  r.srec = reinterpret_cast<double4*>(base + t.srec);
+  r.svid = reinterpret_cast<int32_t*>(base + t.svid);
+  r.ltab = reinterpret_cast<double2*>(base + t.ltab);
   r.counts = reinterpret_cast<int32_t*>(base + t.counts);
   r.cursor = reinterpret_cast<int32_t*>(base + t.cursor);
   r.starts = reinterpret_cast<int32_t*>(base + t.starts);
@@ -1475,7 +1525,6 @@ TreeRun tree_run(void* ws, const TreeLayout& t, int depth, int p) {
   r.bcount = reinterpret_cast<int32_t*>(base + t.bcount);
   r.mom = reinterpret_cast<double2*>(base + t.mom);
   r.loc = reinterpret_cast<double2*>(base + t.loc);
-  r.tab = reinterpret_cast<double*>(base + t.tab);
   r.h2 = reinterpret_cast<double*>(base + t.h2);
   r.flag = reinterpret_cast<int32_t*>(base + t.flag);
   r.lv = {};
@@ -1492,12 +1541,13 @@ TreeRun tree_run(void* ws, const TreeLayout& t, int depth, int p) {
 // Tree over the points (root square, leaves, leaf order) and the moments of every box of levels
 // 2..depth (leaves from the points, coarser levels by translation).
 void launch_upward(const double* X, const double* f, const double* w, const int32_t* off, int M, int P, int p,
-                   int depth, int cshift, bool binomials, bool near, const TreeRun& r, hipStream_t st) {
+                   int depth, int cshift, bool fmm, bool near, const TreeRun& r, hipStream_t st) {
   const int nleaf = 1 << (2 * depth);
   const int pb = (P + kTB - 1) / kTB < 4096 ? (P + kTB - 1) / kTB : 4096;
   const int bb = (P + kTB - 1) / kTB < kBBoxBlocks ? (P + kTB - 1) / kTB : kBBoxBlocks;
-  hipLaunchKernelGGL(k_tc_bbox_partial, dim3(bb), dim3(kTB), 0, st, X, P, r.part);
-  hipLaunchKernelGGL(k_tc_bbox_final, dim3(1), dim3(64), 0, st, r.part, bb, r.geom, p, binomials ? r.tab : nullptr);
+  hipLaunchKernelGGL(k_tc_bbox_partial, dim3(bb), dim3(kTB), 0, st, X, P, r.part,
+                     fmm ? r.ltab : nullptr);
+  hipLaunchKernelGGL(k_tc_bbox_final, dim3(1), dim3(64), 0, st, r.part, bb, r.geom);
   const int zb = (nleaf + kTB - 1) / kTB < 4096 ? (nleaf + kTB - 1) / kTB : 4096;
   hipLaunchKernelGGL(k_tc_zero, dim3(zb), dim3(kTB), 0, st, r.counts, r.cursor, nleaf);
   hipLaunchKernelGGL(k_tc_leaf, dim3(pb), dim3(kTB), 0, st, X, P, r.geom, depth, r.leafid, r.counts);
@@ -1505,11 +1555,10 @@ void launch_upward(const double* X, const double* f, const double* w, const int3
                      r.flag);
   hipLaunchKernelGGL(k_tc_scan, dim3(1), dim3(1024), 0, st, r.counts, nleaf, r.starts, r.wstart, cshift);
   hipLaunchKernelGGL(k_tc_scatter, dim3(pb), dim3(kTB), 0, st, r.leafid, P, r.starts, r.cursor, r.perm);
-  hipLaunchKernelGGL(k_tc_sort, dim3(nleaf), dim3(64), 0, st, r.starts, r.perm);
+  hipLaunchKernelGGL(k_tc_sort, dim3(nleaf), dim3(64), 0, st, X, f, w, P, r.vid, r.starts, r.perm, r.srec, r.svid);
   if (depth < 2) return;
-  hipLaunchKernelGGL(k_tc_p2m, dim3(nleaf), dim3(64), sizeof(double2) * (size_t)kP2MChunk * (p + 3), st, X, f, w, P,
-                     r.perm, r.starts, r.geom, depth, p,
-                     r.mom + r.lv.mom[depth], r.bcount + r.lv.box[depth]);
+  hipLaunchKernelGGL(k_tc_p2m, dim3(nleaf), dim3(64), sizeof(double2) * (size_t)kP2MChunk * (p + 3), st, r.srec,
+                     r.starts, r.geom, depth, p, r.mom + r.lv.mom[depth], r.bcount + r.lv.box[depth]);
   for (int l = depth - 1; l >= 2; --l) {
     const int n = 1 << l;
     hipLaunchKernelGGL(k_tc_m2m, dim3(n * n), dim3(256), 0, st, r.geom, n, p, r.mom + r.lv.mom[l + 1],
@@ -1546,10 +1595,10 @@ hipError_t launch_treecode(const double* X, const double* f, const double* w, co
   const dim3 grid((unsigned)eval_items(P, depth, shift));
   const size_t lds = sizeof(double2) * (size_t)(64 / lanes) * 3 * (p + 1);
   if (lanes == 16)
-    hipLaunchKernelGGL(k_tc_eval<16>, grid, dim3(64), lds, st, X, f, w, P, r.vid, r.perm, r.starts, r.wstart, r.geom,
+    hipLaunchKernelGGL(k_tc_eval<16>, grid, dim3(64), lds, st, r.srec, r.svid, P, r.perm, r.starts, r.wstart, r.geom,
                        depth, p, r.mom, r.bcount, scale, out);
   else
-    hipLaunchKernelGGL(k_tc_eval<8>, grid, dim3(64), lds, st, X, f, w, P, r.vid, r.perm, r.starts, r.wstart, r.geom,
+    hipLaunchKernelGGL(k_tc_eval<8>, grid, dim3(64), lds, st, r.srec, r.svid, P, r.perm, r.starts, r.wstart, r.geom,
                        depth, p, r.mom, r.bcount, scale, out);
   launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   return hipGetLastError();
@@ -1560,15 +1609,15 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
                           int32_t* pairs, int capacity, int32_t* count) {
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, true, near ? M : 0), depth, p);
   if (near) hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(kTB), 0, st, count, r.flag, 1);
-  launch_upward(X, f, w, off, M, P, p, depth, kFmmChunkShift, depth >= 2, near, r, st);
+  launch_upward(X, f, w, off, M, P, p, depth, kFmmChunkShift, true, near, r, st);
   if (depth >= 2) {
     const dim3 g((unsigned)r.nbox), bl(64);
     const size_t lds = m2l_lds_bytes(p);
     switch (m2l_rtiles(p)) {
-      case 1: hipLaunchKernelGGL(k_fmm_m2l<1>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.tab, r.loc); break;
-      case 2: hipLaunchKernelGGL(k_fmm_m2l<2>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.tab, r.loc); break;
-      case 3: hipLaunchKernelGGL(k_fmm_m2l<3>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.tab, r.loc); break;
-      default: hipLaunchKernelGGL(k_fmm_m2l<4>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.tab, r.loc); break;
+      case 1: hipLaunchKernelGGL(k_fmm_m2l<1>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.loc); break;
+      case 2: hipLaunchKernelGGL(k_fmm_m2l<2>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.loc); break;
+      case 3: hipLaunchKernelGGL(k_fmm_m2l<3>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.loc); break;
+      default: hipLaunchKernelGGL(k_fmm_m2l<4>, g, bl, lds, st, r.geom, depth, p, r.mom, r.bcount, r.loc); break;
     }
     if (depth >= 3) {
       const int nleaf = 1 << (2 * depth);
@@ -1577,8 +1626,8 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
     }
   }
   const int items = eval_items(P, depth, kFmmChunkShift);
-  hipLaunchKernelGGL(k_fmm_eval, dim3(items), dim3(64), 0, st, X, f, w, P, r.vid, r.perm, r.starts, r.wstart, r.geom,
-                     depth, p, r.loc, scale, out);
+  hipLaunchKernelGGL(k_fmm_eval, dim3((items + kFmmWaves - 1) / kFmmWaves), dim3(64 * kFmmWaves), 0, st, r.srec, r.svid,
+                     P, r.perm, r.starts, r.wstart, r.geom, depth, p, r.loc, r.ltab, scale, out);
   launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   if (near) {
     hipLaunchKernelGGL(k_fmm_near, dim3(items), dim3(64), 0, st, X, f, w, P, M, off, r.vid, r.perm, r.starts, r.wstart,
