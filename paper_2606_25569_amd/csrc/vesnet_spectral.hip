@@ -10,13 +10,23 @@
 //   d_0 = 0,  d_m = (1/2) (-1)^m cot(pi m / N)  (N even),  (1/2) (-1)^m csc(pi m / N)  (N odd),
 // which equals multiplying Fourier mode k by i k with the even-N Nyquist mode dropped.  The weights sum
 // to zero, so the points enter it relative to the vesicle's first point: rounding then scales with the
-// vesicle's extent, not with its distance from the origin.  It is applied as
-// a direct O(N^2) sum from LDS in float64 (the fourth derivative amplifies rounding by up to (N/2)^4):
-// one wavefront per vesicle of up to 64, 128 or 256 points (k_elastic_wave), one workgroup per larger
-// vesicle of up to 1024 points (k_elastic), tens of microseconds for a whole suspension.
+// vesicle's extent, not with its distance from the origin.  It is applied as a direct O(N^2) product in float64
+// (the fourth derivative amplifies rounding by up to (N/2)^4) on the matrix cores.
+//
+// The product.  Points i = 16 p + r in blocks p of 16: with j = 16 (p - t) + s,
+//   (D u)_i = sum_t sum_s T_t[r][s] u_j,   T_t[r][s] = d[(r - s + 16 t) mod N],
+// so the 16 x 16 matrix T_t multiplies all blocks at once: the columns of the other operand are the blocks (moved by
+// t) of both components, eight blocks x two components to a 16-column accumulator.  t runs over the ceil(N / 16)
+// blocks; where N is no multiple of 16 the pairs of the last t that wrap round a second time, 16 t - s > N - 16, are
+// dropped.  Operands come from LDS (d and u extended by their period, so no index is reduced), two 8-byte reads for
+// 64 cycles of matrix work: the matrix cores bound it.
+// One wavefront holds 128 points; a vesicle of up to 128 points is one wavefront's work, a larger one (up to 1024) is
+// shared by a workgroup's eight, 128 points each.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "vesnet_internal.h"
 
@@ -25,353 +35,310 @@ namespace vesnet {
 namespace {
 
 constexpr int kMaxN = 1024;
-constexpr int kB = 256;
-constexpr int kPer = kMaxN / kB;
+constexpr int kWaves = 8;
+constexpr int kB = 64 * kWaves;
+constexpr int kWavePoints = 128;  // of one wavefront: eight blocks x two components are the 16 columns
+constexpr int kValues = 4;        // accumulator rows of a lane
+
+typedef double double4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int clamp_i(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
-// (D u)_i for the points this thread owns, u and d in LDS.
-__device__ __forceinline__ void apply_d(const double* __restrict__ d, const double* __restrict__ ux,
-                                        const double* __restrict__ uy, int n, double (&ox)[kPer],
-                                        double (&oy)[kPer]) {
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int i = threadIdx.x + k * kB;
-    double sx = 0.0, sy = 0.0;
-    if (i < n) {
-      int idx = i;  // (i - m) mod n, walking m = 0 .. n-1
-      for (int m = 0; m < n; ++m) {
-        const double c = d[m];
-        sx = fma(c, ux[idx], sx);
-        sy = fma(c, uy[idx], sy);
-        idx = idx == 0 ? n - 1 : idx - 1;
-      }
-    }
-    ox[k] = sx;
-    oy[k] = sy;
-  }
+// LDS doubles of a vesicle of up to `points` points: d at indices -15 .. points - 1 (one spare), then u at indices
+// -(points - 16) .. points - 1.
+constexpr int region_doubles(int points) { return points + 16 + 40 * (points / 8 - 1); }
+
+// LDS position of u_j: the components side by side, eight spare doubles every sixteen points, which puts the eight
+// blocks that one read touches on different banks.
+__device__ __forceinline__ int upos(int j) { return 2 * j + 8 * (j >> 4); }
+
+// The other component's value at the same point (neighbouring lanes hold x and y).
+__device__ __forceinline__ double other_component(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0xB1, 0xF, 0xF, false);  // quad_perm 1, 0, 3, 2
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0xB1, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
 }
 
-// LDS position of value j in k_elastic_wave's arrays (one spare double every eight), so that lanes reading
-// values R apart fall in different banks.
-__device__ __forceinline__ int pad8(int j) { return j + (j >> 3); }
+// One vesicle of n points, worked on by one wavefront (kCoop = false) or by the whole workgroup.  Lane l of a
+// wavefront holds component l & 1 of points 16 p + (l >> 4) + 4 q, q = 0 .. 3, of its block p.
+template <bool kCoop>
+struct Curve {
+  double* d;  // d[-15 .. 16 nb - 1]
+  double* u;  // positions of j = -(16 nb - 16) .. 16 nb - 1
+  int n, nb;  // points, blocks of 16
+  int p, c, k4;
+  bool live;  // this wavefront has points
 
-// (D u) at the R consecutive points i0 .. i0 + R - 1 of this lane, u stored twice (u2[j] = u2[j + n] = u_j) so
-// that u_(i - m) mod n is u2[i + n - m].  A window of the R values slides down one position per m: each step
-// reads one new value per component for 2 R FMAs, and every output sums m = 0 .. n-1 in order, as apply_d
-// does.  Points beyond n only ever see window values of points beyond n; their outputs are not used.
-template <int R>
-__device__ __forceinline__ void apply_d_lane(const double* __restrict__ d, const double* __restrict__ ux2,
-                                             const double* __restrict__ uy2, int n, int i0, double (&ox)[R],
-                                             double (&oy)[R]) {
-#pragma unroll
-  for (int r = 0; r < R; ++r) ox[r] = oy[r] = 0.0;
-  if (i0 >= n) return;
-  double wx[R], wy[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    wx[r] = ux2[pad8(i0 + r + n)];
-    wy[r] = uy2[pad8(i0 + r + n)];
+  __device__ __forceinline__ Curve(double* lds, int points) {
+    const int lane = threadIdx.x & 63;
+    const int wave = kCoop ? threadIdx.x >> 6 : 0;
+    n = points;
+    nb = (n + 15) >> 4;
+    p = 8 * wave + ((lane & 15) >> 1);
+    c = lane & 1;
+    k4 = lane >> 4;
+    live = 8 * wave < nb;
+    d = lds + 15;
+    u = lds + 16 * nb + 16 + 40 * (nb - 1);
   }
-  for (int m = 0; m < n; ++m) {
-    const double c = d[m];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      ox[r] = fma(c, wx[r], ox[r]);
-      oy[r] = fma(c, wy[r], oy[r]);
-    }
-#pragma unroll
-    for (int r = R - 1; r > 0; --r) {
-      wx[r] = wx[r - 1];
-      wy[r] = wy[r - 1];
-    }
-    wx[0] = ux2[pad8(i0 + n - m - 1)];
-    wy[0] = uy2[pad8(i0 + n - m - 1)];
-  }
-}
 
-// k_elastic for vesicles of at most 64 R points: one wavefront per vesicle, lane l owning points R l ..
-// R l + R - 1, and LDS sized by 64 R (the derivative weights, then u_x and u_y stored twice), so that many
-// vesicles share a compute unit.  Larger vesicles are left to k_elastic.  The arithmetic of every point is
-// that of k_elastic, in the same order.
-template <int R>
-__global__ __launch_bounds__(64) void k_elastic_wave(const double* __restrict__ X, const double* __restrict__ sigma,
-                                                     double kappa_b, const int32_t* __restrict__ off, int M, int P,
-                                                     double* __restrict__ f, double* __restrict__ w) {
-  constexpr int kCap = 64 * R;
-  extern __shared__ double es[];
-  double* d = es;
-  double* ux = es + kCap;
-  double* uy = ux + pad8(2 * kCap);
-  const double two_pi = 6.28318530717958647693;
-  const int lane = threadIdx.x, i0 = R * lane;
-  for (int v = blockIdx.x; v < M; v += gridDim.x) {
-    const int j0 = clamp_i(off[v], 0, P);
-    const int j1 = max(j0, clamp_i(off[v + 1], 0, P));
-    const int n = j1 - j0;
-    if (n == 0 || n > kCap) continue;
-    wave_sync();  // the previous vesicle is done with LDS
-    for (int m = lane; m < n; m += 64) {
-      double c = 0.0;
-      if (m > 0) {
+  __device__ __forceinline__ void sync() const {
+    if constexpr (kCoop) __syncthreads();
+    else wave_sync();
+  }
+
+  __device__ __forceinline__ int point(int q) const { return 16 * p + k4 + 4 * q; }
+  __device__ __forceinline__ bool owns(int q) const { return point(q) < n; }
+  __device__ __forceinline__ int at(int q) const { return min(point(q), n - 1); }  // for loads without a branch
+
+  // Sets a[k] for k = at, at +- n, ... in [lo, 16 nb).
+  template <class Put>
+  __device__ __forceinline__ void periodic(int at, int lo, const Put& put) const {
+    if (n >= 16) {  // lo >= 1 - n and 16 nb <= n + 15: at most one period to either side
+      put(at);
+      if (at - n >= lo) put(at - n);
+      if (at + n < 16 * nb) put(at + n);
+    } else {
+      for (int k = at - 15 * n; k < 16; k += n)
+        if (k >= lo) put(k);
+    }
+  }
+
+  // The weights, d_{N-m} = -d_m.
+  __device__ __forceinline__ void put_weight(int m, double v) const {
+    periodic(m, -15, [&](int k) { d[k] = v; });
+  }
+  __device__ __forceinline__ void weights() const {
+    const int step = kCoop ? kB : 64, at = kCoop ? threadIdx.x : threadIdx.x & 63;
+    for (int m = at; 2 * m <= n; m += step) {
+      double v = 0.0;
+      if (m > 0 && 2 * m < n) {
         double s, co;
         sincospi((double)m / (double)n, &s, &co);
         const double sg = (m & 1) ? -0.5 : 0.5;
-        c = (n & 1) ? sg / s : sg * co / s;
+        v = (n & 1) ? sg / s : sg * co / s;
+        put_weight(n - m, -v);
       }
-      d[m] = c;
-      ux[pad8(m)] = ux[pad8(m + n)] = X[j0 + m] - X[j0];
-      uy[pad8(m)] = uy[pad8(m + n)] = X[P + j0 + m] - X[P + j0];
+      put_weight(m, v);
     }
-    wave_sync();
-    double ax[R], ay[R], jinv[R], sx[R], sy[R], tx[R], ty[R], bx[R], by[R];
-    apply_d_lane<R>(d, ux, uy, n, i0, ax, ay);  // X_alpha
+  }
+
+  // u for the next product (the previous one is done with it; the caller synchronises before and after).
+  __device__ __forceinline__ void store(const double (&v)[kValues]) const {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const double J = sqrt(ax[r] * ax[r] + ay[r] * ay[r]);
-      jinv[r] = 1.0 / J;
-      sx[r] = ax[r] * jinv[r];  // X_s
-      sy[r] = ay[r] * jinv[r];
-      const int i = i0 + r;
-      if (i < n) w[j0 + i] = J * (two_pi / (double)n);
+    for (int q = 0; q < kValues; ++q) {
+      if (owns(q)) periodic(point(q), 16 - 16 * nb, [&](int k) { u[upos(k) + c] = v[q]; });
     }
-    wave_sync();
+  }
+
+  // D u at this lane's points (a lane beyond the last point repeats the last block, its values are not used).
+  __device__ __forceinline__ void product(double (&out)[kValues]) const {
+    double4v acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+    if (live) {
+      const double* dp = d + ((threadIdx.x & 15) - k4);
+      const double* up = u + 40 * min(p, nb - 1) + 2 * k4 + c;
+      double a[4], b[4];  // the operands of one t, read while the one before is multiplied
+      const auto load = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = i0 + r;
-      if (i < n) {
-        ux[pad8(i)] = ux[pad8(i + n)] = sx[r];
-        uy[pad8(i)] = uy[pad8(i + n)] = sy[r];
-      }
-    }
-    wave_sync();
-    apply_d_lane<R>(d, ux, uy, n, i0, bx, by);  // X_ss * J
-#pragma unroll
-    for (int r = 0; r < R; ++r) { bx[r] *= jinv[r]; by[r] *= jinv[r]; }
-    // tension term (sigma X_s)_s
-#pragma unroll
-    for (int r = 0; r < R; ++r) tx[r] = ty[r] = 0.0;
-    if (sigma) {
-      wave_sync();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int i = i0 + r;
-        if (i < n) {
-          const double sg = sigma[j0 + i];
-          ux[pad8(i)] = ux[pad8(i + n)] = sg * sx[r];
-          uy[pad8(i)] = uy[pad8(i + n)] = sg * sy[r];
+        for (int k = 0; k < 4; ++k) {
+          a[k] = dp[-4 * k];
+          b[k] = up[8 * k];
         }
+        dp += 16;
+        up -= 40;
+      };
+      load();
+      asm volatile("; t = 0");  // keeps these reads apart from the loop's (merged, every t would copy the accumulators)
+      for (int t = 0; t < nb - 1; ++t) {
+        const double a0 = a[0], a1 = a[1], a2 = a[2], a3 = a[3], b0 = b[0], b1 = b[1], b2 = b[2], b3 = b[3];
+        load();
+        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc1, 0, 0, 0);
+        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a2, b2, acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a3, b3, acc1, 0, 0, 0);
       }
-      wave_sync();
-      apply_d_lane<R>(d, ux, uy, n, i0, tx, ty);
-#pragma unroll
-      for (int r = 0; r < R; ++r) { tx[r] *= jinv[r]; ty[r] *= jinv[r]; }
-    }
-    // X_sss, then X_ssss
-    for (int pass = 0; pass < 2; ++pass) {
-      wave_sync();
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int i = i0 + r;
-        if (i < n) {
-          ux[pad8(i)] = ux[pad8(i + n)] = bx[r];
-          uy[pad8(i)] = uy[pad8(i + n)] = by[r];
-        }
-      }
-      wave_sync();
-      apply_d_lane<R>(d, ux, uy, n, i0, bx, by);
-#pragma unroll
-      for (int r = 0; r < R; ++r) { bx[r] *= jinv[r]; by[r] *= jinv[r]; }
+      const int x = 16 * nb - n;  // s < x wraps round
+      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], k4 < x ? 0.0 : b[0], acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], 4 + k4 < x ? 0.0 : b[1], acc1, 0, 0, 0);
+      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[2], 8 + k4 < x ? 0.0 : b[2], acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[3], 12 + k4 < x ? 0.0 : b[3], acc1, 0, 0, 0);
     }
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int i = i0 + r;
-      if (i < n) {
-        f[j0 + i] = fma(-kappa_b, bx[r], tx[r]);
-        f[P + j0 + i] = fma(-kappa_b, by[r], ty[r]);
+    for (int q = 0; q < kValues; ++q) out[q] = acc0[q] + acc1[q];
+  }
+
+  __device__ __forceinline__ void derivative(const double (&v)[kValues], double (&out)[kValues]) const {
+    sync();
+    store(v);
+    sync();
+    product(out);
+  }
+};
+
+// The vesicles of this workgroup: `per` consecutive ones per step of the grid.  body(curve, j0) runs with one
+// wavefront for each vesicle of up to 128 points and with the whole workgroup for larger ones; too_large(j0, n)
+// with the whole workgroup for those of more than 1024 points.
+template <class Body, class TooLarge>
+__device__ __forceinline__ void for_vesicles(double* lds, const int32_t* __restrict__ off, int M, int P, int per,
+                                             const Body& body, const TooLarge& too_large) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int v0 = blockIdx.x * per; v0 < M; v0 += gridDim.x * per) {
+    const int v1 = min(v0 + per, M);
+    if (v0 + wave < v1) {
+      const int j0 = clamp_i(off[v0 + wave], 0, P);
+      const int n = max(j0, clamp_i(off[v0 + wave + 1], 0, P)) - j0;
+      if (n > 0 && n <= kWavePoints)
+        body(Curve<false>(lds + wave * region_doubles(kWavePoints), n), j0);
+    }
+    for (int v = v0; v < v1; ++v) {
+      const int j0 = clamp_i(off[v], 0, P);
+      const int n = max(j0, clamp_i(off[v + 1], 0, P)) - j0;
+      if (n <= kWavePoints) continue;
+      if (n > kMaxN) {
+        too_large(j0, n);
+        continue;
       }
+      __syncthreads();  // the wavefronts' own vesicles are done with LDS
+      body(Curve<true>(lds, n), j0);
+      __syncthreads();
     }
   }
 }
 
+constexpr int kLdsDoubles = kWaves * region_doubles(kWavePoints) > region_doubles(kMaxN)
+                                ? kWaves * region_doubles(kWavePoints) : region_doubles(kMaxN);
+
+// Five products of 32 matrix instructions (64 cycles each) at 128 points: 2000 x 128 is two wavefronts on every SIMD
+// and 8.5 us of matrix work; 49.9 -> 18.8 us (before: vector FMAs, whose operands came from LDS at three reads for four
+// FMAs, and a second launch for vesicles above the wavefront form).
 __global__ __launch_bounds__(kB) void k_elastic(const double* __restrict__ X, const double* __restrict__ sigma,
-                                                double kappa_b, const int32_t* __restrict__ off, int M, int P,
-                                                double* __restrict__ f, double* __restrict__ w, int min_n) {
-  __shared__ double d[kMaxN];
-  __shared__ double ux[kMaxN];
-  __shared__ double uy[kMaxN];
-  const double two_pi = 6.28318530717958647693;
-  for (int v = blockIdx.x; v < M; v += gridDim.x) {
-    const int j0 = clamp_i(off[v], 0, P);
-    const int j1 = max(j0, clamp_i(off[v + 1], 0, P));
-    const int n = j1 - j0;
-    if (n <= min_n) continue;  // empty, or done by k_elastic_wave
-    if (n > kMaxN) {
-      for (int i = threadIdx.x; i < n; i += kB) {
-        f[j0 + i] = NAN;
-        f[P + j0 + i] = NAN;
-        w[j0 + i] = NAN;
-      }
-      continue;
+                                                double kappa_b, const int32_t* __restrict__ off, int M, int P, int per,
+                                                double* __restrict__ f, double* __restrict__ w) {
+  __shared__ double lds[kLdsDoubles];
+  const auto one = [&](const auto& cv, int j0) __attribute__((always_inline)) {
+    const int n = cv.n;
+    const double* Xc = X + (cv.c ? P : 0) + j0;
+    double* fc = f + (cv.c ? P : 0) + j0;
+    double sg[kValues], a[kValues], jinv[kValues], tension[kValues];
+    const double* sg0 = sigma ? sigma + j0 : Xc;  // not used without tension
+    const double x0 = Xc[0];
+#pragma unroll
+    for (int q = 0; q < kValues; ++q) {
+      a[q] = Xc[cv.at(q)] - x0;
+      sg[q] = sg0[cv.at(q)];
+      tension[q] = 0.0;
     }
-    __syncthreads();  // the previous vesicle is done with LDS
-    for (int m = threadIdx.x; m < n; m += kB) {
-      double c = 0.0;
-      if (m > 0) {
-        double s, co;
-        sincospi((double)m / (double)n, &s, &co);
-        const double sg = (m & 1) ? -0.5 : 0.5;
-        c = (n & 1) ? sg / s : sg * co / s;
-      }
-      d[m] = c;
-      ux[m] = X[j0 + m] - X[j0];
-      uy[m] = X[P + j0 + m] - X[P + j0];
+    cv.weights();
+    cv.derivative(a, a);  // X_alpha
+#pragma unroll
+    for (int q = 0; q < kValues; ++q) {
+      const double o = other_component(a[q]);
+      const double J = sqrt(a[q] * a[q] + o * o);
+      jinv[q] = 1.0 / J;
+      if (cv.c == 0 && cv.owns(q)) w[j0 + cv.point(q)] = J * (6.28318530717958647693 / (double)n);
+      a[q] *= jinv[q];  // X_s
+      sg[q] *= a[q];
     }
-    __syncthreads();
-
-    double ax[kPer], ay[kPer], jinv[kPer], sx[kPer], sy[kPer], tx[kPer], ty[kPer], bx[kPer], by[kPer];
-    apply_d(d, ux, uy, n, ax, ay);  // X_alpha
+    if (sigma) {  // (sigma X_s)_s
+      cv.derivative(sg, tension);
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const double J = sqrt(ax[k] * ax[k] + ay[k] * ay[k]);
-      jinv[k] = 1.0 / J;
-      sx[k] = ax[k] * jinv[k];  // X_s
-      sy[k] = ay[k] * jinv[k];
-      const int i = threadIdx.x + k * kB;
-      if (i < n) w[j0 + i] = J * (two_pi / (double)n);
+      for (int q = 0; q < kValues; ++q) tension[q] *= jinv[q];
     }
-    __syncthreads();
+    for (int pass = 0; pass < 3; ++pass) {  // X_ss, X_sss, X_ssss
+      cv.derivative(a, a);
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int i = threadIdx.x + k * kB;
-      if (i < n) { ux[i] = sx[k]; uy[i] = sy[k]; }
-    }
-    __syncthreads();
-    apply_d(d, ux, uy, n, bx, by);  // X_ss * J
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) { bx[k] *= jinv[k]; by[k] *= jinv[k]; }
-    // tension term (sigma X_s)_s
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) tx[k] = ty[k] = 0.0;
-    if (sigma) {
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int i = threadIdx.x + k * kB;
-        if (i < n) {
-          const double sg = sigma[j0 + i];
-          ux[i] = sg * sx[k];
-          uy[i] = sg * sy[k];
-        }
-      }
-      __syncthreads();
-      apply_d(d, ux, uy, n, tx, ty);
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) { tx[k] *= jinv[k]; ty[k] *= jinv[k]; }
-    }
-    // X_sss, then X_ssss
-    for (int pass = 0; pass < 2; ++pass) {
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) {
-        const int i = threadIdx.x + k * kB;
-        if (i < n) { ux[i] = bx[k]; uy[i] = by[k]; }
-      }
-      __syncthreads();
-      apply_d(d, ux, uy, n, bx, by);
-#pragma unroll
-      for (int k = 0; k < kPer; ++k) { bx[k] *= jinv[k]; by[k] *= jinv[k]; }
+      for (int q = 0; q < kValues; ++q) a[q] *= jinv[q];
     }
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int i = threadIdx.x + k * kB;
-      if (i < n) {
-        f[j0 + i] = fma(-kappa_b, bx[k], tx[k]);
-        f[P + j0 + i] = fma(-kappa_b, by[k], ty[k]);
-      }
+    for (int q = 0; q < kValues; ++q)
+      if (cv.owns(q)) fc[cv.point(q)] = fma(-kappa_b, a[q], tension[q]);
+  };
+  const auto too_large = [&](int j0, int n) {
+    for (int i = threadIdx.x; i < n; i += kB) {
+      f[j0 + i] = NAN;
+      f[P + j0 + i] = NAN;
+      w[j0 + i] = NAN;
     }
-  }
-}
-
-// Sum of one value per thread over the workgroup in a fixed order (waves in index order).
-__device__ __forceinline__ double block_sum(double v, double* red) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  __syncthreads();  // red is free
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int k = 0; k < kB / 64; ++k) s += red[k];
-  return s;
+  };
+  for_vesicles(lds, off, M, P, per, one, too_large);
 }
 
 // CreateNearLayers (Algorithm 4, Section 3.3): node a = l * n + k of vesicle v is membrane point
 // k moved along the outward unit normal by d_l = (l - 2) h_v / 2, l = 0..4.  The tangent is the
 // spectral X_alpha / |X_alpha|; the outward side is fixed by the sign of the enclosed signed area
 // (trapezoid rule of (x y_alpha - y x_alpha) / 2), so either orientation of the points works.
+// One product of the force's kind; 100 B per point.  2000 x 32: 10.2 -> 8.5 us; 2000 x 128: 20.6 -> 15.0 us.
 __global__ __launch_bounds__(kB) void k_near_layers(const double* __restrict__ X, const double* __restrict__ w,
-                                                    const int32_t* __restrict__ off, int M, int P,
+                                                    const int32_t* __restrict__ off, int M, int P, int per,
                                                     double* __restrict__ layers) {
-  __shared__ double d[kMaxN];
-  __shared__ double ux[kMaxN];
-  __shared__ double uy[kMaxN];
-  __shared__ double red[kB / 64];
+  __shared__ double lds[kLdsDoubles];
+  __shared__ double red[kWaves];
   const size_t P5 = (size_t)5 * P;
-  for (int v = blockIdx.x; v < M; v += gridDim.x) {
-    const int j0 = clamp_i(off[v], 0, P);
-    const int j1 = max(j0, clamp_i(off[v + 1], 0, P));
-    const int n = j1 - j0;
-    if (n == 0) continue;
-    double* lx = layers + (size_t)5 * j0;
-    double* ly = layers + P5 + (size_t)5 * j0;
-    if (n > kMaxN || n < 3) {
-      for (int a = threadIdx.x; a < 5 * n; a += kB) {
-        lx[a] = NAN;
-        ly[a] = NAN;
-      }
-      continue;
+  const auto undefined = [&](int j0, int n, int at, int step) {
+    for (int a = at; a < 5 * n; a += step) {
+      layers[(size_t)5 * j0 + a] = NAN;
+      layers[P5 + (size_t)5 * j0 + a] = NAN;
     }
-    __syncthreads();  // the previous vesicle is done with LDS
-    for (int m = threadIdx.x; m < n; m += kB) {
-      double c = 0.0;
-      if (m > 0) {
-        double s, co;
-        sincospi((double)m / (double)n, &s, &co);
-        const double sg = (m & 1) ? -0.5 : 0.5;
-        c = (n & 1) ? sg / s : sg * co / s;
-      }
-      d[m] = c;
-      ux[m] = X[j0 + m] - X[j0];  // relative to the first point (derivative and signed area)
-      uy[m] = X[P + j0 + m] - X[P + j0];
+  };
+  const auto one = [&](const auto& cv, int j0) __attribute__((always_inline)) {
+    const int n = cv.n;
+    if (n < 3) {
+      undefined(j0, n, threadIdx.x & 63, 64);
+      return;
     }
-    __syncthreads();
-    double ax[kPer], ay[kPer];
-    apply_d(d, ux, uy, n, ax, ay);  // X_alpha
+    const double* Xc = X + (cv.c ? P : 0) + j0;
+    double* lc = layers + (cv.c ? P5 : 0) + (size_t)5 * j0;
+    double x[kValues], u[kValues], a[kValues];
+    const double x0 = Xc[0];
+#pragma unroll
+    for (int q = 0; q < kValues; ++q) {
+      x[q] = Xc[cv.at(q)];
+      u[q] = x[q] - x0;
+    }
+    const double h = wave_mean_spacing(w + j0, n);
+    cv.weights();
+    cv.derivative(u, a);  // X_alpha
     double part = 0.0;
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int i = threadIdx.x + k * kB;
-      if (i < n) part += ux[i] * ay[k] - uy[i] * ax[k];
+    for (int q = 0; q < kValues; ++q) {
+      const double o = other_component(a[q]);
+      const double jinv = 1.0 / sqrt(a[q] * a[q] + o * o);
+      if (cv.owns(q)) part += cv.c ? -(u[q] * o) : u[q] * o;
+      a[q] = cv.c ? -o * jinv : o * jinv;  // tangent turned clockwise: outward when counter-clockwise
     }
-    const double orient = block_sum(part, red) >= 0.0 ? 1.0 : -1.0;
-    const double h = wave_mean_spacing(w + j0, n);
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) {
-      const int i = threadIdx.x + k * kB;
-      if (i < n) {
-        const double jinv = 1.0 / sqrt(ax[k] * ax[k] + ay[k] * ay[k]);
-        const double nx = orient * ay[k] * jinv;  // tangent turned clockwise: outward when counter-clockwise
-        const double ny = -orient * ax[k] * jinv;
+    for (int m = 32; m >= 1; m >>= 1) part += __shfl_xor(part, m, 64);
+    if constexpr (!std::is_same_v<std::decay_t<decltype(cv)>, Curve<false>>) {
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = part;
+      __syncthreads();
+      part = 0.0;
 #pragma unroll
-        for (int l = 0; l < 5; ++l) {
-          const double dl = 0.5 * (double)(l - 2) * h;
-          lx[l * n + i] = fma(dl, nx, X[j0 + i]);
-          ly[l * n + i] = fma(dl, ny, X[P + j0 + i]);
-        }
-      }
+      for (int k = 0; k < kWaves; ++k) part += red[k];
     }
-  }
+    const double orient = part >= 0.0 ? 1.0 : -1.0;
+#pragma unroll
+    for (int q = 0; q < kValues; ++q) {
+      if (!cv.owns(q)) continue;
+#pragma unroll
+      for (int l = 0; l < 5; ++l) lc[l * n + cv.point(q)] = fma(0.5 * (double)(l - 2) * h, orient * a[q], x[q]);
+    }
+  };
+  for_vesicles(lds, off, M, P, per, one, [&](int j0, int n) { undefined(j0, n, threadIdx.x, kB); });
+}
+
+// Vesicles per workgroup.  While there are fewer workgroups than compute units each gets a vesicle of its own (two
+// wavefronts on one SIMD share its matrix core: 13.9 us for 1024 x 128, 21.6 us for 2000); beyond, up to eight share
+// one, a wavefront each.  Vesicles above 128 points on average take a workgroup each, since one after the other they
+// would leave most of the chip idle (200 x 200: 16.7 us, before 46.3 us with a wavefront each; 64 x 1024: 546 -> 96 us).
+int vesicles_per_block(int M, int P) {
+  if ((int64_t)P > (int64_t)kWavePoints * M) return 1;
+  const int per = (M + 255) / 256;
+  return per < kWaves ? per : kWaves;
+}
+
+int blocks(int M, int per) {
+  const int g = (M + per - 1) / per;
+  return g < 65535 ? g : 65535;
 }
 
 }  // namespace
@@ -379,36 +346,18 @@ __global__ __launch_bounds__(kB) void k_near_layers(const double* __restrict__ X
 hipError_t launch_near_layers(const double* X, const double* w, const int32_t* off, int M, int P, double* layers,
                               void* stream) {
   if (M == 0 || P == 0) return hipSuccess;
-  const int grid = M < 65535 ? M : 65535;
-  hipLaunchKernelGGL(k_near_layers, dim3(grid), dim3(kB), 0, reinterpret_cast<hipStream_t>(stream), X, w, off, M, P,
-                     layers);
+  const int per = vesicles_per_block(M, P);
+  hipLaunchKernelGGL(k_near_layers, dim3(blocks(M, per)), dim3(kB), 0, reinterpret_cast<hipStream_t>(stream), X, w, off,
+                     M, P, per, layers);
   return hipGetLastError();
 }
-
-static size_t pad8_host(int j) { return (size_t)j + (size_t)(j >> 3); }
 
 hipError_t launch_elastic(const double* X, const double* sigma, double kappa_b, const int32_t* off, int M, int P,
                           double* f, double* w, void* stream) {
   if (M == 0 || P == 0) return hipSuccess;
-  const int grid = M < 65535 ? M : 65535;
-  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  // vesicles of up to 64, 128 or 256 points (the bound from the mean size) take one wavefront each
-  const int64_t mean = ((int64_t)P + M - 1) / M;
-  int cap = 0;
-  if (mean <= 64) {
-    cap = 64;
-    hipLaunchKernelGGL(k_elastic_wave<1>, dim3(grid), dim3(64), sizeof(double) * (64 + 2 * pad8_host(128)), st, X,
-                       sigma, kappa_b, off, M, P, f, w);
-  } else if (mean <= 128) {
-    cap = 128;
-    hipLaunchKernelGGL(k_elastic_wave<2>, dim3(grid), dim3(64), sizeof(double) * (128 + 2 * pad8_host(256)), st, X,
-                       sigma, kappa_b, off, M, P, f, w);
-  } else if (mean <= 256) {
-    cap = 256;
-    hipLaunchKernelGGL(k_elastic_wave<4>, dim3(grid), dim3(64), sizeof(double) * (256 + 2 * pad8_host(512)), st, X,
-                       sigma, kappa_b, off, M, P, f, w);
-  }
-  hipLaunchKernelGGL(k_elastic, dim3(grid), dim3(kB), 0, st, X, sigma, kappa_b, off, M, P, f, w, cap);
+  const int per = vesicles_per_block(M, P);
+  hipLaunchKernelGGL(k_elastic, dim3(blocks(M, per)), dim3(kB), 0, reinterpret_cast<hipStream_t>(stream), X, sigma,
+                     kappa_b, off, M, P, per, f, w);
   return hipGetLastError();
 }
 
