@@ -310,144 +310,296 @@ __global__ __launch_bounds__(64) void k_tc_sort(const double* __restrict__ X, co
 // Moments of a box: 4 rows of (p + 1) complex numbers: row 0 M_k[F], row 1 M_k[conj F] (divided by k
 // for k >= 1 once all translations are done), row 2 M_k[conj(zeta) F], row 3 M_k[F] / k (filled last).
 
-__device__ __forceinline__ double2 cpow_int(double2 z, int k) {
-  double2 r = make_double2(1.0, 0.0);
-  double2 b = z;
-  while (k > 0) {
-    if (k & 1) r = cmul(r, b);
-    b = cmul(b, b);
-    k >>= 1;
+typedef double double4v __attribute__((ext_vector_type(4)));
+
+// The value of the neighbouring lane (lanes 2 i and 2 i + 1 exchange).
+__device__ __forceinline__ double quad_swap(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0xB1, 0xF, 0xF, false);  // quad_perm 1, 0, 3, 2
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0xB1, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+
+// x^k for 0 <= k < 64.
+__device__ __forceinline__ double pow_int(double x, int k) {
+  double r = 1.0;
+#pragma unroll
+  for (int b = 0; b < 6; ++b) {
+    if (k & (1 << b)) r *= x;
+    x *= x;
   }
   return r;
 }
 
-// One wavefront per leaf, lane k = order.  The leaf's points pass through LDS 32 at a time, each with
-// its powers zeta^0 .. zeta^p (by repeated multiplication), so lane k reads zeta^k instead of forming it.
-constexpr int kP2MChunk = 32;
-
-__global__ __launch_bounds__(64) void k_tc_p2m(const double4* __restrict__ srec,
-                                               const int32_t* __restrict__ starts, const Geom* __restrict__ geom,
-                                               int depth, int p, double2* __restrict__ mom,
-                                               int32_t* __restrict__ bcount) {
-  extern __shared__ double2 p2m_lds[];  // powers [kP2MChunk][p + 1], then F and conj(zeta) of the chunk
-  double2* Fs = p2m_lds + kP2MChunk * (p + 1);
-  double2* Zc = Fs + kP2MChunk;
-  const int leaf = blockIdx.x;
-  const int k = threadIdx.x;
-  const int n = 1 << depth;
-  const int s0 = starts[leaf], s1 = starts[leaf + 1];
-  if (k == 0) bcount[leaf] = s1 - s0;
-  const double2 c = box_center(*geom, n, leaf / n, leaf % n);
-  double2 m0 = make_double2(0.0, 0.0), m1 = m0, m2 = m0;
-  for (int c0 = s0; c0 < s1; c0 += kP2MChunk) {
-    const int cnt = min(kP2MChunk, s1 - c0);
-    __syncthreads();  // the previous chunk is done
-    if (k < cnt) {
-      const double4 s = srec[c0 + k];
-      const double2 zeta = make_double2(s.x - c.x, s.y - c.y);
-      Fs[k] = make_double2(s.z, s.w);
-      Zc[k] = make_double2(zeta.x, -zeta.y);
-      double2 z = make_double2(1.0, 0.0);
-      for (int m = 0; m <= p; ++m) {
-        p2m_lds[k * (p + 1) + m] = z;
-        z = cmul(z, zeta);
-      }
-    }
-    __syncthreads();
-    if (k <= p) {
-      for (int q = 0; q < cnt; ++q) {
-        const double2 F = Fs[q], zk = p2m_lds[q * (p + 1) + k];
-        const double2 Fz = cmul(F, zk);
-        m0.x += Fz.x;
-        m0.y += Fz.y;
-        const double2 Fcz = cmul(make_double2(F.x, -F.y), zk);
-        m1.x += Fcz.x;
-        m1.y += Fcz.y;
-        const double2 Pz = cmul(Zc[q], Fz);
-        m2.x += Pz.x;
-        m2.y += Pz.y;
-      }
-    }
-  }
-  if (k > p) return;
-  double2* mb = mom + (size_t)leaf * 4 * (p + 1);
-  mb[k] = m0;
-  mb[(p + 1) + k] = m1;
-  mb[2 * (p + 1) + k] = m2;
+// e^(i pi a / 4).
+__device__ __forceinline__ double2 eighth_turn(int a) {
+  constexpr double h = 0.70710678118654752440;
+  const auto cosine = [&](int t) {
+    const int m = t & 3;
+    const double c = m == 0 ? 1.0 : (m == 1 ? h : (m == 2 ? 0.0 : -h));
+    return (t & 4) ? -c : c;
+  };
+  return make_double2(cosine(a), cosine(a + 6));
 }
 
-// 1 / (m + 1), m = 0..kMaxOrder: the binomial recurrence below multiplies instead of dividing.
-__constant__ double kRecip[kMaxOrder + 1] = {
-    1.0 / 1,  1.0 / 2,  1.0 / 3,  1.0 / 4,  1.0 / 5,  1.0 / 6,  1.0 / 7,  1.0 / 8,  1.0 / 9,  1.0 / 10,
-    1.0 / 11, 1.0 / 12, 1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16, 1.0 / 17, 1.0 / 18, 1.0 / 19, 1.0 / 20,
-    1.0 / 21, 1.0 / 22, 1.0 / 23, 1.0 / 24, 1.0 / 25, 1.0 / 26, 1.0 / 27, 1.0 / 28, 1.0 / 29, 1.0 / 30,
-    1.0 / 31, 1.0 / 32, 1.0 / 33, 1.0 / 34, 1.0 / 35, 1.0 / 36, 1.0 / 37, 1.0 / 38, 1.0 / 39, 1.0 / 40,
-    1.0 / 41, 1.0 / 42, 1.0 / 43, 1.0 / 44, 1.0 / 45, 1.0 / 46, 1.0 / 47, 1.0 / 48, 1.0 / 49};
+// A box's moments re-centred to its parent's centre, d = box centre - parent centre:
+//   M'_k = sum_{m <= k} C(k, m) d^(k-m) M_m = d^k sum_m C(k, m) (d^-m M_m)
+// (and the conj(zeta) F row gains conj(d) times the translated F row: left to the sum over the children), by one
+// wavefront on the matrix cores: the triangle of binomials, which every box shares, stays in registers as the first
+// operand, and the six real columns of d^-m M_m (three rows, Re and Im) are the second.  For 8 K >= p + 1 orders.
+// d = delta e^(i pi a / 4), a = 1, 3, 5, 7, so its powers are real powers and eighths of a turn; the division by
+// delta^m is done in two halves, which keeps it finite wherever the moments are.
+// (On the vector units, a lane per order, the moments' broadcasts from LDS bounded it: 5.5 us for 64 boxes on a CU.)
+template <int K>
+struct Recentre {
+  static constexpr int kTiles = (K + 1) / 2, kOrders = 8 * K, kLds = 8 * kOrders;  // LDS doubles of run()
+  static constexpr int steps(int rt) { return 4 * (rt + 1) < 2 * K ? 4 * (rt + 1) : 2 * K; }
+  double a[kTiles][2 * K];
+  int lane, p;
 
-// Parent moments at a level with n boxes per side from the children one level down:
-// M'_k = sum_children sum_{m <= k} C(k, m) d^(k-m) M_m, d = child centre - parent centre; the
-// conj(zeta) F row gains conj(d) times the translated F row.  One workgroup per parent box, wave q
-// translates child q (lane k = order, the child's three rows staged in LDS), and the four results
-// are added in child order.  C(k, m + 1) = C(k, m) (k - m) / (m + 1) is an integer below 2^53 for
-// k <= 48, so rounding the product with the reciprocal to the nearest integer gives it exactly.
-__global__ __launch_bounds__(256) void k_tc_m2m(const Geom* __restrict__ geom, int n, int p,
-                                                const double2* __restrict__ child, const int32_t* __restrict__ ccount,
-                                                double2* __restrict__ parent, int32_t* __restrict__ pcount) {
-  __shared__ double2 cm[4][3 * (kMaxOrder + 1)];
-  const int box = blockIdx.x;
-  const int q = threadIdx.x >> 6, k = threadIdx.x & 63;
-  const int bx = box / n, by = box % n;
-  const int stride = 4 * (p + 1);
-  const double wc = geom->side / (double)(2 * n);  // child width
-  const int cb = (2 * bx + (q >> 1)) * (2 * n) + (2 * by + (q & 1));
-  const int cnt = ccount[cb];
-  if (cnt > 0)
-    for (int e = k; e < 3 * (p + 1); e += 64) cm[q][e] = child[(size_t)cb * stride + e];
-  __syncthreads();
-  double2 t0 = make_double2(0.0, 0.0), t1 = t0, t2 = t0;
-  if (cnt > 0 && k <= p) {
-    const double2 d = make_double2(((double)(q >> 1) - 0.5) * wc, ((double)(q & 1) - 0.5) * wc);
-    const double dd = d.x * d.x + d.y * d.y;
-    const double2 dinv = make_double2(d.x / dd, -d.y / dd);
-    double binom = 1.0;           // C(k, m)
-    double2 dp = cpow_int(d, k);  // d^(k - m)
-    for (int m = 0; m <= k; ++m) {
-      const double2 coef = make_double2(binom * dp.x, binom * dp.y);
-      t0 = cfma(coef, cm[q][m], t0);
-      t1 = cfma(coef, cm[q][(p + 1) + m], t1);
-      t2 = cfma(coef, cm[q][2 * (p + 1) + m], t2);
-      binom = rint(binom * (double)(k - m) * kRecip[m]);
-      dp = cmul(dp, dinv);
-    }
-    const double2 extra = cmul(make_double2(d.x, -d.y), t0);
-    t2.x += extra.x;
-    t2.y += extra.y;
-  }
-  __syncthreads();  // every wave is done reading its child
-  if (k <= p) {     // each wave's row of LDS now holds its three results
-    cm[q][k] = t0;
-    cm[q][(p + 1) + k] = t1;
-    cm[q][2 * (p + 1) + k] = t2;
-  }
-  __syncthreads();
-  if (q == 0) {
-    int tot = 0;
-    for (int c = 0; c < 4; ++c) tot += ccount[(2 * bx + (c >> 1)) * (2 * n) + (2 * by + (c & 1))];
-    if (k == 0) pcount[box] = tot;
-    if (k <= p) {
-      double2 s0 = cm[0][k], s1 = cm[0][(p + 1) + k], s2 = cm[0][2 * (p + 1) + k];
-      for (int c = 1; c < 4; ++c) {
-        s0.x += cm[c][k].x;
-        s0.y += cm[c][k].y;
-        s1.x += cm[c][(p + 1) + k].x;
-        s1.y += cm[c][(p + 1) + k].y;
-        s2.x += cm[c][2 * (p + 1) + k].x;
-        s2.y += cm[c][2 * (p + 1) + k].y;
+  __device__ __forceinline__ explicit Recentre(int order) : lane(threadIdx.x & 63), p(order) {
+#pragma unroll
+    for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+      for (int s = 0; s < steps(rt); ++s) {
+        const int k = 16 * rt + (lane & 15), m = min(4 * s + (lane >> 4), kTabM - 1);
+        const double c = kBinomials.t[m][max(k - m, 0)];
+        a[rt][s] = m <= k ? c : 0.0;
       }
-      double2* pm = parent + (size_t)box * stride;
-      pm[k] = s0;
-      pm[(p + 1) + k] = s1;
-      pm[2 * (p + 1) + k] = s2;
+  }
+
+  // d^k, d = delta e^(i pi turn / 4).
+  __device__ __forceinline__ static double2 power(double delta, int turn, int k) {
+    const double2 e = eighth_turn(turn * k);
+    const double r = pow_int(delta, k);
+    return make_double2(r * e.x, r * e.y);
+  }
+
+  // m0, m1, m2: lane m's moments of order m (0 beyond p).  pw (LDS): d^0 .. d^p.  x (LDS): kLds doubles of this
+  // wavefront, where it leaves the translated rows, [3][p + 1] complex.
+  __device__ __forceinline__ void run(double2 m0, double2 m1, double2 m2, double delta, int turn,
+                                      const double2* __restrict__ pw, double* __restrict__ x) const {
+    if (lane < kOrders) {
+      const double inv = 1.0 / delta;
+      const double r1 = pow_int(inv, lane >> 1), r2 = pow_int(inv, lane - (lane >> 1));
+      const double2 e = eighth_turn(-turn * lane);
+      const auto put = [&](int c, double2 m) {
+        const double2 t = cmul(m, e);
+        x[8 * lane + 2 * c] = t.x * r1 * r2;
+        x[8 * lane + 2 * c + 1] = t.y * r1 * r2;
+      };
+      put(0, m0);
+      put(1, m1);
+      put(2, m2);
+    }
+    wave_sync();
+    double4v acc[kTiles];
+#pragma unroll
+    for (int rt = 0; rt < kTiles; ++rt) acc[rt] = double4v{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 2 * K; ++s) {
+      const double b = x[8 * (4 * s + (lane >> 4)) + (lane & 7)];
+#pragma unroll
+      for (int rt = 0; rt < kTiles; ++rt)
+        if (s < steps(rt)) acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt][s], b, acc[rt], 0, 0, 0);
+    }
+    wave_sync();  // x is read
+    const int c = lane & 15;
+#pragma unroll
+    for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int k = 16 * rt + (lane >> 4) + 4 * v;
+        const double2 e = pw[min(k, p)];
+        const double mine = acc[rt][v], other = quad_swap(mine);  // Re and Im are neighbours
+        if (c < 6 && k <= p) x[2 * ((c >> 1) * (p + 1) + k) + (c & 1)] = fma(mine, e.x, (c & 1) ? other * e.y : -(other * e.y));
+      }
+  }
+};
+
+// A parent's moments of order e mod (p + 1), row e / (p + 1), from the translated rows of its four children (kLds
+// doubles apart): their sum in order, and for the conj(zeta) F row conj(d_q) times the F row of each.
+__device__ __forceinline__ double2 children_sum(const double* __restrict__ x, int apart, int p, double half, int e) {
+  double2 r = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double2* rows = reinterpret_cast<const double2*>(x + q * apart);
+    double2 t = rows[e];
+    if (e >= 2 * (p + 1)) t = cfma(make_double2(q & 2 ? half : -half, q & 1 ? -half : half), rows[e - 2 * (p + 1)], t);
+    r.x += t.x;
+    r.y += t.y;
+  }
+  return r;
+}
+
+// Child q's direction from its parent's centre in eighths of a turn (q & 2: right, q & 1: up).
+__device__ __forceinline__ int child_turn(int q) { return (q & 2) ? ((q & 1) ? 1 : 7) : ((q & 1) ? 3 : 5); }
+
+// Sums of pairs of lanes 32, 16 or 8 apart, of two values at once: the lanes with bit kOff clear get lo's, the others
+// hi's.
+template <int kOff>
+__device__ __forceinline__ double pair_sums(double lo, double hi, int lane) {
+  if constexpr (kOff == 8) {
+    const bool up = lane & 8;
+    const double keep = up ? hi : lo, send = up ? lo : hi;
+    const int a = __builtin_amdgcn_update_dpp(0, __double2loint(send), 0x128, 0xF, 0xF, false);  // row_ror:8
+    const int b = __builtin_amdgcn_update_dpp(0, __double2hiint(send), 0x128, 0xF, 0xF, false);
+    return keep + __hiloint2double(b, a);
+  } else {
+    const auto swap = [](unsigned x, unsigned y) {
+      if constexpr (kOff == 32) return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+      else return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    };
+    const auto l = swap(__double2loint(lo), __double2loint(hi)), h = swap(__double2hiint(lo), __double2hiint(hi));
+    return __hiloint2double(h[0], l[0]) + __hiloint2double(h[1], l[1]);
+  }
+}
+
+// Moments of the leaves, and of their parents where pmom is given: one workgroup per parent box, a wavefront per leaf.
+// A leaf's points go eight at a time: lane (b, g) = (lane mod 8, lane / 8) takes point g and the K consecutive orders
+// K b .. K b + K - 1 of the 8 K >= p + 1, whose first power it forms from zeta^K in three select-multiplies, and adds
+// the products of Re zeta^k and Im zeta^k with (F_x, F_y) and conj(zeta) F = (G_x, G_y) to its eight real sums per
+// order.  At the end the groups' sums are exchanged so that each lane keeps one of the eight sums of its orders.
+// Everything stays in registers: about 80 float64 instructions for K = 4 on eight points and 32 orders.
+// 2000 x 128, order 30: this and the coarser levels 69 -> 37 us (before: powers by 32 lanes through LDS, three LDS
+// reads per point and order; a launch per level whose binomials and powers were serial chains).
+template <int K>
+__global__ __launch_bounds__(256) void k_tc_p2m(const double4* __restrict__ srec, const int32_t* __restrict__ starts,
+                                                const Geom* __restrict__ geom, int depth, int p,
+                                                double2* __restrict__ mom, int32_t* __restrict__ bcount,
+                                                double2* __restrict__ pmom, int32_t* __restrict__ pcount) {
+  __shared__ double sums[4][8][8 * K];  // each wavefront's eight sums; then its operands and translated rows
+  __shared__ double2 pw[4][8 * K];
+  __shared__ int32_t cnt[4];
+  static_assert(Recentre<K>::kLds == 8 * 8 * K, "the sums and the operands share LDS");
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int b = lane & 7, g = lane >> 3;
+  const int n = 1 << depth, box = blockIdx.x;
+  const int lx = 2 * (box >> (depth - 1)) + (q >> 1), ly = 2 * (box & (n / 2 - 1)) + (q & 1);
+  const int leaf = lx * n + ly;
+  const int s0 = starts[leaf], s1 = starts[leaf + 1];
+  const double2 c = box_center(*geom, n, lx, ly);
+  const double half = 0.5 * (geom->side / (double)n);  // d = half (+-1, +-1)
+  const double delta = half * 1.41421356237309504880;
+  const int turn = child_turn(q);
+  if (lane < 8 * K) pw[q][lane] = Recentre<K>::power(delta, turn, lane);
+  double acc[K][8];
+#pragma unroll
+  for (int i = 0; i < K; ++i)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[i][e] = 0.0;
+  double4 next = s0 < s1 ? srec[min(s0 + g, s1 - 1)] : make_double4(0.0, 0.0, 0.0, 0.0);
+  for (int c0 = s0; c0 < s1; c0 += 8) {
+    const double4 r = next;
+    const bool ok = c0 + g < s1;
+    next = srec[min(c0 + 8 + g, s1 - 1)];
+    const double2 z = ok ? make_double2(r.x - c.x, r.y - c.y) : make_double2(0.0, 0.0);
+    const double fx = ok ? r.z : 0.0, fy = ok ? r.w : 0.0;
+    const double f4[4] = {fx, fy, fma(z.x, fx, z.y * fy), fma(z.x, fy, -(z.y * fx))};
+    double2 zk = K & 1 ? z : make_double2(1.0, 0.0), sq = z;  // zeta^K
+#pragma unroll
+    for (int i = 2; i <= K; i <<= 1) {
+      sq = cmul(sq, sq);
+      if (K & i) zk = (K & (i - 1)) ? cmul(zk, sq) : sq;
+    }
+    double2 t = (b & 1) ? zk : make_double2(1.0, 0.0);
+    zk = cmul(zk, zk);
+    double2 u = cmul(t, zk);
+    if (b & 2) t = u;
+    zk = cmul(zk, zk);
+    u = cmul(t, zk);
+    if (b & 4) t = u;
+#pragma unroll
+    for (int i = 0; i < K; ++i) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[i][2 * e] = fma(f4[e], t.x, acc[i][2 * e]);
+        acc[i][2 * e + 1] = fma(f4[e], t.y, acc[i][2 * e + 1]);
+      }
+      if (i + 1 < K) t = cmul(t, z);
+    }
+  }
+  const Recentre<K> up(p);  // its operand loads while the sums are exchanged
+  // the groups' sums: each exchange halves the sums a lane keeps
+#pragma unroll
+  for (int i = 0; i < K; ++i) {
+    double* a = acc[i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] = pair_sums<32>(a[e], a[e + 4], lane);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) a[e] = pair_sums<16>(a[e], a[e + 2], lane);
+    sums[q][g][K * b + i] = pair_sums<8>(a[0], a[1], lane);
+  }
+  wave_sync();
+  double2 m0 = make_double2(0.0, 0.0), m1 = m0, m2 = m0;
+  if (lane <= p) {
+    const auto S = [&](int e) { return sums[q][e][lane]; };  // sums of (F_x, F_y, G_x, G_y) times (Re, Im)
+    m0 = make_double2(S(0) - S(3), S(1) + S(2));
+    m1 = make_double2(S(0) + S(3), S(1) - S(2));
+    m2 = make_double2(S(4) - S(7), S(5) + S(6));
+    double2* mb = mom + (size_t)leaf * 4 * (p + 1);
+    mb[lane] = m0;
+    mb[p + 1 + lane] = m1;
+    mb[2 * (p + 1) + lane] = m2;
+  }
+  if (lane == 0) bcount[leaf] = cnt[q] = s1 - s0;
+  if (pmom == nullptr) return;
+  wave_sync();
+  up.run(m0, m1, m2, delta, turn, pw[q], &sums[q][0][0]);
+  __syncthreads();
+  double2* pm = pmom + (size_t)box * 4 * (p + 1);
+  for (int e = threadIdx.x; e < 3 * (p + 1); e += 256) pm[e] = children_sum(&sums[0][0][0], Recentre<K>::kLds, p, half, e);
+  if (threadIdx.x == 0) pcount[box] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+}
+
+// Moments of the levels from `from` up to `to` (from >= to >= 2) from those of level from + 1: one workgroup per box of
+// level `to` works through its boxes of every level, a wavefront per child, four for a box.  Latency bounds it, about
+// 3 us for sixteen children.
+constexpr int up_waves(int K) { return K < 7 ? 16 : 8; }  // K = 7 needs more than 128 registers
+
+template <int K>
+__global__ __launch_bounds__(64 * up_waves(K)) void k_tc_m2m(const Geom* __restrict__ geom, int from, int to, int p,
+                                                          double2* __restrict__ mom, int32_t* __restrict__ bcount) {
+  __shared__ double x[up_waves(K)][Recentre<K>::kLds];
+  __shared__ double2 pw[4][8 * K];
+  __shared__ int32_t cnt[up_waves(K)];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), boxes = blockDim.x >> 8, lane = threadIdx.x & 63;
+  const int q = wave & 3;
+  const int tx = blockIdx.x >> to, ty = blockIdx.x & ((1 << to) - 1);
+  const int stride = 4 * (p + 1), used = 3 * (p + 1);
+  const double side = geom->side;
+  const int turn = child_turn(q);
+  const Recentre<K> up(p);
+  for (int l = from; l >= to; --l) {
+    const double half = 0.5 * (side / (double)(2 << l));  // of a child's width
+    const double delta = half * 1.41421356237309504880;
+    const int sh = l - to;
+    if (wave < 4 && lane < 8 * K) pw[wave][lane] = Recentre<K>::power(delta, turn, lane);
+    __syncthreads();
+    for (int i0 = 0; i0 < 1 << (2 * sh); i0 += boxes) {
+      const int i = i0 + (wave >> 2);
+      if (i < 1 << (2 * sh)) {
+        const int bx = (tx << sh) + (i >> sh), by = (ty << sh) + (i & ((1 << sh) - 1));
+        const size_t cb = level_box_base(l + 1) + ((size_t)(2 * bx + (q >> 1)) << (l + 1)) + (2 * by + (q & 1));
+        double2 m0 = make_double2(0.0, 0.0), m1 = m0, m2 = m0;
+        if (lane <= p) {
+          const double2* mb = mom + cb * stride;
+          m0 = mb[lane];
+          m1 = mb[p + 1 + lane];
+          m2 = mb[2 * (p + 1) + lane];
+        }
+        if (lane == 0) cnt[wave] = bcount[cb];
+        up.run(m0, m1, m2, delta, turn, pw[q], x[wave]);
+      }
+      __syncthreads();
+      const int mine = min(boxes, (1 << (2 * sh)) - i0);
+      for (int e = threadIdx.x; e < mine * used; e += blockDim.x) {
+        const int c = e / used, k = e - c * used, ib = i0 + c;
+        const int bx = (tx << sh) + (ib >> sh), by = (ty << sh) + (ib & ((1 << sh) - 1));
+        const size_t box = level_box_base(l) + ((size_t)bx << l) + by;
+        mom[box * stride + k] = children_sum(x[4 * c], Recentre<K>::kLds, p, half, k);
+        if (k == 0) bcount[box] = cnt[4 * c] + cnt[4 * c + 1] + cnt[4 * c + 2] + cnt[4 * c + 3];
+      }
+      __syncthreads();  // LDS is free, and this level's boxes are written
     }
   }
 }
@@ -493,8 +645,6 @@ __global__ __launch_bounds__(kTB) void k_tc_finalize(double2* __restrict__ mom, 
 // A child inherits its parent's expansion re-centred by e = c_child - c_parent:
 //   X_l += sum_{m>=l} C(m, l) e^(m-l) X_m  for A, B, C, and B additionally -conj(e) times the shifted C.
 
-typedef double double4v __attribute__((ext_vector_type(4)));
-
 // Dynamic LDS of k_fmm_m2l for order p, KS = ceil((p + 1) / 4) steps of four m and RT = ceil((p + 1) / 16)
 // tiles of 16 orders: the source list, the scaled coefficients
 // X[v][m - 1][s] of a batch (3 series x 4 KS x 8 sources, complex; also the final exchange of 3 x 64 sums),
@@ -513,6 +663,14 @@ inline size_t m2l_lds_bytes(int p) {
   return sizeof(double2) * ((size_t)36 + m2l_xsize(p) + (size_t)kM2LBatch * mm + 2 * kM2LBatch +
                             kM2LBatch / 2);
 }
+
+// 1 / (m + 1), m = 0..kMaxOrder: the binomial recurrence of the local expansions multiplies instead of dividing.
+__constant__ double kRecip[kMaxOrder + 1] = {
+    1.0 / 1,  1.0 / 2,  1.0 / 3,  1.0 / 4,  1.0 / 5,  1.0 / 6,  1.0 / 7,  1.0 / 8,  1.0 / 9,  1.0 / 10,
+    1.0 / 11, 1.0 / 12, 1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16, 1.0 / 17, 1.0 / 18, 1.0 / 19, 1.0 / 20,
+    1.0 / 21, 1.0 / 22, 1.0 / 23, 1.0 / 24, 1.0 / 25, 1.0 / 26, 1.0 / 27, 1.0 / 28, 1.0 / 29, 1.0 / 30,
+    1.0 / 31, 1.0 / 32, 1.0 / 33, 1.0 / 34, 1.0 / 35, 1.0 / 36, 1.0 / 37, 1.0 / 38, 1.0 / 39, 1.0 / 40,
+    1.0 / 41, 1.0 / 42, 1.0 / 43, 1.0 / 44, 1.0 / 45, 1.0 / 46, 1.0 / 47, 1.0 / 48, 1.0 / 49};
 
 // Interaction-list contributions to the local expansion of every non-empty box of levels 2..depth (one
 // launch for all levels, one wavefront per target box), on the matrix cores.  For a source box s at
@@ -1557,13 +1715,27 @@ void launch_upward(const double* X, const double* f, const double* w, const int3
   hipLaunchKernelGGL(k_tc_scatter, dim3(pb), dim3(kTB), 0, st, r.leafid, P, r.starts, r.cursor, r.perm);
   hipLaunchKernelGGL(k_tc_sort, dim3(nleaf), dim3(64), 0, st, X, f, w, P, r.vid, r.starts, r.perm, r.srec, r.svid);
   if (depth < 2) return;
-  hipLaunchKernelGGL(k_tc_p2m, dim3(nleaf), dim3(64), sizeof(double2) * (size_t)kP2MChunk * (p + 3), st, r.srec,
-                     r.starts, r.geom, depth, p, r.mom + r.lv.mom[depth], r.bcount + r.lv.box[depth]);
-  for (int l = depth - 1; l >= 2; --l) {
-    const int n = 1 << l;
-    hipLaunchKernelGGL(k_tc_m2m, dim3(n * n), dim3(256), 0, st, r.geom, n, p, r.mom + r.lv.mom[l + 1],
-                       r.bcount + r.lv.box[l + 1], r.mom + r.lv.mom[l], r.bcount + r.lv.box[l]);
+  const bool up = depth > 2;
+  const dim3 pg(nleaf / 4), pbl(256);
+  double2* pmom = up ? r.mom + r.lv.mom[depth - 1] : nullptr;
+  int32_t* pcount = up ? r.bcount + r.lv.box[depth - 1] : nullptr;
+  // The leaves and their parents, then the coarser levels, two to a launch: one box of the upper level has four below,
+  // whose sixteen children are one pass of a workgroup (3 us; with three levels to a launch, four passes for the lowest:
+  // 26 instead of 18 us at depth 6).
+#define VESNET_UP(K)                                                                                                \
+  case K:                                                                                                           \
+    hipLaunchKernelGGL(k_tc_p2m<K>, pg, pbl, 0, st, r.srec, r.starts, r.geom, depth, p, r.mom + r.lv.mom[depth],    \
+                       r.bcount + r.lv.box[depth], pmom, pcount);                                                   \
+    for (int l = depth - 2, to; l >= 2; l = to - 1) {                                                               \
+      to = l > 2 ? l - 1 : 2;                                                                                       \
+      hipLaunchKernelGGL(k_tc_m2m<K>, dim3(1 << (2 * to)), dim3(l > to ? 64 * up_waves(K) : 256), 0, st, r.geom, l, to, \
+                         p, r.mom, r.bcount);                                                                       \
+    }                                                                                                               \
+    break;
+  switch ((p + 8) / 8) {  // orders per lane: ceil((p + 1) / 8)
+    VESNET_UP(1) VESNET_UP(2) VESNET_UP(3) VESNET_UP(4) VESNET_UP(5) VESNET_UP(6) VESNET_UP(7)
   }
+#undef VESNET_UP
 }
 
 // Work items of an evaluation: a bound on sum over leaves of ceil(count / 2^shift).
