@@ -319,6 +319,16 @@ __device__ __forceinline__ double quad_swap(double v) {
   return __hiloint2double(hi, lo);
 }
 
+// The value two lanes up, and of the other half, in each row of 16 lanes.
+template <int kCtrl>
+__device__ __forceinline__ double row_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), kCtrl, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), kCtrl, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_shift2(double v) { return row_move<0x102>(v); }  // row_shl:2
+__device__ __forceinline__ double row_half(double v) { return row_move<0x128>(v); }    // row_ror:8
+
 // x^k for 0 <= k < 64.
 __device__ __forceinline__ double pow_int(double x, int k) {
   double r = 1.0;
@@ -326,6 +336,17 @@ __device__ __forceinline__ double pow_int(double x, int k) {
   for (int b = 0; b < 6; ++b) {
     if (k & (1 << b)) r *= x;
     x *= x;
+  }
+  return r;
+}
+
+__device__ __forceinline__ double2 cpow_int(double2 x, int k) {
+  double2 r = make_double2(1.0, 0.0);
+#pragma unroll
+  for (int b = 0; b < 6; ++b) {
+    const double2 t = cmul(r, x);
+    if (k & (1 << b)) r = t;
+    x = cmul(x, x);
   }
   return r;
 }
@@ -441,9 +462,7 @@ __device__ __forceinline__ double pair_sums(double lo, double hi, int lane) {
   if constexpr (kOff == 8) {
     const bool up = lane & 8;
     const double keep = up ? hi : lo, send = up ? lo : hi;
-    const int a = __builtin_amdgcn_update_dpp(0, __double2loint(send), 0x128, 0xF, 0xF, false);  // row_ror:8
-    const int b = __builtin_amdgcn_update_dpp(0, __double2hiint(send), 0x128, 0xF, 0xF, false);
-    return keep + __hiloint2double(b, a);
+    return keep + row_half(send);
   } else {
     const auto swap = [](unsigned x, unsigned y) {
       if constexpr (kOff == 32) return __builtin_amdgcn_permlane32_swap(x, y, false, false);
@@ -664,7 +683,7 @@ inline size_t m2l_lds_bytes(int p) {
                             kM2LBatch / 2);
 }
 
-// 1 / (m + 1), m = 0..kMaxOrder: the binomial recurrence of the local expansions multiplies instead of dividing.
+// 1 / (m + 1), m = 0..kMaxOrder.
 __constant__ double kRecip[kMaxOrder + 1] = {
     1.0 / 1,  1.0 / 2,  1.0 / 3,  1.0 / 4,  1.0 / 5,  1.0 / 6,  1.0 / 7,  1.0 / 8,  1.0 / 9,  1.0 / 10,
     1.0 / 11, 1.0 / 12, 1.0 / 13, 1.0 / 14, 1.0 / 15, 1.0 / 16, 1.0 / 17, 1.0 / 18, 1.0 / 19, 1.0 / 20,
@@ -879,86 +898,116 @@ __global__ __launch_bounds__(64, RT < 4 ? 2 : 1) void k_fmm_m2l(const Geom* __re
 // each ancestor (levels 2..depth-1), re-centred from the ancestor's centre straight to the leaf's (the
 // re-centring of a polynomial is exact, so one shift per ancestor equals the chain through the levels).
 // With e = c_leaf - c_anc: X_k += sum_{m>=k} C(m, k) e^(m-k) X_m for A, B, C, and B also -conj(e) times the
-// shifted C.  One wavefront per leaf, all ancestors' rows staged in LDS together; lane = (half h, order k):
-// for p + 1 <= 32 the two halves of the wavefront take alternate ancestors and their sums are added at the
-// end, otherwise one half does all.  The binomials follow their recurrence (C(48, 24) < 2^53: rounding the
-// product with the reciprocal to the nearest integer gives each one exactly).
-__global__ __launch_bounds__(64) void k_fmm_l2l(const Geom* __restrict__ geom, int depth, int p,
-                                               const int32_t* __restrict__ bcount, double2* __restrict__ loc) {
-  extern __shared__ double2 anc[];  // [depth - 2][3 (p + 1)], then 3 x 32 for the halves' exchange
+// shifted C.  One wavefront per leaf, on the matrix cores: X_k = e^-k sum_m C(m, k) (e^m X_m), the triangle of binomials
+// the first operand (in registers, shared by all ancestors) and the e^m X_m of two ancestors, six real columns each,
+// the second.  For 8 K >= p + 1 orders.  Powers of e are real powers of |e| times powers of e / |e|.
+// 2000 x 128, order 30: 25 -> 16.7 us (before: a lane per order, binomials and powers serial chains, three LDS reads
+// per term).
+constexpr int kShiftWaves = 4;
+
+template <int K>
+__global__ __launch_bounds__(64 * kShiftWaves) void k_fmm_l2l(const Geom* __restrict__ geom, int depth, int p,
+                                                              const int32_t* __restrict__ bcount,
+                                                              double2* __restrict__ loc) {
+  constexpr int kTiles = (K + 1) / 2, kOrders = 8 * K;
+  constexpr int kRow = 17;  // doubles per order: 16 columns and a spare one against bank conflicts
+  __shared__ double xs[kShiftWaves][kOrders * kRow + 1];
+  __shared__ double2 inv[kShiftWaves][2][kOrders];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int n = 1 << depth;
-  const int leaf = blockIdx.x;
+  const int leaf = blockIdx.x * kShiftWaves + wave;
   const size_t lbox = level_box_base(depth) + (size_t)leaf;
   if (bcount[lbox] == 0) return;
-  const int lane = threadIdx.x;
+  double* x = xs[wave];
   const int bx = leaf / n, by = leaf % n;
   const int rows = 3 * (p + 1);
   const double wL = geom->side / (double)n;
-  const int nanc = depth - 2;
-  for (int e = lane; e < nanc * rows; e += 64) {
-    const int l = 2 + e / rows, sh = depth - l;
-    const size_t abox = level_box_base(l) + (size_t)(bx >> sh) * (1 << l) + (by >> sh);
-    anc[e] = loc[abox * rows + e % rows];
-  }
-  __syncthreads();
-  const bool split = p + 1 <= 32;
-  const int h = split ? lane >> 5 : 0, k = split ? lane & 31 : lane;
-  const int hstep = split ? 2 : 1;
-  double2 sA = make_double2(0.0, 0.0), sB = sA, sC = sA;
-  if (k <= p && (split || lane <= p)) {
-    for (int a = h; a < nanc; a += hstep) {
-      const int l = 2 + a, sh = depth - l;
+  double a[kTiles][2 * K];
+#pragma unroll
+  for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+    for (int s = 4 * rt; s < 2 * K; ++s) {
+      const int k = 16 * rt + (lane & 15), m = 4 * s + (lane >> 4);
+      const double c = kBinomials.t[min(k, kTabM - 1)][max(m - k, 0)];  // C(m, k)
+      a[rt][s] = m >= k ? c : 0.0;
+    }
+  const int c = lane & 15, series = (c & 7) >> 1;
+  double tot[kTiles][4];
+#pragma unroll
+  for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) tot[rt][v] = 0.0;
+  for (int l0 = 2; l0 < depth; l0 += 2) {
+    double2 e[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int l = l0 + h, sh = depth - l;
       const int ax = bx >> sh, ay = by >> sh;
-      const double2* pl = anc + a * rows;
       // leaf centre - ancestor centre = ((b + 1/2) - (a + 1/2) 2^sh) wL per coordinate: exact before the product
-      const double2 e = make_double2(((double)bx + 0.5 - ((double)ax + 0.5) * (double)(1 << sh)) * wL,
-                                     ((double)by + 0.5 - ((double)ay + 0.5) * (double)(1 << sh)) * wL);
-      double2 tA = make_double2(0.0, 0.0), tB = tA, tC = tA;
-      double2 ej = make_double2(1.0, 0.0);  // e^j
-      double cb = 1.0;                      // C(k + j, k): integers below 2^53, each step exact after rounding
-      for (int j = 0; j <= p - k; ++j) {
-        const double2 ce = make_double2(cb * ej.x, cb * ej.y);
-        tA = cfma(ce, pl[k + j], tA);
-        tB = cfma(ce, pl[(p + 1) + k + j], tB);
-        tC = cfma(ce, pl[2 * (p + 1) + k + j], tC);
-        ej = cmul(ej, e);
-        cb = rint(cb * (double)(k + j + 1) * kRecip[j]);  // C(k + j + 1, k) = C(k + j, k) (k + j + 1) / (j + 1)
+      e[h] = make_double2(((double)bx + 0.5 - ((double)ax + 0.5) * (double)(1 << sh)) * wL,
+                          ((double)by + 0.5 - ((double)ay + 0.5) * (double)(1 << sh)) * wL);
+      double2 v[3] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0), make_double2(0.0, 0.0)};
+      if (l < depth && lane <= p) {
+        const double2* pa = loc + (level_box_base(l) + ((size_t)ax << l) + ay) * rows + lane;
+        v[0] = pa[0];
+        v[1] = pa[p + 1];
+        v[2] = pa[2 * (p + 1)];
       }
-      const double2 shc = cmul(make_double2(e.x, -e.y), tC);
-      sA.x += tA.x;
-      sA.y += tA.y;
-      sB.x += tB.x - shc.x;
-      sB.y += tB.y - shc.y;
-      sC.x += tC.x;
-      sC.y += tC.y;
+      if (l == depth) e[h] = make_double2(1.0, 0.0);  // no ancestor: zero columns
+      if (lane < kOrders) {
+        const double r = sqrt(e[h].x * e[h].x + e[h].y * e[h].y), ri = 1.0 / r;
+        const double2 u = cpow_int(make_double2(e[h].x * ri, e[h].y * ri), lane);
+        const double rm = pow_int(r, lane), rk = pow_int(ri, lane);
+        inv[wave][h][lane] = make_double2(u.x * rk, -(u.y * rk));
+        const double2 em = make_double2(u.x * rm, u.y * rm);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const double2 t = cmul(v[q], em);
+          x[kRow * lane + 8 * h + 2 * q] = t.x;
+          x[kRow * lane + 8 * h + 2 * q + 1] = t.y;
+        }
+      }
     }
+    wave_sync();
+    double4v acc[kTiles];
+#pragma unroll
+    for (int rt = 0; rt < kTiles; ++rt) acc[rt] = double4v{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 2 * K; ++s) {
+      const double b = x[kRow * (4 * s + (lane >> 4)) + c];
+#pragma unroll
+      for (int rt = 0; rt < kTiles; ++rt)
+        if (s >= 4 * rt) acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt][s], b, acc[rt], 0, 0, 0);
+    }
+    const double2 eh = (c & 8) ? e[1] : e[0];
+#pragma unroll
+    for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int k = 16 * rt + (lane >> 4) + 4 * v;
+        const double2 ik = inv[wave][c >> 3][min(k, kOrders - 1)];
+        const double mine = acc[rt][v], other = quad_swap(mine);  // Re and Im are neighbours
+        const double val = fma(mine, ik.x, (c & 1) ? other * ik.y : -(other * ik.y));
+        const double cm = row_shift2(val), co = quad_swap(cm);  // for the lanes of B: C and its other part
+        const double shc = fma(eh.x, cm, (c & 1) ? -(eh.y * co) : eh.y * co);  // conj(e) C
+        tot[rt][v] += series == 1 ? val - shc : val;
+      }
+    wave_sync();  // x and inv are read
   }
-  double2* xch = anc + nanc * rows;
-  if (split) {  // the second half's sums join the first half's
-    if (h == 1) {
-      xch[k] = sA;
-      xch[32 + k] = sB;
-      xch[64 + k] = sC;
+#pragma unroll
+  for (int rt = 0; rt < kTiles; ++rt)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int k = 16 * rt + (lane >> 4) + 4 * v;
+      const double sum = tot[rt][v] + row_half(tot[rt][v]);  // the two ancestors of a pair
+      if (c < 6 && k <= p) x[2 * (series * (p + 1) + k) + (c & 1)] = sum;
     }
-    __syncthreads();
-    if (h == 1) return;
-    if (k <= p) {
-      sA.x += xch[k].x;
-      sA.y += xch[k].y;
-      sB.x += xch[32 + k].x;
-      sB.y += xch[32 + k].y;
-      sC.x += xch[64 + k].x;
-      sC.y += xch[64 + k].y;
-    }
+  wave_sync();
+  double2* lb = loc + lbox * rows;
+  for (int t = lane; t < rows; t += 64) {
+    const double2 v = lb[t];
+    lb[t] = make_double2(v.x + x[2 * t], v.y + x[2 * t + 1]);
   }
-  if (k > p) return;
-  double2* cb_ = loc + lbox * rows;
-  double2 v = cb_[k];
-  cb_[k] = make_double2(v.x + sA.x, v.y + sA.y);
-  v = cb_[(p + 1) + k];
-  cb_[(p + 1) + k] = make_double2(v.x + sB.x, v.y + sB.y);
-  v = cb_[2 * (p + 1) + k];
-  cb_[2 * (p + 1) + k] = make_double2(v.x + sC.x, v.y + sC.y);
 }
 
 // ---------------------------------------------------------------- evaluation
@@ -1793,8 +1842,15 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
     }
     if (depth >= 3) {
       const int nleaf = 1 << (2 * depth);
-      hipLaunchKernelGGL(k_fmm_l2l, dim3(nleaf), dim3(64), sizeof(double2) * ((size_t)(depth - 2) * 3 * (p + 1) + 96),
-                         st, r.geom, depth, p, r.bcount, r.loc);
+#define VESNET_L2L(K)                                                                                              \
+  case K:                                                                                                          \
+    hipLaunchKernelGGL(k_fmm_l2l<K>, dim3(nleaf / kShiftWaves), dim3(64 * kShiftWaves), 0, st, r.geom, depth, p,   \
+                       r.bcount, r.loc);                                                                           \
+    break;
+      switch ((p + 8) / 8) {  // ceil((p + 1) / 8)
+        VESNET_L2L(1) VESNET_L2L(2) VESNET_L2L(3) VESNET_L2L(4) VESNET_L2L(5) VESNET_L2L(6) VESNET_L2L(7)
+      }
+#undef VESNET_L2L
     }
   }
   const int items = eval_items(P, depth, kFmmChunkShift);
