@@ -1012,6 +1012,21 @@ __global__ __launch_bounds__(64 * kShiftWaves) void k_fmm_l2l(const Geom* __rest
 
 // ---------------------------------------------------------------- evaluation
 
+// The leaf of a work item, wstart[leaf] <= item < wstart[leaf + 1]: 64 places are looked at together, so 4,096 leaves
+// take two rounds of memory latency (a binary search took twelve).
+__device__ __forceinline__ int leaf_of_item(const int32_t* __restrict__ wstart, int nleaf, int item) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, end = nleaf;  // wstart[lo] <= item < wstart[end]
+  while (end - lo > 1) {
+    const int step = (end - lo + 63) >> 6;
+    const int at = lo + (lane + 1) * step;
+    const int k = __popcll(__ballot(at < end && wstart[min(at, end)] <= item));
+    lo += k * step;
+    end = min(lo + step, end);
+  }
+  return lo;
+}
+
 __device__ __forceinline__ void direct_term(double zx, double zy, double sx, double sy, double Fx, double Fy,
                                             const double2* __restrict__ ltab, double& ux, double& uy) {
   const double rx = zx - sx, ry = zy - sy;
@@ -1030,7 +1045,7 @@ __device__ __forceinline__ void direct_term(double zx, double zy, double sx, dou
 // sums are added at the end.  The three leaves of a column are one run of the leaf order, and the three runs are
 // staged as one list, 64 records at a time with the next 64 loading meanwhile.  Two targets per lane use each record
 // read from LDS twice.  What bounds it is float64 VALU issue, 30 instructions per (target, source).
-// 2000 x 128, order 30: 263 -> 194 us (160 at one instruction per 4 cycles).
+// 2000 x 128, order 30: 263 -> 187 us (160 at one instruction per 4 cycles).
 constexpr int kFmmT = 2;
 constexpr int kFmmLanes = 8;
 constexpr int kFmmGroups = 64 / kFmmLanes;
@@ -1051,21 +1066,17 @@ __global__ __launch_bounds__(64 * kFmmWaves) void k_fmm_eval(const double4* __re
   // per wavefront: the local expansion (3 (p + 1) <= 147 entries), then 64 source records and ids
   __shared__ double2 stage[kFmmWaves][3 * 64];
   for (int e = threadIdx.x; e < kHalfLogTab; e += 64 * kFmmWaves) ltab[e] = tab[e];
-  __syncthreads();
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   double2* cf = stage[wv];
   double4* src = reinterpret_cast<double4*>(stage[wv]);
   int32_t* sv = reinterpret_cast<int32_t*>(stage[wv] + 2 * 64);
   const int n = 1 << depth;
   const int nleaf = n * n;
   const int item = blockIdx.x * kFmmWaves + wv;
-  if (item >= wstart[nleaf]) return;
-  int lo = 0, hi = nleaf;  // wstart[lo] <= item < wstart[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (wstart[mid] <= item) lo = mid; else hi = mid;
-  }
-  const int leaf = lo;
+  const bool some = item < wstart[nleaf];
+  const int leaf = some ? leaf_of_item(wstart, nleaf, item) : 0;
+  __syncthreads();
+  if (!some) return;
   const int s1 = starts[leaf + 1];
   const int base = starts[leaf] + ((item - wstart[leaf]) << kFmmChunkShift);
   const int tl = lane & (kFmmLanes - 1), grp = lane / kFmmLanes;
@@ -1214,12 +1225,7 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double4* __restrict__ srec
   const int nleaf = n * n;
   const int item = blockIdx.x;
   if (item >= wstart[nleaf]) return;
-  int lo = 0, hi = nleaf;  // wstart[lo] <= item < wstart[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (wstart[mid] <= item) lo = mid; else hi = mid;
-  }
-  const int leaf = lo;
+  const int leaf = leaf_of_item(wstart, nleaf, item);
   const int s0 = starts[leaf], s1 = starts[leaf + 1];
   const int lane = threadIdx.x, tl = lane & (kTreeLanes - 1), grp = lane / kTreeLanes;
   ltab[lane] = log_tab_entry(lane);
@@ -1461,17 +1467,19 @@ __global__ __launch_bounds__(kOwnThreads) void k_tc_own(const double* __restrict
 // Near-field masking of Algorithm 4 on the fast multipole result: vesicle v (not the target's own) is near
 // target i when min_j |x_i - x_j| <= h_v (the rule of the direct masked sum, decided here in FP64 on
 // squared distances).  With every h_v at most the leaf width, all such points lie in the 3 x 3 leaves around
-// the target's leaf.  One wavefront per (leaf, chunk of targets: the evaluation's work list) stages those
-// leaves' points in LDS, up to kNearStage at a time with every lane's loads issued together (a neighbourhood
-// of that many points costs three rounds of memory latency); the 64 / chunk lanes t, t + chunk, ... scan
-// interleaved points for target t, each keeping the distinct near vesicles it meets (at most kNearMax, else
-// bit 0 of *flag), and lane t merges the sets and sorts them ascending.  One atomic per
-// wavefront reserves the pair slots.  The whole wavefront then takes the near vesicles of each target in
-// turn, 64 points at a time, and subtracts their exact direct sum at x_i from out[i]: the FMM had included v
+// the target's leaf.  One wavefront per (leaf, chunk of targets: the evaluation's work list), four to a workgroup,
+// stages those leaves' records in LDS, up to kNearStage at a time with every lane's loads issued together; the 64 /
+// chunk lanes t, t + chunk, ... scan interleaved points for target t, each keeping the distinct near vesicles it meets
+// (at most kNearMax, else bit 0 of *flag), and lane t merges the sets and sorts them ascending.  One atomic per
+// workgroup reserves the pair slots (they all go to one address, about 20 ns each).  The lanes of a target then share
+// the points of its near vesicles and subtract their exact direct sum at x_i from out[i]: the FMM had included v
 // through the direct part or the expansions, and the difference leaves the masked far field with the FMM's
 // truncation error.  The lane partials are combined by a butterfly, so the result is deterministic.
+// 2000 x 32: 56 -> 32 us (before: one atomic per wavefront; the whole wavefront on one target after the other, a
+// memory latency each; points gathered through the permutation).  Five workgroups per compute unit: with the 124
+// registers that the compiler takes unasked it is four, and 36 us.
 constexpr int kNearMax = 16;
-constexpr int kNearStage = 6 * 64;  // points of the 3 x 3 leaves staged at once (six per lane)
+constexpr int kNearStage = 4 * 64;  // points of the 3 x 3 leaves staged at once (four per lane)
 
 __device__ __forceinline__ void near_insert(int (&nv)[kNearMax], int& nn, bool& over, int v) {
   bool seen = false;
@@ -1488,11 +1496,13 @@ __device__ __forceinline__ void near_insert(int (&nv)[kNearMax], int& nn, bool& 
   ++nn;
 }
 
-__global__ __launch_bounds__(64) void k_fmm_near(const double* __restrict__ X, const double* __restrict__ f,
+constexpr int kNearWaves = 4;
+
+__global__ __launch_bounds__(64 * kNearWaves, 5) void k_fmm_near(const double* __restrict__ X, const double* __restrict__ f,
                                                 const double* __restrict__ w, int P, int M,
                                                 const int32_t* __restrict__ off,
-                                                const int32_t* __restrict__ vid, const int32_t* __restrict__ perm,
-                                                const int32_t* __restrict__ starts,
+                                                const double4* __restrict__ srec, const int32_t* __restrict__ svid,
+                                                const int32_t* __restrict__ perm, const int32_t* __restrict__ starts,
                                                 const int32_t* __restrict__ wstart, int depth,
                                                 const double* __restrict__ h2, double scale, double* __restrict__ out,
                                                 int32_t* __restrict__ pairs, int capacity, int32_t* __restrict__ count,
@@ -1500,98 +1510,105 @@ __global__ __launch_bounds__(64) void k_fmm_near(const double* __restrict__ X, c
   constexpr int kChunk = 1 << kFmmChunkShift;
   constexpr int kGroups = 64 / kChunk;  // lanes per target: group g scans every kGroups-th source from g on
   static_assert(kGroups >= 2 && kGroups * kChunk == 64, "a power-of-two chunk of at most 32 targets");
-  __shared__ double sx_[kNearStage], sy_[kNearStage], sh[kNearStage];
-  __shared__ int32_t sv[kNearStage];
+  // a wavefront's staged records, then its groups' sets
+  struct Stage {
+    double x[kNearStage], y[kNearStage], h2[kNearStage];
+    int32_t v[kNearStage];
+  };
+  struct Sets {
+    int32_t list[kGroups - 1][kChunk][kNearMax + 1], count[kGroups - 1][kChunk];
+  };
+  union Shared {
+    Stage st;
+    Sets se;
+    __device__ Shared() {}
+  };
+  __shared__ Shared shared[kNearWaves];
   __shared__ double2 ltab[kLogTab];
-  __shared__ int32_t mlist[kGroups - 1][kChunk][kNearMax + 1];
-  __shared__ int32_t mcount[kGroups - 1][kChunk];
+  __shared__ int32_t found[kNearWaves], first;
   const int n = 1 << depth;
   const int nleaf = n * n;
-  const int item = blockIdx.x;
-  if (item >= wstart[nleaf]) return;
-  int lo = 0, hi = nleaf;  // wstart[lo] <= item < wstart[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (wstart[mid] <= item) lo = mid; else hi = mid;
-  }
-  const int leaf = lo;
-  const int lane = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int item = blockIdx.x * kNearWaves + wave;
+  if (threadIdx.x < kLogTab) ltab[threadIdx.x] = log_tab_entry(threadIdx.x);  // read after the barriers below
+  const bool some = item < wstart[nleaf];  // a wavefront without an item takes a chunk beyond its leaf's last
+  const int leaf = some ? leaf_of_item(wstart, nleaf, item) : 0;
+  Stage& st = shared[wave].st;
+  Sets& se = shared[wave].se;
   const int t = lane & (kChunk - 1), grp = lane / kChunk;
-  ltab[lane] = log_tab_entry(lane);  // read after the barriers below
   const int s0 = starts[leaf], s1 = starts[leaf + 1];
   const int slot = s0 + (item - wstart[leaf]) * kChunk + t;
-  const bool active = slot < s1;
-  const int i = active ? perm[slot] : perm[s0];
-  const double zx = X[i], zy = X[P + i];
-  const int vi = clamp_i(vid[i], 0, M - 1);
+  const bool active = some && slot < s1;
+  const int sl = active ? slot : min(s0, P - 1);
+  const int i = perm[sl];
+  const double zx = srec[sl].x, zy = srec[sl].y;
+  const int vi = clamp_i(svid[sl], 0, M - 1);
   const int ix = leaf / n, iy = leaf % n;
   int nv[kNearMax];
   int nn = 0;
   bool over = false;
-  // point ranges of the 3 x 3 leaves (empty outside the grid) and their running offsets
-  int lb[9], cum[10];
+  // the source runs of columns ix - 1 .. ix + 1 (empty outside the grid), as one list of nsrc slots
+  int run0[3], cum[4];
   cum[0] = 0;
 #pragma unroll
-  for (int a = 0; a < 9; ++a) {
-    const int jx = ix + a / 3 - 1, jy = iy + a % 3 - 1;
-    const bool in = jx >= 0 && jx < n && jy >= 0 && jy < n;
-    const int nl = in ? jx * n + jy : 0;
-    lb[a] = in ? starts[nl] : 0;
-    cum[a + 1] = cum[a] + (in ? starts[nl + 1] - lb[a] : 0);
+  for (int a = 0; a < 3; ++a) {
+    const int jx = ix + a - 1;
+    const bool in = jx >= 0 && jx < n;
+    run0[a] = in ? starts[jx * n + max(iy - 1, 0)] : 0;
+    cum[a + 1] = cum[a] + (in ? starts[jx * n + min(iy + 1, n - 1) + 1] - run0[a] : 0);
   }
-  const int nsrc = cum[9];
+  const int nsrc = some ? cum[3] : 0;
   for (int b0 = 0; b0 < nsrc; b0 += kNearStage) {
     const int cnt = min(kNearStage, nsrc - b0);
-    __syncthreads();  // the previous stage is done
-    int jj[kNearStage / 64];
-#pragma unroll
-    for (int u = 0; u < kNearStage / 64; ++u) {
-      const int e = b0 + lane + 64 * u;
-      int a = 0;
-#pragma unroll
-      for (int c = 1; c < 9; ++c) a += e >= cum[c] ? 1 : 0;
-      jj[u] = e < nsrc ? perm[lb[a] + e - cum[a]] : -1;
-    }
+    double2 pos[kNearStage / 64];
     int vv[kNearStage / 64];
 #pragma unroll
     for (int u = 0; u < kNearStage / 64; ++u) {
-      if (jj[u] >= 0) {
-        const int k = lane + 64 * u;
-        sx_[k] = X[jj[u]];
-        sy_[k] = X[P + jj[u]];
-        vv[u] = clamp_i(vid[jj[u]], 0, M - 1);  // ids index the per-vesicle arrays: never trusted
-        sv[k] = vv[u];
+      const int e = min(b0 + lane + 64 * u, nsrc - 1);
+      const int at = e < cum[1] ? run0[0] + e : e < cum[2] ? run0[1] + e - cum[1] : run0[2] + e - cum[2];
+      pos[u] = make_double2(srec[at].x, srec[at].y);
+      vv[u] = clamp_i(svid[at], 0, M - 1);  // ids index the per-vesicle arrays: never trusted
+    }
+    wave_sync();  // the previous stage is done
+#pragma unroll
+    for (int u = 0; u < kNearStage / 64; ++u) {
+      const int k = lane + 64 * u;
+      st.x[k] = pos[u].x;
+      st.y[k] = pos[u].y;
+      st.v[k] = vv[u];
+      st.h2[k] = h2[vv[u]];
+    }
+    wave_sync();
+    if (active) {
+#pragma unroll 4
+      for (int q = grp; q < cnt; q += kGroups) {
+        const double rx = zx - st.x[q], ry = zy - st.y[q];
+        const int vq = st.v[q];
+        if (!(rx * rx + ry * ry > st.h2[q]) && vq != vi) near_insert(nv, nn, over, vq);
       }
     }
-#pragma unroll
-    for (int u = 0; u < kNearStage / 64; ++u)
-      if (jj[u] >= 0) sh[lane + 64 * u] = h2[vv[u]];
-    __syncthreads();
-    if (!active) continue;
-#pragma unroll 4
-    for (int q = grp; q < cnt; q += kGroups) {
-      const double rx = zx - sx_[q], ry = zy - sy_[q];
-      const int vq = sv[q];
-      if (!(rx * rx + ry * ry > sh[q]) && vq != vi) near_insert(nv, nn, over, vq);
-    }
   }
+  wave_sync();  // the staged records are done: their place now holds the sets
   // merge the other groups' sets into group 0's
   if (grp > 0) {
 #pragma unroll
     for (int k = 0; k < kNearMax; ++k)
-      if (k < nn) mlist[grp - 1][t][k] = nv[k];
-    mcount[grp - 1][t] = nn;
+      if (k < nn) se.list[grp - 1][t][k] = nv[k];
+    se.count[grp - 1][t] = nn;
     nn = 0;
   }
-  __syncthreads();
-  if (grp == 0) {
+  wave_sync();
+  if (grp == 0)
     for (int g2 = 0; g2 < kGroups - 1; ++g2) {
-      const int m = mcount[g2][t];
-      for (int k = 0; k < m; ++k) near_insert(nv, nn, over, mlist[g2][t][k]);
+      const int m = se.count[g2][t];
+      for (int k = 0; k < m; ++k) near_insert(nv, nn, over, se.list[g2][t][k]);
     }
-    // ascending vesicle order: the subtraction order, and so the result, does not depend on the scan
+  int most = 0;  // largest set of the wavefront
+  while (__ballot(nn > most) != 0) ++most;
+  // ascending vesicle order: the subtraction order, and so the result, does not depend on the scan
 #pragma unroll
-    for (int a = 1; a < kNearMax; ++a)
+  for (int a = 1; a < kNearMax; ++a)
+    if (a < most) {
 #pragma unroll
       for (int b = kNearMax - 1; b >= a; --b)
         if (b < nn && nv[b - 1] > nv[b]) {
@@ -1599,20 +1616,26 @@ __global__ __launch_bounds__(64) void k_fmm_near(const double* __restrict__ X, c
           nv[b - 1] = nv[b];
           nv[b] = tmp;
         }
-  }
+    }
   if (__ballot(over) != 0 && lane == 0) atomicOr(flag, 1);
   int incl = nn;  // inclusive prefix of the pair counts over the wavefront (zero outside group 0)
-  for (int o = 1; o < 64; o <<= 1) {
+  for (int o = 1; o < kChunk; o <<= 1) {
     const int y = __shfl_up(incl, o);
     if (lane >= o) incl += y;
   }
-  const int total = __shfl(incl, 63);
+  if (lane == kChunk - 1) found[wave] = incl;
+  __syncthreads();
+  int total = 0, before = 0;
+#pragma unroll
+  for (int q = 0; q < kNearWaves; ++q) {
+    if (q < wave) before += found[q];
+    total += found[q];
+  }
   if (total == 0) return;
-  int base = 0;
-  if (lane == 0) base = atomicAdd(count, total);
-  base = __shfl(base, 0);
+  if (threadIdx.x == 0) first = atomicAdd(count, total);
+  __syncthreads();
   if (grp == 0) {
-    const int b0 = base + incl - nn;
+    const int b0 = first + before + incl - nn;
 #pragma unroll
     for (int k = 0; k < kNearMax; ++k)
       if (k < nn) {
@@ -1620,33 +1643,28 @@ __global__ __launch_bounds__(64) void k_fmm_near(const double* __restrict__ X, c
           pairs[2 * (b0 + k)] = i;
           pairs[2 * (b0 + k) + 1] = nv[k];
         }
-        mlist[0][t][k] = nv[k];
+        se.list[0][t][k] = nv[k];
       }
-    mcount[0][t] = nn;
+    se.count[0][t] = nn;
   }
-  __syncthreads();
-  unsigned long long todo = __ballot(grp == 0 && nn > 0);
-  while (todo) {
-    const int tt = __ffsll(todo) - 1;
-    todo &= todo - 1;
-    const double tx = __shfl(zx, tt), ty = __shfl(zy, tt);
-    const int it = __shfl(i, tt);
-    const int m = mcount[0][tt];
-    double ux = 0.0, uy = 0.0;
-    for (int k = 0; k < m; ++k) {
-      const int v = mlist[0][tt][k];
-      const int v0 = clamp_i(off[v], 0, P), v1 = max(v0, clamp_i(off[v + 1], 0, P));
-      for (int j = v0 + lane; j < v1; j += 64)
-        direct_term(tx, ty, X[j], X[P + j], w[j] * f[j], w[j] * f[P + j], ltab, ux, uy);
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-      ux += __shfl_xor(ux, o);
-      uy += __shfl_xor(uy, o);
-    }
-    if (lane == 0) {
-      out[it] -= ux * scale;
-      out[P + it] -= uy * scale;
-    }
+  wave_sync();
+  const int m = se.count[0][t];
+  double ux = 0.0, uy = 0.0;
+  for (int k = 0; k < m; ++k) {
+    const int v = se.list[0][t][k];
+    const int v0 = clamp_i(off[v], 0, P), v1 = max(v0, clamp_i(off[v + 1], 0, P));
+#pragma unroll 4
+    for (int j = v0 + grp; j < v1; j += kGroups)
+      direct_term(zx, zy, X[j], X[P + j], w[j] * f[j], w[j] * f[P + j], ltab, ux, uy);
+  }
+#pragma unroll
+  for (int o = kChunk; o < 64; o <<= 1) {
+    ux += __shfl_xor(ux, o);
+    uy += __shfl_xor(uy, o);
+  }
+  if (grp == 0 && nn > 0) {
+    out[i] -= ux * scale;
+    out[P + i] -= uy * scale;
   }
 }
 
@@ -1868,8 +1886,8 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
                      P, r.perm, r.starts, r.wstart, r.geom, depth, p, r.loc, r.ltab, scale, out);
   launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   if (near) {
-    hipLaunchKernelGGL(k_fmm_near, dim3(items), dim3(64), 0, st, X, f, w, P, M, off, r.vid, r.perm, r.starts, r.wstart,
-                       depth, r.h2, scale, out, pairs, capacity, count, r.flag);
+    hipLaunchKernelGGL(k_fmm_near, dim3((items + kNearWaves - 1) / kNearWaves), dim3(64 * kNearWaves), 0, st, X, f, w, P, M, off, r.srec, r.svid, r.perm, r.starts,
+                       r.wstart, depth, r.h2, scale, out, pairs, capacity, count, r.flag);
     hipLaunchKernelGGL(k_fmm_near_status, dim3(1), dim3(64), 0, st, r.flag, count);
   }
   return hipGetLastError();
