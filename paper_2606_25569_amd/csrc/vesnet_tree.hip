@@ -86,10 +86,16 @@ struct Binomials {
 };
 __device__ constexpr Binomials kBinomials{};
 
-// Also builds the evaluation's log table when tab is not null.
+// Bounding boxes of the points' parts.  Also builds the evaluation's log table when tab is not null, clears the leaf
+// counters, and with count given the near-field list's count and status.
 __global__ __launch_bounds__(kTB) void k_tc_bbox_partial(const double* __restrict__ X, int P,
-                                                         double* __restrict__ part, double2* __restrict__ tab) {
+                                                         double* __restrict__ part, double2* __restrict__ tab,
+                                                         int32_t* __restrict__ counts, int32_t* __restrict__ cursor,
+                                                         int nleaf, int32_t* __restrict__ count,
+                                                         int32_t* __restrict__ flag) {
   __shared__ double red[4][kTB];
+  for (int e = blockIdx.x * kTB + threadIdx.x; e < nleaf; e += gridDim.x * kTB) counts[e] = cursor[e] = 0;
+  if (count != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *count = *flag = 0;
   if (tab != nullptr)
     for (int e = blockIdx.x * kTB + threadIdx.x; e < kHalfLogTab; e += gridDim.x * kTB) tab[e] = half_log_entry(e);
   double xl = INFINITY, xh = -INFINITY, yl = INFINITY, yh = -INFINITY;
@@ -117,10 +123,11 @@ __global__ __launch_bounds__(kTB) void k_tc_bbox_partial(const double* __restric
   if (threadIdx.x < 4) part[blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ __launch_bounds__(64) void k_tc_bbox_final(const double* __restrict__ part, int nparts,
-                                                      Geom* __restrict__ geom) {
+// The root square of the parts' bounding boxes, by one wavefront; the value is lane 0's.
+__device__ __forceinline__ Geom root_square(const double* __restrict__ part, int nparts) {
+  const int lane = threadIdx.x & 63;
   double xl = INFINITY, xh = -INFINITY, yl = INFINITY, yh = -INFINITY;
-  for (int b = threadIdx.x; b < nparts; b += 64) {
+  for (int b = lane; b < nparts; b += 64) {
     xl = fmin(xl, part[4 * b]);
     xh = fmax(xh, part[4 * b + 1]);
     yl = fmin(yl, part[4 * b + 2]);
@@ -133,24 +140,20 @@ __global__ __launch_bounds__(64) void k_tc_bbox_final(const double* __restrict__
     yl = fmin(yl, __shfl_xor(yl, m, 64));
     yh = fmax(yh, __shfl_xor(yh, m, 64));
   }
-  if (threadIdx.x != 0) return;
+  Geom g;
   {
 #pragma clang fp contract(off)
     double side = fmax(xh - xl, yh - yl);
     if (side == 0.0) side = 1.0;
-    Geom g;
     g.x0 = 0.5 * (xl + xh) - 0.5 * side;
     g.y0 = 0.5 * (yl + yh) - 0.5 * side;
     g.side = side;
-    *geom = g;
   }
+  return g;
 }
 
-__global__ __launch_bounds__(kTB) void k_tc_zero(int32_t* __restrict__ a, int32_t* __restrict__ b, int n) {
-  for (int i = blockIdx.x * kTB + threadIdx.x; i < n; i += gridDim.x * kTB) {
-    a[i] = 0;
-    b[i] = 0;
-  }
+__global__ __launch_bounds__(64) void k_tc_zero(int32_t* __restrict__ a) {
+  if (threadIdx.x == 0) *a = 0;
 }
 
 // Within a wavefront, the lanes whose key equals the first pending lane's form a group: one atomic adds the
@@ -173,42 +176,58 @@ __device__ __forceinline__ int wave_group_add(bool ok, int key, int32_t* __restr
   return pos;
 }
 
-// Leaf of every point and leaf occupancy.
-__global__ __launch_bounds__(kTB) void k_tc_leaf(const double* __restrict__ X, int P, const Geom* __restrict__ geom,
-                                                 int depth, int32_t* __restrict__ leafid, int32_t* __restrict__ counts) {
-  const Geom g = *geom;
-  const int n = 1 << depth;
-  for (int j0 = blockIdx.x * kTB; j0 < P; j0 += gridDim.x * kTB) {  // the same trip count for every lane
-    const int j = j0 + (int)threadIdx.x;
-    const bool ok = j < P;
-    int leaf = 0;
-    if (ok) {
-      int ix, iy;
-      {
-#pragma clang fp contract(off)
-        const double wl = g.side / (double)n;
-        ix = clamp_i((int)floor((X[j] - g.x0) / wl), 0, n - 1);
-        iy = clamp_i((int)floor((X[P + j] - g.y0) / wl), 0, n - 1);
-      }
-      leaf = ix * n + iy;
-      leafid[j] = leaf;
-    }
-    wave_group_add(ok, leaf, counts);
-  }
-}
-
-// Vesicle id of every point: one workgroup per vesicle writes its index over its range (offsets clamped).
+// Leaf of every point and leaf occupancy in the first `pblocks` workgroups; vesicle id of every point in the others, one
+// workgroup per vesicle, which writes its index over its range (offsets clamped).
 // With h2 given, also the squared near-field radius h_v^2 of every vesicle, h_v = sum_j w_j / N_v (the
 // mean arclength spacing, summed in a fixed order), and bit 1 of *flag when h_v exceeds the leaf width
 // (then a point within h_v of a target may lie outside its 3 x 3 leaves).
-__global__ __launch_bounds__(kTB) void k_tc_vid(const int32_t* __restrict__ off, int P, int32_t* __restrict__ vid,
-                                                const double* __restrict__ w, const Geom* __restrict__ geom,
-                                                int depth, double* __restrict__ h2, int32_t* __restrict__ flag) {
-  const int v = blockIdx.x;
+// Every workgroup that needs the root square forms it from the parts' boxes itself: a launch of its own for it, one for
+// the ids and one to clear the counters cost 4 us each.
+__global__ __launch_bounds__(kTB) void k_tc_leaf(const double* __restrict__ X, int P, const double* __restrict__ part,
+                                                 int nparts, int pblocks, int depth, Geom* __restrict__ geom,
+                                                 int32_t* __restrict__ leafid, int32_t* __restrict__ counts,
+                                                 const int32_t* __restrict__ off, int32_t* __restrict__ vid,
+                                                 const double* __restrict__ w, double* __restrict__ h2,
+                                                 int32_t* __restrict__ flag) {
+  __shared__ Geom root;
+  __shared__ double red[kTB];
+  const bool points = (int)blockIdx.x < pblocks;
+  if (points || h2 != nullptr) {
+    if (threadIdx.x < 64) {
+      const Geom g = root_square(part, nparts);
+      if (threadIdx.x == 0) {
+        root = g;
+        if (blockIdx.x == 0) *geom = g;
+      }
+    }
+    __syncthreads();
+  }
+  const int n = 1 << depth;
+  if (points) {
+    const Geom g = root;
+    for (int j0 = blockIdx.x * kTB; j0 < P; j0 += pblocks * kTB) {  // the same trip count for every lane
+      const int j = j0 + (int)threadIdx.x;
+      const bool ok = j < P;
+      int leaf = 0;
+      if (ok) {
+        int ix, iy;
+        {
+#pragma clang fp contract(off)
+          const double wl = g.side / (double)n;
+          ix = clamp_i((int)floor((X[j] - g.x0) / wl), 0, n - 1);
+          iy = clamp_i((int)floor((X[P + j] - g.y0) / wl), 0, n - 1);
+        }
+        leaf = ix * n + iy;
+        leafid[j] = leaf;
+      }
+      wave_group_add(ok, leaf, counts);
+    }
+    return;
+  }
+  const int v = blockIdx.x - pblocks;
   const int v0 = clamp_i(off[v], 0, P), v1 = max(v0, clamp_i(off[v + 1], 0, P));
   for (int j = v0 + (int)threadIdx.x; j < v1; j += kTB) vid[j] = v;
   if (h2 == nullptr) return;
-  __shared__ double red[kTB];
   double a = 0.0;
   for (int j = v0 + (int)threadIdx.x; j < v1; j += kTB) a += w[j];
   red[threadIdx.x] = a;
@@ -220,7 +239,7 @@ __global__ __launch_bounds__(kTB) void k_tc_vid(const int32_t* __restrict__ off,
   if (threadIdx.x == 0) {
     const double h = v1 > v0 ? red[0] / (double)(v1 - v0) : 0.0;
     h2[v] = h * h;
-    if (h > geom->side / (double)(1 << depth)) atomicOr(flag, 2);
+    if (h > root.side / (double)n) atomicOr(flag, 2);
   }
 }
 
@@ -1776,18 +1795,14 @@ TreeRun tree_run(void* ws, const TreeLayout& t, int depth, int p) {
 // Tree over the points (root square, leaves, leaf order) and the moments of every box of levels
 // 2..depth (leaves from the points, coarser levels by translation).
 void launch_upward(const double* X, const double* f, const double* w, const int32_t* off, int M, int P, int p,
-                   int depth, int cshift, bool fmm, bool near, const TreeRun& r, hipStream_t st) {
+                   int depth, int cshift, bool fmm, int32_t* count, const TreeRun& r, hipStream_t st) {
   const int nleaf = 1 << (2 * depth);
   const int pb = (P + kTB - 1) / kTB < 4096 ? (P + kTB - 1) / kTB : 4096;
   const int bb = (P + kTB - 1) / kTB < kBBoxBlocks ? (P + kTB - 1) / kTB : kBBoxBlocks;
-  hipLaunchKernelGGL(k_tc_bbox_partial, dim3(bb), dim3(kTB), 0, st, X, P, r.part,
-                     fmm ? r.ltab : nullptr);
-  hipLaunchKernelGGL(k_tc_bbox_final, dim3(1), dim3(64), 0, st, r.part, bb, r.geom);
-  const int zb = (nleaf + kTB - 1) / kTB < 4096 ? (nleaf + kTB - 1) / kTB : 4096;
-  hipLaunchKernelGGL(k_tc_zero, dim3(zb), dim3(kTB), 0, st, r.counts, r.cursor, nleaf);
-  hipLaunchKernelGGL(k_tc_leaf, dim3(pb), dim3(kTB), 0, st, X, P, r.geom, depth, r.leafid, r.counts);
-  hipLaunchKernelGGL(k_tc_vid, dim3(M), dim3(kTB), 0, st, off, P, r.vid, w, r.geom, depth, near ? r.h2 : nullptr,
-                     r.flag);
+  hipLaunchKernelGGL(k_tc_bbox_partial, dim3(bb), dim3(kTB), 0, st, X, P, r.part, fmm ? r.ltab : nullptr, r.counts,
+                     r.cursor, nleaf, count, r.flag);
+  hipLaunchKernelGGL(k_tc_leaf, dim3(pb + M), dim3(kTB), 0, st, X, P, r.part, bb, pb, depth, r.geom, r.leafid, r.counts,
+                     off, r.vid, w, count ? r.h2 : nullptr, r.flag);
   hipLaunchKernelGGL(k_tc_scan, dim3(1), dim3(1024), 0, st, r.counts, nleaf, r.starts, r.wstart, cshift);
   hipLaunchKernelGGL(k_tc_scatter, dim3(pb), dim3(kTB), 0, st, r.leafid, P, r.starts, r.cursor, r.perm);
   hipLaunchKernelGGL(k_tc_sort, dim3(nleaf), dim3(64), 0, st, X, f, w, P, r.vid, r.starts, r.perm, r.srec, r.svid);
@@ -1835,7 +1850,7 @@ hipError_t launch_treecode(const double* X, const double* f, const double* w, co
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, false), depth, p);
   const int lanes = tree_lanes(P, depth), shift = lanes == 16 ? 5 : 4;  // 2 lanes targets per wavefront
-  launch_upward(X, f, w, off, M, P, p, depth, shift, false, false, r, st);
+  launch_upward(X, f, w, off, M, P, p, depth, shift, false, nullptr, r, st);
   if (depth >= 2) {
     const size_t work = r.nbox * (p + 1);
     const int gb = (int)((work + kTB - 1) / kTB < 4096 ? (work + kTB - 1) / kTB : 4096);
@@ -1857,8 +1872,7 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
                           double scale, int p, int depth, double* out, void* ws, hipStream_t st, bool near,
                           int32_t* pairs, int capacity, int32_t* count) {
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, true, near ? M : 0), depth, p);
-  if (near) hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(kTB), 0, st, count, r.flag, 1);
-  launch_upward(X, f, w, off, M, P, p, depth, kFmmChunkShift, true, near, r, st);
+  launch_upward(X, f, w, off, M, P, p, depth, kFmmChunkShift, true, near ? count : nullptr, r, st);
   if (depth >= 2) {
     const dim3 g((unsigned)r.nbox), bl(64);
     const size_t lds = m2l_lds_bytes(p);
@@ -1902,7 +1916,7 @@ hipError_t launch_fmm(const double* X, const double* f, const double* w, const i
 }
 
 hipError_t launch_zero_count(int32_t* count, void* stream) {
-  hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(kTB), 0, reinterpret_cast<hipStream_t>(stream), count, count, 1);
+  hipLaunchKernelGGL(k_tc_zero, dim3(1), dim3(64), 0, reinterpret_cast<hipStream_t>(stream), count);
   return hipGetLastError();
 }
 
