@@ -1205,55 +1205,74 @@ __global__ __launch_bounds__(64 * kFmmWaves) void k_fmm_eval(const double4* __re
 
 // ---------------------------------------------------------------- treecode evaluation
 //
-// One wavefront per (leaf, chunk of 2 L of its points): L lanes take two targets each, and the G = 64 / L lane groups
-// share the work, in the far part every G-th box of the interaction lists and in the direct part every G-th source;
-// the groups' sums are added at the end.  (With one target per lane and 64 per wavefront, leaves of about 20 points
-// left two thirds of the lanes repeating the others' boxes; and the three Horner chains read 48 bytes of LDS per 12
-// FMAs, twice what LDS delivers beside the FMAs: two targets per lane use each coefficient twice.)
-// The list of boxes is made level by level with one candidate per lane; each step stages the coefficients of G boxes
-// (rows M, D and M / k) in LDS.  What bounds it is float64 VALU issue (73% of the kernel's cycles at L = 16).  Whole
-// calls: 89,457 ragged points, order 20, depth 6, 580 -> 402 us; 29,283, order 30, 347 -> 207 us; 2000 x 128, order
-// 30, 1.26 -> 1.11 ms.
+// One workgroup per part of a leaf of at most 32 points (a leaf's parts are of equal size), four wavefronts: L = 8 .. 16
+// lanes take two targets each, and the groups of L lanes of all four wavefronts share the work, in the far part the
+// boxes of the interaction lists and in the direct part the sources; the groups' sums are added at the end.  (With one
+// target per lane and 64 per wavefront, leaves of about 20 points left two thirds of the lanes repeating the others'
+// boxes; with L fixed at 8 a leaf of 22 points was two parts that staged every box twice, two lanes of five empty; and
+// with a wavefront to itself a part is so much work that the last of 1.4 rounds of wavefronts left the chip half idle.)
+// The list of boxes is made level by level with one candidate per lane.  Each step of a wavefront stages the
+// coefficients of its groups' boxes (rows M, D and M / k) in LDS, read from memory one step ahead; the three Horner
+// chains use each coefficient for both targets of a lane.  What bounds it is float64 VALU issue (143 of 237 us at
+// 89,457 ragged points, order 20, depth 6) and the latency of a step at three wavefronts per SIMD.
+// The kernel there: 337 -> 237 us.  Whole calls: 580 -> 283 us; 29,283 points, order 30, 347 -> 156 us; 8,192, order
+// 12, 105 -> 63 us; 2000 x 128, order 30, 1.26 -> 0.99 ms.
 constexpr int kTreeT = 2;  // targets per lane
-
-// L = 16 where the leaves average more than 44 points, else 8: chunks of 32 leave a sparse leaf's wavefront half
-// empty (28 points per leaf: 249 us at 16, 207 at 8), chunks of 16 stage twice as many boxes per target (62 per
-// leaf: 1.11 ms at 16, 1.30 at 8).
-int tree_lanes(int P, int depth) { return (int64_t)P > (int64_t)44 << (2 * depth) ? 16 : 8; }
+constexpr int kTreeChunkShift = 5;  // log2 of the most targets per wavefront
+constexpr int kTreeWaves = 4;       // wavefronts that share a part
+constexpr int kTreeMinLanes = 8, kTreeMaxGroups = 64 / kTreeMinLanes;
 
 constexpr int kListMax = 27 * (kMaxDepth - 1);     // boxes of all interaction lists of a leaf
 
 // Box of a list entry: level in bits 20-23, column in 10-19, row in 0-9.
 __device__ __forceinline__ int list_entry(int l, int sx, int sy) { return l << 20 | sx << 10 | sy; }
 
-template <int kTreeLanes>
-__global__ __launch_bounds__(64) void k_tc_eval(const double4* __restrict__ srec, const int32_t* __restrict__ svid,
+// a = a t + c in four three-address FMAs.  (The compiler's two-address form needs a copy of every c but for its last
+// user, and one of every sum at the end of the loop: 21 instructions beside 24 FMAs.)
+__device__ __forceinline__ void horner_step(double2& a, double2 t, double2 c) {
+  double2 r;
+  asm("v_fma_f64 %0, -%1, %2, %3" : "=v"(r.x) : "v"(a.y), "v"(t.y), "v"(c.x));
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r.y) : "v"(a.y), "v"(t.x), "v"(c.y));
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(a.y) : "v"(a.x), "v"(t.y), "v"(r.y));
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(a.x) : "v"(a.x), "v"(t.x), "v"(r.x));
+}
+
+// kAhead: entries of a step's coefficients per lane.
+template <int kAhead>
+__global__ __launch_bounds__(64 * kTreeWaves) void k_tc_eval(const double4* __restrict__ srec, const int32_t* __restrict__ svid,
                                                 int P, const int32_t* __restrict__ perm,
                                                 const int32_t* __restrict__ starts,
                                                 const int32_t* __restrict__ wstart, const Geom* __restrict__ geom,
                                                 int depth, int p, const double2* __restrict__ mom,
                                                 const int32_t* __restrict__ bcount, double scale,
-                                                double* __restrict__ out) {
-  constexpr int kTreeGroups = 64 / kTreeLanes;
-  extern __shared__ double2 cf[];  // [kTreeGroups][3 (p + 1)] coefficients of the step's boxes
+                                                int max_groups, double* __restrict__ out) {
+  extern __shared__ double2 cfs[];  // [kTreeWaves][max_groups][3 (p + 1)] coefficients of the step's boxes
   __shared__ int32_t list[kListMax + 1];
-  __shared__ double4 src[64];
-  __shared__ int32_t sv[64];
+  __shared__ unsigned first[kListMax + 1];  // of the boxes' moments
+  __shared__ double4 srcs[kTreeWaves][64];
+  __shared__ int32_t svs[kTreeWaves][64];
   __shared__ double2 ltab[kLogTab];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  double2* cf = cfs + (size_t)wave * max_groups * 3 * (p + 1);
+  double4* src = srcs[wave];
+  int32_t* sv = svs[wave];
   const int n = 1 << depth;
   const int nleaf = n * n;
   const int item = blockIdx.x;
   if (item >= wstart[nleaf]) return;
   const int leaf = leaf_of_item(wstart, nleaf, item);
-  const int s0 = starts[leaf], s1 = starts[leaf + 1];
-  const int lane = threadIdx.x, tl = lane & (kTreeLanes - 1), grp = lane / kTreeLanes;
-  ltab[lane] = log_tab_entry(lane);
-  const int base = s0 + (item - wstart[leaf]) * kTreeT * kTreeLanes;
+  const int s0 = starts[leaf], count = starts[leaf + 1] - s0;
+  const int part = item - wstart[leaf], parts = wstart[leaf + 1] - wstart[leaf];
+  const int base = s0 + (int)((int64_t)count * part / parts), s1 = s0 + (int)((int64_t)count * (part + 1) / parts);
+  const int lanes = max((s1 - base + kTreeT - 1) / kTreeT, kTreeMinLanes), groups = min(64 / lanes, max_groups);
+  const int grp = lane / lanes, tl = lane - grp * lanes;  // grp = groups: no work
+  const int mine = wave * groups, step = kTreeWaves * groups;  // this wavefront's first group of all
+  if (wave == 0) ltab[lane] = log_tab_entry(lane);
   double zx[kTreeT], zy[kTreeT], ux[kTreeT], uy[kTreeT];
   int ti[kTreeT], vi[kTreeT];
 #pragma unroll
   for (int k = 0; k < kTreeT; ++k) {
-    const int slot = base + tl + kTreeLanes * k;
+    const int slot = base + tl + lanes * k;
     const int sl = slot < s1 ? slot : base;  // an empty slot repeats the first target
     ti[k] = perm[sl];
     const double4 z = srec[sl];
@@ -1272,36 +1291,41 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double4* __restrict__ srec
     bool ok = lane < 36 && sx >= 0 && sx < nl && sy >= 0 && sy < nl && (abs(sx - bx) > 1 || abs(sy - by) > 1);
     if (ok) ok = bcount[level_box_base(l) + (size_t)sx * nl + sy] != 0;
     const unsigned long long m = __ballot(ok);
-    if (ok) list[nbox + __popcll(m & ((1ull << lane) - 1ull))] = list_entry(l, sx, sy);
+    if (ok && wave == 0) {
+      const int at = nbox + __popcll(m & ((1ull << lane) - 1ull));
+      list[at] = list_entry(l, sx, sy);
+      first[at] = (unsigned)(level_box_base(l) + (size_t)sx * nl + sy) * 4 * (unsigned)(p + 1);
+    }
     nbox += __popcll(m);
   }
-  wave_sync();
+  __syncthreads();
   const int np = p + 1, row3 = 3 * np;
-  const unsigned inv_row3 = (1u << 20) / (unsigned)row3 + 1u;  // e / row3 = e inv_row3 / 2^20 for e < 8 row3 <= 1176
-  for (int b0 = 0; b0 < nbox; b0 += kTreeGroups) {
+  // Entry e of a step's coefficients: box e / (3 np), then rows M, D, M / k (rows 0, 2 and 3 of the moments).  A lane's
+  // entries have the same place in every step: box << 16 | offset in the box.
+  int place[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    const int e = lane + 64 * u, b = e / row3, r = e - b * row3;
+    place[u] = b < groups ? b << 16 | (r + (r >= np ? np : 0)) : 0;
+  }
+  double2 ahead[kAhead];  // the next step's entries, read while this step's are used
+  const auto entry = [&](int b0, int pl) __attribute__((always_inline)) {
+    return mom[first[min(b0 + (pl >> 16), nbox - 1)] + (pl & 0xffff)];
+  };
+  if (nbox > 0) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) ahead[u] = entry(mine, place[u]);
+  }
+  for (int b0 = mine; b0 < nbox; b0 += step) {
     wave_sync();  // the previous step is done with cf
-    {
-      // entry e of the step's coefficients: box e / (3 np), then rows M, D, M / k (rows 0, 2 and 3 of the moments);
-      // four loads in flight per lane
-      const int cnt = min(kTreeGroups, nbox - b0) * row3;
-      for (int e0 = lane; e0 < cnt; e0 += 256) {
-        double2 v[4];
+    const int cnt = min(groups, nbox - b0) * row3;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int e = min(e0 + 64 * u, cnt - 1);
-          const int b = (int)(((unsigned)e * inv_row3) >> 20);
-          const int r = e - b * row3;
-          const int en = list[b0 + b], l = en >> 20;
-          const size_t box = level_box_base(l) + (size_t)((en >> 10) & 1023) * (1 << l) + (en & 1023);
-          v[u] = mom[box * 4 * np + r + (r >= np ? np : 0)];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (e0 + 64 * u < cnt) cf[e0 + 64 * u] = v[u];
-      }
-    }
+    for (int u = 0; u < kAhead; ++u)
+      if (lane + 64 * u < cnt) cf[lane + 64 * u] = ahead[u];
     wave_sync();
-    if (b0 + grp < nbox) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) ahead[u] = entry(b0 + step, place[u]);  // past the end: the last box
+    if (grp < groups && b0 + grp < nbox) {
       const int en = list[b0 + grp];
       const double2 c = box_center(g, 1 << (en >> 20), (en >> 10) & 1023, en & 1023);
       const double2* cb = cf + grp * row3;
@@ -1318,14 +1342,14 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double4* __restrict__ srec
         t[k] = make_double2(wv[k].x * rw[k], -wv[k].y * rw[k]);
         aS[k] = aD[k] = aE[k] = make_double2(0.0, 0.0);
       }
-#pragma unroll 1
+#pragma unroll 2
       for (int q = p; q >= 1; --q) {
         const double2 cE = cb[q], cD = cb[np + q], cS = cb[2 * np + q];
 #pragma unroll
         for (int k = 0; k < kTreeT; ++k) {
-          aS[k] = cfma(aS[k], t[k], cS);
-          aD[k] = cfma(aD[k], t[k], cD);
-          aE[k] = cfma(aE[k], t[k], cE);
+          horner_step(aS[k], t[k], cS);
+          horner_step(aD[k], t[k], cD);
+          horner_step(aE[k], t[k], cE);
         }
       }
       const double2 M0 = cb[0], D0 = cb[np];
@@ -1354,7 +1378,7 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double4* __restrict__ srec
         sv[lane] = svid[c0 + lane];
       }
       wave_sync();
-      for (int q = grp; q < cnt; q += kTreeGroups) {
+      for (int q = grp < groups ? mine + grp : cnt; q < cnt; q += step) {
         const double4 s = src[q];
         const int cv = sv[q];
 #pragma unroll
@@ -1363,18 +1387,23 @@ __global__ __launch_bounds__(64) void k_tc_eval(const double4* __restrict__ srec
       }
     }
   }
+  wave_sync();  // the records are done: their place holds the groups' sums, added in order
+  src[lane] = make_double4(ux[0], uy[0], ux[1], uy[1]);
+  __syncthreads();
+  if (wave > 0 || grp > 0) return;
+  for (int q = 1; q < step; ++q) {
+    const double4 u = srcs[q / groups][(q % groups) * lanes + tl];
+    ux[0] += u.x;
+    uy[0] += u.y;
+    ux[1] += u.z;
+    uy[1] += u.w;
+  }
 #pragma unroll
-  for (int k = 0; k < kTreeT; ++k) {  // the groups' sums, pairwise in a fixed order
-#pragma unroll
-    for (int o = kTreeLanes; o < 64; o <<= 1) {
-      ux[k] += __shfl_xor(ux[k], o);
-      uy[k] += __shfl_xor(uy[k], o);
-    }
-    if (grp == 0 && base + tl + kTreeLanes * k < s1) {
+  for (int k = 0; k < kTreeT; ++k)
+    if (base + tl + lanes * k < s1) {
       out[ti[k]] = ux[k] * scale;
       out[P + ti[k]] = uy[k] * scale;
     }
-  }
 }
 
 // Own-vesicle sources outside the 3 x 3 leaves around a target were in the expansions: their direct terms
@@ -1849,21 +1878,22 @@ hipError_t launch_treecode(const double* X, const double* f, const double* w, co
   if (depth < 0 || depth > kMaxDepth || p < 1 || p > kMaxOrder) return hipErrorInvalidValue;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, false), depth, p);
-  const int lanes = tree_lanes(P, depth), shift = lanes == 16 ? 5 : 4;  // 2 lanes targets per wavefront
-  launch_upward(X, f, w, off, M, P, p, depth, shift, false, nullptr, r, st);
+  launch_upward(X, f, w, off, M, P, p, depth, kTreeChunkShift, false, nullptr, r, st);
   if (depth >= 2) {
     const size_t work = r.nbox * (p + 1);
     const int gb = (int)((work + kTB - 1) / kTB < 4096 ? (work + kTB - 1) / kTB : 4096);
     hipLaunchKernelGGL(k_tc_finalize, dim3(gb), dim3(kTB), 0, st, r.mom, r.nbox, p);
   }
-  const dim3 grid((unsigned)eval_items(P, depth, shift));
-  const size_t lds = sizeof(double2) * (size_t)(64 / lanes) * 3 * (p + 1);
-  if (lanes == 16)
-    hipLaunchKernelGGL(k_tc_eval<16>, grid, dim3(64), lds, st, r.srec, r.svid, P, r.perm, r.starts, r.wstart, r.geom,
-                       depth, p, r.mom, r.bcount, scale, out);
+  // groups whose boxes fit 48 KB: all eight up to order 31, five at 48
+  const size_t per = sizeof(double2) * (size_t)kTreeWaves * 3 * (p + 1);
+  const int max_groups = (size_t)kTreeMaxGroups * per <= 49152 ? kTreeMaxGroups : (int)(49152 / per);
+  const dim3 grid((unsigned)eval_items(P, depth, kTreeChunkShift)), block(64 * kTreeWaves);
+  if (max_groups * 3 * (p + 1) <= 8 * 64)
+    hipLaunchKernelGGL(k_tc_eval<8>, grid, block, per * max_groups, st, r.srec, r.svid, P, r.perm, r.starts, r.wstart,
+                       r.geom, depth, p, r.mom, r.bcount, scale, max_groups, out);
   else
-    hipLaunchKernelGGL(k_tc_eval<8>, grid, dim3(64), lds, st, r.srec, r.svid, P, r.perm, r.starts, r.wstart, r.geom,
-                       depth, p, r.mom, r.bcount, scale, out);
+    hipLaunchKernelGGL(k_tc_eval<12>, grid, block, per * max_groups, st, r.srec, r.svid, P, r.perm, r.starts, r.wstart,
+                       r.geom, depth, p, r.mom, r.bcount, scale, max_groups, out);
   launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   return hipGetLastError();
 }
