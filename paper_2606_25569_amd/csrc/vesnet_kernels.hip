@@ -20,6 +20,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "vesnet_internal.h"
 
 namespace vesnet {
@@ -501,6 +503,179 @@ __global__ __launch_bounds__(256) void k_reduce_splits(const double* __restrict_
   }
 }
 
+// ----------------------------------------------------------------------------- small problems, one launch
+
+// The direct compensated sum of a small problem without a prepared workspace: one workgroup per 64 targets, one
+// wavefront per source split, which prepares each of its vesicles itself (the reference point by the sums of k_prepare)
+// and adds it as k_forward does, 64 records at a time through LDS; the splits are added in order as k_reduce_splits
+// does.  The same operations in the same order, so the result is that of the three launches bit for bit.  Latency
+// bounds it: 16 x 32, 12.7 us in three launches -> 7.2 us.
+__global__ __launch_bounds__(1024) void k_forward_small32(const double* __restrict__ tg, const double* __restrict__ src,
+                                                          const double* __restrict__ f, const double* __restrict__ w,
+                                                          const int32_t* __restrict__ off, int M, int P, double scale,
+                                                          double* __restrict__ out) {
+  __shared__ float4 recs[16][64];
+  __shared__ double2 sums[16][64];
+  const int split = threadIdx.x >> 6, splits = blockDim.x >> 6, lane = threadIdx.x & 63;
+  float4* rec = recs[split];
+  const int i = blockIdx.x * 64 + lane;
+  const int ii = min(i, P - 1);
+  const double px = tg[ii], py = tg[P + ii];
+  double vx = 0.0, vy = 0.0;
+  const int v_end = (int)(((int64_t)M * (split + 1)) / splits);
+  for (int v = (int)(((int64_t)M * split) / splits); v < v_end; ++v) {
+    const int j0 = clampi(off[v], 0, P);
+    const int j1 = max(j0, clampi(off[v + 1], 0, P));
+    const int n = j1 - j0;
+    double sx = 0.0, sy = 0.0, bx = 0.0, by = 0.0;
+    for (int j = j0 + lane; j < j1; j += 64) {
+      const double wj = w[j];
+      sx += src[j];
+      sy += src[P + j];
+      bx += wj * f[j];
+      by += wj * f[P + j];
+    }
+    sx = wave_sum(sx);
+    sy = wave_sum(sy);
+    bx = wave_sum(bx);
+    by = wave_sum(by);
+    const double cx = n > 0 ? sx / n : 0.0;
+    const double cy = n > 0 ? sy / n : 0.0;
+    const double ddx = px - cx, ddy = py - cy;
+    const double D = ddx * ddx + ddy * ddy;
+    const float Df = (float)D;
+    const float sig = (Df > 1e-30f && Df < 1e30f) ? __builtin_amdgcn_rsqf(Df) : 1.0f;
+    const float dx = (float)(ddx * (double)sig), dy = (float)(ddy * (double)sig), ns = -sig;
+    float lx = 0.0f, ly = 0.0f, rvx = 0.0f, rvy = 0.0f;
+    for (int c0 = j0; c0 < j1; c0 += 64) {
+      const int cnt = min(64, j1 - c0);
+      wave_sync();  // the previous records are done
+      if (lane < cnt) {
+        const int j = c0 + lane;
+        const double wj = w[j];
+        rec[lane] = make_float4((float)(src[j] - cx), (float)(src[P + j] - cy), (float)(wj * f[j]), (float)(wj * f[P + j]));
+      }
+      wave_sync();
+      // every product that k_forward's loop over four records, and the one over the rest, fuses is fused here the same way
+      const auto pair = [&](const float4& s, bool rest) __attribute__((always_inline)) {
+        const float rx = fmaf(s.x, ns, dx), ry = fmaf(s.y, ns, dy);
+        const float d2 = fmaf(rx, rx, ry * ry);
+        const float rho = __builtin_amdgcn_rcpf(d2);
+        const float beta = rest ? fmaf(ry, s.w, rx * s.z) : fmaf(rx, s.z, ry * s.w);
+        const float L = __builtin_amdgcn_logf(d2);
+        const float t = beta * rho;
+        lx = fmaf(L, s.z, lx);
+        ly = fmaf(L, s.w, ly);
+        rvx = fmaf(t, rx, rvx);
+        rvy = fmaf(t, ry, rvy);
+      };
+      int q = 0;
+      for (; q + 4 <= cnt; q += 4) {
+        const float4 s0 = rec[q], s1 = rec[q + 1], s2 = rec[q + 2], s3 = rec[q + 3];
+        pair(s0, false);
+        pair(s1, false);
+        pair(s2, false);
+        pair(s3, false);
+      }
+      for (; q < cnt; ++q) pair(rec[q], true);
+    }
+    const float pvx = fmaf(kHalfLn2, lx, rvx);
+    const float pvy = fmaf(kHalfLn2, ly, rvy);
+    int e;
+    const float m = frexpf(sig, &e);
+    const double lnsig = ((double)e + (double)__builtin_amdgcn_logf(m)) * kLn2;
+    const double cvx = fma(lnsig, bx, (double)pvx);
+    const double cvy = fma(lnsig, by, (double)pvy);
+    const bool keep = i < j0 || i >= j1;  // not the target's own vesicle
+    vx += keep ? cvx : 0.0;
+    vy += keep ? cvy : 0.0;
+  }
+  sums[split][lane] = make_double2(vx, vy);
+  __syncthreads();
+  if (split > 0 || i >= P) return;
+  double tx = 0.0, ty = 0.0;
+  for (int k = 0; k < splits; ++k) {
+    tx += sums[k][lane].x;
+    ty += sums[k][lane].y;
+  }
+  out[i] = scale * tx;
+  out[P + i] = scale * ty;
+}
+
+// The direct float64 sum of a small problem in one launch: one workgroup of sixteen wavefronts per kT = 4, 8 or 16
+// targets; each wavefront takes a sixteenth of the sources, 64 records at a time through LDS, each of its lane groups
+// every 64 / kT-th of them, and the sums are added at the end in a fixed order.  Float64 VALU issue bounds it from about
+// a thousand points on, below it latency.  48 x 32: 19.4 us in three launches -> 8.0 us; 16 x 32: 13.8 -> 4.2 us.
+template <int kT>
+__global__ __launch_bounds__(1024) void k_forward_small64(const double* __restrict__ tg, const double* __restrict__ src,
+                                                          const double* __restrict__ f, const double* __restrict__ w,
+                                                          const int32_t* __restrict__ off, int M, int P, double scale,
+                                                          double* __restrict__ out) {
+  constexpr int kWaves = 16, kGroups = 64 / kT;
+  __shared__ double4 recs[kWaves][64];
+  __shared__ double2 sums[kWaves][kT];
+  __shared__ double2 ltab[kLogTab];
+  __shared__ int2 own[kT];  // point range of the target's own vesicle
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, t = lane & (kT - 1), g = lane / kT;
+  double4* rec = recs[wave];
+  const int i0 = blockIdx.x * kT, i = i0 + t;
+  const int e0 = (int)(((int64_t)P * wave) / kWaves), e1 = (int)(((int64_t)P * (wave + 1)) / kWaves);
+  if (threadIdx.x < kT) own[threadIdx.x] = make_int2(0, 0);
+  if (wave == kWaves - 1) ltab[lane] = log_tab_entry(lane);
+  const int ii = min(i, P - 1);
+  const double px = tg[ii], py = tg[P + ii];
+  __syncthreads();
+  for (int v = threadIdx.x; v < M; v += 64 * kWaves) {
+    const int a = clampi(off[v], 0, P), b = max(a, clampi(off[v + 1], 0, P));
+    for (int k = max(a, i0); k < min(b, i0 + kT); ++k) own[k - i0] = make_int2(a, b);
+  }
+  __syncthreads();
+  const int2 mine = own[t];
+  double lx = 0.0, ly = 0.0, rvx = 0.0, rvy = 0.0;
+  for (int c0 = e0; c0 < e1; c0 += 64) {
+    const int cnt = min(64, e1 - c0);
+    wave_sync();  // the previous records are done
+    if (lane < cnt) {
+      const int j = c0 + lane;
+      const double wj = w[j];
+      rec[lane] = make_double4(src[j], src[P + j], wj * f[j], wj * f[P + j]);
+    }
+    wave_sync();
+#pragma unroll 2
+    for (int q = g; q < cnt; q += kGroups) {
+      const double4 s = rec[q];
+      const bool skip = c0 + q >= mine.x && c0 + q < mine.y;
+      const double rx = px - s.x, ry = py - s.y;
+      const double d2 = ry * ry + rx * rx;
+      const double L = log_reduced(d2, ltab);
+      const double tt = (ry * s.w + rx * s.z) * recip(d2);
+      if (!skip) {
+        lx += L * s.z;
+        ly += L * s.w;
+        rvx += tt * rx;
+        rvy += tt * ry;
+      }
+    }
+  }
+  double vx = fma(-0.5, lx, rvx), vy = fma(-0.5, ly, rvy);
+#pragma unroll
+  for (int o = kT; o < 64; o <<= 1) {
+    vx += __shfl_xor(vx, o, 64);
+    vy += __shfl_xor(vy, o, 64);
+  }
+  if (g == 0) sums[wave][t] = make_double2(vx, vy);
+  __syncthreads();
+  if (threadIdx.x >= kT || i >= P) return;
+  double tx = 0.0, ty = 0.0;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    tx += sums[k][t].x;
+    ty += sums[k][t].y;
+  }
+  out[i] = scale * tx;
+  out[P + i] = scale * ty;
+}
+
 // ----------------------------------------------------------------------------- batched
 
 // Plan, step 1: size of each suspension (points), work items per suspension.
@@ -775,6 +950,29 @@ hipError_t launch_forward(int prec, int T, int B, bool lds, bool mf, int splits,
   const int64_t n = 2 * (int64_t)P;
   const int grid = (int)((n + 255) / 256 < 16384 ? (n + 255) / 256 : 16384);
   hipLaunchKernelGGL(k_reduce_splits, dim3(grid), dim3(256), 0, st, partial, P, splits, scale, out);
+  return hipGetLastError();
+}
+
+// Targets per workgroup of the small float64 sum: the fewest that leave every compute unit at most one workgroup.
+template <class Launch>
+static void small64(int P, const Launch& launch) {
+  if (P <= 1024) launch(std::integral_constant<int, 4>{});
+  else if (P <= 2048) launch(std::integral_constant<int, 8>{});
+  else launch(std::integral_constant<int, 16>{});
+}
+
+hipError_t launch_forward_small(int prec, int splits, const double* tg, const double* src, const double* f,
+                                const double* w, const int32_t* off, int M, int P, double scale, double* out,
+                                void* stream) {
+  hipStream_t st = S_(stream);
+  if (prec == P32C)
+    hipLaunchKernelGGL(k_forward_small32, dim3((P + 63) / 64), dim3(64 * splits), 0, st, tg, src, f, w, off, M, P, scale,
+                       out);
+  else
+    small64(P, [&](auto kT) {
+      hipLaunchKernelGGL(k_forward_small64<kT.value>, dim3((P + kT.value - 1) / kT.value), dim3(1024), 0, st, tg, src, f, w,
+                         off, M, P, scale, out);
+    });
   return hipGetLastError();
 }
 
