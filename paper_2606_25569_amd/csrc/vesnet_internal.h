@@ -209,6 +209,9 @@ hipError_t launch_prepare(int prec, const double* pts, const double* vec, const 
 hipError_t launch_forward_small(int prec, int splits, const double* tg, const double* src, const double* f,
                                 const double* w, const int32_t* off, int M, int P, double scale, double* out,
                                 void* stream);
+hipError_t launch_adjoint_small64(const double* X, const double* f, const double* w, const double* gout,
+                                  const int32_t* off, int M, int P, double scale, double* gX, double* gf, double* gw,
+                                  void* stream);
 hipError_t launch_forward(int prec, int T, int B, bool lds, bool mf, int splits, const double* tg, int P, int M,
                           const PreparedView& pv, double scale, double* out, double* partial, void* stream);
 // Symmetric form (float32-compensated, targets = sources): sizes of its tables and the launch.

@@ -676,6 +676,113 @@ __global__ __launch_bounds__(1024) void k_forward_small64(const double* __restri
   out[P + i] = scale * ty;
 }
 
+// The float64 adjoint for one point array (targets = sources, positions differentiated in both roles) of a small
+// problem in one launch, shared out as k_forward_small64.  With r = x_i - x_j, F = w f and g the gradient of the
+// velocity, each ordered pair adds G(r) g_j to v_i (the gradient of F_i) and the r-gradient of g_i . G F_j + F_i . G g_j
+// to that of x_i.  Twice the pairs of the symmetric form, but no zeroing, atomics or finishing pass.
+// 48 x 32: 17.2 us in three launches -> 11.8 us; 16 x 32: 17.2 -> 6.0 us.
+template <int kT>
+__global__ __launch_bounds__(1024) void k_adjoint_small64(const double* __restrict__ X, const double* __restrict__ f,
+                                                          const double* __restrict__ w, const double* __restrict__ gout,
+                                                          const int32_t* __restrict__ off, int M, int P, double scale,
+                                                          double* __restrict__ gX, double* __restrict__ gf,
+                                                          double* __restrict__ gw) {
+  constexpr int kWaves = 16, kGroups = 64 / kT;
+  __shared__ double4 recs[kWaves][64];
+  __shared__ double2 grecs[kWaves][64];
+  __shared__ double4 sums[kWaves][kT];
+  __shared__ double2 ltab[kLogTab];
+  __shared__ int2 own[kT];  // point range of the target's own vesicle
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, t = lane & (kT - 1), g = lane / kT;
+  double4* rec = recs[wave];
+  double2* grec = grecs[wave];
+  const int i0 = blockIdx.x * kT, i = i0 + t;
+  const int e0 = (int)(((int64_t)P * wave) / kWaves), e1 = (int)(((int64_t)P * (wave + 1)) / kWaves);
+  if (threadIdx.x < kT) own[threadIdx.x] = make_int2(0, 0);
+  if (wave == kWaves - 1) ltab[lane] = log_tab_entry(lane);
+  const int ii = min(i, P - 1);
+  const double px = X[ii], py = X[P + ii], ax = gout[ii], ay = gout[P + ii];
+  const double Fx = w[ii] * f[ii], Fy = w[ii] * f[P + ii];
+  __syncthreads();
+  for (int v = threadIdx.x; v < M; v += 64 * kWaves) {
+    const int a = clampi(off[v], 0, P), b = max(a, clampi(off[v + 1], 0, P));
+    for (int k = max(a, i0); k < min(b, i0 + kT); ++k) own[k - i0] = make_int2(a, b);
+  }
+  __syncthreads();
+  const int2 mine = own[t];
+  double lx = 0.0, ly = 0.0, vx = 0.0, vy = 0.0, sF = 0.0, sG = 0.0, hx = 0.0, hy = 0.0;
+  for (int c0 = e0; c0 < e1; c0 += 64) {
+    const int cnt = min(64, e1 - c0);
+    wave_sync();  // the previous records are done
+    if (lane < cnt) {
+      const int j = c0 + lane;
+      const double wj = w[j];
+      rec[lane] = make_double4(X[j], X[P + j], wj * f[j], wj * f[P + j]);
+      grec[lane] = make_double2(gout[j], gout[P + j]);
+    }
+    wave_sync();
+    for (int q = g; q < cnt; q += kGroups) {
+      const double4 s = rec[q];
+      const double2 b = grec[q];
+      const bool skip = c0 + q >= mine.x && c0 + q < mine.y;
+      const double rx = px - s.x, ry = py - s.y;
+      const double d2 = ry * ry + rx * rx;
+      const double rho = recip(d2);
+      const double L = log_reduced(d2, ltab);
+      const double ar = (ay * ry + ax * rx) * rho, Fr = (Fy * ry + Fx * rx) * rho;  // of this point: g . r, F . r
+      const double br = b.y * ry + b.x * rx, sr = s.w * ry + s.z * rx;              // of the other
+      const double gam = ay * s.w + ax * s.z + (Fy * b.y + Fx * b.x);
+      const double kr = (-2.0 * (ar * sr + Fr * br) - gam) * rho;
+      const double tb = br * rho, ts = sr * rho;
+      if (!skip) {
+        lx += L * b.x;
+        ly += L * b.y;
+        vx += tb * rx;
+        vy += tb * ry;
+        sF += tb;
+        sG += ts;
+        hx += rx * kr + (s.z * ar + b.x * Fr);
+        hy += ry * kr + (s.w * ar + b.y * Fr);
+      }
+    }
+  }
+  vx = fma(-0.5, lx, vx);
+  vy = fma(-0.5, ly, vy);
+  hx += ax * sG + Fx * sF;
+  hy += ay * sG + Fy * sF;
+#pragma unroll
+  for (int o = kT; o < 64; o <<= 1) {
+    vx += __shfl_xor(vx, o, 64);
+    vy += __shfl_xor(vy, o, 64);
+    hx += __shfl_xor(hx, o, 64);
+    hy += __shfl_xor(hy, o, 64);
+  }
+  if (g == 0) sums[wave][t] = make_double4(vx, vy, hx, hy);
+  __syncthreads();
+  if (threadIdx.x >= kT || i >= P) return;
+  vx = vy = hx = hy = 0.0;
+#pragma unroll
+  for (int k = 0; k < kWaves; ++k) {
+    const double4 u = sums[k][t];
+    vx += u.x;
+    vy += u.y;
+    hx += u.z;
+    hy += u.w;
+  }
+  if (gX) {
+    gX[i] = scale * hx;
+    gX[P + i] = scale * hy;
+  }
+  vx *= scale;
+  vy *= scale;
+  if (gf) {
+    const double wi = w[i];
+    gf[i] = wi * vx;
+    gf[P + i] = wi * vy;
+  }
+  if (gw) gw[i] = f[i] * vx + f[P + i] * vy;
+}
+
 // ----------------------------------------------------------------------------- batched
 
 // Plan, step 1: size of each suspension (points), work items per suspension.
@@ -973,6 +1080,17 @@ hipError_t launch_forward_small(int prec, int splits, const double* tg, const do
       hipLaunchKernelGGL(k_forward_small64<kT.value>, dim3((P + kT.value - 1) / kT.value), dim3(1024), 0, st, tg, src, f, w,
                          off, M, P, scale, out);
     });
+  return hipGetLastError();
+}
+
+hipError_t launch_adjoint_small64(const double* X, const double* f, const double* w, const double* gout,
+                                  const int32_t* off, int M, int P, double scale, double* gX, double* gf, double* gw,
+                                  void* stream) {
+  hipStream_t st = S_(stream);
+  small64(P, [&](auto kT) {
+    hipLaunchKernelGGL(k_adjoint_small64<kT.value>, dim3((P + kT.value - 1) / kT.value), dim3(1024), 0, st, X, f, w, gout,
+                       off, M, P, scale, gX, gf, gw);
+  });
   return hipGetLastError();
 }
 
