@@ -12,6 +12,7 @@ Stokeslet of eq. (Stokeslet) read as -ln|r| I + r r^T/|r|^2, trapezoid rule
 from __future__ import annotations
 
 import ctypes
+import functools
 import json
 import os
 import tempfile
@@ -25,11 +26,12 @@ _P = ctypes.c_void_p
 
 
 def _ptr(t):
-    return _P(t.data_ptr()) if t is not None else _P(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
-    return _P(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle (torch.cuda.current_stream() makes an object of it: 2 us of a 13 us call)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check_vec(name, t, P):
@@ -90,7 +92,25 @@ def _cfg_struct(config):
 
 
 def workspace_bytes(P, M, precision, config=None):
+    if config is None:
+        return _default_workspace_bytes(P, M, L.precision_code(precision))
     return int(L.lib().vesnet_farfield_workspace_bytes(P, M, L.precision_code(precision), _cfg_arg(config)))
+
+
+# functions of the sizes alone
+@functools.lru_cache(maxsize=256)
+def _default_workspace_bytes(P, M, prec):
+    return int(L.lib().vesnet_farfield_workspace_bytes(P, M, prec, None))
+
+
+@functools.lru_cache(maxsize=256)
+def _backward_workspace_bytes(P, M, prec):
+    return int(L.lib().vesnet_backward_workspace_bytes(P, M, prec))
+
+
+@functools.lru_cache(maxsize=256)
+def _backward_points_workspace_bytes(P, M, prec):
+    return int(L.lib().vesnet_backward_points_workspace_bytes(P, M, prec))
 
 
 def _workspace(nbytes, device):
@@ -104,12 +124,14 @@ def farfield_forward(targets, sources, force_density, arc_weights, partition, mu
     """Forward sum without autograd; returns out (2, P) float64."""
     part = as_partition(partition)
     P, M = part.n_points, part.n_vesicles
-    for n, t in (("targets", targets), ("sources", sources), ("force_density", force_density)):
-        _check_vec(n, t, P)
+    _check_vec("targets", targets, P)
+    if sources is not targets:
+        _check_vec("sources", sources, P)
+    _check_vec("force_density", force_density, P)
     _check_w(arc_weights, P)
     prec = L.precision_code(precision)
     if out is None:
-        out = torch.empty((2, P), dtype=torch.float64, device=targets.device)
+        out = targets.new_empty((2, P))
     need = workspace_bytes(P, M, prec, config)
     if workspace is None or workspace.numel() < need:
         workspace = _workspace(need, targets.device)
@@ -311,7 +333,7 @@ def farfield_backward(targets, sources, force_density, arc_weights, partition, m
     gs = torch.empty((2, P), dtype=torch.float64, device=dev) if need[1] else None
     gf = torch.empty((2, P), dtype=torch.float64, device=dev) if need[2] else None
     gw = torch.empty((P,), dtype=torch.float64, device=dev) if need[3] else None
-    ws = _workspace(L.lib().vesnet_backward_workspace_bytes(P, M, prec), dev)
+    ws = _workspace(_backward_workspace_bytes(P, M, prec), dev)
     L.check(L.lib().vesnet_farfield_stokeslet_backward(
         _ptr(targets), _ptr(sources), _ptr(force_density), _ptr(arc_weights), _ptr(part.device), M, P, float(mu),
         _ptr(grad_out), _ptr(gt), _ptr(gs), _ptr(gf), _ptr(gw), prec, _ptr(ws), ws.numel(), _stream()))
@@ -330,7 +352,7 @@ def farfield_backward_points(points, force_density, arc_weights, partition, mu, 
     gx = torch.empty((2, P), dtype=torch.float64, device=dev) if need[0] else None
     gf = torch.empty((2, P), dtype=torch.float64, device=dev) if need[1] else None
     gw = torch.empty((P,), dtype=torch.float64, device=dev) if need[2] else None
-    ws = _workspace(L.lib().vesnet_backward_points_workspace_bytes(P, M, prec), dev)
+    ws = _workspace(_backward_points_workspace_bytes(P, M, prec), dev)
     L.check(L.lib().vesnet_farfield_stokeslet_backward_points(
         _ptr(points), _ptr(force_density), _ptr(arc_weights), _ptr(part.device), M, P, float(mu), _ptr(grad_out),
         _ptr(gx), _ptr(gf), _ptr(gw), prec, _ptr(ws), ws.numel(), _stream()))
