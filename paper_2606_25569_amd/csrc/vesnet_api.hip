@@ -397,8 +397,9 @@ namespace {
 
 // Evaluation from a prepared workspace with a resolved shape; symmetric selects the form that
 // evaluates each unordered pair once (targets must be the prepared sources).
+// (in: the compensated symmetric form prepares the region itself.)
 int evaluate_resolved(const double* targets, int32_t M, int32_t P, double mu, double* out, int prec, const Shape& s,
-                      bool symmetric, void* ws, size_t ws_bytes, void* stream) {
+                      bool symmetric, const SymmetricInput* in, void* ws, size_t ws_bytes, void* stream) {
   int rc;
   if ((rc = check_workspace(ws, ws_bytes, forward_bytes(P, M, prec, s)))) return rc;
   char* cur = aligned_base(ws);
@@ -408,7 +409,7 @@ int evaluate_resolved(const double* targets, int32_t M, int32_t P, double mu, do
   if (symmetric) {
     if (s.pair != 2 && s.splits > 1) cur += align_up((size_t)2 * s.splits * P * sizeof(double));
     e = prec == P64 ? launch_forward_symmetric64(s.symT, s.symNs, P, M, pv, carve_symmetric64(cur, P), scale, out, stream)
-                    : launch_forward_symmetric(s.symT, s.symNs, P, M, pv, carve_symmetric(cur, P, M), scale, out, stream);
+                    : launch_forward_symmetric(s.symT, s.symNs, P, M, pv, carve_symmetric(cur, P, M), in, scale, out, stream);
     if (e != hipSuccess) return hip_fail(e, "symmetric forward launch");
   } else {
     double* partial = s.splits > 1 ? reinterpret_cast<double*>(cur) : nullptr;
@@ -417,6 +418,23 @@ int evaluate_resolved(const double* targets, int32_t M, int32_t P, double mu, do
     if (e != hipSuccess) return hip_fail(e, "forward launch");
   }
   return ok();
+}
+
+// Preparation and evaluation of checked arguments with a resolved shape (automatic: not the caller's).
+int forward_resolved(const double* targets, const double* sources, const double* f, const double* w, const int32_t* off,
+                     int32_t M, int32_t P, double mu, double* out, int prec, const Shape& s, bool symmetric,
+                     bool automatic, void* ws, size_t ws_bytes, void* stream) {
+  if (automatic && !symmetric && takes_small(P, M, prec)) {
+    hipError_t e = launch_forward_small(prec, s.splits, targets, sources, f, w, off, M, P, 1.0 / (4.0 * kPi * mu), out,
+                                        stream);
+    if (e != hipSuccess) return hip_fail(e, "forward launch");
+    return ok();
+  }
+  const SymmetricInput in{sources, f, w, nullptr, off};
+  if (symmetric && prec == P32C) return evaluate_resolved(targets, M, P, mu, out, prec, s, true, &in, ws, ws_bytes, stream);
+  int rc;
+  if ((rc = vesnet_farfield_prepare(sources, f, w, off, M, P, prec, ws, ws_bytes, stream))) return rc;
+  return evaluate_resolved(targets, M, P, mu, out, prec, s, symmetric, nullptr, ws, ws_bytes, stream);
 }
 
 }  // namespace
@@ -431,7 +449,7 @@ extern "C" int vesnet_farfield_evaluate(const double* targets, const int32_t* of
   if (!out) return fail(VESNET_ERR_INVALID_ARGUMENT, "out is NULL");
   Shape s;
   if ((rc = resolve_shape(cfg, P, M, prec, &s))) return rc;
-  return evaluate_resolved(targets, M, P, mu, out, prec, s, s.pair == 2, ws, ws_bytes, stream);
+  return evaluate_resolved(targets, M, P, mu, out, prec, s, s.pair == 2, nullptr, ws, ws_bytes, stream);
 }
 
 extern "C" int vesnet_farfield_stokeslet(const double* targets, const double* sources, const double* f,
@@ -450,14 +468,7 @@ extern "C" int vesnet_farfield_stokeslet(const double* targets, const double* so
   const bool symmetric =
       s.pair == 2 || (s.pair == 0 && targets == sources && has_symmetric(prec) && s.accumulate == 1 && s.symT > 0);
   if ((rc = check_workspace(ws, ws_bytes, forward_bytes(P, M, prec, s)))) return rc;
-  if (!cfg && !symmetric && takes_small(P, M, prec)) {
-    hipError_t e = launch_forward_small(prec, s.splits, targets, sources, f, w, off, M, P, 1.0 / (4.0 * kPi * mu), out,
-                                        stream);
-    if (e != hipSuccess) return hip_fail(e, "forward launch");
-    return ok();
-  }
-  if ((rc = vesnet_farfield_prepare(sources, f, w, off, M, P, prec, ws, ws_bytes, stream))) return rc;
-  return evaluate_resolved(targets, M, P, mu, out, prec, s, symmetric, ws, ws_bytes, stream);
+  return forward_resolved(targets, sources, f, w, off, M, P, mu, out, prec, s, symmetric, !cfg, ws, ws_bytes, stream);
 }
 
 // ============================================================================ membrane force
@@ -1177,11 +1188,9 @@ extern "C" int vesnet_farfield_stokeslet_backward_points(const double* points, c
     PreparedView pvG = carve_prepared(cur, P, M, prec, true);
     SymmetricView sv = carve_symmetric(cur, P, M);
     double* gx = grad_points ? grad_points : reinterpret_cast<double*>(cur);
-    e = launch_prepare(prec, points, f, w, off, M, P, pvF, stream);
-    if (e == hipSuccess) e = launch_prepare(prec, points, gout, nullptr, off, M, P, pvG, stream);
-    if (e != hipSuccess) return hip_fail(e, "backward prepare launch");
-    e = launch_backward_symmetric(symT, sym_strips(P, M, symT, 4096), P, M, pvF, pvG, sv, reinterpret_cast<double*>(sv.acc), f, w, scale, gx,
-                                  grad_f, grad_w, stream);
+    const SymmetricInput in{points, f, w, gout, off};
+    e = launch_backward_symmetric(symT, sym_strips(P, M, symT, 4096), P, M, pvF, pvG, sv,
+                                  reinterpret_cast<double*>(sv.acc), in, scale, gx, grad_f, grad_w, stream);
     if (e != hipSuccess) return hip_fail(e, "symmetric backward launch");
     return ok();
   }
@@ -1378,6 +1387,5 @@ extern "C" int vesnet_farfield_stokeslet_noalloc(const double* targets, const do
                 P, M, need, cap);
   void* ws = nullptr;
   if ((rc = scratch_on_current_device(&ws))) return rc;
-  if ((rc = vesnet_farfield_prepare(sources, f, w, off, M, P, prec, ws, cap, stream))) return rc;
-  return evaluate_resolved(targets, M, P, mu, out, prec, s, symmetric, ws, cap, stream);
+  return forward_resolved(targets, sources, f, w, off, M, P, mu, out, prec, s, symmetric, !cfg, ws, cap, stream);
 }

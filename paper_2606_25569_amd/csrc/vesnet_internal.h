@@ -221,8 +221,14 @@ int64_t sym_max_blocks(int P, int M, int T);
 int64_t sym_units(int64_t nb);
 // whether the unit count of the symmetric form at T targets per thread fits one launch (2^31 - 1)
 bool sym_fits(int P, int M, int T);
+// What the compensated symmetric launches prepare themselves (g: the adjoint's velocity gradient).
+struct SymmetricInput {
+  const double *pts, *f, *w, *g;
+  const int32_t* off;
+};
+// in: the arrays, prepared by the launch itself; null for a region prepared before.
 hipError_t launch_forward_symmetric(int T, int ns, int P, int M, const PreparedView& pv, const SymmetricView& sv,
-                                    double scale, double* out, void* stream);
+                                    const SymmetricInput* in, double scale, double* out, void* stream);
 // The float64 symmetric form, T = 1 .. 4: blocks of 256 T points, each block pair cut into ns strips of columns
 // (ns divides 16; ns times the unordered block pairs must fit one launch).
 int64_t sym64_blocks(int64_t P, int T);
@@ -247,9 +253,8 @@ hipError_t launch_add_f64(double* a, const double* b, int64_t n, void* stream);
 // Its adjoint for targets = sources: pvF prepared from (points, f, w), pvG from (points, dL/du, no
 // weights); vsum is a [2][P] float64 scratch; grad_points is required, grad_f and grad_w may be null.
 hipError_t launch_backward_symmetric(int T, int ns, int P, int M, const PreparedView& pvF, const PreparedView& pvG,
-                                     const SymmetricView& sv, double* vsum, const double* f, const double* w,
-                                     double scale, double* grad_points, double* grad_f, double* grad_w,
-                                     void* stream);
+                                     const SymmetricView& sv, double* vsum, const SymmetricInput& in, double scale,
+                                     double* grad_points, double* grad_f, double* grad_w, void* stream);
 // The same in float64 (T = 1 .. 4, ns column strips per block pair) from the arrays themselves.
 hipError_t launch_backward_symmetric64(int T, int ns, int P, int M, const double* X, const double* f, const double* w,
                                        const int32_t* off, const double* gout, const Adjoint64View& av, double scale,

@@ -97,6 +97,15 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   return x;
 }
 
+// Fixed-point exponent of partial sums bounded by 520 sum |F|_1 (see k_sym_plan).
+__device__ __forceinline__ int sym_exponent(double fsum) {
+  const double bound = 520.0 * fsum;
+  if (!(bound > 0.0 && isfinite(bound))) return 0;
+  int e;
+  frexp(bound, &e);  // bound < 2^e
+  return 62 - e;
+}
+
 // Plan: the cycle table of every vesicle in point order, the number of blocks and the
 // fixed-point exponent.  One workgroup of 1024 threads; everything in a fixed order.
 __global__ __launch_bounds__(1024) void k_sym_plan(const int2* __restrict__ vrange, const double2* __restrict__ vaux,
@@ -176,6 +185,93 @@ __global__ __launch_bounds__(256) void k_sym_cycles(const int4* __restrict__ cyc
       sy += F.y;
     }
     fcyc[c] = make_double2(sx, sy);
+  }
+}
+
+// k_prepare, k_sym_plan and k_sym_cycles of up to kSymFused vesicles in one launch, a wavefront per vesicle, which
+// counts the cycles of the vesicles before it itself: the same values in the same order, but for the fixed-point
+// exponent, which the units form (meta[1] is not written).  zero0 and zero1 (or null): 2 P words cleared.  kAdjoint:
+// also the records of g, and the cycle sums are those of g; else of F = w f.
+// 504 x 32: three launches -> one, 104.4 -> 99.9 us a call; 512 x 64 and its adjoint: nine -> two, 932 -> 914 us.
+constexpr int kSymFused = 1024;
+
+template <bool kAdjoint>
+__global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ pts, const double* __restrict__ f,
+                                                    const double* __restrict__ w, const double* __restrict__ g,
+                                                    const int32_t* __restrict__ off, int M, int P, int cb, int ncyc_max,
+                                                    double4* __restrict__ vtab, double2* __restrict__ vaux,
+                                                    float4* __restrict__ recF, float4* __restrict__ recG,
+                                                    int4* __restrict__ cyc, double2* __restrict__ ccyc,
+                                                    int32_t* __restrict__ meta, unsigned long long* __restrict__ zero0,
+                                                    unsigned long long* __restrict__ zero1) {
+  __shared__ double2 carried[64];
+  const int lane = threadIdx.x, v = blockIdx.x;
+  const auto clamped = [&](int u) { return min(max(off[u], 0), P); };
+  for (int64_t e = (int64_t)v * 64 + lane; e < 2 * (int64_t)P; e += (int64_t)M * 64) {
+    zero0[e] = 0ull;
+    if (zero1) zero1[e] = 0ull;
+  }
+  int first = 0;  // cycles of the vesicles before
+  for (int u = lane; u < v; u += 64) first += (max(0, clamped(u + 1) - clamped(u)) + kRing - 1) / kRing;
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) first += __shfl_xor(first, m, 64);
+  const int j0 = clamped(v), j1 = max(j0, clamped(v + 1)), n = j1 - j0;
+  double sx = 0.0, sy = 0.0, bx = 0.0, by = 0.0, sa = 0.0;
+  for (int j = j0 + lane; j < j1; j += 64) {
+    const double wj = w[j];
+    sx += pts[j];
+    sy += pts[P + j];
+    const double ex = wj * f[j], ey = wj * f[P + j];
+    bx += ex;
+    by += ey;
+    sa += fabs(ex) + fabs(ey);
+  }
+  sx = wave_sum_d(sx);
+  sy = wave_sum_d(sy);
+  bx = wave_sum_d(bx);
+  by = wave_sum_d(by);
+  sa = wave_sum_d(sa);
+  const double cx = n > 0 ? sx / n : 0.0, cy = n > 0 ? sy / n : 0.0;
+  double r2 = 0.0;
+  for (int c0 = j0; c0 < j1; c0 += 64) {
+    const int j = c0 + lane;
+    wave_sync();  // the previous points are done
+    if (j < j1) {
+      const double wj = w[j];
+      const double x = pts[j], y = pts[P + j];
+      const double ex = wj * f[j], ey = wj * f[P + j];
+      r2 = fmax(r2, (x - cx) * (x - cx) + (y - cy) * (y - cy));
+      recF[j] = make_float4((float)(x - cx), (float)(y - cy), (float)ex, (float)ey);
+      if constexpr (kAdjoint) {
+        const double gx = g[j], gy = g[P + j];
+        recG[j] = make_float4((float)(x - cx), (float)(y - cy), (float)gx, (float)gy);
+        carried[lane] = make_double2(gx, gy);
+      } else {
+        carried[lane] = make_double2(ex, ey);
+      }
+    }
+    wave_sync();
+    const int k0 = c0 + kRing * lane, cnt = min(kRing, j1 - k0), e = first + (k0 - j0) / kRing;
+    if (lane < 64 / kRing && cnt > 0 && e < ncyc_max) {
+      double tx = 0.0, ty = 0.0;
+      for (int m = 0; m < cnt; ++m) {
+        const double2 F = carried[kRing * lane + m];
+        tx += F.x;
+        ty += F.y;
+      }
+      cyc[e] = make_int4(k0, cnt, v, 0);
+      ccyc[e] = make_double2(tx, ty);
+    }
+  }
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) r2 = fmax(r2, __shfl_xor(r2, m, 64));
+  if (lane != 0) return;
+  vtab[v] = make_double4(cx, cy, bx, by);
+  vaux[v] = make_double2(sa, r2);
+  if (v == M - 1) {
+    const int ncyc = min(first + (n + kRing - 1) / kRing, ncyc_max);
+    meta[0] = ncyc;
+    meta[2] = (ncyc + cb - 1) / cb;
   }
 }
 
@@ -483,15 +579,35 @@ __device__ __forceinline__ void sym_eval_unit(int P, const double4* __restrict__
   }
 }
 
-// One unit {bx, by} per workgroup (see the file header).
-template <int T>
+// The fixed-point exponent (see k_sym_plan) from the vesicles' sums of |F|_1, by a whole workgroup of kSymThreads.
+__device__ __forceinline__ int vesicles_exponent(const double2* __restrict__ vaux, int M) {
+  __shared__ double s_sum[kSymWaves];
+  double a = 0.0;
+  for (int v = threadIdx.x; v < M; v += kSymThreads) a += vaux[v].x;
+  a = wave_sum_d(a);
+  if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = a;
+  __syncthreads();
+  double tot = 0.0;
+#pragma unroll
+  for (int k = 0; k < kSymWaves; ++k) tot += s_sum[k];
+  return sym_exponent(tot);
+}
+
+// One unit {bx, by} per workgroup (see the file header).  kFused: after k_sym_prepare of M vesicles.
+template <int T, bool kFused>
 __global__ __launch_bounds__(kSymThreads) void k_sym_main(
     int P, int ns, const double4* __restrict__ vtab, const double2* __restrict__ vaux, const float4* __restrict__ rec,
-    const int4* __restrict__ cyc, const double2* __restrict__ fcyc, const int32_t* __restrict__ meta,
-    unsigned long long* __restrict__ acc) {
+    const int4* __restrict__ cyc, const double2* __restrict__ fcyc,
+    std::conditional_t<kFused, int32_t, const int32_t>* __restrict__ meta, int M, unsigned long long* __restrict__ acc) {
   constexpr int CB = kRows * T;
   const int ncyc = meta[0];
-  const int S = meta[1];
+  int S;
+  if constexpr (kFused) {
+    S = vesicles_exponent(vaux, M);
+    if (blockIdx.x == 0 && threadIdx.x == 0) meta[1] = S;  // for k_sym_finish
+  } else {
+    S = meta[1];
+  }
   const int nb = meta[2];
   if (nb <= 0) return;
   int bx, by, s0, s1;
@@ -560,15 +676,6 @@ __device__ __forceinline__ void fixed_add2(unsigned long long* __restrict__ a, u
   const double r = x - ldexp(h, -S);  // exact
   atomicAdd(a, (unsigned long long)(long long)h);
   atomicAdd(a + two_p, (unsigned long long)(long long)rint(ldexp(r, S + kLoBits)));
-}
-
-// Fixed-point exponent of partial sums bounded by 520 sum |F|_1 (see k_sym_plan).
-__device__ __forceinline__ int sym_exponent(double fsum) {
-  const double bound = 520.0 * fsum;
-  if (!(bound > 0.0 && isfinite(bound))) return 0;
-  int e;
-  frexp(bound, &e);  // bound < 2^e
-  return 62 - e;
 }
 
 // Start of a float64 call: the accumulator words and marks cleared and the log table built (every workgroup a
@@ -1776,22 +1883,38 @@ int64_t sym_units(int64_t nb) {
 
 bool sym_fits(int P, int M, int T) { return sym_units(sym_max_blocks(P, M, T)) <= (int64_t)INT32_MAX; }
 
+// Above this many vesicles the counting of those before (M^2 / 2 offsets) and the units' sums of M bounds would cost
+// more than the launches they save.
+bool sym_fused(int M) { return M <= kSymFused; }
+
 hipError_t launch_backward_symmetric(int T, int ns, int P, int M, const PreparedView& pvF, const PreparedView& pvG,
-                                     const SymmetricView& sv, double* vsum, const double* f, const double* w,
+                                     const SymmetricView& sv, double* vsum, const SymmetricInput& in,
                                      double scale, double* grad_points, double* grad_f, double* grad_w,
                                      void* stream) {
   if (P == 0) return hipSuccess;
   if (!grad_points || !vsum) return hipErrorInvalidValue;
+  const double* f = in.f;
+  const double* w = in.w;
   hipStream_t st = Sx_(stream);
   const int cb = sym_cycles_per_block(T);
   const int ncyc_max = (int)sym_max_cycles(P, M);
   const int nb_max = (int)sym_max_blocks(P, M, T);
-  hipLaunchKernelGGL(k_sym_plan, dim3(1), dim3(1024), 0, st, pvF.vrange, pvF.vaux, M, cb, ncyc_max, sv.cyc, sv.meta);
-  const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
-  // cycle sums of g (its float64 copy is the f64 array of the g-prepared region)
-  hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pvG.f64, P, sv.fcyc, sv.acc);
-  hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, grad_points, 2 * (int64_t)P);
-  hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, vsum, 2 * (int64_t)P);
+  if (sym_fused(M)) {
+    hipLaunchKernelGGL(k_sym_prepare<true>, dim3(M), dim3(64), 0, st, in.pts, f, w, in.g, in.off, M, P, cb, ncyc_max,
+                       pvF.vtab, pvF.vaux, static_cast<float4*>(pvF.rec), static_cast<float4*>(pvG.rec), sv.cyc, sv.fcyc,
+                       sv.meta, reinterpret_cast<unsigned long long*>(grad_points),
+                       reinterpret_cast<unsigned long long*>(vsum));
+  } else {
+    hipError_t e = launch_prepare(P32C, in.pts, f, w, in.off, M, P, pvF, stream);
+    if (e == hipSuccess) e = launch_prepare(P32C, in.pts, in.g, nullptr, in.off, M, P, pvG, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_sym_plan, dim3(1), dim3(1024), 0, st, pvF.vrange, pvF.vaux, M, cb, ncyc_max, sv.cyc, sv.meta);
+    const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
+    // cycle sums of g (its float64 copy is the f64 array of the g-prepared region)
+    hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pvG.f64, P, sv.fcyc, sv.acc);
+    hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, grad_points, 2 * (int64_t)P);
+    hipLaunchKernelGGL(k_zero_f64, dim3(cgrid), dim3(256), 0, st, vsum, 2 * (int64_t)P);
+  }
   const dim3 grid((unsigned)(sym_units(nb_max) * ns));
   const float4* recF = static_cast<const float4*>(pvF.rec);
   const float4* recG = static_cast<const float4*>(pvG.rec);
@@ -1977,22 +2100,37 @@ hipError_t launch_forward_symmetric64(int T, int ns, int P, int M, const Prepare
 }
 
 hipError_t launch_forward_symmetric(int T, int ns, int P, int M, const PreparedView& pv, const SymmetricView& sv,
-                                    double scale, double* out, void* stream) {
+                                    const SymmetricInput* in, double scale, double* out, void* stream) {
   if (P == 0) return hipSuccess;
   hipStream_t st = Sx_(stream);
   const int cb = sym_cycles_per_block(T);
   const int ncyc_max = (int)sym_max_cycles(P, M);
   const int nb_max = (int)sym_max_blocks(P, M, T);
-  hipLaunchKernelGGL(k_sym_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, M, cb, ncyc_max, sv.cyc, sv.meta);
-  const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pv.f64, P, sv.fcyc, sv.acc);
+  const bool fused = in != nullptr && sym_fused(M);
+  if (fused) {
+    hipLaunchKernelGGL(k_sym_prepare<false>, dim3(M), dim3(64), 0, st, in->pts, in->f, in->w, nullptr, in->off, M, P, cb,
+                       ncyc_max, pv.vtab, pv.vaux, static_cast<float4*>(pv.rec), nullptr, sv.cyc, sv.fcyc, sv.meta, sv.acc,
+                       nullptr);
+  } else {
+    if (in != nullptr) {
+      const hipError_t e = launch_prepare(P32C, in->pts, in->f, in->w, in->off, M, P, pv, stream);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_sym_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, M, cb, ncyc_max, sv.cyc, sv.meta);
+    const int cgrid = (int)std::min<int64_t>((2 * (int64_t)P + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_sym_cycles, dim3(cgrid), dim3(256), 0, st, sv.cyc, sv.meta, pv.f64, P, sv.fcyc, sv.acc);
+  }
   const dim3 grid((unsigned)(sym_units(nb_max) * ns));
   const float4* rec = static_cast<const float4*>(pv.rec);
   switch (T) {
 #define VESNET_SYM_CASE(TT)                                                                                    \
   case TT:                                                                                                     \
-    hipLaunchKernelGGL(k_sym_main<TT>, grid, dim3(kSymThreads), 0, st, P, ns, pv.vtab, pv.vaux, rec, sv.cyc,   \
-                       sv.fcyc, sv.meta, sv.acc);                                                               \
+    if (fused)                                                                                                 \
+      hipLaunchKernelGGL((k_sym_main<TT, true>), grid, dim3(kSymThreads), 0, st, P, ns, pv.vtab, pv.vaux, rec, \
+                         sv.cyc, sv.fcyc, sv.meta, M, sv.acc);                                                 \
+    else                                                                                                       \
+      hipLaunchKernelGGL((k_sym_main<TT, false>), grid, dim3(kSymThreads), 0, st, P, ns, pv.vtab, pv.vaux,     \
+                         rec, sv.cyc, sv.fcyc, sv.meta, M, sv.acc);                                            \
     break;
     VESNET_SYM_CASE(1) VESNET_SYM_CASE(2) VESNET_SYM_CASE(3) VESNET_SYM_CASE(4) VESNET_SYM_CASE(8)
 #undef VESNET_SYM_CASE
