@@ -15,7 +15,7 @@
 // level l = 2..L, the interaction list of its level-l ancestor (children of the parent's 3 x 3
 // neighbourhood not adjacent to the ancestor) through the expansions, and the 3 x 3 leaves around its own
 // directly, skipping its own vesicle; own-vesicle sources outside those leaves, which the expansions
-// included, are subtracted exactly (k_tc_own).  Everything is FP64.
+// included, are subtracted exactly (own_terms).  Everything is FP64.
 //
 // Treecode: every target evaluates the series of every box of its lists (k_tc_eval); the
 // evaluation merges the conj-F log series and Psi into one series D, and writes w conj(Phi) as
@@ -176,7 +176,7 @@ __device__ __forceinline__ int wave_group_add(bool ok, int key, int32_t* __restr
   return pos;
 }
 
-// Leaf of every point and leaf occupancy in the first `pblocks` workgroups; vesicle id of every point in the others, one
+// Leaf of every point and leaf occupancy in the first `pblocks` workgroups, which also clear the output; vesicle id of every point in the others, one
 // workgroup per vesicle, which writes its index over its range (offsets clamped).
 // With h2 given, also the squared near-field radius h_v^2 of every vesicle, h_v = sum_j w_j / N_v (the
 // mean arclength spacing, summed in a fixed order), and bit 1 of *flag when h_v exceeds the leaf width
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kTB) void k_tc_leaf(const double* __restrict__ X, i
                                                  int32_t* __restrict__ leafid, int32_t* __restrict__ counts,
                                                  const int32_t* __restrict__ off, int32_t* __restrict__ vid,
                                                  const double* __restrict__ w, double* __restrict__ h2,
-                                                 int32_t* __restrict__ flag) {
+                                                 int32_t* __restrict__ flag, double* __restrict__ out) {
   __shared__ Geom root;
   __shared__ double red[kTB];
   const bool points = (int)blockIdx.x < pblocks;
@@ -219,6 +219,7 @@ __global__ __launch_bounds__(kTB) void k_tc_leaf(const double* __restrict__ X, i
         }
         leaf = ix * n + iy;
         leafid[j] = leaf;
+        out[j] = out[P + j] = 0.0;
       }
       wave_group_add(ok, leaf, counts);
     }
@@ -492,7 +493,111 @@ __device__ __forceinline__ double pair_sums(double lo, double hi, int lane) {
   }
 }
 
+__device__ __forceinline__ void direct_term(double zx, double zy, double sx, double sy, double Fx, double Fy,
+                                            const double2* __restrict__ ltab, double& ux, double& uy) {
+  const double rx = zx - sx, ry = zy - sy;
+  const double q = rx * rx + ry * ry;
+  const double lg = -0.5 * log_reduced(q, ltab);
+  const double s = (rx * Fx + ry * Fy) * recip(q);
+  ux = fma(lg, Fx, fma(s, rx, ux));
+  uy = fma(lg, Fy, fma(s, ry, uy));
+}
+
+// Own-vesicle sources outside the 3 x 3 leaves around a target are in the expansions: their direct terms, to be
+// subtracted.  A wavefront takes 64 consecutive targets of a vesicle and the vesicle's points 64 at a time.
+// Neighbouring points share a leaf, so a chunk is a few runs of one leaf each: the first pass finds the runs, and each
+// lane tests the runs and lists its far stretches of points (6% of the pairs at 2000 x 128, none for most vesicles of
+// a shallow tree: then the chunk's records are not read at all).  The lanes' stretches are then evaluated side by side,
+// as many steps as the longest list (38 us at 2000 x 128 with every lane testing every point, 21 by runs).  out of the
+// wavefront's targets is written, -scale times their sum, where any of them has such terms.
+constexpr int kOwnChunk = 64;
+struct OwnLds {
+  double2 ltab[kLogTab];
+  double sx[kOwnChunk], sy[kOwnChunk], sfx[kOwnChunk], sfy[kOwnChunk];
+  int32_t run0[kOwnChunk + 1], runl[kOwnChunk];  // first point and leaf of every run
+  uint16_t lst[kOwnChunk / 2 + 1][64];           // lst[k][lane]: its k-th far stretch, begin | end << 8
+};
+
+__device__ void own_terms(OwnLds& m, const double* __restrict__ X, const double* __restrict__ f,
+                          const double* __restrict__ w, int P, int v0, int v1, int t0,
+                          const int32_t* __restrict__ leafid, int depth, double scale, double* __restrict__ out) {
+  const int t = threadIdx.x & 63;
+  const int mask = (1 << depth) - 1;
+  const int i = t0 + t;
+  const bool act = i < v1;
+  const int li = leafid[act ? i : v0];
+  const int ix = li >> depth, iy = li & mask;
+  double zx = 0.0, zy = 0.0, ux = 0.0, uy = 0.0;
+  bool any = false;  // the table and the targets are there
+  for (int c0 = v0; c0 < v1; c0 += kOwnChunk) {
+    const int cnt = min(kOwnChunk, v1 - c0);
+    const int leaf = leafid[c0 + min(t, cnt - 1)];
+    const int before = __shfl_up(leaf, 1);
+    const bool head = t < cnt && (t == 0 || leaf != before);
+    const unsigned long long hm = __ballot(head);
+    const int nrun = __popcll(hm);
+    wave_sync();  // the previous chunk is done
+    if (head) {
+      const int at = __popcll(hm & ((1ull << t) - 1ull));
+      m.run0[at] = t;
+      m.runl[at] = leaf;
+    }
+    if (t == 0) m.run0[nrun] = cnt;
+    wave_sync();
+    int nf = 0, ns = 0, end = -1, begin = 0;  // far points and stretches; the open stretch
+    for (int r = 0; r < nrun; ++r) {
+      const int lr = m.runl[r], b = m.run0[r], e = m.run0[r + 1];
+      if (abs((lr >> depth) - ix) <= 1 && abs((lr & mask) - iy) <= 1) continue;
+      nf += e - b;
+      if (b != end) {
+        if (end > 0) m.lst[ns++][t] = (uint16_t)(begin | end << 8);
+        begin = b;
+      }
+      end = e;
+    }
+    if (end > 0) m.lst[ns++][t] = (uint16_t)(begin | end << 8);
+    if (!act) nf = 0;
+    if (!__any(nf > 0)) continue;
+    if (!any) {
+      m.ltab[t] = log_tab_entry(t);
+      const int ii = act ? i : v0;
+      zx = X[ii];
+      zy = X[P + ii];
+      any = true;
+    }
+    if (t < cnt) {
+      const int j = c0 + t;
+      m.sx[t] = X[j];
+      m.sy[t] = X[P + j];
+      m.sfx[t] = w[j] * f[j];
+      m.sfy[t] = w[j] * f[P + j];
+    }
+    wave_sync();
+    int most = nf;  // longest list of the wavefront
+    for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
+    int q = 0, qe = 0, s = 0;
+    for (int k = 0; k < most; ++k) {
+      if (k < nf) {
+        if (q == qe) {
+          const int se = m.lst[s++][t];
+          q = se & 255;
+          qe = se >> 8;
+        }
+        direct_term(zx, zy, m.sx[q], m.sy[q], m.sfx[q], m.sfy[q], m.ltab, ux, uy);
+        ++q;
+      }
+    }
+  }
+  if (act && any) {
+    out[i] = -(ux * scale);
+    out[P + i] = -(uy * scale);
+  }
+}
+
 // Moments of the leaves, and of their parents where pmom is given: one workgroup per parent box, a wavefront per leaf.
+// The workgroups after the nleaf / 4 of the moments form the own-vesicle terms, two wavefronts per vesicle: as a launch
+// of its own that pass took 21 us at 2000 x 128 (here 17 more than the moments alone) and its start and end another
+// 2 to 4; whole calls 343.5 -> 340.7 us there, near step of 2000 x 32 386.3 -> 381.8.
 // A leaf's points go eight at a time: lane (b, g) = (lane mod 8, lane / 8) takes point g and the K consecutive orders
 // K b .. K b + K - 1 of the 8 K >= p + 1, whose first power it forms from zeta^K in three select-multiplies, and adds
 // the products of Re zeta^k and Im zeta^k with (F_x, F_y) and conj(zeta) F = (G_x, G_y) to its eight real sums per
@@ -501,15 +606,38 @@ __device__ __forceinline__ double pair_sums(double lo, double hi, int lane) {
 // 2000 x 128, order 30: this and the coarser levels 69 -> 37 us (before: powers by 32 lanes through LDS, three LDS
 // reads per point and order; a launch per level whose binomials and powers were serial chains).
 template <int K>
-__global__ __launch_bounds__(256) void k_tc_p2m(const double4* __restrict__ srec, const int32_t* __restrict__ starts,
+__global__ __launch_bounds__(256, K <= 4 ? 4 : 2) void k_tc_p2m(const double4* __restrict__ srec, const int32_t* __restrict__ starts,
                                                 const Geom* __restrict__ geom, int depth, int p,
                                                 double2* __restrict__ mom, int32_t* __restrict__ bcount,
-                                                double2* __restrict__ pmom, int32_t* __restrict__ pcount) {
-  __shared__ double sums[4][8][8 * K];  // each wavefront's eight sums; then its operands and translated rows
-  __shared__ double2 pw[4][8 * K];
-  __shared__ int32_t cnt[4];
+                                                double2* __restrict__ pmom, int32_t* __restrict__ pcount,
+                                                const double* __restrict__ X, const double* __restrict__ f,
+                                                const double* __restrict__ w, int P, const int32_t* __restrict__ off, int M,
+                                                const int32_t* __restrict__ leafid, double scale,
+                                                double* __restrict__ out) {
+  struct MomentLds {
+    double sums[4][8][8 * K];  // each wavefront's eight sums; then its operands and translated rows
+    double2 pw[4][8 * K];
+    int32_t cnt[4];
+  };
+  __shared__ union Lds {
+    MomentLds moments;
+    OwnLds own[4];
+    __device__ Lds() {}
+  } lds;
+  auto& sums = lds.moments.sums;
+  auto& pw = lds.moments.pw;
+  auto& cnt = lds.moments.cnt;
   static_assert(Recentre<K>::kLds == 8 * 8 * K, "the sums and the operands share LDS");
   const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int own = (int)blockIdx.x - (1 << (2 * depth - 2));
+  if (own >= 0) {
+    const int v = 2 * own + (q >> 1);
+    if (v >= M) return;
+    const int v0 = clamp_i(off[v], 0, P), v1 = max(v0, clamp_i(off[v + 1], 0, P));  // offsets never trusted
+    for (int t0 = v0 + 64 * (q & 1); t0 < v1; t0 += 128)
+      own_terms(lds.own[q], X, f, w, P, v0, v1, t0, leafid, depth, scale, out);
+    return;
+  }
   const int b = lane & 7, g = lane >> 3;
   const int n = 1 << depth, box = blockIdx.x;
   const int lx = 2 * (box >> (depth - 1)) + (q >> 1), ly = 2 * (box & (n / 2 - 1)) + (q & 1);
@@ -1046,16 +1174,6 @@ __device__ __forceinline__ int leaf_of_item(const int32_t* __restrict__ wstart, 
   return lo;
 }
 
-__device__ __forceinline__ void direct_term(double zx, double zy, double sx, double sy, double Fx, double Fy,
-                                            const double2* __restrict__ ltab, double& ux, double& uy) {
-  const double rx = zx - sx, ry = zy - sy;
-  const double q = rx * rx + ry * ry;
-  const double lg = -0.5 * log_reduced(q, ltab);
-  const double s = (rx * Fx + ry * Fy) * recip(q);
-  ux = fma(lg, Fx, fma(s, rx, ux));
-  uy = fma(lg, Fy, fma(s, ry, uy));
-}
-
 // ---------------------------------------------------------------- fast multipole evaluation
 //
 // One wavefront per (leaf, chunk of 16 of its points), four to a workgroup, which share the 1024-entry log table:
@@ -1197,8 +1315,8 @@ __global__ __launch_bounds__(64 * kFmmWaves) void k_fmm_eval(const double4* __re
       uy[k] += __shfl_xor(uy[k], o);
     }
     if (grp == 0 && base + tl + kFmmLanes * k < s1) {
-      out[ti[k]] = ux[k] * scale;
-      out[P + ti[k]] = uy[k] * scale;
+      out[ti[k]] += ux[k] * scale;  // to the own-vesicle terms
+      out[P + ti[k]] += uy[k] * scale;
     }
   }
 }
@@ -1401,115 +1519,9 @@ __global__ __launch_bounds__(64 * kTreeWaves) void k_tc_eval(const double4* __re
 #pragma unroll
   for (int k = 0; k < kTreeT; ++k)
     if (base + tl + lanes * k < s1) {
-      out[ti[k]] = ux[k] * scale;
-      out[P + ti[k]] = uy[k] * scale;
+      out[ti[k]] += ux[k] * scale;  // to the own-vesicle terms
+      out[P + ti[k]] += uy[k] * scale;
     }
-}
-
-// Own-vesicle sources outside the 3 x 3 leaves around a target were in the expansions: their direct terms
-// are subtracted from the finished velocity.  One workgroup of two wavefronts per vesicle, targets 128 at a
-// time, the vesicle's points in chunks.  Neighbouring points share a leaf, so a chunk is a few runs of one leaf each:
-// the first pass finds the runs, and each lane tests the runs and lists its far stretches of points (6% of the pairs
-// at 2000 x 128, none for most vesicles of a shallow tree: then the chunk's records are not read at all).  Each
-// wavefront then evaluates its lanes' stretches side by side, as many steps as its longest list.
-// 2000 x 128: 38 -> 21 us (before: every point of the chunk was tested by every lane).
-constexpr int kOwnChunk = 128;
-constexpr int kOwnThreads = 128;
-
-__global__ __launch_bounds__(kOwnThreads) void k_tc_own(const double* __restrict__ X, const double* __restrict__ f,
-                                                        const double* __restrict__ w, int P,
-                                                        const int32_t* __restrict__ off,
-                                                        const int32_t* __restrict__ leafid, int depth, double scale,
-                                                        double* __restrict__ out) {
-  __shared__ double sx_[kOwnChunk], sy_[kOwnChunk], sfx[kOwnChunk], sfy[kOwnChunk];
-  __shared__ int32_t sl[kOwnChunk];
-  __shared__ int32_t run0[kOwnChunk + 1], runl[kOwnChunk];  // first point and leaf of every run
-  __shared__ uint16_t lst[kOwnChunk / 2 + 1][kOwnThreads];  // lst[k][thread]: its k-th far stretch, begin | end << 8
-  __shared__ double2 ltab[kLogTab];
-  __shared__ int heads[kOwnThreads / 64];  // runs that begin in each wavefront's part
-  const int v = blockIdx.x;
-  const int v0 = clamp_i(off[v], 0, P), v1 = max(v0, clamp_i(off[v + 1], 0, P));  // offsets never trusted
-  if (v1 - v0 < 2) return;
-  const int t = threadIdx.x;
-  const int mask = (1 << depth) - 1;
-  bool table = false;  // ltab is filled
-  for (int t0 = v0; t0 < v1; t0 += kOwnThreads) {
-    const int i = t0 + t;
-    const bool act = i < v1;
-    const int li = leafid[act ? i : v0];
-    const int ix = li >> depth, iy = li & mask;
-    double zx = 0.0, zy = 0.0, ux = 0.0, uy = 0.0;
-    bool any = false;
-    for (int c0 = v0; c0 < v1; c0 += kOwnChunk) {
-      const int cnt = min(kOwnChunk, v1 - c0);
-      __syncthreads();  // the previous chunk is done
-      if (t < cnt) sl[t] = leafid[c0 + t];
-      __syncthreads();
-      const bool head = t < cnt && (t == 0 || sl[t] != sl[t - 1]);
-      const unsigned long long hm = __ballot(head);
-      if ((t & 63) == 0) heads[t >> 6] = __popcll(hm);
-      __syncthreads();
-      int at = __popcll(hm & ((1ull << (t & 63)) - 1ull)), nrun = 0;
-      for (int q = 0; q < kOwnThreads / 64; ++q) {
-        if (q < t >> 6) at += heads[q];
-        nrun += heads[q];
-      }
-      if (head) {
-        run0[at] = t;
-        runl[at] = sl[t];
-      }
-      if (t == 0) run0[nrun] = cnt;
-      __syncthreads();
-      int nf = 0, ns = 0, end = -1, begin = 0;  // far points and stretches; the open stretch
-      for (int r = 0; r < nrun; ++r) {
-        const int lr = runl[r], b = run0[r], e = run0[r + 1];
-        if (abs((lr >> depth) - ix) <= 1 && abs((lr & mask) - iy) <= 1) continue;
-        nf += e - b;
-        if (b != end) {
-          if (end > 0) lst[ns++][t] = (uint16_t)(begin | end << 8);
-          begin = b;
-        }
-        end = e;
-      }
-      if (end > 0) lst[ns++][t] = (uint16_t)(begin | end << 8);
-      if (!act) nf = 0;
-      if (!__syncthreads_or(nf)) continue;
-      if (!table && t < kLogTab) ltab[t] = log_tab_entry(t);
-      table = true;
-      if (t < cnt) {
-        const int j = c0 + t;
-        sx_[t] = X[j];
-        sy_[t] = X[P + j];
-        sfx[t] = w[j] * f[j];
-        sfy[t] = w[j] * f[P + j];
-      }
-      if (!any) {
-        const int ii = act ? i : v0;
-        zx = X[ii];
-        zy = X[P + ii];
-        any = true;
-      }
-      __syncthreads();
-      int most = nf;  // longest list of the wavefront
-      for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
-      int q = 0, qe = 0, s = 0;
-      for (int k = 0; k < most; ++k) {
-        if (k < nf) {
-          if (q == qe) {
-            const int se = lst[s++][t];
-            q = se & 255;
-            qe = se >> 8;
-          }
-          direct_term(zx, zy, sx_[q], sy_[q], sfx[q], sfy[q], ltab, ux, uy);
-          ++q;
-        }
-      }
-    }
-    if (act && any) {
-      out[i] -= ux * scale;
-      out[P + i] -= uy * scale;
-    }
-  }
 }
 
 // Near-field masking of Algorithm 4 on the fast multipole result: vesicle v (not the target's own) is near
@@ -1824,20 +1836,21 @@ TreeRun tree_run(void* ws, const TreeLayout& t, int depth, int p) {
 // Tree over the points (root square, leaves, leaf order) and the moments of every box of levels
 // 2..depth (leaves from the points, coarser levels by translation).
 void launch_upward(const double* X, const double* f, const double* w, const int32_t* off, int M, int P, int p,
-                   int depth, int cshift, bool fmm, int32_t* count, const TreeRun& r, hipStream_t st) {
+                   int depth, int cshift, bool fmm, int32_t* count, double scale, double* out, const TreeRun& r,
+                   hipStream_t st) {
   const int nleaf = 1 << (2 * depth);
   const int pb = (P + kTB - 1) / kTB < 4096 ? (P + kTB - 1) / kTB : 4096;
   const int bb = (P + kTB - 1) / kTB < kBBoxBlocks ? (P + kTB - 1) / kTB : kBBoxBlocks;
   hipLaunchKernelGGL(k_tc_bbox_partial, dim3(bb), dim3(kTB), 0, st, X, P, r.part, fmm ? r.ltab : nullptr, r.counts,
                      r.cursor, nleaf, count, r.flag);
   hipLaunchKernelGGL(k_tc_leaf, dim3(pb + M), dim3(kTB), 0, st, X, P, r.part, bb, pb, depth, r.geom, r.leafid, r.counts,
-                     off, r.vid, w, count ? r.h2 : nullptr, r.flag);
+                     off, r.vid, w, count ? r.h2 : nullptr, r.flag, out);
   hipLaunchKernelGGL(k_tc_scan, dim3(1), dim3(1024), 0, st, r.counts, nleaf, r.starts, r.wstart, cshift);
   hipLaunchKernelGGL(k_tc_scatter, dim3(pb), dim3(kTB), 0, st, r.leafid, P, r.starts, r.cursor, r.perm);
   hipLaunchKernelGGL(k_tc_sort, dim3(nleaf), dim3(64), 0, st, X, f, w, P, r.vid, r.starts, r.perm, r.srec, r.svid);
   if (depth < 2) return;
   const bool up = depth > 2;
-  const dim3 pg(nleaf / 4), pbl(256);
+  const dim3 pg(nleaf / 4 + (M + 1) / 2), pbl(256);
   double2* pmom = up ? r.mom + r.lv.mom[depth - 1] : nullptr;
   int32_t* pcount = up ? r.bcount + r.lv.box[depth - 1] : nullptr;
   // The leaves and their parents, then the coarser levels, two to a launch: one box of the upper level has four below,
@@ -1846,7 +1859,7 @@ void launch_upward(const double* X, const double* f, const double* w, const int3
 #define VESNET_UP(K)                                                                                                \
   case K:                                                                                                           \
     hipLaunchKernelGGL(k_tc_p2m<K>, pg, pbl, 0, st, r.srec, r.starts, r.geom, depth, p, r.mom + r.lv.mom[depth],    \
-                       r.bcount + r.lv.box[depth], pmom, pcount);                                                   \
+                       r.bcount + r.lv.box[depth], pmom, pcount, X, f, w, P, off, M, r.leafid, scale, out);         \
     for (int l = depth - 2, to; l >= 2; l = to - 1) {                                                               \
       to = l > 2 ? l - 1 : 2;                                                                                       \
       hipLaunchKernelGGL(k_tc_m2m<K>, dim3(1 << (2 * to)), dim3(l > to ? 64 * up_waves(K) : 256), 0, st, r.geom, l, to, \
@@ -1862,13 +1875,6 @@ void launch_upward(const double* X, const double* f, const double* w, const int3
 // Work items of an evaluation: a bound on sum over leaves of ceil(count / 2^shift).
 int eval_items(int P, int depth, int shift) { return (1 << (2 * depth)) + ((P + (1 << shift) - 1) >> shift); }
 
-// Own-vesicle correction; without expansions (depth < 2) every own-vesicle source is in the 3 x 3 leaves.
-void launch_own(const double* X, const double* f, const double* w, const int32_t* off, int M, int P, int depth,
-                double scale, const TreeRun& r, double* out, hipStream_t st) {
-  if (depth >= 2)
-    hipLaunchKernelGGL(k_tc_own, dim3(M), dim3(kOwnThreads), 0, st, X, f, w, P, off, r.leafid, depth, scale, out);
-}
-
 }  // namespace
 
 // Everything is built on the device; the launches need no host copy and no synchronisation.
@@ -1878,7 +1884,7 @@ hipError_t launch_treecode(const double* X, const double* f, const double* w, co
   if (depth < 0 || depth > kMaxDepth || p < 1 || p > kMaxOrder) return hipErrorInvalidValue;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, false), depth, p);
-  launch_upward(X, f, w, off, M, P, p, depth, kTreeChunkShift, false, nullptr, r, st);
+  launch_upward(X, f, w, off, M, P, p, depth, kTreeChunkShift, false, nullptr, scale, out, r, st);
   if (depth >= 2) {
     const size_t work = r.nbox * (p + 1);
     const int gb = (int)((work + kTB - 1) / kTB < 4096 ? (work + kTB - 1) / kTB : 4096);
@@ -1894,7 +1900,6 @@ hipError_t launch_treecode(const double* X, const double* f, const double* w, co
   else
     hipLaunchKernelGGL(k_tc_eval<12>, grid, block, per * max_groups, st, r.srec, r.svid, P, r.perm, r.starts, r.wstart,
                        r.geom, depth, p, r.mom, r.bcount, scale, max_groups, out);
-  launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   return hipGetLastError();
 }
 
@@ -1902,7 +1907,7 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
                           double scale, int p, int depth, double* out, void* ws, hipStream_t st, bool near,
                           int32_t* pairs, int capacity, int32_t* count) {
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, true, near ? M : 0), depth, p);
-  launch_upward(X, f, w, off, M, P, p, depth, kFmmChunkShift, true, near ? count : nullptr, r, st);
+  launch_upward(X, f, w, off, M, P, p, depth, kFmmChunkShift, true, near ? count : nullptr, scale, out, r, st);
   if (depth >= 2) {
     const dim3 g((unsigned)r.nbox), bl(64);
     const size_t lds = m2l_lds_bytes(p);
@@ -1928,7 +1933,6 @@ static hipError_t run_fmm(const double* X, const double* f, const double* w, con
   const int items = eval_items(P, depth, kFmmChunkShift);
   hipLaunchKernelGGL(k_fmm_eval, dim3((items + kFmmWaves - 1) / kFmmWaves), dim3(64 * kFmmWaves), 0, st, r.srec, r.svid,
                      P, r.perm, r.starts, r.wstart, r.geom, depth, p, r.loc, r.ltab, scale, out);
-  launch_own(X, f, w, off, M, P, depth, scale, r, out, st);
   if (near) {
     hipLaunchKernelGGL(k_fmm_near, dim3((items + kNearWaves - 1) / kNearWaves), dim3(64 * kNearWaves), 0, st, X, f, w, P, M, off, r.srec, r.svid, r.perm, r.starts,
                        r.wstart, depth, r.h2, scale, out, pairs, capacity, count, r.flag);
