@@ -244,42 +244,64 @@ __global__ __launch_bounds__(kTB) void k_tc_leaf(const double* __restrict__ X, i
   }
 }
 
-// Exclusive scans of the leaf occupancies (starts) and of their chunks of 2^cshift targets (wave starts).
+// Exclusive scans of the leaf occupancies (starts) and of their chunks of 2^cshift targets (wave starts), by one
+// workgroup: 4,096 leaves at a time, four consecutive ones a thread, each wavefront's sums by shuffles and the sixteen
+// wavefronts' through LDS.  Latency bounds it: depth 6 6.8 -> 4.8 us, depth 7 34 -> 7.2 (before: every thread walked its
+// leaves one by one, ten rounds of two barriers).
 __global__ __launch_bounds__(1024) void k_tc_scan(const int32_t* __restrict__ counts, int nleaf,
                                                   int32_t* __restrict__ starts, int32_t* __restrict__ wstart,
                                                   int cshift) {
-  __shared__ int32_t sa[1024];
-  __shared__ int32_t sb[1024];
-  const int t = threadIdx.x;
-  const int seg = (nleaf + 1023) / 1024;
-  const int b0 = min(t * seg, nleaf), b1 = min(b0 + seg, nleaf);
-  int32_t a = 0, b = 0;
-  for (int i = b0; i < b1; ++i) {
-    a += counts[i];
-    b += (counts[i] + (1 << cshift) - 1) >> cshift;
-  }
-  const int32_t own_a = a, own_b = b;
-  sa[t] = a;
-  sb[t] = b;
-  __syncthreads();
-  for (int d = 1; d < 1024; d <<= 1) {  // inclusive scan of the segment sums (Hillis-Steele)
-    const int32_t xa = t >= d ? sa[t - d] : 0, xb = t >= d ? sb[t - d] : 0;
+  __shared__ int2 total[2][16];  // of the wavefronts, alternating between passes
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int up = (1 << cshift) - 1;
+  const auto load = [&](int i) {
+    if (i + 4 <= nleaf) return *reinterpret_cast<const int4*>(counts + i);
+    return make_int4(i < nleaf ? counts[i] : 0, i + 1 < nleaf ? counts[i + 1] : 0, i + 2 < nleaf ? counts[i + 2] : 0, 0);
+  };
+  const auto store = [&](int32_t* __restrict__ to, int i, int first, int x, int y, int z) {
+    const int4 v = make_int4(first, first + x, first + x + y, first + x + y + z);
+    if (i + 4 <= nleaf) {
+      *reinterpret_cast<int4*>(to + i) = v;
+    } else {
+      if (i < nleaf) to[i] = v.x;
+      if (i + 1 < nleaf) to[i + 1] = v.y;
+      if (i + 2 < nleaf) to[i + 2] = v.z;
+    }
+  };
+  int a0 = 0, b0 = 0;  // sums of the earlier passes
+  int4 next = load(4 * t);
+  for (int base = 0, pass = 0; base < nleaf; base += 4096, pass ^= 1) {
+    const int4 c = next;
+    next = load(base + 4096 + 4 * t);
+    const int4 d = make_int4((c.x + up) >> cshift, (c.y + up) >> cshift, (c.z + up) >> cshift, (c.w + up) >> cshift);
+    const int own_a = c.x + c.y + c.z + c.w, own_b = d.x + d.y + d.z + d.w;
+    int a = own_a, b = own_b;
+    for (int o = 1; o < 64; o <<= 1) {  // inclusive over the wavefront
+      const int xa = __shfl_up(a, o), xb = __shfl_up(b, o);
+      if (lane >= o) {
+        a += xa;
+        b += xb;
+      }
+    }
+    if (lane == 63) total[pass][wave] = make_int2(a, b);
     __syncthreads();
-    sa[t] += xa;
-    sb[t] += xb;
-    __syncthreads();
+    int ea = a0 + a - own_a, eb = b0 + b - own_b;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int2 w = total[pass][q];
+      if (q < wave) {
+        ea += w.x;
+        eb += w.y;
+      }
+      a0 += w.x;
+      b0 += w.y;
+    }
+    store(starts, base + 4 * t, ea, c.x, c.y, c.z);
+    store(wstart, base + 4 * t, eb, d.x, d.y, d.z);
   }
-  if (t == 1023) {
-    starts[nleaf] = sa[t];
-    wstart[nleaf] = sb[t];
-  }
-  a = sa[t] - own_a;  // exclusive
-  b = sb[t] - own_b;
-  for (int i = b0; i < b1; ++i) {
-    starts[i] = a;
-    wstart[i] = b;
-    a += counts[i];
-    b += (counts[i] + (1 << cshift) - 1) >> cshift;
+  if (t == 0) {
+    starts[nleaf] = a0;
+    wstart[nleaf] = b0;
   }
 }
 
@@ -313,6 +335,8 @@ __global__ __launch_bounds__(64) void k_tc_sort(const double* __restrict__ X, co
   }
   for (int a = threadIdx.x; a < n; a += 64) {
     const int32_t j = sort ? key[a] : perm[s0 + a];
+    const double4 rec = make_double4(X[j], X[P + j], w[j] * f[j], w[j] * f[P + j]);  // on its way during the ranking
+    const int32_t id = vid[j];
     int slot = s0 + a;
     if (sort) {
       int rank = 0;
@@ -320,8 +344,8 @@ __global__ __launch_bounds__(64) void k_tc_sort(const double* __restrict__ X, co
       slot = s0 + rank;
       perm[slot] = j;
     }
-    srec[slot] = make_double4(X[j], X[P + j], w[j] * f[j], w[j] * f[P + j]);
-    svid[slot] = vid[j];
+    srec[slot] = rec;
+    svid[slot] = id;
   }
 }
 
