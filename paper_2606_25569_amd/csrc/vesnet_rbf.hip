@@ -20,8 +20,10 @@
 // reads L_JJ) and L_IJ = T_IJ W^T.  The two right-hand sides are carried through the panels, y_J = W (u_J - sum_k
 // L_Jk y_k), and the back substitution L^T c = y takes c_J = W_JJ^T (y_J - sum_{I>J} L_IJ^T c_I).  The rows are padded
 // to a multiple of 32 with an identity block, which leaves the factor and the solution unchanged.
-// What bounds it: 2000 x 32 moves 0.84 GB of tiles (the slots of 2000 vesicles do not fit the caches) at 5 TB/s; with
-// fewer or longer vesicles it is the latency of a panel, about 40 us at 128 points.  2000 x 32: 294 -> 180 us; 48 x 32:
+// What bounds it: at 2000 x 32, two wavefronts per SIMD, issue (19,375 VALU instructions and 736 FP64 matrix
+// instructions each, about 45% and 24% of the time) and what of the serial pivots' latency the other wavefront leaves
+// uncovered; a fifth less tile traffic changed nothing.  With fewer or longer vesicles it is the latency of a panel,
+// about 40 us at 128 points.  2000 x 32: 294 -> 171 us; 48 x 32:
 // 149 -> 82 us; 500 x 128: 4.22 -> 0.72 ms; 200 x 200: 13.6 -> 1.31 ms (before: layer-major order, every lower tile,
 // row-major tiles staged through LDS, 32-row pivots by lane reads).
 //

@@ -1752,7 +1752,7 @@ __global__ __launch_bounds__(64 * kNearWaves, 5) void k_fmm_near(const double* _
   }
 }
 
-// The list's status: a negative count when the masking could not be completed (see k_fmm_near and k_tc_vid).
+// The list's status: a negative count when the masking could not be completed (see k_fmm_near and k_tc_leaf).
 __global__ __launch_bounds__(64) void k_fmm_near_status(const int32_t* __restrict__ flag, int32_t* __restrict__ count) {
   if (threadIdx.x != 0) return;
   const int32_t fl = *flag;
