@@ -618,6 +618,29 @@ __device__ void own_terms(OwnLds& m, const double* __restrict__ X, const double*
   }
 }
 
+// The treecode's last form of a box's rows, once the box is translated to its parent: row 3 = M_k[F] / k (k >= 1) for
+// the log series of F, and row 2 = D_k, the coefficients of t^(k+1) in (S[conj F] - Psi) / 2:
+// D_k = (M_{k+1}[conj F] / (k+1) - M_k[conj(zeta) F]) / 2, D_p = -M_p[conj(zeta) F] / 2.  The evaluation then needs three
+// series instead of four.  Lane k brings row entries k; every lane of the wavefront takes part.
+__device__ __forceinline__ void finish_box(double2* __restrict__ mb, double2 m0, double2 m1, double2 m2, int p, int k) {
+  const double2 b = make_double2(__shfl_down(m1.x, 1), __shfl_down(m1.y, 1));
+  if (k > p) return;
+  double2 d = make_double2(-0.5 * m2.x, -0.5 * m2.y);
+  if (k < p) {
+    const double ik = 0.5 / (double)(k + 1);
+    d.x = fma(b.x, ik, d.x);
+    d.y = fma(b.y, ik, d.y);
+  }
+  mb[2 * (p + 1) + k] = d;
+  mb[3 * (p + 1) + k] = k == 0 ? make_double2(0.0, 0.0) : make_double2(m0.x / (double)k, m0.y / (double)k);
+}
+
+// The same for a box whose rows are in memory.
+__device__ __forceinline__ void finish_stored_box(double2* __restrict__ mb, int p, int k) {
+  const int at = min(k, p);
+  finish_box(mb, mb[at], mb[p + 1 + at], mb[2 * (p + 1) + at], p, k);
+}
+
 // Moments of the leaves, and of their parents where pmom is given: one workgroup per parent box, a wavefront per leaf.
 // The workgroups after the nleaf / 4 of the moments form the own-vesicle terms, two wavefronts per vesicle: as a launch
 // of its own that pass took 21 us at 2000 x 128 (here 17 more than the moments alone) and its start and end another
@@ -633,7 +656,7 @@ template <int K>
 __global__ __launch_bounds__(256, K <= 4 ? 4 : 2) void k_tc_p2m(const double4* __restrict__ srec, const int32_t* __restrict__ starts,
                                                 const Geom* __restrict__ geom, int depth, int p,
                                                 double2* __restrict__ mom, int32_t* __restrict__ bcount,
-                                                double2* __restrict__ pmom, int32_t* __restrict__ pcount,
+                                                double2* __restrict__ pmom, int32_t* __restrict__ pcount, bool finish,
                                                 const double* __restrict__ X, const double* __restrict__ f,
                                                 const double* __restrict__ w, int P, const int32_t* __restrict__ off, int M,
                                                 const int32_t* __restrict__ leafid, double scale,
@@ -729,8 +752,9 @@ __global__ __launch_bounds__(256, K <= 4 ? 4 : 2) void k_tc_p2m(const double4* _
     double2* mb = mom + (size_t)leaf * 4 * (p + 1);
     mb[lane] = m0;
     mb[p + 1 + lane] = m1;
-    mb[2 * (p + 1) + lane] = m2;
+    if (!finish) mb[2 * (p + 1) + lane] = m2;
   }
+  if (finish) finish_box(mom + (size_t)leaf * 4 * (p + 1), m0, m1, m2, p, lane);
   if (lane == 0) bcount[leaf] = cnt[q] = s1 - s0;
   if (pmom == nullptr) return;
   wave_sync();
@@ -739,16 +763,22 @@ __global__ __launch_bounds__(256, K <= 4 ? 4 : 2) void k_tc_p2m(const double4* _
   double2* pm = pmom + (size_t)box * 4 * (p + 1);
   for (int e = threadIdx.x; e < 3 * (p + 1); e += 256) pm[e] = children_sum(&sums[0][0][0], Recentre<K>::kLds, p, half, e);
   if (threadIdx.x == 0) pcount[box] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  if (finish && depth == 3) {  // the parents are the coarsest boxes
+    __syncthreads();
+    if (q == 0) finish_stored_box(pm, p, lane);
+  }
 }
 
 // Moments of the levels from `from` up to `to` (from >= to >= 2) from those of level from + 1: one workgroup per box of
-// level `to` works through its boxes of every level, a wavefront per child, four for a box.  Latency bounds it, about
+// level `to` works through its boxes of every level, a wavefront per child, four for a box, which also brings the child
+// to the treecode's last form where `finish` is given (as a launch of its own that took 5 us).  Latency bounds it, about
 // 3 us for sixteen children.
 constexpr int up_waves(int K) { return K < 7 ? 16 : 8; }  // K = 7 needs more than 128 registers
 
 template <int K>
 __global__ __launch_bounds__(64 * up_waves(K)) void k_tc_m2m(const Geom* __restrict__ geom, int from, int to, int p,
-                                                          double2* __restrict__ mom, int32_t* __restrict__ bcount) {
+                                                          double2* __restrict__ mom, int32_t* __restrict__ bcount,
+                                                          bool finish) {
   __shared__ double x[up_waves(K)][Recentre<K>::kLds];
   __shared__ double2 pw[4][8 * K];
   __shared__ int32_t cnt[up_waves(K)];
@@ -777,6 +807,7 @@ __global__ __launch_bounds__(64 * up_waves(K)) void k_tc_m2m(const Geom* __restr
           m1 = mb[p + 1 + lane];
           m2 = mb[2 * (p + 1) + lane];
         }
+        if (finish) finish_box(mom + cb * stride, m0, m1, m2, p, lane);
         if (lane == 0) cnt[wave] = bcount[cb];
         up.run(m0, m1, m2, delta, turn, pw[q], x[wave]);
       }
@@ -792,29 +823,8 @@ __global__ __launch_bounds__(64 * up_waves(K)) void k_tc_m2m(const Geom* __restr
       __syncthreads();  // LDS is free, and this level's boxes are written
     }
   }
-}
-
-// After all translations: row 3 = M_k[F] / k (k >= 1) for the log series of F, and row 2 = D_k, the
-// coefficients of t^(k+1) in (S[conj F] - Psi) / 2: D_k = (M_{k+1}[conj F] / (k+1) - M_k[conj(zeta) F]) / 2,
-// D_p = -M_p[conj(zeta) F] / 2.  The evaluation then needs three series instead of four.
-__global__ __launch_bounds__(kTB) void k_tc_finalize(double2* __restrict__ mom, size_t nbox, int p) {
-  const size_t stride = 4 * (size_t)(p + 1);
-  for (size_t e = (size_t)blockIdx.x * kTB + threadIdx.x; e < nbox * (p + 1); e += (size_t)gridDim.x * kTB) {
-    const size_t box = e / (p + 1);
-    const int k = (int)(e - box * (p + 1));
-    double2* mb = mom + box * stride;
-    const double2 a = mb[k];
-    mb[3 * (p + 1) + k] = k == 0 ? make_double2(0.0, 0.0) : make_double2(a.x / (double)k, a.y / (double)k);
-    const double2 psi = mb[2 * (p + 1) + k];
-    double2 d = make_double2(-0.5 * psi.x, -0.5 * psi.y);
-    if (k < p) {
-      const double2 b = mb[(p + 1) + k + 1];
-      const double ik = 0.5 / (double)(k + 1);
-      d.x = fma(b.x, ik, d.x);
-      d.y = fma(b.y, ik, d.y);
-    }
-    mb[2 * (p + 1) + k] = d;
-  }
+  if (finish && to == 2 && wave == 0)  // no level above: this workgroup's box is finished here
+    finish_stored_box(mom + (level_box_base(2) + blockIdx.x) * stride, p, lane);
 }
 
 // ---------------------------------------------------------------- fast multipole translations
@@ -1883,11 +1893,11 @@ void launch_upward(const double* X, const double* f, const double* w, const int3
 #define VESNET_UP(K)                                                                                                \
   case K:                                                                                                           \
     hipLaunchKernelGGL(k_tc_p2m<K>, pg, pbl, 0, st, r.srec, r.starts, r.geom, depth, p, r.mom + r.lv.mom[depth],    \
-                       r.bcount + r.lv.box[depth], pmom, pcount, X, f, w, P, off, M, r.leafid, scale, out);         \
+                       r.bcount + r.lv.box[depth], pmom, pcount, !fmm, X, f, w, P, off, M, r.leafid, scale, out);   \
     for (int l = depth - 2, to; l >= 2; l = to - 1) {                                                               \
       to = l > 2 ? l - 1 : 2;                                                                                       \
       hipLaunchKernelGGL(k_tc_m2m<K>, dim3(1 << (2 * to)), dim3(l > to ? 64 * up_waves(K) : 256), 0, st, r.geom, l, to, \
-                         p, r.mom, r.bcount);                                                                       \
+                         p, r.mom, r.bcount, !fmm);                                                                 \
     }                                                                                                               \
     break;
   switch ((p + 8) / 8) {  // orders per lane: ceil((p + 1) / 8)
@@ -1909,11 +1919,6 @@ hipError_t launch_treecode(const double* X, const double* f, const double* w, co
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const TreeRun r = tree_run(ws, tree_layout(P, depth, p, false), depth, p);
   launch_upward(X, f, w, off, M, P, p, depth, kTreeChunkShift, false, nullptr, scale, out, r, st);
-  if (depth >= 2) {
-    const size_t work = r.nbox * (p + 1);
-    const int gb = (int)((work + kTB - 1) / kTB < 4096 ? (work + kTB - 1) / kTB : 4096);
-    hipLaunchKernelGGL(k_tc_finalize, dim3(gb), dim3(kTB), 0, st, r.mom, r.nbox, p);
-  }
   // groups whose boxes fit 48 KB: all eight up to order 31, five at 48
   const size_t per = sizeof(double2) * (size_t)kTreeWaves * 3 * (p + 1);
   const int max_groups = (size_t)kTreeMaxGroups * per <= 49152 ? kTreeMaxGroups : (int)(49152 / per);
