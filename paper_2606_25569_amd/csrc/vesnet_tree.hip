@@ -90,11 +90,11 @@ __device__ constexpr Binomials kBinomials{};
 // counters, and with count given the near-field list's count and status.
 __global__ __launch_bounds__(kTB) void k_tc_bbox_partial(const double* __restrict__ X, int P,
                                                          double* __restrict__ part, double2* __restrict__ tab,
-                                                         int32_t* __restrict__ counts, int32_t* __restrict__ cursor,
+                                                         int32_t* __restrict__ counts,
                                                          int nleaf, int32_t* __restrict__ count,
                                                          int32_t* __restrict__ flag) {
   __shared__ double red[4][kTB];
-  for (int e = blockIdx.x * kTB + threadIdx.x; e < nleaf; e += gridDim.x * kTB) counts[e] = cursor[e] = 0;
+  for (int e = blockIdx.x * kTB + threadIdx.x; e < nleaf; e += gridDim.x * kTB) counts[e] = 0;
   if (count != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *count = *flag = 0;
   if (tab != nullptr)
     for (int e = blockIdx.x * kTB + threadIdx.x; e < kHalfLogTab; e += gridDim.x * kTB) tab[e] = half_log_entry(e);
@@ -156,28 +156,28 @@ __global__ __launch_bounds__(64) void k_tc_zero(int32_t* __restrict__ a) {
   if (threadIdx.x == 0) *a = 0;
 }
 
-// Within a wavefront, the lanes whose key equals the first pending lane's form a group: one atomic adds the
-// group's size to counter[key] and returns the group's base, and each lane takes base + its rank among the
-// group's lanes.  Consecutive points mostly share a leaf, so a wavefront needs a few atomics instead of 64.
+// Within a wavefront, the lanes of equal keys form a group: one atomic adds the group's size to counter[key] and returns
+// the group's base, and each lane takes base + its rank among the group's lanes.  Consecutive points mostly share a
+// leaf, so a wavefront needs a few atomics instead of 64; they are issued together.
 __device__ __forceinline__ int wave_group_add(bool ok, int key, int32_t* __restrict__ counter) {
   const int lane = threadIdx.x & 63;
-  unsigned long long todo = __ballot(ok);
-  int pos = 0;
+  unsigned long long todo = __ballot(ok), group = 0;
   while (todo) {
-    const int leader = __ffsll(todo) - 1;
-    const int lk = __shfl(key, leader);
+    const int lk = __shfl(key, __ffsll(todo) - 1);
     const unsigned long long same = __ballot(ok && key == lk);  // not yet placed: earlier groups had other keys
-    int base = 0;
-    if (lane == leader) base = atomicAdd(counter + lk, __popcll(same));
-    base = __shfl(base, leader);
-    if ((same >> lane) & 1ull) pos = base + __popcll(same & ((1ull << lane) - 1ull));
+    if ((same >> lane) & 1ull) group = same;
     todo &= ~same;
   }
-  return pos;
+  const int leader = __ffsll(group) - 1;
+  int base = 0;
+  if (ok && lane == leader) base = atomicAdd(counter + key, __popcll(group));
+  base = __shfl(base, max(leader, 0));
+  return base + __popcll(group & ((1ull << lane) - 1ull));
 }
 
-// Leaf of every point and leaf occupancy in the first `pblocks` workgroups, which also clear the output; vesicle id of every point in the others, one
-// workgroup per vesicle, which writes its index over its range (offsets clamped).
+// Leaf of every point, its place in the leaf and the leaf occupancies in the first `pblocks` workgroups, which also
+// clear the output; vesicle id of every point in the others, one workgroup per vesicle, which writes its index over its
+// range (offsets clamped).
 // With h2 given, also the squared near-field radius h_v^2 of every vesicle, h_v = sum_j w_j / N_v (the
 // mean arclength spacing, summed in a fixed order), and bit 1 of *flag when h_v exceeds the leaf width
 // (then a point within h_v of a target may lie outside its 3 x 3 leaves).
@@ -186,6 +186,7 @@ __device__ __forceinline__ int wave_group_add(bool ok, int key, int32_t* __restr
 __global__ __launch_bounds__(kTB) void k_tc_leaf(const double* __restrict__ X, int P, const double* __restrict__ part,
                                                  int nparts, int pblocks, int depth, Geom* __restrict__ geom,
                                                  int32_t* __restrict__ leafid, int32_t* __restrict__ counts,
+                                                 int32_t* __restrict__ place,
                                                  const int32_t* __restrict__ off, int32_t* __restrict__ vid,
                                                  const double* __restrict__ w, double* __restrict__ h2,
                                                  int32_t* __restrict__ flag, double* __restrict__ out) {
@@ -221,7 +222,8 @@ __global__ __launch_bounds__(kTB) void k_tc_leaf(const double* __restrict__ X, i
         leafid[j] = leaf;
         out[j] = out[P + j] = 0.0;
       }
-      wave_group_add(ok, leaf, counts);
+      const int at = wave_group_add(ok, leaf, counts);
+      if (ok) place[j] = at;
     }
     return;
   }
@@ -305,16 +307,11 @@ __global__ __launch_bounds__(1024) void k_tc_scan(const int32_t* __restrict__ co
   }
 }
 
+// Every point to its place in its leaf (the order of the atomics).
 __global__ __launch_bounds__(kTB) void k_tc_scatter(const int32_t* __restrict__ leafid, int P,
-                                                    const int32_t* __restrict__ starts, int32_t* __restrict__ cursor,
-                                                    int32_t* __restrict__ perm) {
-  for (int j0 = blockIdx.x * kTB; j0 < P; j0 += gridDim.x * kTB) {  // the same trip count for every lane
-    const int j = j0 + (int)threadIdx.x;
-    const bool ok = j < P;
-    const int leaf = ok ? leafid[j] : 0;
-    const int pos = wave_group_add(ok, leaf, cursor);
-    if (ok) perm[starts[leaf] + pos] = j;
-  }
+                                                    const int32_t* __restrict__ starts,
+                                                    const int32_t* __restrict__ place, int32_t* __restrict__ perm) {
+  for (int j = blockIdx.x * kTB + threadIdx.x; j < P; j += gridDim.x * kTB) perm[starts[leafid[j]] + place[j]] = j;
 }
 
 // Points of each leaf in ascending index order (deterministic sums).  One wavefront per leaf: the
@@ -1775,7 +1772,7 @@ __global__ __launch_bounds__(64) void k_fmm_near_status(const int32_t* __restric
 // Workspace layout shared by the size queries and the launchers; the fast multipole method adds the
 // local expansions (3 rows per box) and the binomial table.
 struct TreeLayout {
-  size_t geom, part, leafid, vid, perm, srec, svid, counts, cursor, starts, wstart, bcount, mom, loc, ltab, h2, flag,
+  size_t geom, part, leafid, vid, perm, srec, svid, counts, starts, wstart, bcount, mom, loc, ltab, h2, flag,
       total;
 };
 
@@ -1796,7 +1793,6 @@ static TreeLayout tree_layout(int P, int depth, int p, bool fmm, int near_M = 0)
   t.srec = o;       o += align_up(sizeof(double4) * (size_t)P);
   t.svid = o;       o += align_up(sizeof(int32_t) * (size_t)P);
   t.counts = o;     o += align_up(sizeof(int32_t) * nleaf);
-  t.cursor = o;     o += align_up(sizeof(int32_t) * nleaf);
   t.starts = o;     o += align_up(sizeof(int32_t) * (nleaf + 1));
   t.wstart = o;     o += align_up(sizeof(int32_t) * (nleaf + 1));
   t.bcount = o;     o += align_up(sizeof(int32_t) * (boxes > 0 ? boxes : 1));
@@ -1826,7 +1822,7 @@ namespace {
 struct TreeRun {
   Geom* geom;
   double* part;
-  int32_t *leafid, *vid, *perm, *counts, *cursor, *starts, *wstart, *bcount;
+  int32_t *leafid, *vid, *perm, *counts, *starts, *wstart, *bcount;
   double4* srec;   // records and vesicle ids in leaf order
   int32_t* svid;
   double2 *mom, *loc, *ltab;
@@ -1848,7 +1844,6 @@ TreeRun tree_run(void* ws, const TreeLayout& t, int depth, int p) {
   r.svid = reinterpret_cast<int32_t*>(base + t.svid);
   r.ltab = reinterpret_cast<double2*>(base + t.ltab);
   r.counts = reinterpret_cast<int32_t*>(base + t.counts);
-  r.cursor = reinterpret_cast<int32_t*>(base + t.cursor);
   r.starts = reinterpret_cast<int32_t*>(base + t.starts);
   r.wstart = reinterpret_cast<int32_t*>(base + t.wstart);
   r.bcount = reinterpret_cast<int32_t*>(base + t.bcount);
@@ -1876,11 +1871,11 @@ void launch_upward(const double* X, const double* f, const double* w, const int3
   const int pb = (P + kTB - 1) / kTB < 4096 ? (P + kTB - 1) / kTB : 4096;
   const int bb = (P + kTB - 1) / kTB < kBBoxBlocks ? (P + kTB - 1) / kTB : kBBoxBlocks;
   hipLaunchKernelGGL(k_tc_bbox_partial, dim3(bb), dim3(kTB), 0, st, X, P, r.part, fmm ? r.ltab : nullptr, r.counts,
-                     r.cursor, nleaf, count, r.flag);
+                     nleaf, count, r.flag);
   hipLaunchKernelGGL(k_tc_leaf, dim3(pb + M), dim3(kTB), 0, st, X, P, r.part, bb, pb, depth, r.geom, r.leafid, r.counts,
-                     off, r.vid, w, count ? r.h2 : nullptr, r.flag, out);
+                     r.svid /* places, until the sort */, off, r.vid, w, count ? r.h2 : nullptr, r.flag, out);
   hipLaunchKernelGGL(k_tc_scan, dim3(1), dim3(1024), 0, st, r.counts, nleaf, r.starts, r.wstart, cshift);
-  hipLaunchKernelGGL(k_tc_scatter, dim3(pb), dim3(kTB), 0, st, r.leafid, P, r.starts, r.cursor, r.perm);
+  hipLaunchKernelGGL(k_tc_scatter, dim3(pb), dim3(kTB), 0, st, r.leafid, P, r.starts, r.svid, r.perm);
   hipLaunchKernelGGL(k_tc_sort, dim3(nleaf), dim3(64), 0, st, X, f, w, P, r.vid, r.starts, r.perm, r.srec, r.svid);
   if (depth < 2) return;
   const bool up = depth > 2;
