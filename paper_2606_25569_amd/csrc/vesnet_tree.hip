@@ -621,6 +621,7 @@ __device__ void own_terms(OwnLds& m, const double* __restrict__ X, const double*
 // series instead of four.  Lane k brings row entries k; every lane of the wavefront takes part.
 __device__ __forceinline__ void finish_box(double2* __restrict__ mb, double2 m0, double2 m1, double2 m2, int p, int k) {
   const double2 b = make_double2(__shfl_down(m1.x, 1), __shfl_down(m1.y, 1));
+  asm volatile("" : "+v"(k));  // the reciprocals are formed here: kept across a caller's loop they spill
   if (k > p) return;
   double2 d = make_double2(-0.5 * m2.x, -0.5 * m2.y);
   if (k < p) {
