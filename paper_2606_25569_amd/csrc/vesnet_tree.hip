@@ -408,8 +408,10 @@ __device__ __forceinline__ double2 eighth_turn(int a) {
 // (and the conj(zeta) F row gains conj(d) times the translated F row: left to the sum over the children), by one
 // wavefront on the matrix cores: the triangle of binomials, which every box shares, stays in registers as the first
 // operand, and the six real columns of d^-m M_m (three rows, Re and Im) are the second.  For 8 K >= p + 1 orders.
-// d = delta e^(i pi a / 4), a = 1, 3, 5, 7, so its powers are real powers and eighths of a turn; the division by
-// delta^m is done in two halves, which keeps it finite wherever the moments are.
+// d = delta e^(i pi a / 4), a = 1, 3, 5, 7, so its powers are real powers and eighths of a turn.  The division by
+// delta^m takes the power of two of delta apart, which scales exactly, and the rest lies in [1/2, 1): the quotients
+// overflow only where the moments in units of the box do, and the orders above p, which hold zeros, cannot turn into
+// zero times infinity.
 // (On the vector units, a lane per order, the moments' broadcasts from LDS bounded it: 5.5 us for 64 boxes on a CU.)
 template <int K>
 struct Recentre {
@@ -441,13 +443,13 @@ struct Recentre {
   __device__ __forceinline__ void run(double2 m0, double2 m1, double2 m2, double delta, int turn,
                                       const double2* __restrict__ pw, double* __restrict__ x) const {
     if (lane < kOrders) {
-      const double inv = 1.0 / delta;
-      const double r1 = pow_int(inv, lane >> 1), r2 = pow_int(inv, lane - (lane >> 1));
+      int ex;
+      const double r = pow_int(1.0 / frexp(delta, &ex), lane);
       const double2 e = eighth_turn(-turn * lane);
       const auto put = [&](int c, double2 m) {
         const double2 t = cmul(m, e);
-        x[8 * lane + 2 * c] = t.x * r1 * r2;
-        x[8 * lane + 2 * c + 1] = t.y * r1 * r2;
+        x[8 * lane + 2 * c] = ldexp(t.x, -ex * lane) * r;
+        x[8 * lane + 2 * c + 1] = ldexp(t.y, -ex * lane) * r;
       };
       put(0, m0);
       put(1, m1);
@@ -1079,7 +1081,9 @@ __global__ __launch_bounds__(64, RT < 4 ? 2 : 1) void k_fmm_m2l(const Geom* __re
 // With e = c_leaf - c_anc: X_k += sum_{m>=k} C(m, k) e^(m-k) X_m for A, B, C, and B also -conj(e) times the
 // shifted C.  One wavefront per leaf, on the matrix cores: X_k = e^-k sum_m C(m, k) (e^m X_m), the triangle of binomials
 // the first operand (in registers, shared by all ancestors) and the e^m X_m of two ancestors, six real columns each,
-// the second.  For 8 K >= p + 1 orders.  Powers of e are real powers of |e| times powers of e / |e|.
+// the second.  For 8 K >= p + 1 orders.  Powers of e are real powers of |e| times powers of e / |e|; the power of two of
+// |e| is taken apart and scales exactly, the rest lies in [1/2, 1), so that no power overflows (the orders above p hold
+// zeros, and zero times infinity would spoil every order).
 // 2000 x 128, order 30: 25 -> 16.7 us (before: a lane per order, binomials and powers serial chains, three LDS reads
 // per term).
 constexpr int kShiftWaves = 4;
@@ -1118,6 +1122,7 @@ __global__ __launch_bounds__(64 * kShiftWaves) void k_fmm_l2l(const Geom* __rest
     for (int v = 0; v < 4; ++v) tot[rt][v] = 0.0;
   for (int l0 = 2; l0 < depth; l0 += 2) {
     double2 e[2];
+    int ex[2];  // |e| = (1/2 .. 1) 2^ex
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int l = l0 + h, sh = depth - l;
@@ -1133,15 +1138,16 @@ __global__ __launch_bounds__(64 * kShiftWaves) void k_fmm_l2l(const Geom* __rest
         v[2] = pa[2 * (p + 1)];
       }
       if (l == depth) e[h] = make_double2(1.0, 0.0);  // no ancestor: zero columns
+      const double r = sqrt(e[h].x * e[h].x + e[h].y * e[h].y), ri = 1.0 / r;
+      const double rf = frexp(r, &ex[h]);
       if (lane < kOrders) {
-        const double r = sqrt(e[h].x * e[h].x + e[h].y * e[h].y), ri = 1.0 / r;
         const double2 u = cpow_int(make_double2(e[h].x * ri, e[h].y * ri), lane);
-        const double rm = pow_int(r, lane), rk = pow_int(ri, lane);
+        const double rm = pow_int(rf, lane), rk = pow_int(1.0 / rf, lane);
         inv[wave][h][lane] = make_double2(u.x * rk, -(u.y * rk));
         const double2 em = make_double2(u.x * rm, u.y * rm);
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-          const double2 t = cmul(v[q], em);
+          const double2 t = cmul(make_double2(ldexp(v[q].x, ex[h] * lane), ldexp(v[q].y, ex[h] * lane)), em);
           x[kRow * lane + 8 * h + 2 * q] = t.x;
           x[kRow * lane + 8 * h + 2 * q + 1] = t.y;
         }
@@ -1159,6 +1165,7 @@ __global__ __launch_bounds__(64 * kShiftWaves) void k_fmm_l2l(const Geom* __rest
         if (s >= 4 * rt) acc[rt] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[rt][s], b, acc[rt], 0, 0, 0);
     }
     const double2 eh = (c & 8) ? e[1] : e[0];
+    const int exh = (c & 8) ? ex[1] : ex[0];
 #pragma unroll
     for (int rt = 0; rt < kTiles; ++rt)
 #pragma unroll
@@ -1166,7 +1173,7 @@ __global__ __launch_bounds__(64 * kShiftWaves) void k_fmm_l2l(const Geom* __rest
         const int k = 16 * rt + (lane >> 4) + 4 * v;
         const double2 ik = inv[wave][c >> 3][min(k, kOrders - 1)];
         const double mine = acc[rt][v], other = quad_swap(mine);  // Re and Im are neighbours
-        const double val = fma(mine, ik.x, (c & 1) ? other * ik.y : -(other * ik.y));
+        const double val = ldexp(fma(mine, ik.x, (c & 1) ? other * ik.y : -(other * ik.y)), -exh * k);
         const double cm = row_shift2(val), co = quad_swap(cm);  // for the lanes of B: C and its other part
         const double shc = fma(eh.x, cm, (c & 1) ? -(eh.y * co) : eh.y * co);  // conj(e) C
         tot[rt][v] += series == 1 ? val - shc : val;
