@@ -153,7 +153,9 @@ VESNET_API int vesnet_farfield_evaluate(const double* targets, const int32_t* ve
                              const vesnet_tile_config* cfg, void* workspace, size_t workspace_bytes,
                              void* stream);
 
-/* prepare + evaluate. */
+/* prepare + evaluate, in fewer launches where that is faster; the workspace holds
+   the prepared region afterwards either way, so that vesnet_farfield_evaluate can
+   follow at other targets. */
 VESNET_API int vesnet_farfield_stokeslet(const double* targets, const double* sources, const double* force_density,
                               const double* arc_weights, const int32_t* vesicle_offsets, int32_t n_vesicles,
                               int32_t n_points, double mu, double* out, int precision,

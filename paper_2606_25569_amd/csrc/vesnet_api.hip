@@ -420,13 +420,16 @@ int evaluate_resolved(const double* targets, int32_t M, int32_t P, double mu, do
   return ok();
 }
 
-// Preparation and evaluation of checked arguments with a resolved shape (automatic: not the caller's).
+// Preparation and evaluation of checked arguments with a resolved shape (automatic: not the caller's).  Every route
+// leaves a prepared region in the workspace.
 int forward_resolved(const double* targets, const double* sources, const double* f, const double* w, const int32_t* off,
                      int32_t M, int32_t P, double mu, double* out, int prec, const Shape& s, bool symmetric,
                      bool automatic, void* ws, size_t ws_bytes, void* stream) {
   if (automatic && !symmetric && takes_small(P, M, prec)) {
+    char* cur = aligned_base(ws);
+    const PreparedView pv = carve_prepared(cur, P, M, prec, fwd_forces(prec));
     hipError_t e = launch_forward_small(prec, s.splits, targets, sources, f, w, off, M, P, 1.0 / (4.0 * kPi * mu), out,
-                                        stream);
+                                        pv, stream);
     if (e != hipSuccess) return hip_fail(e, "forward launch");
     return ok();
   }

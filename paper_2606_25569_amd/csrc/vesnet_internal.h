@@ -206,9 +206,10 @@ struct PlanView {
 
 hipError_t launch_prepare(int prec, const double* pts, const double* vec, const double* wts, const int32_t* off,
                           int M, int P, const PreparedView& pv, void* stream);
+// One launch; leaves the prepared region as launch_prepare does.
 hipError_t launch_forward_small(int prec, int splits, const double* tg, const double* src, const double* f,
                                 const double* w, const int32_t* off, int M, int P, double scale, double* out,
-                                void* stream);
+                                const PreparedView& pv, void* stream);
 hipError_t launch_adjoint_small64(const double* X, const double* f, const double* w, const double* gout,
                                   const int32_t* off, int M, int P, double scale, double* gX, double* gf, double* gw,
                                   void* stream);

@@ -61,63 +61,65 @@ __device__ __forceinline__ double wave_sum(double x) {
 // vesicle the sum of |w vec|_1 (fixed-order wave tree) and the largest squared distance of a
 // point from c.
 template <int PREC>
-__global__ __launch_bounds__(64) void k_prepare(const double* __restrict__ pts, const double* __restrict__ vec,
+__device__ __forceinline__ void prepare_vesicle(const double* __restrict__ pts, const double* __restrict__ vec,
                                                 const double* __restrict__ wts, const int32_t* __restrict__ off_in,
-                                                int M, int P, int2* __restrict__ vrange, int32_t* __restrict__ vid,
-                                                double4* __restrict__ vtab, double* __restrict__ hlen,
-                                                void* __restrict__ rec, double2* __restrict__ f64,
-                                                double2* __restrict__ vaux) {
-  const int lane = threadIdx.x;
-  for (int v = blockIdx.x; v < M; v += gridDim.x) {
-    const int j0 = clampi(off_in[v], 0, P);
-    const int j1 = max(j0, clampi(off_in[v + 1], 0, P));
-    double sx = 0.0, sy = 0.0, bx = 0.0, by = 0.0, sw = 0.0, sa = 0.0;
-    for (int j = j0 + lane; j < j1; j += 64) {
-      const double wj = wts ? wts[j] : 1.0;
-      sx += pts[j];
-      sy += pts[P + j];
-      const double ex = wj * vec[j], ey = wj * vec[P + j];
-      bx += ex;
-      by += ey;
-      sa += fabs(ex) + fabs(ey);
-      sw += wj;
-    }
-    sx = wave_sum(sx);
-    sy = wave_sum(sy);
-    bx = wave_sum(bx);
-    by = wave_sum(by);
-    sw = wave_sum(sw);
-    if (vaux) sa = wave_sum(sa);
-    const int n = j1 - j0;
-    const double cx = n > 0 ? sx / n : 0.0;
-    const double cy = n > 0 ? sy / n : 0.0;
-    if (lane == 0) {
-      vrange[v] = make_int2(j0, j1);
-      vtab[v] = make_double4(cx, cy, bx, by);
-      hlen[v] = n > 0 ? sw / n : 0.0;
-    }
-    double r2 = 0.0;
-    for (int j = j0 + lane; j < j1; j += 64) {
-      const double wj = wts ? wts[j] : 1.0;
-      const double x = pts[j], y = pts[P + j];
-      const double ex = wj * vec[j], ey = wj * vec[P + j];
-      vid[j] = v;
-      if (f64) f64[j] = make_double2(ex, ey);
-      r2 = fmax(r2, (x - cx) * (x - cx) + (y - cy) * (y - cy));
-      if constexpr (PREC == P32C) {
-        static_cast<float4*>(rec)[j] = make_float4((float)(x - cx), (float)(y - cy), (float)ex, (float)ey);
-      } else if constexpr (PREC == P32N) {
-        static_cast<float4*>(rec)[j] = make_float4((float)x, (float)y, (float)ex, (float)ey);
-      } else {
-        static_cast<double4*>(rec)[j] = make_double4(x, y, ex, ey);
-      }
-    }
-    if (vaux) {
-#pragma unroll
-      for (int m = 32; m >= 1; m >>= 1) r2 = fmax(r2, __shfl_xor(r2, m, 64));
-      if (lane == 0) vaux[v] = make_double2(sa, r2);
+                                                int v, int P, const PreparedView& pv) {
+  const int lane = threadIdx.x & 63;
+  const int j0 = clampi(off_in[v], 0, P);
+  const int j1 = max(j0, clampi(off_in[v + 1], 0, P));
+  double sx = 0.0, sy = 0.0, bx = 0.0, by = 0.0, sw = 0.0, sa = 0.0;
+  for (int j = j0 + lane; j < j1; j += 64) {
+    const double wj = wts ? wts[j] : 1.0;
+    sx += pts[j];
+    sy += pts[P + j];
+    const double ex = wj * vec[j], ey = wj * vec[P + j];
+    bx += ex;
+    by += ey;
+    sa += fabs(ex) + fabs(ey);
+    sw += wj;
+  }
+  sx = wave_sum(sx);
+  sy = wave_sum(sy);
+  bx = wave_sum(bx);
+  by = wave_sum(by);
+  sw = wave_sum(sw);
+  if (pv.vaux) sa = wave_sum(sa);
+  const int n = j1 - j0;
+  const double cx = n > 0 ? sx / n : 0.0;
+  const double cy = n > 0 ? sy / n : 0.0;
+  if (lane == 0) {
+    pv.vrange[v] = make_int2(j0, j1);
+    pv.vtab[v] = make_double4(cx, cy, bx, by);
+    pv.hlen[v] = n > 0 ? sw / n : 0.0;
+  }
+  double r2 = 0.0;
+  for (int j = j0 + lane; j < j1; j += 64) {
+    const double wj = wts ? wts[j] : 1.0;
+    const double x = pts[j], y = pts[P + j];
+    const double ex = wj * vec[j], ey = wj * vec[P + j];
+    pv.vid[j] = v;
+    if (pv.f64) pv.f64[j] = make_double2(ex, ey);
+    r2 = fmax(r2, (x - cx) * (x - cx) + (y - cy) * (y - cy));
+    if constexpr (PREC == P32C) {
+      static_cast<float4*>(pv.rec)[j] = make_float4((float)(x - cx), (float)(y - cy), (float)ex, (float)ey);
+    } else if constexpr (PREC == P32N) {
+      static_cast<float4*>(pv.rec)[j] = make_float4((float)x, (float)y, (float)ex, (float)ey);
+    } else {
+      static_cast<double4*>(pv.rec)[j] = make_double4(x, y, ex, ey);
     }
   }
+  if (pv.vaux) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) r2 = fmax(r2, __shfl_xor(r2, m, 64));
+    if (lane == 0) pv.vaux[v] = make_double2(sa, r2);
+  }
+}
+
+template <int PREC>
+__global__ __launch_bounds__(64) void k_prepare(const double* __restrict__ pts, const double* __restrict__ vec,
+                                                const double* __restrict__ wts, const int32_t* __restrict__ off_in,
+                                                int M, int P, PreparedView pv) {
+  for (int v = blockIdx.x; v < M; v += gridDim.x) prepare_vesicle<PREC>(pts, vec, wts, off_in, v, P, pv);
 }
 
 template <int PREC> struct Real;
@@ -526,15 +528,22 @@ __global__ __launch_bounds__(256) void k_reduce_splits(const double* __restrict_
 // The direct compensated sum of a small problem without a prepared workspace: one workgroup per 64 targets, one
 // wavefront per source split, which prepares each of its vesicles itself (the reference point by the sums of k_prepare)
 // and adds it as k_forward does, 64 records at a time through LDS; the splits are added in order as k_reduce_splits
-// does.  The same operations in the same order, so the result is that of the three launches bit for bit.  Latency
-// bounds it: 16 x 32, 12.7 us in three launches -> 7.2 us.
+// does.  The same operations in the same order, so the result is that of the three launches bit for bit.  Workgroups
+// beyond those of the targets, a wavefront per vesicle, leave the prepared region for later evaluations beside it.
+// Latency bounds it: 16 x 32, 12.7 us in three launches -> 7.2 us.
 __global__ __launch_bounds__(1024) void k_forward_small32(const double* __restrict__ tg, const double* __restrict__ src,
                                                           const double* __restrict__ f, const double* __restrict__ w,
                                                           const int32_t* __restrict__ off, int M, int P, double scale,
-                                                          double* __restrict__ out) {
+                                                          double* __restrict__ out, PreparedView pv) {
   __shared__ float4 recs[16][64];
   __shared__ double2 sums[16][64];
-  const int split = threadIdx.x >> 6, splits = blockDim.x >> 6, lane = threadIdx.x & 63;
+  const int split = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), splits = blockDim.x >> 6, lane = threadIdx.x & 63;
+  const int blocks = (P + 63) / 64;
+  if ((int)blockIdx.x >= blocks) {
+    const int v = ((int)blockIdx.x - blocks) * splits + split;
+    if (v < M) prepare_vesicle<P32C>(src, f, w, off, v, P, pv);
+    return;
+  }
   float4* rec = recs[split];
   const int i = blockIdx.x * 64 + lane;
   const int ii = min(i, P - 1);
@@ -622,14 +631,21 @@ __global__ __launch_bounds__(1024) void k_forward_small32(const double* __restri
 
 // The direct float64 sum of a small problem in one launch: one workgroup of sixteen wavefronts per kT = 4, 8 or 16
 // targets; each wavefront takes a sixteenth of the sources, 64 records at a time through LDS, each of its lane groups
-// every 64 / kT-th of them, and the sums are added at the end in a fixed order.  Float64 VALU issue bounds it from about
-// a thousand points on, below it latency.  48 x 32: 19.4 us in three launches -> 8.0 us; 16 x 32: 13.8 -> 4.2 us.
+// every 64 / kT-th of them, and the sums are added at the end in a fixed order.  Workgroups beyond those of the targets
+// leave the prepared region, as in k_forward_small32.  Float64 VALU issue bounds it from about a thousand points on,
+// below it latency.  48 x 32: 19.4 us in three launches -> 8.0 us; 16 x 32: 13.8 -> 4.2 us.
 template <int kT>
 __global__ __launch_bounds__(1024) void k_forward_small64(const double* __restrict__ tg, const double* __restrict__ src,
                                                           const double* __restrict__ f, const double* __restrict__ w,
                                                           const int32_t* __restrict__ off, int M, int P, double scale,
-                                                          double* __restrict__ out) {
+                                                          double* __restrict__ out, PreparedView pv) {
   constexpr int kWaves = 16, kGroups = 64 / kT;
+  const int blocks = (P + kT - 1) / kT;
+  if ((int)blockIdx.x >= blocks) {
+    const int v = ((int)blockIdx.x - blocks) * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (v < M) prepare_vesicle<P64>(src, f, w, off, v, P, pv);
+    return;
+  }
   __shared__ double4 recs[kWaves][64];
   __shared__ double2 sums[kWaves][kT];
   __shared__ double2 ltab[kLogTab];
@@ -1019,12 +1035,15 @@ hipError_t launch_prepare(int prec, const double* pts, const double* vec, const 
   if (M == 0) return hipSuccess;
   const int grid = M < 65535 ? M : 65535;
   switch (prec) {
-    case P64: hipLaunchKernelGGL(k_prepare<P64>, dim3(grid), dim3(64), 0, S_(stream), pts, vec, wts, off, M, P,
-                                 pv.vrange, pv.vid, pv.vtab, pv.hlen, pv.rec, pv.f64, pv.vaux); break;
-    case P32C: hipLaunchKernelGGL(k_prepare<P32C>, dim3(grid), dim3(64), 0, S_(stream), pts, vec, wts, off, M, P,
-                                  pv.vrange, pv.vid, pv.vtab, pv.hlen, pv.rec, pv.f64, pv.vaux); break;
-    case P32N: hipLaunchKernelGGL(k_prepare<P32N>, dim3(grid), dim3(64), 0, S_(stream), pts, vec, wts, off, M, P,
-                                  pv.vrange, pv.vid, pv.vtab, pv.hlen, pv.rec, pv.f64, pv.vaux); break;
+    case P64:
+      hipLaunchKernelGGL(k_prepare<P64>, dim3(grid), dim3(64), 0, S_(stream), pts, vec, wts, off, M, P, pv);
+      break;
+    case P32C:
+      hipLaunchKernelGGL(k_prepare<P32C>, dim3(grid), dim3(64), 0, S_(stream), pts, vec, wts, off, M, P, pv);
+      break;
+    case P32N:
+      hipLaunchKernelGGL(k_prepare<P32N>, dim3(grid), dim3(64), 0, S_(stream), pts, vec, wts, off, M, P, pv);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1088,15 +1107,16 @@ static void small64(int P, const Launch& launch) {
 
 hipError_t launch_forward_small(int prec, int splits, const double* tg, const double* src, const double* f,
                                 const double* w, const int32_t* off, int M, int P, double scale, double* out,
-                                void* stream) {
+                                const PreparedView& pv, void* stream) {
   hipStream_t st = S_(stream);
+  // workgroups of the targets, then of the vesicles, one wavefront each
   if (prec == P32C)
-    hipLaunchKernelGGL(k_forward_small32, dim3((P + 63) / 64), dim3(64 * splits), 0, st, tg, src, f, w, off, M, P, scale,
-                       out);
+    hipLaunchKernelGGL(k_forward_small32, dim3((P + 63) / 64 + (M + splits - 1) / splits), dim3(64 * splits), 0, st, tg,
+                       src, f, w, off, M, P, scale, out, pv);
   else
     small64(P, [&](auto kT) {
-      hipLaunchKernelGGL(k_forward_small64<kT.value>, dim3((P + kT.value - 1) / kT.value), dim3(1024), 0, st, tg, src, f, w,
-                         off, M, P, scale, out);
+      hipLaunchKernelGGL(k_forward_small64<kT.value>, dim3((P + kT.value - 1) / kT.value + (M + 15) / 16), dim3(1024), 0,
+                         st, tg, src, f, w, off, M, P, scale, out, pv);
     });
   return hipGetLastError();
 }

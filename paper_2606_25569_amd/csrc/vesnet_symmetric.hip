@@ -191,7 +191,8 @@ __global__ __launch_bounds__(256) void k_sym_cycles(const int4* __restrict__ cyc
 // k_prepare, k_sym_plan and k_sym_cycles of up to kSymFused vesicles in one launch, a wavefront per vesicle, which
 // counts the cycles of the vesicles before it itself: the same values in the same order, but for the fixed-point
 // exponent, which the units form (meta[1] is not written).  zero0 and zero1 (or null): 2 P words cleared.  kAdjoint:
-// also the records of g, and the cycle sums are those of g; else of F = w f.
+// also the records of g, and the cycle sums are those of g; else of F = w f, and the whole prepared region is left, for
+// later evaluations from it.
 // 504 x 32: three launches -> one, 104.4 -> 99.9 us a call; 512 x 64 and its adjoint: nine -> two, 932 -> 914 us.
 constexpr int kSymFused = 1024;
 
@@ -199,12 +200,12 @@ template <bool kAdjoint>
 __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ pts, const double* __restrict__ f,
                                                     const double* __restrict__ w, const double* __restrict__ g,
                                                     const int32_t* __restrict__ off, int M, int P, int cb, int ncyc_max,
-                                                    double4* __restrict__ vtab, double2* __restrict__ vaux,
-                                                    float4* __restrict__ recF, float4* __restrict__ recG,
+                                                    PreparedView pv, float4* __restrict__ recG,
                                                     int4* __restrict__ cyc, double2* __restrict__ ccyc,
                                                     int32_t* __restrict__ meta, unsigned long long* __restrict__ zero0,
                                                     unsigned long long* __restrict__ zero1) {
   __shared__ double2 carried[64];
+  float4* recF = static_cast<float4*>(pv.rec);
   const int lane = threadIdx.x, v = blockIdx.x;
   const auto clamped = [&](int u) { return min(max(off[u], 0), P); };
   for (int64_t e = (int64_t)v * 64 + lane; e < 2 * (int64_t)P; e += (int64_t)M * 64) {
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) first += __shfl_xor(first, m, 64);
   const int j0 = clamped(v), j1 = max(j0, clamped(v + 1)), n = j1 - j0;
-  double sx = 0.0, sy = 0.0, bx = 0.0, by = 0.0, sa = 0.0;
+  double sx = 0.0, sy = 0.0, bx = 0.0, by = 0.0, sa = 0.0, sw = 0.0;
   for (int j = j0 + lane; j < j1; j += 64) {
     const double wj = w[j];
     sx += pts[j];
@@ -225,12 +226,14 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
     bx += ex;
     by += ey;
     sa += fabs(ex) + fabs(ey);
+    sw += wj;
   }
   sx = wave_sum_d(sx);
   sy = wave_sum_d(sy);
   bx = wave_sum_d(bx);
   by = wave_sum_d(by);
   sa = wave_sum_d(sa);
+  if constexpr (!kAdjoint) sw = wave_sum_d(sw);
   const double cx = n > 0 ? sx / n : 0.0, cy = n > 0 ? sy / n : 0.0;
   double r2 = 0.0;
   for (int c0 = j0; c0 < j1; c0 += 64) {
@@ -248,6 +251,8 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
         carried[lane] = make_double2(gx, gy);
       } else {
         carried[lane] = make_double2(ex, ey);
+        pv.f64[j] = make_double2(ex, ey);
+        pv.vid[j] = v;
       }
     }
     wave_sync();
@@ -266,8 +271,12 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) r2 = fmax(r2, __shfl_xor(r2, m, 64));
   if (lane != 0) return;
-  vtab[v] = make_double4(cx, cy, bx, by);
-  vaux[v] = make_double2(sa, r2);
+  pv.vtab[v] = make_double4(cx, cy, bx, by);
+  pv.vaux[v] = make_double2(sa, r2);
+  if constexpr (!kAdjoint) {
+    pv.vrange[v] = make_int2(j0, j1);
+    pv.hlen[v] = n > 0 ? sw / n : 0.0;
+  }
   if (v == M - 1) {
     const int ncyc = min(first + (n + kRing - 1) / kRing, ncyc_max);
     meta[0] = ncyc;
@@ -1901,7 +1910,7 @@ hipError_t launch_backward_symmetric(int T, int ns, int P, int M, const Prepared
   const int nb_max = (int)sym_max_blocks(P, M, T);
   if (sym_fused(M)) {
     hipLaunchKernelGGL(k_sym_prepare<true>, dim3(M), dim3(64), 0, st, in.pts, f, w, in.g, in.off, M, P, cb, ncyc_max,
-                       pvF.vtab, pvF.vaux, static_cast<float4*>(pvF.rec), static_cast<float4*>(pvG.rec), sv.cyc, sv.fcyc,
+                       pvF, static_cast<float4*>(pvG.rec), sv.cyc, sv.fcyc,
                        sv.meta, reinterpret_cast<unsigned long long*>(grad_points),
                        reinterpret_cast<unsigned long long*>(vsum));
   } else {
@@ -2109,8 +2118,7 @@ hipError_t launch_forward_symmetric(int T, int ns, int P, int M, const PreparedV
   const bool fused = in != nullptr && sym_fused(M);
   if (fused) {
     hipLaunchKernelGGL(k_sym_prepare<false>, dim3(M), dim3(64), 0, st, in->pts, in->f, in->w, nullptr, in->off, M, P, cb,
-                       ncyc_max, pv.vtab, pv.vaux, static_cast<float4*>(pv.rec), nullptr, sv.cyc, sv.fcyc, sv.meta, sv.acc,
-                       nullptr);
+                       ncyc_max, pv, nullptr, sv.cyc, sv.fcyc, sv.meta, sv.acc, nullptr);
   } else {
     if (in != nullptr) {
       const hipError_t e = launch_prepare(P32C, in->pts, in->f, in->w, in->off, M, P, pv, stream);
