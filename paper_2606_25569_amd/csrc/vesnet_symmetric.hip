@@ -106,6 +106,25 @@ __device__ __forceinline__ int sym_exponent(double fsum) {
   return 62 - e;
 }
 
+// The same of the float64 form, also where 520 fsum overflows.
+__device__ __forceinline__ int sym64_exponent(double fsum) {
+  if (!(fsum > 0.0 && isfinite(fsum))) return 0;
+  int e0, e;
+  const double m = frexp(fsum, &e0);
+  frexp(520.0 * m, &e);
+  return 62 - e0 - e;
+}
+
+// A vesicle's share of that bound in the float64 form, a = sum |F|_1 over its points [r.x, r.y): none where a force is
+// not finite, since every output that such a force enters is marked for it, and the vesicle's own keep their values.
+// (An infinite share is the overflow of finite forces: then every output is NaN.)
+__device__ __forceinline__ double bound_share(double a, int2 r, const double4* __restrict__ rec) {
+  if (!isfinite(a))
+    for (int j = r.x; j < r.y; ++j)
+      if (!isfinite(rec[j].z) || !isfinite(rec[j].w)) return 0.0;
+  return a;
+}
+
 // Plan: the cycle table of every vesicle in point order, the number of blocks and the
 // fixed-point exponent.  One workgroup of 1024 threads; everything in a fixed order.
 __global__ __launch_bounds__(1024) void k_sym_plan(const int2* __restrict__ vrange, const double2* __restrict__ vaux,
@@ -690,7 +709,9 @@ __device__ __forceinline__ void fixed_add2(unsigned long long* __restrict__ a, u
 // Start of a float64 call: the accumulator words and marks cleared and the log table built (every workgroup a
 // share), and for a single suspension (M > 0) its exponent (workgroup 0; the vesicles' sums in a fixed order).
 // meta[3]: 1 when the bound itself is not finite (then every output is NaN).
-__global__ __launch_bounds__(1024) void k_sym64_init(const double2* __restrict__ vaux, int M, int64_t nwords,
+__global__ __launch_bounds__(1024) void k_sym64_init(const double2* __restrict__ vaux,
+                                                     const int2* __restrict__ vrange,
+                                                     const double4* __restrict__ rec, int M, int64_t nwords,
                                                      unsigned long long* __restrict__ acc,
                                                      uint32_t* __restrict__ bad, int64_t nbad,
                                                      double2* __restrict__ tab, int32_t* __restrict__ meta) {
@@ -703,15 +724,15 @@ __global__ __launch_bounds__(1024) void k_sym64_init(const double2* __restrict__
   if (blockIdx.x != 0 || M <= 0) return;
   __shared__ double s_dsum[16];
   double fa = 0.0;
-  for (int v = threadIdx.x; v < M; v += 1024) fa += vaux[v].x;
+  for (int v = threadIdx.x; v < M; v += 1024) fa += bound_share(vaux[v].x, vrange[v], rec);
   fa = wave_sum_d(fa);
   if ((threadIdx.x & 63) == 0) s_dsum[threadIdx.x >> 6] = fa;
   __syncthreads();
   if (threadIdx.x == 0) {
     double tot = 0.0;
     for (int k = 0; k < 16; ++k) tot += s_dsum[k];
-    meta[1] = sym_exponent(tot);
-    meta[3] = isfinite(520.0 * tot) ? 0 : 1;
+    meta[1] = sym64_exponent(tot);
+    meta[3] = isfinite(tot) ? 0 : 1;
   }
 }
 static_assert(kSymTab == 1024, "k_sym64_init builds one entry per thread");
@@ -1179,6 +1200,7 @@ __global__ __launch_bounds__(256) void k_symb_finish(const unsigned long long* _
 // can make the units outrun the host's bound.  One workgroup of 1024 threads, in a fixed order.
 __global__ __launch_bounds__(1024) void k_symb64_plan(const int2* __restrict__ vrange,
                                                       const double2* __restrict__ vaux,
+                                                      const double4* __restrict__ rec,
                                                       const int32_t* __restrict__ sus_off, int M, int P, int nsus,
                                                       int bp, int ns, int4* __restrict__ stab,
                                                       int32_t* __restrict__ ustart, int32_t* __restrict__ pstart,
@@ -1194,9 +1216,9 @@ __global__ __launch_bounds__(1024) void k_symb64_plan(const int2* __restrict__ v
   for (int s = wv; s < nsus; s += 16) {  // one wavefront per suspension
     const int2 rs = vr[s];
     double fs = 0.0;
-    for (int v = rs.x + lane; v < rs.y; v += 64) fs += vaux[v].x;
+    for (int v = rs.x + lane; v < rs.y; v += 64) fs += bound_share(vaux[v].x, vrange[v], rec);
     fs = wave_sum_d(fs);
-    if (lane == 0) stab[s] = make_int4(0, 0, isfinite(520.0 * fs) ? 0 : 1, sym_exponent(fs));
+    if (lane == 0) stab[s] = make_int4(0, 0, isfinite(fs) ? 0 : 1, sym64_exponent(fs));
   }
   __syncthreads();
   disjoint_ranges(
@@ -2033,10 +2055,11 @@ hipError_t launch_batched_symmetric(int T, int grid, int P, int M, const Prepare
 int64_t sym64_blocks(int64_t P, int T) { return (P + kSymThreads * T - 1) / (kSymThreads * T); }
 
 // Clears the float64 region's sums and marks and builds its table (and the exponent of a single suspension).
-static void launch_sym64_init(const double2* vaux, int M, int P, const Symmetric64View& sv, hipStream_t st) {
+static void launch_sym64_init(const PreparedView& pv, int M, int P, const Symmetric64View& sv, hipStream_t st) {
   const int64_t words = 4 * (int64_t)P, marks = ((int64_t)2 * P + 3) / 4;
   const int grid = (int)std::min<int64_t>((words + 1023) / 1024, 1024);
-  hipLaunchKernelGGL(k_sym64_init, dim3(grid), dim3(1024), 0, st, vaux, M, words, sv.acc,
+  hipLaunchKernelGGL(k_sym64_init, dim3(grid), dim3(1024), 0, st, pv.vaux, pv.vrange,
+                     static_cast<const double4*>(pv.rec), M, words, sv.acc,
                      reinterpret_cast<uint32_t*>(sv.bad), marks, sv.tab, sv.meta);
 }
 
@@ -2064,10 +2087,10 @@ hipError_t launch_batched_symmetric64(int T, int ns, int grid, int P, int M, con
   if (P == 0 || S == 0) return hipSuccess;
   if (grid < 1 || ns < 1 || kRows % ns != 0) return hipErrorInvalidValue;
   hipStream_t st = Sx_(stream);
-  launch_sym64_init(pv.vaux, 0, P, sv, st);
-  hipLaunchKernelGGL(k_symb64_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, sus_off, M, P, S, kSymThreads * T,
-                     ns, bv.stab, bv.ustart, bv.pstart, bv.vr, sv.meta, bv.count);
+  launch_sym64_init(pv, 0, P, sv, st);
   const double4* rec = static_cast<const double4*>(pv.rec);
+  hipLaunchKernelGGL(k_symb64_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, rec, sus_off, M, P, S,
+                     kSymThreads * T, ns, bv.stab, bv.ustart, bv.pstart, bv.vr, sv.meta, bv.count);
   if (T == 1)
     hipLaunchKernelGGL(k_symb64_main<1>, dim3(grid), dim3(kSymThreads), 0, st, P, ns, rec, pv.vid, sv.tab, bv.stab,
                        bv.ustart, S, sv.meta, bv.count, sv.acc, sv.bad);
@@ -2087,7 +2110,7 @@ hipError_t launch_forward_symmetric64(int T, int ns, int P, int M, const Prepare
   if (P == 0) return hipSuccess;
   if (ns < 1 || kRows % ns != 0) return hipErrorInvalidValue;
   hipStream_t st = Sx_(stream);
-  launch_sym64_init(pv.vaux, M, P, sv, st);
+  launch_sym64_init(pv, M, P, sv, st);
   const int64_t units = sym_units(sym64_blocks(P, T)) * ns;
   if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)units);
