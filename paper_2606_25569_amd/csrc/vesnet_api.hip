@@ -1097,7 +1097,8 @@ int points_bwd_T(int32_t P, int32_t M, int prec) {
 
 size_t adjoint64_bytes(int32_t P) {
   return align_up((size_t)P * sizeof(double4)) + align_up((size_t)P * sizeof(int32_t)) +
-         align_up(1024 * sizeof(double2)) + align_up((size_t)2 * P * sizeof(double));
+         align_up(1024 * sizeof(double2)) + align_up((size_t)2 * kAdjSets * P * sizeof(double)) +
+         align_up((size_t)2 * (kAdjSets - 1) * P * sizeof(double));
 }
 
 Adjoint64View carve_adjoint64(char*& cur, int32_t P) {
@@ -1109,7 +1110,9 @@ Adjoint64View carve_adjoint64(char*& cur, int32_t P) {
   av.tab = reinterpret_cast<double2*>(cur);
   cur += align_up(1024 * sizeof(double2));
   av.vsum = reinterpret_cast<double*>(cur);
-  cur += align_up((size_t)2 * P * sizeof(double));
+  cur += align_up((size_t)2 * kAdjSets * P * sizeof(double));
+  av.gmore = reinterpret_cast<double*>(cur);
+  cur += align_up((size_t)2 * (kAdjSets - 1) * P * sizeof(double));
   return av;
 }
 

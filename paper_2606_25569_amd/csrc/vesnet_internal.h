@@ -181,8 +181,10 @@ struct Adjoint64View {
   double4* rec;   // [P] (x, y, w f_x, w f_y)
   int32_t* vid;   // [P] vesicle id
   double2* tab;   // [1024] log table
-  double* vsum;   // [2][P] sums of G g
+  double* vsum;   // [kAdjSets][2][P] sums of G g
+  double* gmore;  // [kAdjSets - 1][2][P] sums of the position gradient beside those in its own array
 };
+constexpr int kAdjSets = 3;
 
 // Device views of the batched symmetric form's plan (after the symmetric region).
 struct SymBatchView {

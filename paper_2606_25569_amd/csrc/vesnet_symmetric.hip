@@ -649,7 +649,8 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_main(
 // Float64 needs no compensation per source vesicle, so nothing here follows the vesicles: blocks are 256 T
 // consecutive points, ring cycles 16 consecutive points whatever vesicles they belong to (only the last cycle
 // of a suspension is padded; cut at the vesicles, 17 to 63 points each, 47% of the pair evaluations were
-// padding), rows are summed over a whole unit without flushes, and the block table needs no plan kernel.  The
+// padding), rows are summed chunk by chunk of 64 columns whatever the vesicles (summed over a whole unit in one chain
+// they rounded 1.4 times as much in all), and the block table needs no plan kernel.  The
 // own vesicle is dropped pair by pair, but only in units whose row and column points share a vesicle (ids are
 // compared at both ends; at most the diagonal and the neighbouring block pairs): there the accumulations are
 // selected, so that not even a non-finite value of an own-vesicle pair enters.
@@ -761,7 +762,7 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
   // vesicle ids do not decrease: the two point ranges share a vesicle when their id ranges meet
   const bool masked = diag || !(vid[r1 - 1] < vid[c0] || vid[c1 - 1] < vid[r0]);
 
-  double tx[T], ty[T], fx[T], fy[T], ax[T], ay[T];
+  double tx[T], ty[T], fx[T], fy[T], ax[T], ay[T], sx[T], sy[T];  // a: sums of a chunk of columns, s: of all
   int tv[T];
 #pragma unroll
   for (int k = 0; k < T; ++k) {
@@ -773,7 +774,7 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
     ty[k] = t.y;
     fx[k] = t.z;
     fy[k] = t.w;
-    ax[k] = ay[k] = 0.0;
+    ax[k] = ay[k] = sx[k] = sy[k] = 0.0;
   }
 
   auto ring = [&](int buf, int cc, auto mask_tag) __attribute__((always_inline)) {
@@ -874,6 +875,12 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
       for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::true_type{});
     else
       for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::false_type{});
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+      sx[k] += ax[k];
+      sy[k] += ay[k];
+      ax[k] = ay[k] = 0.0;
+    }
     stage_store(buf ^ 1, nxt, nv);
     __syncthreads();
   }
@@ -882,8 +889,8 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
   for (int k = 0; k < T; ++k) {
     const int i = r0 + (k * kRows + row) * kRing + p;
     if (i < r1) {
-      fixed_add2(&acc[i], &bad[i], two_p, ax[k], S);
-      fixed_add2(&acc[(size_t)P + i], &bad[(size_t)P + i], two_p, ay[k], S);
+      fixed_add2(&acc[i], &bad[i], two_p, sx[k], S);
+      fixed_add2(&acc[(size_t)P + i], &bad[(size_t)P + i], two_p, sy[k], S);
     }
   }
 }
@@ -1636,7 +1643,9 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_bwd(
 //   a = g_ix F_jx + F_ix g_jx,  b = g_iy F_jy + F_iy g_jy,  d = g_ix F_jy + g_iy F_jx + F_ix g_jy + F_iy g_jx,
 // H = grad (a A + b B + d c) = ( t (m (a - b) - 2 b) + u d m,  u (m (a - b) - 2 a) - t d m ):
 // 55 instructions per unordered pair with the logarithm and the reciprocal.  The four sums are added with
-// float64 atomics, as in k_sym_bwd.
+// float64 atomics, as in k_sym_bwd, but to one of kAdjSets copies of each: with strips a point takes up to a few hundred
+// additions, which all round at the size of its whole sum.  (Rows in one chain over a unit and one copy gave forces'
+// gradients 2.2 times the rounding error at 2000 x 32, and 1.4 times at 504 x 32; the times are the same.)
 constexpr int kChunkA = 2;  // source cycles per LDS chunk: 31 KB with the table, so LDS holds five units
 
 // Records, vesicle ids and table, and the cleared sums of v and H: one wavefront per vesicle (its points, offsets
@@ -1645,7 +1654,8 @@ __global__ __launch_bounds__(64) void k_sym64_adj_init(const double* __restrict_
                                                        const double* __restrict__ w, const int32_t* __restrict__ off,
                                                        int M, int P, double4* __restrict__ rec,
                                                        int32_t* __restrict__ vid, double2* __restrict__ tab,
-                                                       double* __restrict__ vsum, double* __restrict__ gsum) {
+                                                       double* __restrict__ vsum, double* __restrict__ gsum,
+                                                       double* __restrict__ gmore) {
   const int lane = threadIdx.x;
   for (int v = blockIdx.x; v < M; v += gridDim.x) {
     const int j0 = min(max(off[v], 0), P), j1 = max(j0, min(max(off[v + 1], 0), P));
@@ -1655,7 +1665,9 @@ __global__ __launch_bounds__(64) void k_sym64_adj_init(const double* __restrict_
     }
   }
   const int64_t stride = (int64_t)gridDim.x * 64, first = blockIdx.x * (int64_t)64 + lane;
-  for (int64_t e = first; e < 2 * (int64_t)P; e += stride) vsum[e] = gsum[e] = 0.0;
+  for (int64_t e = first; e < 2 * (int64_t)P; e += stride) gsum[e] = 0.0;
+  for (int64_t e = first; e < 2 * kAdjSets * (int64_t)P; e += stride) vsum[e] = 0.0;
+  for (int64_t e = first; e < 2 * (kAdjSets - 1) * (int64_t)P; e += stride) gmore[e] = 0.0;
   for (int64_t e = first; e < kSymTab; e += stride) tab[e] = half_log_entry((int)e);
 }
 
@@ -1677,6 +1689,7 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
   const bool masked = diag || !(vid[r1 - 1] < vid[c0] || vid[c1 - 1] < vid[r0]);
 
   double tx[T], ty[T], fx[T], fy[T], gx[T], gy[T], vx[T], vy[T], hx[T], hy[T];
+  double svx[T], svy[T], shx[T], shy[T];  // the sums of all columns; v and h are those of a chunk
   int tv[T];
 #pragma unroll
   for (int k = 0; k < T; ++k) {
@@ -1690,7 +1703,7 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
     fy[k] = t.w;
     gx[k] = in ? g[i] : 0.0;
     gy[k] = in ? g[(size_t)P + i] : 0.0;
-    vx[k] = vy[k] = hx[k] = hy[k] = 0.0;
+    vx[k] = vy[k] = hx[k] = hy[k] = svx[k] = svy[k] = shx[k] = shy[k] = 0.0;
   }
 
   auto ring = [&](int buf, int cc, auto mask_tag) __attribute__((always_inline)) {
@@ -1815,6 +1828,14 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
       for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::true_type{});
     else
       for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::false_type{});
+#pragma unroll
+    for (int k = 0; k < T; ++k) {
+      svx[k] += vx[k];
+      svy[k] += vy[k];
+      shx[k] += hx[k];
+      shy[k] += hy[k];
+      vx[k] = vy[k] = hx[k] = hy[k] = 0.0;
+    }
     stage_store(buf ^ 1, nxt);
     __syncthreads();
   }
@@ -1823,10 +1844,10 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
   for (int k = 0; k < T; ++k) {
     const int i = r0 + (k * kRows + row) * kRing + p;
     if (i < r1) {
-      atomicAdd(&vsum[i], vx[k]);
-      atomicAdd(&vsum[(size_t)P + i], vy[k]);
-      atomicAdd(&gsum[i], hx[k]);
-      atomicAdd(&gsum[(size_t)P + i], hy[k]);
+      atomicAdd(&vsum[i], svx[k]);
+      atomicAdd(&vsum[(size_t)P + i], svy[k]);
+      atomicAdd(&gsum[i], shx[k]);
+      atomicAdd(&gsum[(size_t)P + i], shy[k]);
     }
   }
 }
@@ -1836,8 +1857,8 @@ template <int T>
 __global__ __launch_bounds__(kSymThreads) void k_sym64_bwd(int P, int ns, const double4* __restrict__ rec,
                                                            const double* __restrict__ g,
                                                            const int32_t* __restrict__ vid,
-                                                           const double2* __restrict__ tab,
-                                                           double* __restrict__ gsum, double* __restrict__ vsum) {
+                                                           const double2* __restrict__ tab, double* __restrict__ gsum,
+                                                           double* __restrict__ gmore, double* __restrict__ vsum) {
   __shared__ Adj64Lds lds;
   __shared__ double2 ltab[kSymTab];
   constexpr int BP = kSymThreads * T;
@@ -1847,6 +1868,10 @@ __global__ __launch_bounds__(kSymThreads) void k_sym64_bwd(int P, int ns, const 
   const int c0 = by * BP + (L % ns) * (BP / ns), c1 = min(P, c0 + BP / ns);
   if (c0 >= c1) return;
   for (int e = threadIdx.x; e < kSymTab; e += kSymThreads) ltab[e] = tab[e];
+  // a row point's additions differ in the strip, a column point's in the row block
+  const int set = (bx + L % ns) % kAdjSets;
+  if (set > 0) gsum = gmore + (size_t)(set - 1) * 2 * P;
+  vsum += (size_t)set * 2 * P;
   // the diagonal block's rows past the strip hold no pair of it; half the rows or fewer take the narrower form
   const int r0 = bx * BP, r1 = min(bx == by ? c1 : P, r0 + BP);
   if (T > 1 && r1 - r0 <= kSymThreads)
@@ -1876,6 +1901,34 @@ __global__ __launch_bounds__(256) void k_sym_bwd_finish(const double* __restrict
       gX[P + j] *= scale;
     }
     const double vx = scale * vsum[j], vy = scale * vsum[P + j];
+    if (gf) {
+      gf[j] = w[j] * vx;
+      gf[P + j] = w[j] * vy;
+    }
+    if (gw) gw[j] = f[j] * vx + f[P + j] * vy;
+  }
+}
+
+// The same after the float64 adjoint, whose sums come in kAdjSets copies.
+__global__ __launch_bounds__(256) void k_sym64_bwd_finish(const double* __restrict__ vsum,
+                                                          const double* __restrict__ gmore,
+                                                          const double* __restrict__ f, const double* __restrict__ w,
+                                                          int P, double scale, double* __restrict__ gX,
+                                                          double* __restrict__ gf, double* __restrict__ gw) {
+  const size_t n = 2 * (size_t)P;
+  for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < P; j += gridDim.x * blockDim.x) {
+    double hx = gX[j], hy = gX[P + j], vx = vsum[j], vy = vsum[P + j];
+#pragma unroll
+    for (int k = 1; k < kAdjSets; ++k) {
+      hx += gmore[(k - 1) * n + j];
+      hy += gmore[(k - 1) * n + P + j];
+      vx += vsum[k * n + j];
+      vy += vsum[k * n + P + j];
+    }
+    gX[j] = hx * scale;
+    gX[P + j] = hy * scale;
+    vx *= scale;
+    vy *= scale;
     if (gf) {
       gf[j] = w[j] * vx;
       gf[P + j] = w[j] * vy;
@@ -1973,7 +2026,7 @@ hipError_t launch_backward_symmetric64(int T, int ns, int P, int M, const double
   hipStream_t st = Sx_(stream);
   const int igrid = (int)std::min<int64_t>(std::max<int64_t>(M, (2 * (int64_t)P + 255) / 256), 65535);
   hipLaunchKernelGGL(k_sym64_adj_init, dim3(igrid), dim3(64), 0, st, X, f, w, off, M, P, av.rec, av.vid, av.tab, av.vsum,
-                     grad_points);
+                     grad_points, av.gmore);
   const int64_t units = sym_units(sym64_blocks(P, T)) * ns;
   if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)units);
@@ -1981,15 +2034,15 @@ hipError_t launch_backward_symmetric64(int T, int ns, int P, int M, const double
 #define VESNET_ADJ64_CASE(TT)                                                                                     \
   case TT:                                                                                                        \
     hipLaunchKernelGGL(k_sym64_bwd<TT>, grid, dim3(kSymThreads), 0, st, P, ns, av.rec, gout, av.vid, av.tab,      \
-                       grad_points, av.vsum);                                                                     \
+                       grad_points, av.gmore, av.vsum);                                                           \
     break;
     VESNET_ADJ64_CASE(1) VESNET_ADJ64_CASE(2) VESNET_ADJ64_CASE(3) VESNET_ADJ64_CASE(4)
 #undef VESNET_ADJ64_CASE
     default: return hipErrorInvalidValue;
   }
   const int fgrid = (P + 255) / 256 < 16384 ? (P + 255) / 256 : 16384;
-  hipLaunchKernelGGL(k_sym_bwd_finish, dim3(fgrid), dim3(256), 0, st, av.vsum, f, w, P, scale, grad_points, grad_f,
-                     grad_w);
+  hipLaunchKernelGGL(k_sym64_bwd_finish, dim3(fgrid), dim3(256), 0, st, av.vsum, av.gmore, f, w, P, scale, grad_points,
+                     grad_f, grad_w);
   return hipGetLastError();
 }
 
