@@ -133,10 +133,14 @@ __device__ __forceinline__ double2 half_log_entry(int i) {
 }
 
 // -1/2 ln q for a finite q > 0: q = mant 2^e, r = mant a - 1/2, |r| < 2.8e-4, -1/2 log1p(2r) =
-// -r + r^2 - 4/3 r^3 + 2 r^4 (the next term is below 5.5e-18; the table entry alone carries up to 2.8e-17),
-// e ln 2 by one FMA as in log_reduced_n.  With 2r every coefficient but 4/3 is an inline constant, so no step
-// needs a second scalar operand (a copy to a VGPR).
+// -r + r^2 - 4/3 r^3 + 2 r^4 (the next term is below 5.5e-18; the table entry alone carries up to 2.8e-17).  With 2r
+// every coefficient but 4/3 is an inline constant, so no step needs a second scalar operand (a copy to a VGPR).
+// e ln 2 is added with ln 2 in a high and a low part; kOneWord: rounded to a double, one FMA less and an absolute error
+// of up to |e| 1.2e-17 more (rms error for q in 2^8 .. 2^10 1.7e-16 instead of 1.3e-16).
+template <bool kOneWord = false>
 __device__ __forceinline__ double neg_half_log(double q, const double2* __restrict__ tab) {
+  constexpr double kLn2Hi = 6.93147180369123816490e-01;
+  constexpr double kLn2Lo = 1.90821492927058770002e-10;
   int e;
   const double mant = frexp(q, &e);
   const double2 t = tab[(__double2hiint(mant) >> 10) & (kHalfLogTab - 1)];  // in range for every input
@@ -144,7 +148,9 @@ __device__ __forceinline__ double neg_half_log(double q, const double2* __restri
   double pol = fma(r, 2.0, -4.0 / 3.0);
   pol = fma(pol, r, 1.0);
   pol = fma(pol, r, -1.0);
-  return fma((double)e, -0.5 * 0.69314718055994530942, fma(r, pol, t.y));
+  const double ed = (double)e;
+  if constexpr (kOneWord) return fma(ed, -0.5 * 0.69314718055994530942, fma(r, pol, t.y));
+  return fma(ed, -0.5 * kLn2Hi, fma(ed, -0.5 * kLn2Lo, fma(r, pol, t.y)));
 }
 
 // Device views of a prepared workspace region.

@@ -31,8 +31,10 @@ namespace {
 constexpr double kLn2 = 0.69314718055994530942;
 constexpr float kHalfLn2 = -0.34657359027997265471f;  // -(1/2) ln 2 : converts log2(q) to -ln|r|
 // Float64 in workgroups of 256 threads takes its logarithm from the 1024-entry table of -1/2 ln, 16 KB of LDS that
-// every workgroup forms itself (4 entries per thread, about 1 us): 6 FMAs instead of 11 with 64 entries.  16,128 points
-// 285 -> 266 us, 64,000 points 4.01 -> 3.62 ms, masked 4.33 -> 3.79 ms.  Smaller workgroups keep the 64 entries: forming
+// every workgroup forms itself (4 entries per thread, about 1 us): 7 FMAs instead of 11 with 64 entries.  Whole calls:
+// 16,128 points 317 -> 272 us, 64,000 points 4.05 -> 3.76 ms, masked 4.46 -> 3.99 ms (with ln 2 in one word, one FMA
+// less, 268 us, 3.70 and 3.94 ms, and every logarithm off by 1.2e-17 times its exponent).  Smaller workgroups keep the
+// 64 entries: forming
 // 1024 costs them more than it saves, and the table keeps wavefronts off the compute unit (64 threads, 64,000 points:
 // 5.17 -> 5.63 ms).
 constexpr bool big_table(int prec, int threads) { return prec == P64 && threads >= 256; }

@@ -792,7 +792,7 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
         const double rx = tx[k] - sr.x;
         const double ry = ty[k] - sr.y;
         const double q = fma(ry, ry, rx * rx);
-        const double l = neg_half_log(q, ltab);
+        const double l = neg_half_log<true>(q, ltab);
         const double rho = recip(q);
         const double t = rx * rho, u = ry * rho;
         const double A = fma(rx, t, l), B = fma(ry, u, l), c = ry * t;
@@ -1723,7 +1723,7 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
         const double rx = tx[k] - sr.x;
         const double ry = ty[k] - sr.y;
         const double q = fma(ry, ry, rx * rx);
-        const double l = neg_half_log(q, ltab);
+        const double l = neg_half_log<true>(q, ltab);
         const double rho = recip(q);
         const double t = rx * rho, u = ry * rho;
         const double e = rx * t;

@@ -1220,7 +1220,7 @@ __device__ __forceinline__ int leaf_of_item(const int32_t* __restrict__ wstart, 
 // terms of the leaf's local expansion (group g the powers g, g + 8, ...: Horner in zeta^8, then zeta^g); the groups'
 // sums are added at the end.  The three leaves of a column are one run of the leaf order, and the three runs are
 // staged as one list, 64 records at a time with the next 64 loading meanwhile.  Two targets per lane use each record
-// read from LDS twice.  What bounds it is float64 VALU issue, 30 instructions per (target, source).
+// read from LDS twice.  What bounds it is float64 VALU issue, 31 instructions per (target, source).
 // 2000 x 128, order 30: 263 -> 187 us (160 at one instruction per 4 cycles).
 constexpr int kFmmT = 2;
 constexpr int kFmmLanes = 8;
