@@ -1239,7 +1239,7 @@ __global__ __launch_bounds__(64 * kFmmWaves) void k_fmm_eval(const double4* __re
                                                              const double2* __restrict__ tab, double scale,
                                                              double* __restrict__ out) {
   __shared__ double2 ltab[kHalfLogTab];
-  // per wavefront: the local expansion (3 (p + 1) <= 147 entries), then 64 source records and ids
+  // per wavefront: 64 source records and ids, then the local expansion (3 (p + 1) <= 147 entries)
   __shared__ double2 stage[kFmmWaves][3 * 64];
   for (int e = threadIdx.x; e < kHalfLogTab; e += 64 * kFmmWaves) ltab[e] = tab[e];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1288,37 +1288,6 @@ __global__ __launch_bounds__(64 * kFmmWaves) void k_fmm_eval(const double4* __re
     vi[k] = svid[sl];
     ux[k] = uy[k] = 0.0;
   }
-  // the leaf's local expansion: u += -A(zeta)/2 - conj(B(zeta))/2 + zeta conj(C(zeta))/2, linear in the terms
-  if (depth >= 2) {
-    const int np = p + 1;
-    const double2* lb = loc + (level_box_base(depth) + (size_t)leaf) * 3 * np;
-#pragma unroll
-    for (int u = 0; u < 3; ++u)
-      if (lane + 64 * u < 3 * np) cf[lane + 64 * u] = lb[lane + 64 * u];
-    wave_sync();
-    const double2 c = box_center(*geom, n, ix, iy);
-    const int k1 = grp + kFmmGroups * ((p - grp) / kFmmGroups);  // highest power of the group (if grp <= p)
-#pragma unroll
-    for (int k = 0; k < kFmmT; ++k) {
-      const double2 zt = make_double2(zx[k] - c.x, zy[k] - c.y);
-      const double2 z2 = cmul(zt, zt), z4 = cmul(z2, z2), z8 = cmul(z4, z4);
-      double2 zg = (grp & 1) ? zt : make_double2(1.0, 0.0);
-      if (grp & 2) zg = cmul(zg, z2);
-      if (grp & 4) zg = cmul(zg, z4);
-      double2 A = make_double2(0.0, 0.0), B = A, C = A;
-      if (grp <= p)
-        for (int q = k1; q >= 0; q -= kFmmGroups) {
-          A = cfma(A, z8, cf[q]);
-          B = cfma(B, z8, cf[np + q]);
-          C = cfma(C, z8, cf[2 * np + q]);
-        }
-      A = cmul(A, zg);
-      B = cmul(B, zg);
-      C = cmul(C, zg);
-      ux[k] += -0.5 * A.x - 0.5 * B.x + 0.5 * (zt.x * C.x + zt.y * C.y);
-      uy[k] += -0.5 * A.y + 0.5 * B.y + 0.5 * (zt.y * C.x - zt.x * C.y);
-    }
-  }
   // the 3 x 3 leaves directly, own vesicle skipped
   for (int c0 = 0; c0 < nsrc; c0 += 64) {
     const int cnt = min(64, nsrc - c0);
@@ -1344,6 +1313,39 @@ __global__ __launch_bounds__(64 * kFmmWaves) void k_fmm_eval(const double4* __re
           ux[k] = fma(l, s.z, fma(t, rx, ux[k]));
           uy[k] = fma(l, s.w, fma(t, ry, uy[k]));
         }
+    }
+  }
+  // the leaf's local expansion: u += -A(zeta)/2 - conj(B(zeta))/2 + zeta conj(C(zeta))/2, linear in the terms;
+  // after the direct part, whose many terms would each round at the size of the whole (3 times the error at order 40)
+  if (depth >= 2) {
+    const int np = p + 1;
+    const double2* lb = loc + (level_box_base(depth) + (size_t)leaf) * 3 * np;
+    wave_sync();  // the records are done
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+      if (lane + 64 * u < 3 * np) cf[lane + 64 * u] = lb[lane + 64 * u];
+    wave_sync();
+    const double2 c = box_center(*geom, n, ix, iy);
+    const int k1 = grp + kFmmGroups * ((p - grp) / kFmmGroups);  // highest power of the group (if grp <= p)
+#pragma unroll
+    for (int k = 0; k < kFmmT; ++k) {
+      const double2 zt = make_double2(zx[k] - c.x, zy[k] - c.y);
+      const double2 z2 = cmul(zt, zt), z4 = cmul(z2, z2), z8 = cmul(z4, z4);
+      double2 zg = (grp & 1) ? zt : make_double2(1.0, 0.0);
+      if (grp & 2) zg = cmul(zg, z2);
+      if (grp & 4) zg = cmul(zg, z4);
+      double2 A = make_double2(0.0, 0.0), B = A, C = A;
+      if (grp <= p)
+        for (int q = k1; q >= 0; q -= kFmmGroups) {
+          A = cfma(A, z8, cf[q]);
+          B = cfma(B, z8, cf[np + q]);
+          C = cfma(C, z8, cf[2 * np + q]);
+        }
+      A = cmul(A, zg);
+      B = cmul(B, zg);
+      C = cmul(C, zg);
+      ux[k] += -0.5 * A.x - 0.5 * B.x + 0.5 * (zt.x * C.x + zt.y * C.y);
+      uy[k] += -0.5 * A.y + 0.5 * B.y + 0.5 * (zt.y * C.x - zt.x * C.y);
     }
   }
 #pragma unroll
