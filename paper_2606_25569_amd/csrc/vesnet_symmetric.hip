@@ -707,22 +707,29 @@ __device__ __forceinline__ void fixed_add2(unsigned long long* __restrict__ a, u
   atomicAdd(a + two_p, (unsigned long long)(long long)rint(ldexp(r, S + kLoBits)));
 }
 
-// Start of a float64 call: the accumulator words and marks cleared and the log table built (every workgroup a
-// share), and for a single suspension (M > 0) its exponent (workgroup 0; the vesicles' sums in a fixed order).
+// The accumulator words (4 P) and marks (2 P bytes, padded to words) of a float64 call cleared and its log table built,
+// workgroup b of n of 1024 threads; the last one builds the table.
+struct Sym64Start {
+  unsigned long long* acc;
+  uint32_t* bad;
+  double2* tab;
+  int P;
+};
+__device__ __forceinline__ void sym64_start(const Sym64Start& st, int b, int n) {
+  const int64_t stride = (int64_t)n * 1024, first = b * (int64_t)1024 + threadIdx.x;
+  for (int64_t e = first; e < 4 * (int64_t)st.P; e += stride) st.acc[e] = 0ull;
+  for (int64_t e = first; e < (2 * (int64_t)st.P + 3) / 4; e += stride) st.bad[e] = 0u;
+  if (b == n - 1) st.tab[threadIdx.x] = half_log_entry(threadIdx.x);
+}
+
+// Start of a single suspension's call: the above, and its exponent (workgroup 0; the vesicles' sums in a fixed order).
 // meta[3]: 1 when the bound itself is not finite (then every output is NaN).
 __global__ __launch_bounds__(1024) void k_sym64_init(const double2* __restrict__ vaux,
                                                      const int2* __restrict__ vrange,
-                                                     const double4* __restrict__ rec, int M, int64_t nwords,
-                                                     unsigned long long* __restrict__ acc,
-                                                     uint32_t* __restrict__ bad, int64_t nbad,
-                                                     double2* __restrict__ tab, int32_t* __restrict__ meta) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  for (int64_t e = first; e < nwords; e += stride) acc[e] = 0ull;
-  for (int64_t e = first; e < nbad; e += stride) bad[e] = 0u;
-  // the last workgroup builds the table, the first the exponent (one workgroup does both when it is alone)
-  if (blockIdx.x == gridDim.x - 1) tab[threadIdx.x] = half_log_entry(threadIdx.x);
-  if (blockIdx.x != 0 || M <= 0) return;
+                                                     const double4* __restrict__ rec, int M, Sym64Start st,
+                                                     int32_t* __restrict__ meta) {
+  sym64_start(st, blockIdx.x, gridDim.x);
+  if (blockIdx.x != 0) return;
   __shared__ double s_dsum[16];
   double fa = 0.0;
   for (int v = threadIdx.x; v < M; v += 1024) fa += bound_share(vaux[v].x, vrange[v], rec);
@@ -736,7 +743,7 @@ __global__ __launch_bounds__(1024) void k_sym64_init(const double2* __restrict__
     meta[3] = isfinite(tot) ? 0 : 1;
   }
 }
-static_assert(kSymTab == 1024, "k_sym64_init builds one entry per thread");
+static_assert(kSymTab == 1024, "sym64_start builds one entry per thread");
 
 // LDS of a unit besides the table: source cycles (x, y, F_x, F_y) and vesicle ids, each stored twice, and the
 // wavefronts' column sums, double buffered by chunk.
@@ -1204,7 +1211,8 @@ __global__ __launch_bounds__(256) void k_symb_finish(const unsigned long long* _
 
 // Plan: per suspension stab[s] = (first point, end point, 1 when its bound is not finite, exponent) and its first
 // unit (ns strips per block pair of bp points); ranges of vesicles and of points are made disjoint, so no input
-// can make the units outrun the host's bound.  One workgroup of 1024 threads, in a fixed order.
+// can make the units outrun the host's bound.  One workgroup of 1024 threads, in a fixed order; the others start the
+// call.
 __global__ __launch_bounds__(1024) void k_symb64_plan(const int2* __restrict__ vrange,
                                                       const double2* __restrict__ vaux,
                                                       const double4* __restrict__ rec,
@@ -1212,20 +1220,27 @@ __global__ __launch_bounds__(1024) void k_symb64_plan(const int2* __restrict__ v
                                                       int bp, int ns, int4* __restrict__ stab,
                                                       int32_t* __restrict__ ustart, int32_t* __restrict__ pstart,
                                                       int2* __restrict__ vr, int32_t* __restrict__ meta,
-                                                      int32_t* __restrict__ count) {
+                                                      int32_t* __restrict__ count, Sym64Start start) {
   __shared__ int s_w[16];
+  if (blockIdx.x > 0) {
+    sym64_start(start, blockIdx.x - 1, gridDim.x - 1);
+    return;
+  }
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   disjoint_ranges(
       nsus, s_w,
       [&](int s) { return make_int2(min(max(sus_off[s], 0), M), min(max(sus_off[s + 1], 0), M)); },
       [&](int s, int2 r) { vr[s] = r; });
   __syncthreads();
-  for (int s = wv; s < nsus; s += 16) {  // one wavefront per suspension
+  // a wavefront per suspension, or eight lanes where they hold 16 vesicles or fewer on average (1000 suspensions of four:
+  // the kernel 70 -> 16 us)
+  const int lanes = M > 16 * (int64_t)nsus ? 64 : 8;
+  for (int s = t / lanes; s < nsus; s += 1024 / lanes) {
     const int2 rs = vr[s];
     double fs = 0.0;
-    for (int v = rs.x + lane; v < rs.y; v += 64) fs += bound_share(vaux[v].x, vrange[v], rec);
-    fs = wave_sum_d(fs);
-    if (lane == 0) stab[s] = make_int4(0, 0, isfinite(fs) ? 0 : 1, sym64_exponent(fs));
+    for (int v = rs.x + t % lanes; v < rs.y; v += lanes) fs += bound_share(vaux[v].x, vrange[v], rec);
+    for (int m = lanes / 2; m >= 1; m >>= 1) fs += __shfl_xor(fs, m, 64);
+    if (t % lanes == 0) stab[s] = make_int4(0, 0, isfinite(fs) ? 0 : 1, sym64_exponent(fs));
   }
   __syncthreads();
   disjoint_ranges(
@@ -2107,13 +2122,11 @@ hipError_t launch_batched_symmetric(int T, int grid, int P, int M, const Prepare
 
 int64_t sym64_blocks(int64_t P, int T) { return (P + kSymThreads * T - 1) / (kSymThreads * T); }
 
-// Clears the float64 region's sums and marks and builds its table (and the exponent of a single suspension).
-static void launch_sym64_init(const PreparedView& pv, int M, int P, const Symmetric64View& sv, hipStream_t st) {
-  const int64_t words = 4 * (int64_t)P, marks = ((int64_t)2 * P + 3) / 4;
-  const int grid = (int)std::min<int64_t>((words + 1023) / 1024, 1024);
-  hipLaunchKernelGGL(k_sym64_init, dim3(grid), dim3(1024), 0, st, pv.vaux, pv.vrange,
-                     static_cast<const double4*>(pv.rec), M, words, sv.acc,
-                     reinterpret_cast<uint32_t*>(sv.bad), marks, sv.tab, sv.meta);
+// Workgroups that start a float64 call.
+static int sym64_start_grid(int P) { return (int)std::min<int64_t>((4 * (int64_t)P + 1023) / 1024, 1024); }
+
+static Sym64Start sym64_start_of(const Symmetric64View& sv, int P) {
+  return {sv.acc, reinterpret_cast<uint32_t*>(sv.bad), sv.tab, P};
 }
 
 int64_t symb64_max_units(int P, int S, int T, int ns) {
@@ -2140,10 +2153,10 @@ hipError_t launch_batched_symmetric64(int T, int ns, int grid, int P, int M, con
   if (P == 0 || S == 0) return hipSuccess;
   if (grid < 1 || ns < 1 || kRows % ns != 0) return hipErrorInvalidValue;
   hipStream_t st = Sx_(stream);
-  launch_sym64_init(pv, 0, P, sv, st);
   const double4* rec = static_cast<const double4*>(pv.rec);
-  hipLaunchKernelGGL(k_symb64_plan, dim3(1), dim3(1024), 0, st, pv.vrange, pv.vaux, rec, sus_off, M, P, S,
-                     kSymThreads * T, ns, bv.stab, bv.ustart, bv.pstart, bv.vr, sv.meta, bv.count);
+  hipLaunchKernelGGL(k_symb64_plan, dim3(1 + sym64_start_grid(P)), dim3(1024), 0, st, pv.vrange, pv.vaux, rec, sus_off, M,
+                     P, S, kSymThreads * T, ns, bv.stab, bv.ustart, bv.pstart, bv.vr, sv.meta, bv.count,
+                     sym64_start_of(sv, P));
   if (T == 1)
     hipLaunchKernelGGL(k_symb64_main<1>, dim3(grid), dim3(kSymThreads), 0, st, P, ns, rec, pv.vid, sv.tab, bv.stab,
                        bv.ustart, S, sv.meta, bv.count, sv.acc, sv.bad);
@@ -2163,7 +2176,8 @@ hipError_t launch_forward_symmetric64(int T, int ns, int P, int M, const Prepare
   if (P == 0) return hipSuccess;
   if (ns < 1 || kRows % ns != 0) return hipErrorInvalidValue;
   hipStream_t st = Sx_(stream);
-  launch_sym64_init(pv, M, P, sv, st);
+  hipLaunchKernelGGL(k_sym64_init, dim3(sym64_start_grid(P)), dim3(1024), 0, st, pv.vaux, pv.vrange,
+                     static_cast<const double4*>(pv.rec), M, sym64_start_of(sv, P), sv.meta);
   const int64_t units = sym_units(sym64_blocks(P, T)) * ns;
   if (units > (int64_t)INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)units);
