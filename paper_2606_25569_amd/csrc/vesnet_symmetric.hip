@@ -213,7 +213,11 @@ __global__ __launch_bounds__(256) void k_sym_cycles(const int4* __restrict__ cyc
 // also the records of g, and the cycle sums are those of g; else of F = w f, and the whole prepared region is left, for
 // later evaluations from it.
 // 504 x 32: three launches -> one, 104.4 -> 99.9 us a call; 512 x 64 and its adjoint: nine -> two, 932 -> 914 us.
+// Latency bounds it, so a wavefront takes 256 points at a time (64 at a time: 500 x 16 and one vesicle of 20,000 points
+// 531 us a call, now 499).
 constexpr int kSymFused = 1024;
+
+constexpr int kPrepStep = 256;  // points of a step, four per lane
 
 template <bool kAdjoint>
 __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ pts, const double* __restrict__ f,
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
                                                     int4* __restrict__ cyc, double2* __restrict__ ccyc,
                                                     int32_t* __restrict__ meta, unsigned long long* __restrict__ zero0,
                                                     unsigned long long* __restrict__ zero1) {
-  __shared__ double2 carried[64];
+  __shared__ double2 carried[kPrepStep];
   float4* recF = static_cast<float4*>(pv.rec);
   const int lane = threadIdx.x, v = blockIdx.x;
   const auto clamped = [&](int u) { return min(max(off[u], 0), P); };
@@ -237,6 +241,7 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
   for (int m = 32; m >= 1; m >>= 1) first += __shfl_xor(first, m, 64);
   const int j0 = clamped(v), j1 = max(j0, clamped(v + 1)), n = j1 - j0;
   double sx = 0.0, sy = 0.0, bx = 0.0, by = 0.0, sa = 0.0, sw = 0.0;
+#pragma unroll 4
   for (int j = j0 + lane; j < j1; j += 64) {
     const double wj = w[j];
     sx += pts[j];
@@ -255,28 +260,31 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
   if constexpr (!kAdjoint) sw = wave_sum_d(sw);
   const double cx = n > 0 ? sx / n : 0.0, cy = n > 0 ? sy / n : 0.0;
   double r2 = 0.0;
-  for (int c0 = j0; c0 < j1; c0 += 64) {
-    const int j = c0 + lane;
+  for (int c0 = j0; c0 < j1; c0 += kPrepStep) {
     wave_sync();  // the previous points are done
-    if (j < j1) {
-      const double wj = w[j];
-      const double x = pts[j], y = pts[P + j];
-      const double ex = wj * f[j], ey = wj * f[P + j];
-      r2 = fmax(r2, (x - cx) * (x - cx) + (y - cy) * (y - cy));
-      recF[j] = make_float4((float)(x - cx), (float)(y - cy), (float)ex, (float)ey);
-      if constexpr (kAdjoint) {
-        const double gx = g[j], gy = g[P + j];
-        recG[j] = make_float4((float)(x - cx), (float)(y - cy), (float)gx, (float)gy);
-        carried[lane] = make_double2(gx, gy);
-      } else {
-        carried[lane] = make_double2(ex, ey);
-        pv.f64[j] = make_double2(ex, ey);
-        pv.vid[j] = v;
+#pragma unroll
+    for (int q = 0; q < kPrepStep; q += 64) {
+      const int j = c0 + q + lane;
+      if (j < j1) {
+        const double wj = w[j];
+        const double x = pts[j], y = pts[P + j];
+        const double ex = wj * f[j], ey = wj * f[P + j];
+        r2 = fmax(r2, (x - cx) * (x - cx) + (y - cy) * (y - cy));
+        recF[j] = make_float4((float)(x - cx), (float)(y - cy), (float)ex, (float)ey);
+        if constexpr (kAdjoint) {
+          const double gx = g[j], gy = g[P + j];
+          recG[j] = make_float4((float)(x - cx), (float)(y - cy), (float)gx, (float)gy);
+          carried[q + lane] = make_double2(gx, gy);
+        } else {
+          carried[q + lane] = make_double2(ex, ey);
+          pv.f64[j] = make_double2(ex, ey);
+          pv.vid[j] = v;
+        }
       }
     }
     wave_sync();
     const int k0 = c0 + kRing * lane, cnt = min(kRing, j1 - k0), e = first + (k0 - j0) / kRing;
-    if (lane < 64 / kRing && cnt > 0 && e < ncyc_max) {
+    if (lane < kPrepStep / kRing && cnt > 0 && e < ncyc_max) {
       double tx = 0.0, ty = 0.0;
       for (int m = 0; m < cnt; ++m) {
         const double2 F = carried[kRing * lane + m];
@@ -2205,7 +2213,10 @@ hipError_t launch_forward_symmetric(int T, int ns, int P, int M, const PreparedV
   const int cb = sym_cycles_per_block(T);
   const int ncyc_max = (int)sym_max_cycles(P, M);
   const int nb_max = (int)sym_max_blocks(P, M, T);
-  const bool fused = in != nullptr && sym_fused(M);
+  // a wavefront per vesicle is a serial chain: with few large vesicles the separate kernels, whose cycle sums and
+  // clearing use the whole chip, are faster (4 x 16,384 1.26 ms against 1.29, 16 x 2,048 359 us against 357; the adjoint,
+  // which they prepare twice, gains at every size)
+  const bool fused = in != nullptr && sym_fused(M) && P <= 2048 * (int64_t)M;
   if (fused) {
     hipLaunchKernelGGL(k_sym_prepare<false>, dim3(M), dim3(64), 0, st, in->pts, in->f, in->w, nullptr, in->off, M, P, cb,
                        ncyc_max, pv, nullptr, sv.cyc, sv.fcyc, sv.meta, sv.acc, nullptr);
