@@ -38,9 +38,22 @@ constexpr float kHalfLn2 = -0.34657359027997265471f;  // -(1/2) ln 2 : converts 
 // threads, 64,000 points: 5.17 -> 5.63 ms).
 constexpr bool big_table(int prec, int threads) { return prec == P64 && threads >= 256; }
 
-// Records per LDS tile (with the big table beside it 16 KB).
+// Records per LDS tile (with the big table beside it 15.75 KB, so that five workgroups fit a compute unit also where they
+// keep a few words more).
 template <int PREC, int B>
-constexpr int kTile = big_table(PREC, B) ? 512 : 1024;
+constexpr int kTile = big_table(PREC, B) ? 504 : 1024;
+
+// The table's entries, and its forming by a workgroup of B threads, which synchronises before its first use.
+template <int PREC, int B>
+constexpr int kTabEntries = PREC != P64 ? 1 : big_table(PREC, B) ? kHalfLogTab : kLogTab;
+template <int PREC, int B>
+__device__ __forceinline__ void form_table(double2* __restrict__ ltab) {
+  if constexpr (big_table(PREC, B)) {
+    for (int e = threadIdx.x; e < kHalfLogTab; e += B) ltab[e] = half_log_entry(e);
+  } else if constexpr (PREC == P64) {
+    if (threadIdx.x < kLogTab) ltab[threadIdx.x] = log_tab_entry(threadIdx.x);
+  }
+}
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -165,13 +178,16 @@ struct Acc {
 //   features (1, s_x, s_y) and (F_x, F_y): one v_mfma_f32_4x4x1f32 each, with the features
 //   in the A operand (lane 4b+m of block b carries feature m) and the per-target value in
 //   the B operand, so lane l's accumulator row m is feature m's sum for its own target.
-template <int PREC, int T, int B, bool NEED_V, bool NEED_GRAD, bool LDS, bool NEAR = false, bool MF = false>
+// ltab: float64's table in LDS; FORM: formed here (else by the caller, for several calls).
+template <int PREC, int T, int B, bool NEED_V, bool NEED_GRAD, bool LDS, bool NEAR = false, bool MF = false,
+          bool FORM = true>
 __device__ __forceinline__ void gather(int i_begin, int i_end, int v_begin, int v_end, const double* __restrict__ pts,
                                        const double* __restrict__ avec, const double* __restrict__ awts, int P,
                                        const int32_t* __restrict__ vid, const int2* __restrict__ vrange,
                                        const double4* __restrict__ vtab,
-                                       const typename Real<PREC>::R* __restrict__ rec, Acc<PREC> (&acc)[T],
-                                       int (&idx)[T], bool (&valid)[T], NearOut near = NearOut{}) {
+                                       const typename Real<PREC>::R* __restrict__ rec, double2* __restrict__ ltab,
+                                       Acc<PREC> (&acc)[T], int (&idx)[T], bool (&valid)[T],
+                                       NearOut near = NearOut{}) {
   using real = typename Real<PREC>::T;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -207,15 +223,9 @@ __device__ __forceinline__ void gather(int i_begin, int i_end, int v_begin, int 
   using Rec = typename Real<PREC>::R;
   __shared__ Rec tile[LDS ? kTile<PREC, B> : 1];
   int tile_lo = 0, tile_hi = 0;
-  // float64: the logarithm's table
   constexpr bool kBig = big_table(PREC, B);
-  __shared__ double2 ltab[PREC == P64 && NEED_V ? (kBig ? kHalfLogTab : kLogTab) : 1];
-  if constexpr (PREC == P64 && NEED_V) {
-    if constexpr (kBig) {
-      for (int e = threadIdx.x; e < kHalfLogTab; e += B) ltab[e] = half_log_entry(e);
-    } else if (threadIdx.x < kLogTab) {
-      ltab[threadIdx.x] = log_tab_entry(threadIdx.x);
-    }
+  if constexpr (PREC == P64 && NEED_V && FORM) {
+    form_table<PREC, B>(ltab);
     __syncthreads();
   }
 
@@ -460,8 +470,9 @@ __global__ __launch_bounds__(B) void k_forward(const double* __restrict__ tg, in
   Acc<PREC> acc[T];
   int idx[T];
   bool valid[T];
+  __shared__ double2 ltab[kTabEntries<PREC, B>];
   gather<PREC, T, B, true, false, LDS, false, MF>(i_begin, i_end, v_begin, v_end, tg, nullptr, nullptr, P, vid,
-                                                  vrange, vtab, rec, acc, idx, valid);
+                                                  vrange, vtab, rec, ltab, acc, idx, valid);
 #pragma unroll
   for (int k = 0; k < T; ++k) {
     if (!valid[k]) continue;
@@ -493,8 +504,9 @@ __global__ __launch_bounds__(B) void k_forward_near(const double* __restrict__ t
   Acc<PREC> acc[T];
   int idx[T];
   bool valid[T];
+  __shared__ double2 ltab[kTabEntries<PREC, B>];
   gather<PREC, T, B, true, false, LDS, true>(i_begin, i_end, v_begin, v_end, tg, nullptr, nullptr, P, vid, vrange,
-                                             vtab, rec, acc, idx, valid, near);
+                                             vtab, rec, ltab, acc, idx, valid, near);
 #pragma unroll
   for (int k = 0; k < T; ++k) {
     if (!valid[k]) continue;
@@ -880,6 +892,8 @@ __global__ __launch_bounds__(B) void k_forward_batched(const double* __restrict_
                                                        const int32_t* __restrict__ item_start,
                                                        int32_t* __restrict__ counter, double* __restrict__ out) {
   __shared__ int32_t s_item;
+  __shared__ double2 ltab[kTabEntries<PREC, B>];
+  form_table<PREC, B>(ltab);  // once: formed again for every item it cost 7% (32 suspensions of 80 x 64)
   const int tile = B * T;
   const int total = item_start[S];
   for (;;) {
@@ -907,8 +921,8 @@ __global__ __launch_bounds__(B) void k_forward_batched(const double* __restrict_
     Acc<PREC> acc[T];
     int idx[T];
     bool valid[T];
-    gather<PREC, T, B, true, false, LDS>(i_begin, i_end, vb, ve, tg, nullptr, nullptr, P, vid, vrange, vtab, rec,
-                                         acc, idx, valid);
+    gather<PREC, T, B, true, false, LDS, false, false, false>(i_begin, i_end, vb, ve, tg, nullptr, nullptr, P, vid,
+                                                              vrange, vtab, rec, ltab, acc, idx, valid);
 #pragma unroll
     for (int q = 0; q < T; ++q) {
       if (!valid[q]) continue;
@@ -941,7 +955,7 @@ __global__ __launch_bounds__(B) void k_bwd_targets(const double* __restrict__ tg
   int idx[T];
   bool valid[T];
   gather<PREC, T, B, false, true, true>(i_begin, i_end, v_begin, v_end, tg, gout, nullptr, P, vid, vrange, vtab,
-                                         rec, acc, idx, valid);
+                                        rec, nullptr, acc, idx, valid);
 #pragma unroll
   for (int k = 0; k < T; ++k) {
     if (!valid[k]) continue;
@@ -995,8 +1009,9 @@ __global__ __launch_bounds__(B) void k_bwd_sources(const double* __restrict__ sr
   Acc<PREC> acc[T];
   int idx[T];
   bool valid[T];
-  gather<PREC, T, B, true, true, true>(i_begin, i_end, v_begin, v_end, src, f, w, P, vid, vrange, vtab, rec, acc,
-                                        idx, valid);
+  __shared__ double2 ltab[kTabEntries<PREC, B>];
+  gather<PREC, T, B, true, true, true>(i_begin, i_end, v_begin, v_end, src, f, w, P, vid, vrange, vtab, rec, ltab, acc,
+                                       idx, valid);
 #pragma unroll
   for (int k = 0; k < T; ++k) {
     if (!valid[k]) continue;
