@@ -382,8 +382,10 @@ VESNET_API int vesnet_farfield_fmm_nearmasked(const double* points, const double
      queues, one per XCD, drained through counters in the workspace by
      blocks_per_cu workgroups per compute unit (0: as many as fit).  The results
      are bitwise reproducible (the fixed-point sums do not depend on the order),
-     and a compensated suspension's output equals that of a single symmetric
-     call with the same T bit for bit.
+     and a compensated suspension's output equals, bit for bit, that of a single
+     call with pair_form 2 and this T as its targets_per_thread.  (A single call
+     that leaves targets_per_thread to the library may cut block pairs into
+     strips, whose row sums round once more each at the fixed-point resolution.)
   * direct (every other call, or pair_form 1): work items (suspension, block
      of targets) ordered largest suspension first on the device and handed
      out through a counter in the workspace.
