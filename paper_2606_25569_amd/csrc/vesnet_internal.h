@@ -81,47 +81,29 @@ __device__ __forceinline__ double2 log_tab_entry_n(int i) {
   return make_double2(a2, -log_pos(a2));
 }
 
-// Natural log of a finite q > 0 with an N-entry table: q = mant 2^e, mant in [1/2, 1); r = mant (2a) - 1
-// (exact product, one rounding), |r| <= 1/(2Nc) + c/(16N) (c in [1, 2), to first order), ln mant =
-// -ln 2a + log1p(r), log1p by its series; ln 2 in a high and a low part as in log_pos.  The series stops
-// where the next term is below 5e-18: through r^7 for N = 64 (|r| < 0.0089), through r^5 for N = 512
-// (|r| < 0.0012).  Both forms are accurate in absolute terms (near q = 1 the result is a difference of
-// terms of order ln 2, and the table entry alone carries up to about 5e-17).  The 512-entry form adds
-// e ln 2 with one FMA and ln 2 rounded to a double, an extra absolute error of at most |e| 2.3e-17 (a
-// quarter of an ulp of ln q at |e| = 20).  About 18 (N = 64) or 15 (N = 512) operations, no division.
-template <int N>
-__device__ __forceinline__ double log_reduced_n(double q, const double2* __restrict__ tab) {
-  static_assert(N == 64 || N == 512, "series lengths are set for 64 and 512 entries");
-  constexpr int kShift = N == 64 ? 14 : 11;  // the top log2(N) mantissa bits end at bit 19 of the high word
+// Natural log of a finite q > 0 with a 64-entry table (one entry per lane of a wavefront): q = mant 2^e, mant in
+// [1/2, 1); r = mant (2a) - 1 (exact product, one rounding), |r| <= 1/(2 64 c) + c/(16 64) < 0.0089 (c in [1, 2), to
+// first order), ln mant = -ln 2a + log1p(r), log1p by its series through r^7 (the next term is below 5e-18); ln 2 in a
+// high and a low part as in log_pos.  Accurate in absolute terms (near q = 1 the result is a difference of terms of
+// order ln 2, and the table entry alone carries up to about 5e-17).  About 18 operations, no division.
+constexpr int kLogTab = 64;
+__device__ __forceinline__ double2 log_tab_entry(int i) { return log_tab_entry_n<kLogTab>(i); }
+__device__ __forceinline__ double log_reduced(double q, const double2* __restrict__ tab) {
   constexpr double kLn2Hi = 6.93147180369123816490e-01;
   constexpr double kLn2Lo = 1.90821492927058770002e-10;
   int e;
   const double mant = frexp(q, &e);
-  const int i = (__double2hiint(mant) >> kShift) & (N - 1);  // in range for every input
-  const double2 t = tab[i];
+  const double2 t = tab[(__double2hiint(mant) >> 14) & (kLogTab - 1)];  // the top mantissa bits: in range for every input
   const double r = fma(mant, t.x, -1.0);
-  double pol;
-  if constexpr (N == 64) {
-    pol = 1.0 / 7.0;
-    pol = fma(pol, r, -1.0 / 6.0);
-    pol = fma(pol, r, 1.0 / 5.0);
-  } else {
-    pol = 1.0 / 5.0;
-  }
+  double pol = 1.0 / 7.0;
+  pol = fma(pol, r, -1.0 / 6.0);
+  pol = fma(pol, r, 1.0 / 5.0);
   pol = fma(pol, r, -1.0 / 4.0);
   pol = fma(pol, r, 1.0 / 3.0);
   pol = fma(pol, r, -0.5);
   pol = fma(pol, r, 1.0);
   const double ed = (double)e;
-  if constexpr (N == 64) return fma(ed, kLn2Hi, fma(ed, kLn2Lo, fma(r, pol, t.y)));
-  return fma(ed, 0.69314718055994530942, fma(r, pol, t.y));
-}
-
-// The 64-entry form (one entry per lane of a wavefront), used by the direct float64 kernel and the trees.
-constexpr int kLogTab = 64;
-__device__ __forceinline__ double2 log_tab_entry(int i) { return log_tab_entry_n<kLogTab>(i); }
-__device__ __forceinline__ double log_reduced(double q, const double2* __restrict__ tab) {
-  return log_reduced_n<kLogTab>(q, tab);
+  return fma(ed, kLn2Hi, fma(ed, kLn2Lo, fma(r, pol, t.y)));
 }
 
 // The 1024-entry form of -1/2 ln q, the factor of the Stokeslet's log term (the symmetric float64 kernels and the

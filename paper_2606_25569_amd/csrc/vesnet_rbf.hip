@@ -579,14 +579,11 @@ __global__ __launch_bounds__(kEB) void k_rbf_eval_near(const double* __restrict_
 
 }  // namespace
 
-static size_t rbf_slot_tile_doubles(int nmax) {
-  const int nb = (5 * nmax + kT - 1) / kT;
-  return (size_t)nb * (nb + 3) / 2 * (kT * kT);
-}
-
+// Doubles of a vesicle's slot.  The lower tiles take nb (nb + 1) / 2 of them; nb tiles and two vectors more are the size
+// that callers of the C interface have met, and it stays what a workspace is measured by.
 size_t rbf_slot_doubles(int nmax) {
   const int nb = (5 * nmax + kT - 1) / kT;
-  return rbf_slot_tile_doubles(nmax) + (size_t)2 * nb * kT;
+  return (size_t)nb * (nb + 3) / 2 * (kT * kT) + (size_t)2 * nb * kT;
 }
 
 hipError_t launch_rbf_fit(const double* layers, const double* vel, const double* w, const int32_t* off, int M, int P,

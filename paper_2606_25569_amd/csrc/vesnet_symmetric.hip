@@ -97,7 +97,9 @@ __device__ __forceinline__ double wave_sum_d(double x) {
   return x;
 }
 
-// Fixed-point exponent of partial sums bounded by 520 sum |F|_1 (see k_sym_plan).
+// Fixed-point exponent of partial sums.  Every term of every one is at most (|ln q|/2 + 1) |F|_1 <= 520 |F|_1 in magnitude
+// (log2|r'|^2 within the float32 range, |k| <= 60), so with 520 sum |F|_1 < 2^(62 - S) the fixed-point integers stay below
+// 2^62.
 __device__ __forceinline__ int sym_exponent(double fsum) {
   const double bound = 520.0 * fsum;
   if (!(bound > 0.0 && isfinite(bound))) return 0;
@@ -171,17 +173,7 @@ __global__ __launch_bounds__(1024) void k_sym_plan(const int2* __restrict__ vran
     for (int k = 0; k < 16; ++k) tot += s_dsum[k];
     const int ncyc = min(run, ncyc_max);
     meta[0] = ncyc;
-    // Every term of every partial sum is at most (|ln q|/2 + 1) |F|_1 <= 520 |F|_1 in magnitude
-    // (log2|r'|^2 within the float32 range, |k| <= 60), so every partial sum of the fixed-point
-    // integers stays below 2^62.
-    const double bound = 520.0 * tot;
-    int S = 0;
-    if (bound > 0.0 && isfinite(bound)) {
-      int e;
-      frexp(bound, &e);  // bound < 2^e
-      S = 62 - e;
-    }
-    meta[1] = S;
+    meta[1] = sym_exponent(tot);
     meta[2] = (ncyc + cb - 1) / cb;
   }
 }
@@ -311,11 +303,6 @@ __global__ __launch_bounds__(64) void k_sym_prepare(const double* __restrict__ p
   }
 }
 
-// The unit (row block bx, column block by) of this workgroup, false when it has none.  Units are the
-// pairs {bx, bx + d mod nb}, d = 0 .. nb/2 (for even nb, d = nb/2 only for bx < nb/2), numbered row
-// block by row block.  Workgroups are handed to the eight XCDs in turn (workgroup g to XCD g mod 8), so
-// each XCD is given one contiguous range of that numbering: its concurrent units share a row block and
-// a window of about nb/2 consecutive column blocks, which stays in the XCD's own L2.
 // Unit number L (0 <= L < nb (nb + 1) / 2) of nb blocks, row block by row block, as the pair {bx, by}.
 __device__ __forceinline__ void sym_unit_blocks(int nb, int L, int& bx, int& by) {
   const int h = nb >> 1;
@@ -351,8 +338,11 @@ __device__ __forceinline__ int vesicle_cut(const int4* __restrict__ cyc, int c0,
   return c1;
 }
 
-// The unit of this workgroup among the nb blocks' pairs, each cut into ns strips of the column block: row block
-// bx, column block by, and the strip's cycles [s0, s1) of block by's [by cb, min(ncyc, (by + 1) cb)); false when
+// The unit of this workgroup among the nb blocks' pairs, each cut into ns strips of the column block.  Units are the
+// pairs {bx, bx + d mod nb}, d = 0 .. nb/2 (for even nb, d = nb/2 only for bx < nb/2), numbered row block by row block.
+// Workgroups are handed to the eight XCDs in turn (workgroup g to XCD g mod 8), so each XCD is given one contiguous range
+// of that numbering: its concurrent units share a row block and a window of about nb/2 consecutive column blocks, which
+// stays in the XCD's own L2.  Row block bx, column block by, and the strip's cycles [s0, s1) of block by's [by cb, min(ncyc, (by + 1) cb)); false when
 // it has none.  Strips end at vesicle starts, so that the float32 partial sums of a (target, vesicle) are the
 // same for every ns (a vesicle longer than a strip leaves the following ones empty).
 __device__ __forceinline__ bool sym_unit(int nb, int ns, int cb, int ncyc, const int4* __restrict__ cyc, int& bx,
@@ -615,7 +605,7 @@ __device__ __forceinline__ void sym_eval_unit(int P, const double4* __restrict__
   }
 }
 
-// The fixed-point exponent (see k_sym_plan) from the vesicles' sums of |F|_1, by a whole workgroup of kSymThreads.
+// The fixed-point exponent (see sym_exponent) from the vesicles' sums of |F|_1, by a whole workgroup of kSymThreads.
 __device__ __forceinline__ int vesicles_exponent(const double2* __restrict__ vaux, int M) {
   __shared__ double s_sum[kSymWaves];
   double a = 0.0;
@@ -1091,16 +1081,7 @@ __global__ __launch_bounds__(1024) void k_symb_plan(const int2* __restrict__ vra
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) cnt += __shfl_xor(cnt, m, 64);
     fs = wave_sum_d(fs);
-    if (lane == 0) {
-      const double bound = 520.0 * fs;  // as in k_sym_plan
-      int S = 0;
-      if (bound > 0.0 && isfinite(bound)) {
-        int e;
-        frexp(bound, &e);
-        S = 62 - e;
-      }
-      stab[s] = make_int4(cnt, 0, (cnt + cb - 1) / cb, S);
-    }
+    if (lane == 0) stab[s] = make_int4(cnt, 0, (cnt + cb - 1) / cb, sym_exponent(fs));
   }
   __syncthreads();
   // exclusive scans over the suspensions: first cycle and first unit

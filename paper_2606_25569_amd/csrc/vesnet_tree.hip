@@ -1780,7 +1780,7 @@ __global__ __launch_bounds__(64) void k_fmm_near_status(const int32_t* __restric
 }  // namespace
 
 // Workspace layout shared by the size queries and the launchers; the fast multipole method adds the
-// local expansions (3 rows per box) and the binomial table.
+// local expansions (3 rows per box) and the evaluation's log table.
 struct TreeLayout {
   size_t geom, part, leafid, vid, perm, srec, svid, counts, starts, wstart, bcount, mom, loc, ltab, h2, flag,
       total;
