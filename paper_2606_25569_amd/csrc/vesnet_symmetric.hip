@@ -648,7 +648,10 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_main(
 // consecutive points, ring cycles 16 consecutive points whatever vesicles they belong to (only the last cycle
 // of a suspension is padded; cut at the vesicles, 17 to 63 points each, 47% of the pair evaluations were
 // padding), rows are summed chunk by chunk of 64 columns whatever the vesicles (summed over a whole unit in one chain
-// they rounded 1.4 times as much in all), and the block table needs no plan kernel.  The
+// they rounded 1.4 times as much in all), the matrix's diagonal terms apart from the others (over a vesicle without net
+// force the partial sums are tens of times its terms, and both FMAs of a pair rounded at their size: 1.2 to 1.4 times
+// the error for the same time; four pairs summed by themselves first halve it, for 2.7% more), and the block table needs
+// no plan kernel.  The
 // own vesicle is dropped pair by pair, but only in units whose row and column points share a vesicle (ids are
 // compared at both ends; at most the diagonal and the neighbouring block pairs): there the accumulations are
 // selected, so that not even a non-finite value of an own-vesicle pair enters.
@@ -767,7 +770,8 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
   // vesicle ids do not decrease: the two point ranges share a vesicle when their id ranges meet
   const bool masked = diag || !(vid[r1 - 1] < vid[c0] || vid[c1 - 1] < vid[r0]);
 
-  double tx[T], ty[T], fx[T], fy[T], ax[T], ay[T], sx[T], sy[T];  // a: sums of a chunk of columns, s: of all
+  // a and b: sums of a chunk of columns, of the matrix's diagonal terms and of the others; s: of all
+  double tx[T], ty[T], fx[T], fy[T], ax[T], ay[T], bx[T], by[T], sx[T], sy[T];
   int tv[T];
 #pragma unroll
   for (int k = 0; k < T; ++k) {
@@ -779,7 +783,7 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
     ty[k] = t.y;
     fx[k] = t.z;
     fy[k] = t.w;
-    ax[k] = ay[k] = sx[k] = sy[k] = 0.0;
+    ax[k] = ay[k] = bx[k] = by[k] = sx[k] = sy[k] = 0.0;
   }
 
   auto ring = [&](int buf, int cc, auto mask_tag) __attribute__((always_inline)) {
@@ -801,14 +805,16 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
         const double rho = recip(q);
         const double t = rx * rho, u = ry * rho;
         const double A = fma(rx, t, l), B = fma(ry, u, l), c = ry * t;
-        const double nax = fma(A, sr.z, fma(c, sr.w, ax[k]));
-        const double nay = fma(c, sr.z, fma(B, sr.w, ay[k]));
+        const double nax = fma(A, sr.z, ax[k]), nbx = fma(c, sr.w, bx[k]);
+        const double nay = fma(B, sr.w, ay[k]), nby = fma(c, sr.z, by[k]);
         const double ncx = fma(A, fx[k], k == 0 ? c * fy[k] : fma(c, fy[k], lcx));
         const double ncy = fma(c, fx[k], k == 0 ? B * fy[k] : fma(B, fy[k], lcy));
         // own-vesicle pairs, and in the diagonal block one of each two orderings (ids do not decrease)
         const bool act = !kMask || (diag ? tv[k] < sv : tv[k] != sv);
         ax[k] = act ? nax : ax[k];
         ay[k] = act ? nay : ay[k];
+        bx[k] = act ? nbx : bx[k];
+        by[k] = act ? nby : by[k];
         lcx = act ? ncx : lcx;
         lcy = act ? ncy : lcy;
       }
@@ -882,9 +888,9 @@ __device__ __forceinline__ void sym64_eval_unit(Sym64Lds& lds, int P, const doub
       for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::false_type{});
 #pragma unroll
     for (int k = 0; k < T; ++k) {
-      sx[k] += ax[k];
-      sy[k] += ay[k];
-      ax[k] = ay[k] = 0.0;
+      sx[k] += ax[k] + bx[k];
+      sy[k] += ay[k] + by[k];
+      ax[k] = ay[k] = bx[k] = by[k] = 0.0;
     }
     stage_store(buf ^ 1, nxt, nv);
     __syncthreads();
@@ -1693,7 +1699,8 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
   const bool masked = diag || !(vid[r1 - 1] < vid[c0] || vid[c1 - 1] < vid[r0]);
 
   double tx[T], ty[T], fx[T], fy[T], gx[T], gy[T], vx[T], vy[T], hx[T], hy[T];
-  double svx[T], svy[T], shx[T], shy[T];  // the sums of all columns; v and h are those of a chunk
+  // the sums of all columns; v, q (the matrix's off-diagonal terms of v) and h are those of a chunk
+  double svx[T], svy[T], shx[T], shy[T], qx[T], qy[T];
   int tv[T];
 #pragma unroll
   for (int k = 0; k < T; ++k) {
@@ -1707,7 +1714,7 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
     fy[k] = t.w;
     gx[k] = in ? g[i] : 0.0;
     gy[k] = in ? g[(size_t)P + i] : 0.0;
-    vx[k] = vy[k] = hx[k] = hy[k] = svx[k] = svy[k] = shx[k] = shy[k] = 0.0;
+    vx[k] = vy[k] = qx[k] = qy[k] = hx[k] = hy[k] = svx[k] = svy[k] = shx[k] = shy[k] = 0.0;
   }
 
   auto ring = [&](int buf, int cc, auto mask_tag) __attribute__((always_inline)) {
@@ -1738,7 +1745,8 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
         const double n = m * (a - b), dm = d * m;
         const double Hx = fma(t, fma(-2.0, b, n), u * dm);
         const double Hy = fma(u, fma(-2.0, a, n), -t * dm);
-        const double nvx = fma(A, sg.x, fma(c, sg.y, vx[k])), nvy = fma(c, sg.x, fma(B, sg.y, vy[k]));
+        const double nvx = fma(A, sg.x, vx[k]), nqx = fma(c, sg.y, qx[k]);
+        const double nvy = fma(B, sg.y, vy[k]), nqy = fma(c, sg.x, qy[k]);
         const double nhx = hx[k] + Hx, nhy = hy[k] + Hy;
         const double nlvx = fma(A, gx[k], k == 0 ? c * gy[k] : fma(c, gy[k], lvx));
         const double nlvy = fma(c, gx[k], k == 0 ? B * gy[k] : fma(B, gy[k], lvy));
@@ -1746,6 +1754,8 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
         const bool act = !kMask || (diag ? tv[k] < sv : tv[k] != sv);
         vx[k] = act ? nvx : vx[k];
         vy[k] = act ? nvy : vy[k];
+        qx[k] = act ? nqx : qx[k];
+        qy[k] = act ? nqy : qy[k];
         hx[k] = act ? nhx : hx[k];
         hy[k] = act ? nhy : hy[k];
         lvx = act ? nlvx : lvx;
@@ -1834,11 +1844,11 @@ __device__ __forceinline__ void adj64_eval_unit(Adj64Lds& lds, int P, const doub
       for (int cc = 0; cc < ncc; ++cc) ring(buf, cc, std::false_type{});
 #pragma unroll
     for (int k = 0; k < T; ++k) {
-      svx[k] += vx[k];
-      svy[k] += vy[k];
+      svx[k] += vx[k] + qx[k];
+      svy[k] += vy[k] + qy[k];
       shx[k] += hx[k];
       shy[k] += hy[k];
-      vx[k] = vy[k] = hx[k] = hy[k] = 0.0;
+      vx[k] = vy[k] = qx[k] = qy[k] = hx[k] = hy[k] = 0.0;
     }
     stage_store(buf ^ 1, nxt);
     __syncthreads();
