@@ -323,7 +323,7 @@ VESNET_API int vesnet_farfield_treecode(const double* points, const double* forc
    Deterministic under the same condition as the treecode.
      arguments, layouts, ownership and errors as vesnet_farfield_treecode;
      workspace : device, vesnet_fmm_workspace_bytes(P, depth, order) bytes (the treecode's plus
-                 3 (order+1) complex numbers per box and a binomial table) */
+                 3 (order+1) complex numbers per box and a logarithm table) */
 /* Default depth of the fast multipole method: leaves of at most about 64 points up to order 32 and 128
    above, where the M2L work (order^2 per pair of boxes) outweighs the direct part (measured best on the
    2000 x 128 and 8000 x 64 suspensions at orders 30 and 40). */

@@ -175,7 +175,7 @@ int sym_strips(int32_t P, int32_t M, int T, int64_t want) {
 
 // Targets per thread and column strips of the float64 symmetric form (T = 0: too small for it); want_T: the
 // caller's targets per thread, or 0.  Four targets per thread where that alone gives 4096 units (four rounds of
-// the 1024 workgroups that fit at once; 2000 x 128: 34.2 ms against 35.1 at two), else two, with strips until
+// the 1024 workgroups that fit at once; 2000 x 128: 35.1 ms against 36.4 at two), else two, with strips until
 // there are 4096 units or a strip is down to four cycles (40,008 points: 0.96 ms with two strips, 1.00 without;
 // 16,128 points: 0.178 ms with eight, 0.246 without), or to two where even that leaves the chip idle (4,096
 // points: 31 us against 36).  Below 4096 points the direct form is as fast (2,048 points: 23 us against 26).

@@ -32,8 +32,8 @@ constexpr double kLn2 = 0.69314718055994530942;
 constexpr float kHalfLn2 = -0.34657359027997265471f;  // -(1/2) ln 2 : converts log2(q) to -ln|r|
 // Float64 in workgroups of 256 threads takes its logarithm from the 1024-entry table of -1/2 ln, 16 KB of LDS that
 // every workgroup forms itself (4 entries per thread, about 1 us): 7 FMAs instead of 11 with 64 entries.  Whole calls:
-// 16,128 points 317 -> 272 us, 64,000 points 4.05 -> 3.76 ms, masked 4.46 -> 3.99 ms (with ln 2 in one word, one FMA
-// less, 268 us, 3.70 and 3.94 ms, and every logarithm off by 1.2e-17 times its exponent).  Smaller workgroups keep the
+// 16,128 points 275 -> 263 us, 64,000 points 4.03 -> 3.80 ms, masked 4.46 -> 3.99 ms (with ln 2 in one word, one FMA
+// less, 258 us, 3.68 and 3.94 ms, and every logarithm off by 1.2e-17 times its exponent).  Smaller workgroups keep the
 // 64 entries: forming 1024 costs them more than it saves, and the table keeps wavefronts off the compute unit (64
 // threads, 64,000 points: 5.17 -> 5.63 ms).
 constexpr bool big_table(int prec, int threads) { return prec == P64 && threads >= 256; }

@@ -667,7 +667,7 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_main(
 // the table, with 1024 entries (series through r^4); the table is built once per call and copied to LDS by each
 // unit.  Column sums travel around the ring by DPP moves of both halves of each double.  What bounds it is
 // float64 VALU issue (4 cycles per instruction and wavefront, 16 for the hardware reciprocal).  Measured before
-// and after: 2000 x 128 35.6 -> 34.2 ms, 1020 vesicles of 17 to 63 points (40,008 points) 1.45 -> 0.95 ms.
+// and after, on one card: 2000 x 128 36.7 -> 35.1 ms, 1020 vesicles of 17 to 63 points (40,008 points) 1.45 -> 0.97 ms.
 //
 // Sums leave the workgroup as two 64-bit fixed-point words:
 // hi = rint(x 2^S) and lo = rint((x - hi 2^-S) 2^(S + kLoBits)) (the first difference is exact), each added
