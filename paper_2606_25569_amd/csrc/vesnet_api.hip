@@ -816,9 +816,9 @@ int check_batched_args(const double* targets, const double* sources, const doubl
 // units, half of the empty ones counted (a strip past a suspension's last point; taking one costs half of what a short
 // unit does): as many strips as leave at most 1024 of them at 16 strips, one round of the units that fit at once, 1536 at
 // 8, 2560 at 4 and 1920 at 2, and no more than divide the mean suspension further; nor so many that seven in eight are
-// empty, past 512 of them (64 suspensions of 2 x 16: 34 us with 16 strips, 30 without).  Measured against the direct form, which the
-// batched call had before (us, direct -> this): 1000 suspensions of 4 x 32 124 -> 89 (131 with the 8 strips that 4096
-// units asked for), 256 of 4 x 32 55 -> 49, 64 of 20 x 32 92 -> 66, 8 of 10 x 128 128 -> 38.
+// empty, past 512 of them (64 suspensions of 2 x 16: 34 us with 16 strips, 30 without).  Measured against the direct
+// form, which the batched call had before (us, direct -> this): 1000 suspensions of 4 x 32 124 -> 89 (131 with the 8
+// strips that 4096 units asked for), 256 of 4 x 32 55 -> 49, 64 of 20 x 32 92 -> 66, 8 of 10 x 128 128 -> 38.
 int batched64_shape(const vesnet_tile_config* cfg, int32_t P, int32_t S, int* ns) {
   const int64_t mean = (int64_t)P / std::max(1, S);
   int T = mean >= 1536 ? 2 : 1;

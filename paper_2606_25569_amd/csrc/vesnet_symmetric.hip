@@ -340,11 +340,11 @@ __device__ __forceinline__ int vesicle_cut(const int4* __restrict__ cyc, int c0,
 
 // The unit of this workgroup among the nb blocks' pairs, each cut into ns strips of the column block.  Units are the
 // pairs {bx, bx + d mod nb}, d = 0 .. nb/2 (for even nb, d = nb/2 only for bx < nb/2), numbered row block by row block.
-// Workgroups are handed to the eight XCDs in turn (workgroup g to XCD g mod 8), so each XCD is given one contiguous range
-// of that numbering: its concurrent units share a row block and a window of about nb/2 consecutive column blocks, which
-// stays in the XCD's own L2.  Row block bx, column block by, and the strip's cycles [s0, s1) of block by's [by cb, min(ncyc, (by + 1) cb)); false when
-// it has none.  Strips end at vesicle starts, so that the float32 partial sums of a (target, vesicle) are the
-// same for every ns (a vesicle longer than a strip leaves the following ones empty).
+// Workgroups are handed to the eight XCDs in turn (workgroup g to XCD g mod 8), so each XCD is given one contiguous
+// range of that numbering: its concurrent units share a row block and a window of about nb/2 consecutive column blocks,
+// which stays in the XCD's own L2.  Row block bx, column block by, and the strip's cycles [s0, s1) of block by's [by
+// cb, min(ncyc, (by + 1) cb)); false when it has none.  Strips end at vesicle starts, so that the float32 partial sums
+// of a (target, vesicle) are the same for every ns (a vesicle longer than a strip leaves the following ones empty).
 __device__ __forceinline__ bool sym_unit(int nb, int ns, int cb, int ncyc, const int4* __restrict__ cyc, int& bx,
                                          int& by, int& s0, int& s1) {
   const int h = nb >> 1;
@@ -644,17 +644,16 @@ __global__ __launch_bounds__(kSymThreads) void k_sym_main(
 
 // ------------------------------------------------------------------ float64 symmetric form
 // The same circulant schedule of unordered block pairs and rings of 16 lanes, in float64 on global coordinates.
-// Float64 needs no compensation per source vesicle, so nothing here follows the vesicles: blocks are 256 T
-// consecutive points, ring cycles 16 consecutive points whatever vesicles they belong to (only the last cycle
-// of a suspension is padded; cut at the vesicles, 17 to 63 points each, 47% of the pair evaluations were
-// padding), rows are summed chunk by chunk of 64 columns whatever the vesicles (summed over a whole unit in one chain
-// they rounded 1.4 times as much in all), the matrix's diagonal terms apart from the others (over a vesicle without net
-// force the partial sums are tens of times its terms, and both FMAs of a pair rounded at their size: 1.2 to 1.4 times
-// the error for the same time; four pairs summed by themselves first halve it, for 2.7% more), and the block table needs
-// no plan kernel.  The
-// own vesicle is dropped pair by pair, but only in units whose row and column points share a vesicle (ids are
-// compared at both ends; at most the diagonal and the neighbouring block pairs): there the accumulations are
-// selected, so that not even a non-finite value of an own-vesicle pair enters.
+// Float64 needs no compensation per source vesicle, so nothing here follows the vesicles: blocks are 256 T consecutive
+// points, ring cycles 16 consecutive points whatever vesicles they belong to (only the last cycle of a suspension is
+// padded; cut at the vesicles, 17 to 63 points each, 47% of the pair evaluations were padding), rows are summed chunk
+// by chunk of 64 columns whatever the vesicles (summed over a whole unit in one chain they rounded 1.4 times as much in
+// all), the matrix's diagonal terms apart from the others (over a vesicle without net force the partial sums are tens
+// of times its terms, and both FMAs of a pair rounded at their size: 1.2 to 1.4 times the error for 1% less time; four
+// pairs summed by themselves first halve it, for 2.7% more), and the block table needs no plan kernel.  The own vesicle
+// is dropped pair by pair, but only in units whose row and column points share a vesicle (ids are compared at both
+// ends; at most the diagonal and the neighbouring block pairs): there the accumulations are selected, so that not even
+// a non-finite value of an own-vesicle pair enters.
 //
 // Work split: a unit is the row block against one of `ns` equal strips of the column block.  One unit per
 // block pair leaves most of the chip idle on small problems and a nearly empty last round on middling ones;
